@@ -11,8 +11,8 @@
 // so a limb makes two round trips to HBM for n = 65536 (and for n = 4096).
 //
 // Two butterfly arithmetics, chosen per limb (uniform per workgroup):
-//   IntArith : Harvey's lazy butterflies with Shoup twiddles on u64 (any modulus below 2^62);
-//              ~32 VALU instructions per butterfly on this machine.
+//   IntArith : lazy butterflies with Shoup twiddles on u64 (any modulus below 2^61); about 21 VALU instructions per
+//              butterfly on this machine with its share of the folds.
 //   FpArith  : for moduli below 2^50, residues held as exact integers in doubles.  FP64 FMA
 //              issues at full rate here, and a modular product is 6 instructions:
 //                  h = y*w; l = fma(y, w, -h)            (exact product h + l)
@@ -39,12 +39,27 @@ struct NttTables {
 };
 
 // ---- integer arithmetic --------------------------------------------------------------------------
+// Residues stay lazy: a value is only kept below 2^64, i.e. below 16 q (8 q for 61-bit moduli, `tight`).  A product by a
+// Shoup twiddle drops the low partial products of its quotient (at most two units too small), so it lies in [0, 4q)
+// for every 64-bit operand, and costs 13 instructions instead of the 17 of the exact quotient; additions are not reduced.
+// Every second stage all values (forward) or the sums (inverse) are folded: with 2^(b-1) < q = 2^b - c < 2^b,
+// v = (v mod 2^b) + (v >> b) c < q + 17 c < 2q, three instructions.  (The primes of a context are the first ones below
+// 2^b in steps of 2n, so c is below 2^32 by far.)  Bounds, in units of q:
+//   forward  2 -> 6 -> 10 -> fold < 2 (two stages), 61-bit: 2 -> 6 -> fold
+//   inverse  4 -> 8 (sum), 4 (product) -> 16 (sum, folded), 4; 61-bit: 4 -> 8 (sum, folded), 4
+// Measured against exact quotients with a conditional subtraction per butterfly (32 instructions) and twiddles read
+// where they are used: 8 limbs under 60-bit primes 11.1 + 10.6 -> 9.3 + 9.8 us (inverse rows + columns), 64 limbs
+// 29.5 + 28.3 -> 26.9 + 24.6 us.
 struct IntArith {
     typedef u64 T;
-    u64 q, q2, ni, nip;
+    u64 q, ni, nip;
+    unsigned c, bs, mask;         // 2^b - q, b - 32, low bits of the upper word
+    bool tight;                   // 8 q is the most a word holds: fold after every stage
     const u64 *w, *wp;
     __device__ __forceinline__ void init(const NttTables &t, int mi, int n) {
-        q = t.modc[mi].q, q2 = 2 * q;
+        q = t.modc[mi].q;
+        bs = 32 - __clz((unsigned)(q >> 32));
+        c = (unsigned)((1ULL << (bs + 32)) - q), mask = (1u << bs) - 1u, tight = bs > 28;
         w = t.tw + (size_t)mi * n, wp = t.twp + (size_t)mi * n;
         ni = nip = 0;
         if (t.ninv) ni = t.ninv[mi], nip = t.ninvp[mi];
@@ -53,22 +68,41 @@ struct IntArith {
     __device__ __forceinline__ T from_mid(u64 raw) const { return raw; }
     __device__ __forceinline__ u64 to_mid(T v) const { return v; }
     typedef u64 W;
-    __device__ __forceinline__ void load_tw(u64 idx, W &a, W &b) const { a = w[idx], b = wp[idx]; }
-    __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {           // in, out below 4q
-        u64 x = X >= q2 ? X - q2 : X;
-        u64 t = mul_shoup_lazy(Y, a, b, q);
+    __device__ __forceinline__ u64 mul_lazy(u64 a, u64 x, u64 xp) const {     // a x mod q in [0, 4q)
+        const unsigned a0 = (unsigned)a, a1 = (unsigned)(a >> 32), p0 = (unsigned)xp, p1 = (unsigned)(xp >> 32);
+        const u64 h = (u64)a1 * p1 + ((u64)__umulhi(a1, p0) + __umulhi(a0, p1));
+        return a * x - h * q;
+    }
+    __device__ __forceinline__ u64 fold(u64 v) const {
+        const unsigned hi = (unsigned)(v >> 32);
+        return (u64)(hi >> bs) * c + (((u64)(hi & mask) << 32) | (unsigned)v);
+    }
+    __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {
+        const u64 t = mul_lazy(Y, a, b), x = X;
         X = x + t;
-        Y = x - t + q2;
+        Y = (x + 4 * q) - t;
     }
-    __device__ __forceinline__ void gs(T &X, T &Y, W a, W b) const {           // in, out below 2q
-        u64 s = X + Y, d = X - Y + q2;
-        X = s >= q2 ? s - q2 : s;
-        Y = mul_shoup_lazy(d, a, b, q);
+    __device__ __forceinline__ void gs(T &X, T &Y, W a, W b) const {
+        const u64 d = (X + (tight ? 4 * q : 8 * q)) - Y;
+        X = X + Y;
+        Y = mul_lazy(d, a, b);
     }
-    __device__ __forceinline__ u64 to_rest_fwd(T v) const {
-        v = v >= q2 ? v - q2 : v;
-        return v >= q ? v - q : v;
+    // stage a (of a group of four, 0 first) is done on all sixteen values
+    __device__ __forceinline__ void after_fwd(int a, T (&v)[16]) const {
+        if ((a & 1) || tight) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) v[k] = fold(v[k]);
+        }
     }
+    // stage a (3 first): the sums sit where bit 3 - a of the index is clear
+    __device__ __forceinline__ void after_inv(int a, T (&v)[16]) const {
+        if (!(a & 1) || tight) {
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+                if (!(k & (8 >> a))) v[k] = fold(v[k]);
+        }
+    }
+    __device__ __forceinline__ u64 to_rest_fwd(T v) const { return v >= q ? v - q : v; }
     __device__ __forceinline__ u64 to_rest_inv(T v) const { return mul_shoup(v, ni, nip, q); }
 };
 
@@ -97,7 +131,8 @@ struct FpArith {
     __device__ __forceinline__ T from_mid(u64 raw) const { return __longlong_as_double((long long)raw); }
     __device__ __forceinline__ u64 to_mid(T v) const { return (u64)__double_as_longlong(v); }
     typedef double W;
-    __device__ __forceinline__ void load_tw(u64 idx, W &a, W &b) const { a = w[idx], b = wq[idx]; }
+    __device__ __forceinline__ void after_fwd(int, T (&)[16]) const {}
+    __device__ __forceinline__ void after_inv(int, T (&)[16]) const {}
     // With table twiddles (0 <= w < q, w/q correctly rounded) |r| <= 1.04 q; with generated ones
     // (|w| <= 0.9 q, w/q taken as w * (1/q)) |r| <= 1.2 q.  Either way every value stays below 2.1 q.
     __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {
@@ -122,19 +157,23 @@ struct FpArith {
 
 // Twiddle providers for four stages starting at stage s0 with base0 = 2^s0 + (block index):
 // stage s0 + a, group g uses table entry (base0 << a) + g.
-// Integer limbs read the entry and its companion where the butterfly uses them.  FP64 limbs read all fifteen
-// entries up front (one exposure to memory latency instead of one per stage, and the loads overlap the data loads
-// or the LDS exchange in front of them); the second factor w/q is taken as w * (1/q), one multiplication instead
+// Both arithmetics read all fifteen entries up front (one exposure to memory latency instead of one per stage, and the
+// loads overlap the data loads or the LDS exchange in front of them).  Integer limbs read the Shoup companions with
+// them; FP64 limbs take the second factor w/q as w * (1/q), one multiplication instead
 // of a second table: the quotient estimate may then be off by one more unit, the product stays exact
 // (|r| <= 1.3 q for |y| <= 2.1 q).
 template <class A>
 struct TableTw;
 template <>
 struct TableTw<IntArith> {
-    const IntArith &ar;
-    u64 base0;
-    __device__ __forceinline__ TableTw(const IntArith &a_, u64 b0) : ar(a_), base0(b0) {}
-    __device__ __forceinline__ void get(int a, int g, u64 &w0, u64 &w1) const { ar.load_tw((base0 << a) + g, w0, w1); }
+    u64 w[15], wp[15];
+    __device__ __forceinline__ TableTw(const IntArith &ar, u64 b0) {
+#pragma unroll
+        for (int a = 0; a < 4; a++)
+#pragma unroll
+            for (int g = 0; g < (1 << a); g++) w[(1 << a) - 1 + g] = ar.w[(b0 << a) + g], wp[(1 << a) - 1 + g] = ar.wp[(b0 << a) + g];
+    }
+    __device__ __forceinline__ void get(int a, int g, u64 &w0, u64 &w1) const { w0 = w[(1 << a) - 1 + g], w1 = wp[(1 << a) - 1 + g]; }
 };
 template <>
 struct TableTw<FpArith> {
@@ -187,6 +226,7 @@ __device__ __forceinline__ void radix16_fwd_tw(typename A::T (&v)[16], const A &
                 ar.ct(v[k], v[k + half], w0, w1);
             }
         }
+        ar.after_fwd(a, v);
     }
 }
 // The inverse of the above (stages in the opposite order).
@@ -205,6 +245,7 @@ __device__ __forceinline__ void radix16_inv_tw(typename A::T (&v)[16], const A &
                 ar.gs(v[k], v[k + half], w0, w1);
             }
         }
+        ar.after_inv(a, v);
     }
 }
 // last four stages of the row pass: generated twiddles for FP64 limbs, table for the others

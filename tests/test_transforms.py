@@ -1,0 +1,79 @@
+"""The transforms against the oracle under moduli of every arithmetic they choose between (FP64 below 2^50, lazy integers
+above, the tighter folding of 61-bit moduli), and the host-side bounds their lazy integer arithmetic rests on."""
+import numpy as np
+import pytest
+
+from oracle import params
+
+
+def _moduli(bits, n, count):
+    return params.scan_primes(bits, n, count)
+
+
+@pytest.mark.parametrize("n", [4096, 65536])
+def test_primes_of_a_context_are_close_below_their_power_of_two(n):
+    """fold() replaces v by (v mod 2^b) + (v >> b) c with a 32-bit c = 2^b - q and lands below 2q."""
+    for bits in range(51, 62):
+        for q in _moduli(bits, n, 64):
+            c = (1 << bits) - q
+            assert 0 < c < 1 << 32 and q > 1 << (bits - 1)
+            worst = ((1 << bits) - 1) + ((1 << 64) >> bits) * c
+            assert worst < 2 * q
+
+
+def test_lazy_product_stays_below_4q():
+    """mul_lazy(): the quotient from three of the four partial products is at most two units short."""
+    rng = np.random.default_rng(5)
+    m32 = (1 << 32) - 1
+    for bits in (51, 54, 60, 61):
+        q = _moduli(bits, 4096, 1)[0]
+        for i in range(4000):
+            a = int(rng.integers(0, 1 << 63)) * 2 + 1 if i % 3 else (1 << 64) - 1 - int(rng.integers(0, 1 << 20))
+            w = int(rng.integers(0, q)) if i % 5 else q - 1
+            wp = (w << 64) // q
+            a0, a1, p0, p1 = a & m32, a >> 32, wp & m32, wp >> 32
+            h = a1 * p1 + ((a1 * p0) >> 32) + ((a0 * p1) >> 32)
+            assert h < 1 << 64
+            r = a * w - h * q
+            assert 0 <= r < 4 * q and r % q == a * w % q
+
+
+def _brev(n):
+    logn = n.bit_length() - 1
+    i = np.arange(n, dtype=np.uint32)
+    r = np.zeros(n, dtype=np.uint32)
+    for b in range(logn):
+        r |= ((i >> b) & 1) << (logn - 1 - b)
+    return r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,q0_bits,qi_bits,p_bits", [
+    (4096, 50, 40, 60), (4096, 61, 61, 61), (4096, 51, 54, 58),
+    (65536, 50, 49, 60), (65536, 61, 51, 61),
+])
+def test_transform_matches_the_oracle(n, q0_bits, qi_bits, p_bits):
+    import torch
+    from oracle import ckks
+    from paper_2602_11470_amd import binding as B
+    n_qi, n_p = 4, 2
+    qs = _moduli(q0_bits, n, n_qi + 1) if q0_bits == qi_bits else _moduli(q0_bits, n, 1) + _moduli(qi_bits, n, n_qi)
+    ps = [p for p in _moduli(p_bits, n, n_p + n_qi + 1) if p not in qs][:n_p]
+    mods = qs + ps
+    gctx = B.Context(n, n_qi + 1, n_p, 2, q0_bits, qi_bits, p_bits, 2.0 ** 30)
+    assert [int(x) for x in gctx.moduli()] == mods
+    octx = ckks.Context(params.Params(n=n, q=qs, p=ps, alpha=2, scale=2.0 ** 30))
+    rng = np.random.default_rng(n + p_bits)
+    brev = _brev(n)
+    for limbs in (1, 3, 2 * len(mods) + 1):
+        idx = [(5 * i + limbs) % len(mods) for i in range(limbs)]
+        a = np.stack([rng.integers(0, mods[i], n, dtype=np.uint64) for i in idx])
+        a[0, :64] = mods[idx[0]] - 1
+        a[-1, 64:256] = 0
+        want = octx.ntt(a.copy(), idx)[:, brev]
+        dev = torch.from_numpy(a.view(np.int64)).cuda()
+        gctx.ntt(dev, idx)
+        assert np.array_equal(dev.cpu().numpy().view(np.uint64), want)
+        gctx.ntt(dev, idx, inverse=True)
+        assert np.array_equal(dev.cpu().numpy().view(np.uint64), a)
+    gctx.close()
