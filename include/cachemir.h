@@ -117,7 +117,7 @@ void cm_ctx_destroy(cm_ctx *ctx);
  *     under (else CM_E_INVAL).
  *   CM_OPT_TWO_STEP_MASKS  value != 0: cm_kv_append(_group) forms its masked products as stored
  *     ciphertexts and rescales them afterwards, instead of forming them inside the rescale's transform
- *     (n = 65536 only; a cross-check of that fused path, bit-identical results). */
+ *     (a cross-check of that fused path, bit-identical results). */
 enum { CM_OPT_EVK_STORED_A = 1, CM_OPT_TWO_STEP_MASKS = 2 };
 cm_status cm_ctx_set_option(cm_ctx *ctx, int32_t option, int32_t value);
 /* host out[n_q + n_p]: q_0..q_L then p_0..p_{K-1}. */

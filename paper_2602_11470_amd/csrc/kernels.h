@@ -87,8 +87,6 @@ bool launch_inner_product_multi_key(cm_ctx *ctx, const IpBatch &b, const IpKeys 
 void launch_inner_product_shared_key(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st, u64 g = 0);
 // out[2][ext][n] = (P c0, P c1), zero on the special limbs
 void launch_raise_by_P(cm_ctx *ctx, u64 *out, const u64 *in, int level, hipStream_t st, int count = 1);   // count stacked ciphertexts
-void launch_moddown_finish(cm_ctx *ctx, u64 *out, const u64 *u, const u64 *conv, const u64 *d_pinv, const u64 *addend,
-                           int addend_comps, int level, u64 g, const u64 *accum, hipStream_t st, int ncomp = 2);
 void launch_rescale_reduce(cm_ctx *ctx, u64 *red, const u64 *last, int ncomp, int level, hipStream_t st);
 void launch_rescale_finish(cm_ctx *ctx, u64 *out, const u64 *in, const u64 *red, const u64 *d_qlinv, int ncomp, int level, hipStream_t st,
                            bool accumulate = false);
@@ -124,7 +122,7 @@ struct FinishBatch {
     const u64 *mul_pt = nullptr;
     unsigned mul_g[CM_KS_BATCH] = {};
 };
-// forward transform of conv[items*ncomp*(level+1)][n] (mods 0..level repeating) with that tail; n = 65536 only
+// forward transform of conv[items*ncomp*(level+1)][n] (mods 0..level repeating) with that tail
 // with src: the first pass reads row d_src_rows[i] of src for limb i (words below twice that limb's modulus) instead of conv
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st,
                            const u64 *src = nullptr, const int *d_src_rows = nullptr);

@@ -955,34 +955,6 @@ void launch_inner_product(cm_ctx *ctx, u64 *u0, u64 *u1, const u64 *dig, const u
                            evk_a_of(ctx), ctx->d_ubound);
 }
 
-// ---- ModDown tail: out = (u - conv) * P^{-1} (+ addend, optionally through the Galois map) ------------
-// batch (blockIdx.z) = component; u rows [ext][n], conv rows [level+1][n], out rows [level+1][n]
-__global__ __launch_bounds__(TPB) void k_moddown_finish(u64 *out, const u64 *__restrict__ u, const u64 *__restrict__ conv,
-                                 const u64 *__restrict__ pinv, const u64 *__restrict__ addend,
-                                 const ModC *__restrict__ modc, int n, int logn, unsigned g, size_t u_stride,
-                                 size_t conv_stride, size_t out_stride, int addend_comp_only, const u64 *accum) {
-    unsigned i = blockIdx.x * TPB + threadIdx.x;
-    int l = blockIdx.y, c = blockIdx.z;
-    u64 q = modc[l].q;
-    u64 d = submod(u[c * u_stride + (size_t)l * n + i], conv[c * conv_stride + (size_t)l * n + i], q);
-    u64 v = mul_shoup(d, pinv[2 * l], pinv[2 * l + 1], q);
-    if (addend && c <= addend_comp_only) {
-        unsigned s = g ? perm_src(i, g, logn) : i;
-        v = addmod(v, addend[c * out_stride + (size_t)l * n + s], q);
-    }
-    if (accum) v = addmod(v, accum[c * out_stride + (size_t)l * n + i], q);      // out = accum + result
-    out[c * out_stride + (size_t)l * n + i] = v;
-}
-void launch_moddown_finish(cm_ctx *ctx, u64 *out, const u64 *u, const u64 *conv, const u64 *d_pinv, const u64 *addend,
-                           int addend_comps, int level, u64 g, const u64 *accum, hipStream_t st, int ncomp) {
-    Prof prof_(ctx, CM_K_MODDOWN_FINISH, 1, st);
-    int ext = level + 1 + ctx->K;
-    size_t n = ctx->n;
-    hipLaunchKernelGGL(k_moddown_finish, dim3(ctx->n / TPB, level + 1, ncomp), dim3(TPB), 0, st, out, u, conv, d_pinv,
-                       addend, ctx->d_modc, ctx->n, ctx->logn, (unsigned)g, (size_t)ext * n, (size_t)(level + 1) * n,
-                       (size_t)(level + 1) * n, addend_comps - 1, accum);
-}
-
 // ---- rescale ---------------------------------------------------------------------------------
 // last[comp][n]: coefficient-domain last limb in [0, q_l) -> red[comp][l][n] = last mod q_i
 __global__ void k_rescale_reduce(u64 *red, const u64 *last, const ModC *modc, int level, int n) {

@@ -8,7 +8,7 @@
 // (radix 16), then the workgroup transposes through LDS and runs four more.
 //   column kernel : stages 0..7, a tile of 256 rows x 16 adjacent columns (rows n2 apart)
 //   row kernel    : the remaining log2(n2) stages on contiguous blocks of n2 words
-// so a limb makes two round trips to HBM for n = 65536 (and for n = 4096).
+// so a limb makes two round trips to HBM for n = 65536.  For n = 4096 the limb is one tile and both parts run in one kernel.
 //
 // Two butterfly arithmetics, chosen per limb (uniform per workgroup):
 //   IntArith : lazy butterflies with Shoup twiddles on u64 (any modulus below 2^61); about 21 VALU instructions per
@@ -87,11 +87,12 @@ struct IntArith {
         X = X + Y;
         Y = mul_lazy(d, a, b);
     }
-    // stage a (of a group of four, 0 first) is done on all sixteen values
-    __device__ __forceinline__ void after_fwd(int a, T (&v)[16]) const {
-        if ((a & 1) || tight) {
+    // stage s of the transform is done on all the lane's values
+    template <int NV>
+    __device__ __forceinline__ void after_fwd(int s, T (&v)[NV]) const {
+        if ((s & 1) || tight) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = fold(v[k]);
+            for (int k = 0; k < NV; k++) v[k] = fold(v[k]);
         }
     }
     // stage a (3 first): the sums sit where bit 3 - a of the index is clear
@@ -131,7 +132,8 @@ struct FpArith {
     __device__ __forceinline__ T from_mid(u64 raw) const { return __longlong_as_double((long long)raw); }
     __device__ __forceinline__ u64 to_mid(T v) const { return (u64)__double_as_longlong(v); }
     typedef double W;
-    __device__ __forceinline__ void after_fwd(int, T (&)[16]) const {}
+    template <int NV>
+    __device__ __forceinline__ void after_fwd(int, T (&)[NV]) const {}
     __device__ __forceinline__ void after_inv(int, T (&)[16]) const {}
     // With table twiddles (0 <= w < q, w/q correctly rounded) |r| <= 1.04 q; with generated ones
     // (|w| <= 0.9 q, w/q taken as w * (1/q)) |r| <= 1.2 q.  Either way every value stays below 2.1 q.
@@ -426,42 +428,9 @@ __device__ __forceinline__ void transpose16(typename A::T (&v)[16], const A &ar,
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(x[k]);
 }
 
-// ---- row passes on contiguous blocks of 256 words (n = 65536): a workgroup owns 16 blocks ---------------
-template <class A, bool TAIL>
-__device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int chunk,
-                                                 int limb, const FinishBatch &fb) {
-    A ar;
-    ar.init(t, mi, n);
-    const int sub = threadIdx.x & 15, blk = threadIdx.x >> 4;
-    const u64 B = (u64)chunk * 16 + blk;
-    typename A::T v[16];
-    u64 raw[16];
-    if (t.stream_loads) {
-#pragma unroll
-        for (int k = 0; k < 16; k++) raw[k] = __builtin_nontemporal_load(p + blk * 256 + sub + 16 * k);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; k++) raw[k] = p[blk * 256 + sub + 16 * k];
-    }
-    {
-        const TableTw<A> tw(ar, 256 + B);           // in flight together with the data
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(raw[k]);
-        radix16_fwd_tw(v, ar, tw);
-    }
-    transpose16(v, ar, sub);           // word sub + 16 k of the block -> word 16 sub + k
-    radix16_fwd_last(v, ar, 4096 + B * 16 + sub);
-    // Each lane now owns 16 contiguous words.  A trip through LDS (the only one of this pass) hands every lane the
-    // words tid, tid + 256, ... of the tile instead, so that all global traffic below is coalesced.
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + 16 * sub + k)] = ar.to_rest_fwd(v[k]);
-    __syncthreads();
-    if (!TAIL) {
-#pragma unroll
-        for (int k = 0; k < 16; k++) NTT_ST(p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
-        return;
-    }
-    // fused ModDown tail: this limb is NTT(conv) of item r, component c, limb l
+// The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of 4096 sit in LDS.
+__device__ __forceinline__ void finish_tail(const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
+    // this limb is NTT(conv) of item r, component c, limb l
     const int per = fb.ncomp * (fb.level + 1);
     const int r = limb / per, c = fb.comp0 + (limb % per) / (fb.level + 1), l = limb % (fb.level + 1);
     const u64 q = t.modc[l].q, pi = fb.pinv[2 * l], pis = fb.pinv[2 * l + 1];
@@ -524,6 +493,44 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
         if (ac) x = addmod(x, cc[k], q);
         op[256 * k] = x;
     }
+}
+
+// ---- row passes on contiguous blocks of 256 words (n = 65536): a workgroup owns 16 blocks ---------------
+template <class A, bool TAIL>
+__device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int chunk,
+                                                 int limb, const FinishBatch &fb) {
+    A ar;
+    ar.init(t, mi, n);
+    const int sub = threadIdx.x & 15, blk = threadIdx.x >> 4;
+    const u64 B = (u64)chunk * 16 + blk;
+    typename A::T v[16];
+    u64 raw[16];
+    if (t.stream_loads) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) raw[k] = __builtin_nontemporal_load(p + blk * 256 + sub + 16 * k);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) raw[k] = p[blk * 256 + sub + 16 * k];
+    }
+    {
+        const TableTw<A> tw(ar, 256 + B);           // in flight together with the data
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(raw[k]);
+        radix16_fwd_tw(v, ar, tw);
+    }
+    transpose16(v, ar, sub);           // word sub + 16 k of the block -> word 16 sub + k
+    radix16_fwd_last(v, ar, 4096 + B * 16 + sub);
+    // Each lane now owns 16 contiguous words.  A trip through LDS (the only one of this pass) hands every lane the
+    // words tid, tid + 256, ... of the tile instead, so that all global traffic below is coalesced.
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + 16 * sub + k)] = ar.to_rest_fwd(v[k]);
+    __syncthreads();
+    if (!TAIL) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) NTT_ST(p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
+        return;
+    }
+    finish_tail(lds, t, n, chunk, limb, fb);
 }
 template <class A>
 __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
@@ -596,62 +603,137 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
         rows256_inv_body<IntArith>(lds, p, ps, psrow, g, t, mi, n, chunk);
 }
 
-// ---- row passes on blocks of 16 words (n = 4096): every lane owns one block ---------------------------------
-template <class A>
-__device__ __forceinline__ void rows16_fwd_body(u64 *p, const NttTables &t, int mi, int n, u64 B) {
+// ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
+// The limb is one 256 x 16 tile: eight stages down the columns as above, then the last four on rows of 16 contiguous
+// words, one row per lane, all exchanges in LDS.  Bound by the chain of its twelve stages, not by bytes (32 KiB per
+// limb): the limb used to take two launches, a column and a row pass, and at 2 to 25 limbs a launch costs its few
+// microseconds whatever it moves.  With the ModDown / rescale tail in the same kernel a rotation of the 5 + 1 ring went
+// from 12 launches to 7, a 64 x 64 product on it (11 rotations) from 693 to 562 us.
+template <class A, bool TAIL>
+__device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int limb,
+                                              const FinishBatch &fb) {
     A ar;
     ar.init(t, mi, n);
+    const int tid = threadIdx.x, c = tid & 15, sub = tid >> 4;
     typename A::T v[16];
+    u64 raw[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = ar.from_mid(p[k]);
-    radix16_fwd_tw(v, ar, TableTw<A>(ar, 256 + B));
+    for (int k = 0; k < 16; k++) raw[k] = ps[(sub + 16 * k) * 16 + c];
+    {
+        const TableTw<A> tw(ar, 1);
 #pragma unroll
-    for (int k = 0; k < 16; k++) p[k] = ar.to_rest_fwd(v[k]);
+        for (int k = 0; k < 16; k++) v[k] = ar.from_rest(raw[k]);
+        radix16_fwd_tw(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad((sub + 16 * k) * 16 + c)] = ar.to_mid(v[k]);
+    {
+        const TableTw<A> tw(ar, 16 + sub);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
+        radix16_fwd_tw(v, ar, tw);
+    }
+    // a lane writes back the words it read, then takes row tid
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad((16 * sub + k) * 16 + c)] = ar.to_mid(v[k]);
+    {
+        const TableTw<A> tw(ar, 256 + tid);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(tid * 16 + k)]);
+        radix16_fwd_tw(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad(tid * 16 + k)] = ar.to_rest_fwd(v[k]);
+    __syncthreads();
+    if (TAIL) {
+        finish_tail(lds, t, n, 0, limb, fb);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) p[tid + 256 * k] = lds[pad(tid + 256 * k)];
 }
 template <class A>
-__device__ __forceinline__ void rows16_inv_body(u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
-                                                const NttTables &t, int mi, int n, u64 B) {
+__device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n) {
     A ar;
     ar.init(t, mi, n);
+    const int tid = threadIdx.x, c = tid & 15, sub = tid >> 4;
     typename A::T v[16];
-    const int logn = 31 - __clz(n);
+    {
+        const int logn = 31 - __clz(n);
+        u64 w[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++)
-        v[k] = ar.from_rest(g ? psrow[perm_src((unsigned)(B * 16 + k), g, logn)] : ps[k]);
-    radix16_inv_tw(v, ar, TableTw<A>(ar, 256 + B));
+        for (int k = 0; k < 16; k++) w[k] = ps[g ? perm_src((unsigned)(tid + 256 * k), g, logn) : tid + 256 * k];
 #pragma unroll
-    for (int k = 0; k < 16; k++) p[k] = ar.to_mid(v[k]);
+        for (int k = 0; k < 16; k++) lds[pad(tid + 256 * k)] = w[k];
+        const TableTw<A> tw(ar, 256 + tid);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_rest(lds[pad(tid * 16 + k)]);
+        radix16_inv_tw(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad(tid * 16 + k)] = ar.to_mid(v[k]);
+    {
+        const TableTw<A> tw(ar, 16 + sub);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
+        radix16_inv_tw(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad((16 * sub + k) * 16 + c)] = ar.to_mid(v[k]);
+    {
+        const TableTw<A> tw(ar, 1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((sub + 16 * k) * 16 + c)]);
+        radix16_inv_tw(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) p[(sub + 16 * k) * 16 + c] = ar.to_rest_inv(v[k]);
 }
-__global__ __launch_bounds__(NTT_THREADS) void ntt_rows16_fwd(u64 *__restrict__ data, const int *__restrict__ rows,
-                                                             const int *__restrict__ mod_idx, NttTables t, int n) {
-    const int per = n >> 12;
-    const int limb = blockIdx.x / per, chunk = blockIdx.x % per;
-    const int mi = mod_idx[limb];
-    const u64 B = (u64)chunk * 256 + threadIdx.x;
-    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + B * 16;
+// grid.x = limbs.  The transform may run in place: every word is read before the first is written.
+template <bool TAIL>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_full_fwd(u64 *data, const u64 *src, const int *__restrict__ src_rows,
+                                                           const int *__restrict__ rows, const int *__restrict__ mod_idx,
+                                                           NttTables t, int n, FinishBatch fb) {
+    __shared__ u64 lds[LDS_WORDS];
+    const int limb = blockIdx.x, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n;
+    const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p;
     if (t.fpq[mi].q != 0.0)
-        rows16_fwd_body<FpArith>(p, t, mi, n, B);
+        full_fwd_body<FpArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
     else
-        rows16_fwd_body<IntArith>(p, t, mi, n, B);
+        full_fwd_body<IntArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
 }
-__global__ __launch_bounds__(NTT_THREADS) void ntt_rows16_inv(u64 *__restrict__ data, const u64 *__restrict__ src,
-                                                             const int *__restrict__ src_rows,
-                                                             const int *__restrict__ rows,
-                                                             const int *__restrict__ mod_idx, NttTables t, int n,
-                                                             unsigned g) {
-    const int per = n >> 12;
-    const int limb = blockIdx.x / per, chunk = blockIdx.x % per;
-    const int mi = mod_idx[limb];
-    const u64 B = (u64)chunk * 256 + threadIdx.x;
-    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + B * 16;
-    const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - B * 16;
-    const u64 *ps = psrow + B * 16;
+__global__ __launch_bounds__(NTT_THREADS) void ntt_full_inv(u64 *data, const u64 *src, const int *__restrict__ src_rows,
+                                                           const int *__restrict__ rows, const int *__restrict__ mod_idx,
+                                                           NttTables t, int n, unsigned g) {
+    __shared__ u64 lds[LDS_WORDS];
+    const int limb = blockIdx.x, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n;
+    const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p;
     if (t.fpq[mi].q != 0.0)
-        rows16_inv_body<FpArith>(p, ps, psrow, g, t, mi, n, B);
+        full_inv_body<FpArith>(lds, p, ps, g, t, mi, n);
     else
-        rows16_inv_body<IntArith>(p, ps, psrow, g, t, mi, n, B);
+        full_inv_body<IntArith>(lds, p, ps, g, t, mi, n);
 }
 
+static NttTables tables_of(const cm_ctx *ctx, bool inverse, int limbs) {
+    NttTables t;
+    t.modc = ctx->d_modc, t.fpq = ctx->d_fpq;
+    t.stream_loads = limbs >= 256;
+    if (!inverse) {
+        t.tw = ctx->d_tw, t.twp = ctx->d_twp, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
+        t.ninv = t.ninvp = nullptr, t.ninvd = t.ninvqd = nullptr;
+    } else {
+        t.tw = ctx->d_itw, t.twp = ctx->d_itwp, t.twd = ctx->d_itwd, t.twqd = ctx->d_itwqd;
+        t.ninv = ctx->d_ninv, t.ninvp = ctx->d_ninvp, t.ninvd = ctx->d_ninvd, t.ninvqd = ctx->d_ninvqd;
+    }
+    return t;
+}
 // data rows d_rows[i] (or i) are transformed in place; with src != nullptr the first pass reads row
 // src_rows[i] (or i) of src instead, so the transform is out of place and src is left untouched.
 // With g != 0 (inverse, out of place only) the source is read through the Galois permutation, i.e.
@@ -663,27 +745,17 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
     Prof prof_(ctx, inverse ? CM_K_NTT_INV : CM_K_NTT_FWD, limbs, st);
     const int n = ctx->n, n2 = n >> 8;
     dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
-    NttTables t;
-    t.modc = ctx->d_modc, t.fpq = ctx->d_fpq;
-    t.stream_loads = limbs >= 256;
-    if (!inverse) {
-        t.tw = ctx->d_tw, t.twp = ctx->d_twp, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
-        t.ninv = t.ninvp = nullptr, t.ninvd = t.ninvqd = nullptr;
+    const NttTables t = tables_of(ctx, inverse, limbs);
+    if (!inverse && n2 == 256) {
         hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, n2);
-        if (n2 == 256)
-            hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, FinishBatch());
-        else
-            hipLaunchKernelGGL(ntt_rows16_fwd, grid, block, 0, st, data, d_rows, d_mod_idx, t, n);
-    } else {
-        t.tw = ctx->d_itw, t.twp = ctx->d_itwp, t.twd = ctx->d_itwd, t.twqd = ctx->d_itwqd;
-        t.ninv = ctx->d_ninv, t.ninvp = ctx->d_ninvp, t.ninvd = ctx->d_ninvd, t.ninvqd = ctx->d_ninvqd;
-        if (n2 == 256)
-            hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n,
-                               (unsigned)g);
-        else
-            hipLaunchKernelGGL(ntt_rows16_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n,
-                               (unsigned)g);
+        hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, FinishBatch());
+    } else if (!inverse) {
+        hipLaunchKernelGGL(ntt_full_fwd<false>, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, FinishBatch());
+    } else if (n2 == 256) {
+        hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
         hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
+    } else {
+        hipLaunchKernelGGL(ntt_full_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
     }
 }
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st, const u64 *src,
@@ -692,13 +764,14 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
     if (limbs <= 0) return;
     Prof prof_(ctx, CM_K_NTT_FWD, limbs, st);
     dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
-    NttTables t;
-    t.modc = ctx->d_modc, t.fpq = ctx->d_fpq;
-    t.stream_loads = limbs >= 256;
-    t.tw = ctx->d_tw, t.twp = ctx->d_twp, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
-    t.ninv = t.ninvp = nullptr, t.ninvd = t.ninvqd = nullptr;
-    hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, conv, src, d_src_rows, (const int *)nullptr, d_mods, t, n, n >> 8);
-    hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, conv, (const int *)nullptr, d_mods, t, n, fb);
+    const NttTables t = tables_of(ctx, false, limbs);
+    const int *none = nullptr;
+    if (n == 4096) {
+        hipLaunchKernelGGL(ntt_full_fwd<true>, grid, block, 0, st, conv, src, d_src_rows, none, d_mods, t, n, fb);
+        return;
+    }
+    hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, conv, src, d_src_rows, none, d_mods, t, n, n >> 8);
+    hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, conv, none, d_mods, t, n, fb);
 }
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs,
                      bool inverse, hipStream_t st) {

@@ -250,16 +250,11 @@ cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int ad
     if (!addend) addend_comps = 0, g = 0;
     launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
     launch_base_conv(ctx, k.d_moddown, 2, 0, level + 1, A.conv, u, (size_t)k.ext * n, (size_t)(level + 1) * n, nullptr, 0, st);
-    if (ctx->n == 65536) {
-        FinishBatch fb;
-        fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = addend_comps;
-        fb.u[0] = u, fb.out[0] = out, fb.accum[0] = accum, fb.g[0] = (unsigned)g;
-        fb.addend[0] = addend, fb.pinv = get_pinv(ctx, level);
-        launch_ntt_fwd_finish(ctx, A.conv, k.d_q_mods3, fb, st);
-        return CM_OK;
-    }
-    launch_ntt(ctx, A.conv, k.d_q_mods3, 2 * (level + 1), false, st);
-    launch_moddown_finish(ctx, out, u, A.conv, get_pinv(ctx, level), addend, addend_comps, level, g, accum, st);
+    FinishBatch fb;
+    fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = addend_comps;
+    fb.u[0] = u, fb.out[0] = out, fb.accum[0] = accum, fb.g[0] = (unsigned)g;
+    fb.addend[0] = addend, fb.pinv = get_pinv(ctx, level);
+    launch_ntt_fwd_finish(ctx, A.conv, k.d_q_mods3, fb, st);
     return CM_OK;
 }
 
@@ -315,28 +310,21 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
                           const u64 *gs, const u64 *const *accums, u64 *const *outs, hipStream_t st) {
     Arena A = arena_of(ctx);
     const int level = k.level;
-    const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n, cblk = 2 * (size_t)(level + 1) * n;
+    const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n;
     launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
     launch_base_conv(ctx, k.d_moddown, 2 * m, 0, level + 1, A.bconv, bu, (size_t)k.ext * n, (size_t)(level + 1) * n, nullptr,
                      0, st);
     auto add_of = [&](int r) { return addends ? addends[r] : nullptr; };
     auto acc_of = [&](int r) { return accums ? accums[r] : nullptr; };
-    if (ctx->n == 65536) {
-        FinishBatch fb;
-        fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = addends ? addend_comps : 0;
-        for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr;
-        for (int r = 0; r < m; r++) {
-            fb.u[r] = bu + r * ublk, fb.out[r] = outs[r], fb.accum[r] = acc_of(r), fb.addend[r] = add_of(r);
-            fb.g[r] = add_of(r) && gs ? (unsigned)gs[r] : 0;
-        }
-        fb.pinv = get_pinv(ctx, level);
-        launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
-    } else {
-        launch_ntt(ctx, A.bconv, k.d_bq_mods, m * 2 * (level + 1), false, st);
-        for (int r = 0; r < m; r++)
-            launch_moddown_finish(ctx, outs[r], bu + r * ublk, A.bconv + r * cblk, get_pinv(ctx, level), add_of(r),
-                                  add_of(r) ? addend_comps : 0, level, add_of(r) && gs ? gs[r] : 0, acc_of(r), st);
+    FinishBatch fb;
+    fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = addends ? addend_comps : 0;
+    for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr;
+    for (int r = 0; r < m; r++) {
+        fb.u[r] = bu + r * ublk, fb.out[r] = outs[r], fb.accum[r] = acc_of(r), fb.addend[r] = add_of(r);
+        fb.g[r] = add_of(r) && gs ? (unsigned)gs[r] : 0;
     }
+    fb.pinv = get_pinv(ctx, level);
+    launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
 }
 cm_status moddown_batch_into(cm_ctx *ctx, u64 *us, int level, int m, const u64 *const *addends, int addend_comps, u64 g,
                              const u64 *const *accums, u64 *const *outs, hipStream_t st) {
@@ -368,14 +356,6 @@ cm_status moddown_many_second(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *con
         launch_ntt_rows(ctx, bu, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st);
         launch_base_conv(ctx, k.d_moddown, m, 0, level + 1, A.bconv, bu + (size_t)k.ext * n, ublk, (size_t)(level + 1) * n,
                          nullptr, 0, st);
-        if (ctx->n != 65536) {                              // no fused tail at the small ring sizes
-            launch_ntt(ctx, A.bconv, k.d_bq_mods, m * (level + 1), false, st);
-            for (int r = 0; r < m; r++)
-                launch_moddown_finish(ctx, outs[base + r] + (size_t)(level + 1) * n, bu + r * ublk + (size_t)k.ext * n,
-                                      A.bconv + (size_t)r * (level + 1) * n, get_pinv(ctx, level), nullptr, 0, level, 0,
-                                      nullptr, st, 1);
-            continue;
-        }
         FinishBatch fb;
         fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
         for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
@@ -393,12 +373,6 @@ cm_status moddown_second_keep(cm_ctx *ctx, const u64 *R, int level, u64 *out, hi
     // the K special limbs of the second component, to the coefficient domain in a buffer of their own
     launch_ntt_src(ctx, A.tmp[0], nullptr, R, k.d_sp1_rows, k.d_sp_mods, ctx->K, true, st, 0);
     launch_base_conv(ctx, k.d_moddown0, 1, 0, level + 1, A.bconv, A.tmp[0], 0, 0, nullptr, 0, st);
-    if (ctx->n != 65536) {
-        launch_ntt(ctx, A.bconv, k.d_bq_mods, level + 1, false, st);
-        launch_moddown_finish(ctx, out + (size_t)(level + 1) * n, R + (size_t)k.ext * n, A.bconv, get_pinv(ctx, level), nullptr, 0,
-                              level, 0, nullptr, st, 1);
-        return CM_OK;
-    }
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
@@ -417,14 +391,6 @@ cm_status moddown_second_keep_many(cm_ctx *ctx, const u64 *Rs, int level, int m,
     launch_ntt_src(ctx, A.tmp[0], nullptr, Rs, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st, 0);
     launch_base_conv(ctx, k.d_moddown0, m, 0, level + 1, A.bconv, A.tmp[0], (size_t)ctx->K * n, (size_t)(level + 1) * n, nullptr,
                      0, st);
-    if (ctx->n != 65536) {
-        launch_ntt(ctx, A.bconv, k.d_bq_mods, m * (level + 1), false, st);
-        for (int r = 0; r < m; r++)
-            launch_moddown_finish(ctx, outs[r] + (size_t)(level + 1) * n, Rs + r * ublk + (size_t)k.ext * n,
-                                  A.bconv + (size_t)r * (level + 1) * n, get_pinv(ctx, level), nullptr, 0, level, 0, nullptr,
-                                  st, 1);
-        return CM_OK;
-    }
     FinishBatch fb;
     fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
@@ -873,7 +839,7 @@ struct RescaleTabs {
 static cm_status rescale_core(cm_ctx *ctx, const RescaleTabs &k, const u64 *in, int ncomp, int level, u64 *out,
                               hipStream_t st, u64 *last, u64 *red, bool accumulate) {
     launch_ntt_src(ctx, last, nullptr, in, k.last_rows, k.last_mods, ncomp, true, st);
-    const bool fused = ctx->n == 65536 && ncomp % 2 == 0;
+    const bool fused = ncomp % 2 == 0;
     // the residues of the last limb enter the transforms of the other limbs reduced to their moduli; where the last
     // modulus is below twice the others the first pass of the fused transform takes them as they are (the transform is
     // linear and its output canonical, so the result is the same) and the reduction pass is not run
@@ -916,7 +882,7 @@ cm_status rescale_into(cm_ctx *ctx, const u64 *in, int ncomp, int level, u64 *ou
 bool rescale_masked_into(cm_ctx *ctx, const MulPtBatch &mb, int cnt, const u64 *pt, int level, u64 *out, hipStream_t st,
                          u64 *last, u64 *red, bool accumulate) {
     const KsLevelFull &k = ks_level_full(ctx, level);
-    if (ctx->n != 65536 || !k.last_fits || cnt < 1 || cnt > CM_KS_BATCH || !last || !red) return false;
+    if (!k.last_fits || cnt < 1 || cnt > CM_KS_BATCH || !last || !red) return false;
     if (ctx->two_step_masks) return false;                  // CM_OPT_TWO_STEP_MASKS: multiply, store, then rescale
     launch_mul_pt_rot_last(ctx, last, mb, cnt, pt, level + 1, st);
     launch_ntt(ctx, last, k.d_last_mods, 2 * cnt, true, st);
