@@ -55,6 +55,23 @@ __device__ __forceinline__ u64 addmod(u64 a, u64 b, u64 q) {
 }
 __device__ __forceinline__ u64 submod(u64 a, u64 b, u64 q) { return a >= b ? a - b : a + q - b; }
 
+// Sum of products d * w with d below 2^50 held as two 25-bit halves (d = d0 + 2^25 d1) and w any 64-bit word: four
+// 32 x 32 -> 64-bit multiply-adds into four accumulators that cannot overflow for up to 16 terms (each term is below
+// 2^57), so a product costs four instructions and no carry chain; the accumulators are combined once per sum.  The
+// generic form (64 x 64 -> 128 with carries, about ten instructions) stays for the 60-bit moduli.
+struct Acc50 {
+    u64 t00 = 0, t01 = 0, t10 = 0, t11 = 0;
+    __device__ __forceinline__ void mac(unsigned d0, unsigned d1, u64 w) {
+        const unsigned w0 = (unsigned)w, w1 = (unsigned)(w >> 32);
+        t00 += (u64)d0 * w0, t01 += (u64)d0 * w1, t10 += (u64)d1 * w0, t11 += (u64)d1 * w1;
+    }
+    __device__ __forceinline__ u128 total() const {
+        return (u128)t00 + ((u128)t01 << 32) + ((u128)t10 << 25) + ((u128)t11 << 57);
+    }
+};
+#define LOW25 0x1FFFFFFu
+#define LOW30 0x3FFFFFFFu
+
 // Position i of the evaluation order holds the value at psi^(2 brev(i) + 1); the Galois map
 // X -> X^g moves the value at exponent e*g to exponent e: out[i] = in[perm_src(i, g)].  It maps
 // aligned blocks of 2^k positions onto aligned blocks (and i^1 to src^1).
@@ -82,19 +99,31 @@ struct ConvTable {            // fast base conversion src -> dst (all indices in
     std::vector<u64> inv_hat;     // [ns]   (hat_m^{-1} mod q_m), plain
     std::vector<u64> inv_hat_sh;  // [ns]   Shoup companion
     std::vector<u64> hat_mont;    // [ns*nt] (hat_m mod r) 2^64 mod r
+    std::vector<u64> hat;         // [ns*nt] hat_m mod r
     std::vector<int> src, dst;
 };
 
 // The same table in the form the conversion kernel reads (one per digit / per direction).
 #define CONV_MAX_SRC 8
 #define CONV_MAX_DST 64
+// split: how a product y_m * weight is formed without carry chains (all source moduli below 2^50; source moduli below 2^60
+// and target moduli below 2^50; otherwise plain 128-bit sums).  Rows past ns are zero (a zero inverse, zero weights, input
+// row 0), so that a kernel may run over a fixed number of sources.
+enum { CONV_SPLIT_25 = 0, CONV_SPLIT_30 = 1, CONV_SPLIT_NONE = 2 };
+// one target modulus: everything the conversion to it reads, in one record
+struct ConvTarget {
+    int mod, row;                 // modulus index, output row
+    double qd, qinvd;             // the modulus and its inverse as doubles, qd = 0 from 2^50 on (integer arithmetic)
+    double w[CONV_MAX_SRC];       // hat_m mod q (exact for moduli below 2^50)
+    u64 q, qinv;                  // modulus, q^{-1} mod 2^64
+    u64 wm[CONV_MAX_SRC];         // hat_m mod q in multiplier form
+};
 struct ConvDev {
-    int ns, nt;
-    int src_mod[CONV_MAX_SRC], in_rows[CONV_MAX_SRC];
-    u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC];
-    int dst_mod[CONV_MAX_DST], out_rows[CONV_MAX_DST];
-    u64 src_q[CONV_MAX_SRC], dst_q[CONV_MAX_DST], dst_qinv[CONV_MAX_DST];   // moduli and q^{-1} mod 2^64 inline
-    u64 hat_mont[CONV_MAX_SRC * CONV_MAX_DST];      // [m * nt + r]
+    int ns, nt, split;
+    int in_rows[CONV_MAX_SRC];
+    u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC], src_q[CONV_MAX_SRC];
+    double src_qd[CONV_MAX_SRC], inv_hat_d[CONV_MAX_SRC], inv_hat_dq[CONV_MAX_SRC];   // q_m, inv_hat_m, inv_hat_m / q_m as doubles
+    ConvTarget t[CONV_MAX_DST + 1];          // one past the end may be read ahead
 };
 
 // per-kernel-family timing with HIP events on the launching stream (off unless enabled)

@@ -164,7 +164,7 @@ static ConvTable make_conv(cm_ctx *ctx, const std::vector<int> &src, const std::
     t.nt = (int)dst.size();
     t.src = src;
     t.dst = dst;
-    std::vector<u64> inv_hat(t.ns), inv_hat_sh(t.ns), hat_mont((size_t)t.ns * t.nt);
+    std::vector<u64> inv_hat(t.ns), inv_hat_sh(t.ns), hat_mont((size_t)t.ns * t.nt), hat(hat_mont.size());
     for (int m = 0; m < t.ns; m++) {
         u64 qm = ctx->mod[src[m]];
         u64 h = 1;
@@ -177,12 +177,14 @@ static ConvTable make_conv(cm_ctx *ctx, const std::vector<int> &src, const std::
             u64 hr = 1;
             for (int o = 0; o < t.ns; o++)
                 if (o != m) hr = h_mulmod(hr, ctx->mod[src[o]] % qr, qr);
+            hat[(size_t)m * t.nt + r] = hr;
             hat_mont[(size_t)m * t.nt + r] = (u64)((((u128)hr) << 64) % qr);
         }
     }
     t.inv_hat = inv_hat;
     t.inv_hat_sh = inv_hat_sh;
     t.hat_mont = hat_mont;
+    t.hat = hat;
     return t;
 }
 static void free_conv(ConvTable &) {}

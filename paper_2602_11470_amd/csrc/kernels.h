@@ -37,10 +37,6 @@ bool mask_ntt_supported(int E);
 void launch_mask_ntt_setup(cm_ctx *ctx, u64 *Mhat, const u64 *M, const u64 *tw, const u64 *einv, int E, int limbs, hipStream_t st);
 void launch_mask_ntt(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *Mhat, const u64 *tw, const u64 *einv, int nk, int E, int shared,
                      int limbs, hipStream_t st);
-// batch item z: table (z % tab_period)*tab_step (tab_period 0 = batch), input (z / in_group)*in_stride, output z*out_stride
-void launch_base_conv(cm_ctx *ctx, const ConvDev *d_tabs, int batch, int tab_step, int max_nt, u64 *out, const u64 *in,
-                      size_t in_stride, size_t out_stride, const u64 *own_src, u64 own_g, hipStream_t st,
-                      int tab_period = 0, int in_group = 1, size_t own_stride = 0);
 // (u0, u1)[ext][n] = sum_j perm_g(dig_j) * evk_j  [+ P * perm_g(c0) on the ciphertext limbs of u0]  [+ extra[2][ext][n]]
 void launch_inner_product(cm_ctx *ctx, u64 *u0, u64 *u1, const u64 *dig, const u64 *evk, int beta, int level, u64 g,
                           hipStream_t st, const u64 *c0 = nullptr, const u64 *extra = nullptr);
@@ -126,6 +122,20 @@ struct FinishBatch {
 // with src: the first pass reads row d_src_rows[i] of src for limb i (words below twice that limb's modulus) instead of conv
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st,
                            const u64 *src = nullptr, const int *d_src_rows = nullptr);
+
+// Base conversion of `batch` items and the forward transform of the results.  Item z: table (z % tab_period)*tab_step
+// (tab_period 0 = batch), input (z / in_group)*in_stride, output z*out_stride; own_src: the items' own source rows are
+// copied from it (through the Galois map own_g if non-zero).  d_rows, d_mods: the converted limbs as rows of `out` with
+// their modulus indices (d_rows null: 0, 1, 2, ..), with fb: that transform ends in the tail.
+struct ConvBatch {
+    const ConvDev *tabs = nullptr;
+    int batch = 1, tab_step = 0, max_nt = 0, tab_period = 0, in_group = 1;
+    size_t in_stride = 0, out_stride = 0, own_stride = 0;
+    const u64 *own_src = nullptr;
+    unsigned own_g = 0;
+};
+void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
+                     int limbs, const FinishBatch *fb = nullptr);
 
 // ops.hip internals shared with vmm.hip
 bool rescale_masked_into(cm_ctx *ctx, const MulPtBatch &mb, int cnt, const u64 *pt, int level, u64 *out, hipStream_t st,

@@ -344,114 +344,6 @@ void launch_automorphism(cm_ctx *ctx, u64 *out, const u64 *in, int rows, u64 g, 
     hipLaunchKernelGGL(k_automorphism, dim3(ctx->n / TPB, rows), dim3(TPB), 0, st, out, in, ctx->n, ctx->logn, (unsigned)g);
 }
 
-// Sum of products d * w with d below 2^50 held as two 25-bit halves (d = d0 + 2^25 d1) and w any 64-bit word: four
-// 32 x 32 -> 64-bit multiply-adds into four accumulators that cannot overflow for up to 16 terms (each term is below
-// 2^57), so a product costs four instructions and no carry chain; the accumulators are combined once per sum.  The
-// generic form (64 x 64 -> 128 with carries, about ten instructions) stays for the 60-bit moduli.
-struct Acc50 {
-    u64 t00 = 0, t01 = 0, t10 = 0, t11 = 0;
-    __device__ __forceinline__ void mac(unsigned d0, unsigned d1, u64 w) {
-        const unsigned w0 = (unsigned)w, w1 = (unsigned)(w >> 32);
-        t00 += (u64)d0 * w0, t01 += (u64)d0 * w1, t10 += (u64)d1 * w0, t11 += (u64)d1 * w1;
-    }
-    __device__ __forceinline__ u128 total() const {
-        return (u128)t00 + ((u128)t01 << 32) + ((u128)t10 << 25) + ((u128)t11 << 57);
-    }
-};
-#define LOW25 0x1FFFFFFu
-// converted limbs are written with non-temporal stores (next read by the transform kernel, after the whole launch)
-#define CONV_ST(ptr, val) __builtin_nontemporal_store((u64)(val), (ptr))
-// ---- fast base conversion ----------------------------------------------------------------------
-// in rows in_rows[m] (coefficient domain, residues under src moduli) -> out rows out_rows[r]:
-//   y_m = a_m * inv_hat_m mod q_m;  out_r = sum_m y_m * hat_{m,r} mod q_r   (no correction term)
-// blockIdx.z = batch item: table (z % tab_period)*tab_step, input at (z / in_group)*in_stride,
-// output at z*out_stride (the digits of a raise use one table each and share the input; the two
-// components of a ModDown share the table; a raise of several polynomials runs its digits over
-// z % beta and its polynomials over z / beta).  blockIdx.y = group of CONV_TG targets; the cheap y_m are recomputed per group so
-// that a conversion fills the machine.  If own_src is given, group 0 also copies the source rows
-// of own_src (the evaluation-domain input) to the same rows of the output.
-// NS = compile-time bound on the source count: the table rows past ns are all zero (a zero inverse, a zero modulus, zero
-// weights, input row 0), so the arithmetic runs unconditionally over NS rows and every load of a lane is in flight at once
-// instead of one load-wait-use chain per source.
-template <int CONV_TG, int NS>
-__global__ __launch_bounds__(TPB) void k_base_conv(u64 *__restrict__ out, const u64 *__restrict__ in,
-                                                   const ConvDev *__restrict__ tabs, int tab_step, int tab_period,
-                                                   int in_group, int n, size_t in_stride, size_t out_stride,
-                                                   const u64 *__restrict__ own_src, size_t own_stride, unsigned own_g,
-                                                   int logn) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    const ConvDev &t = tabs[(blockIdx.z % tab_period) * tab_step];
-    const int ns = t.ns, nt = t.nt;
-    const int r0 = blockIdx.y * CONV_TG;
-    if (r0 >= nt) return;
-    in += (blockIdx.z / in_group) * in_stride;
-    out += blockIdx.z * out_stride;
-    u64 x[NS], y[NS];
-#pragma unroll
-    for (int m = 0; m < NS; m++) x[m] = in[(size_t)t.in_rows[m] * n + i];
-    if (own_src && r0 == 0) {
-        own_src += (blockIdx.z / in_group) * own_stride;
-        const unsigned s = own_g ? perm_src((unsigned)i, own_g, logn) : (unsigned)i;
-        u64 o[NS];
-#pragma unroll
-        for (int m = 0; m < NS; m++) o[m] = own_src[(size_t)t.in_rows[m] * n + s];
-#pragma unroll
-        for (int m = 0; m < NS; m++)
-            if (m < ns) out[(size_t)t.in_rows[m] * n + i] = o[m];
-    }
-#pragma unroll
-    for (int m = 0; m < NS; m++) y[m] = mul_shoup(x[m], t.inv_hat[m], t.inv_hat_sh[m], t.src_q[m]);
-    // source moduli below 2^50 (the digits of a ModUp): carry-free split products, four multiply-adds per term
-    u64 qmax = 0;
-#pragma unroll
-    for (int m = 0; m < NS; m++) qmax = t.src_q[m] > qmax ? t.src_q[m] : qmax;
-    if (qmax < (1ULL << 50)) {
-        unsigned y0[NS], y1[NS];
-#pragma unroll
-        for (int m = 0; m < NS; m++) y0[m] = (unsigned)y[m] & LOW25, y1[m] = (unsigned)(y[m] >> 25);
-#pragma unroll
-        for (int rr = 0; rr < CONV_TG; rr++) {
-            const int r = r0 + rr;
-            if (r < nt) {
-                Acc50 acc;
-#pragma unroll
-                for (int m = 0; m < NS; m++) acc.mac(y0[m], y1[m], t.hat_mont[m * nt + r]);
-                CONV_ST(out + (size_t)t.out_rows[r] * n + i, redc(acc.total(), t.dst_q[r], t.dst_qinv[r]));
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int rr = 0; rr < CONV_TG; rr++) {
-        const int r = r0 + rr;
-        if (r < nt) {
-            u128 acc = 0;
-#pragma unroll
-            for (int m = 0; m < NS; m++) acc += (u128)y[m] * t.hat_mont[m * nt + r];
-            CONV_ST(out + (size_t)t.out_rows[r] * n + i, redc(acc, t.dst_q[r], t.dst_qinv[r]));
-        }
-    }
-}
-void launch_base_conv(cm_ctx *ctx, const ConvDev *d_tabs, int batch, int tab_step, int max_nt, u64 *out, const u64 *in,
-                      size_t in_stride, size_t out_stride, const u64 *own_src, u64 own_g, hipStream_t st, int tab_period,
-                      int in_group, size_t own_stride) {
-    if (tab_period <= 0) tab_period = batch;
-    Prof prof_(ctx, CM_K_BASE_CONV, batch * max_nt, st);
-    // 8 targets per lane (measured best of 2 / 4 / 8 / 12 / 24 at the benchmark's shapes); the source bound is the larger
-    // of the digit size and the special prime count, rounded up to an instantiated one
-    const int TG = 8, ns = ctx->alpha > ctx->K ? ctx->alpha : ctx->K;
-    const dim3 grid(ctx->n / TPB, (max_nt + TG - 1) / TG, batch);
-#define CONV_LAUNCH(NS_)                                                                                                 \
-    hipLaunchKernelGGL((k_base_conv<8, NS_>), grid, dim3(TPB), 0, st, out, in, d_tabs, tab_step, tab_period, in_group, ctx->n, \
-                       in_stride, out_stride, own_src, own_stride, (unsigned)own_g, ctx->logn)
-    if (ns <= 1) CONV_LAUNCH(1);
-    else if (ns <= 2) CONV_LAUNCH(2);
-    else if (ns <= 4) CONV_LAUNCH(4);
-    else if (ns <= 6) CONV_LAUNCH(6);
-    else CONV_LAUNCH(8);
-#undef CONV_LAUNCH
-}
-
 // ---- evaluation-key inner product ------------------------------------------------------------------
 // u0[r] = sum_j dig[j][r] * evk[j][0][mod(r)],  u1 likewise with evk[j][1]; r over the level's
 // extended basis.  With g != 0 the digits are read through the Galois permutation (hoisted

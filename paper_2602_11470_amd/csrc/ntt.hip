@@ -38,6 +38,16 @@ struct NttTables {
     int stream_loads;
 };
 
+// element idx of a uniform array by a 32-bit byte offset (one register and the scalar base, no 64-bit address arithmetic)
+template <class T>
+__device__ __forceinline__ T *word_at(T *base, unsigned idx) {
+    return (T *)((char *)base + idx * (unsigned)sizeof(T));
+}
+template <class T>
+__device__ __forceinline__ const T *word_at(const T *base, unsigned idx) {
+    return (const T *)((const char *)base + idx * (unsigned)sizeof(T));
+}
+
 // ---- integer arithmetic --------------------------------------------------------------------------
 // Residues stay lazy: a value is only kept below 2^64, i.e. below 16 q (8 q for 61-bit moduli, `tight`).  A product by a
 // Shoup twiddle drops the low partial products of its quotient (at most two units too small), so it lies in [0, 4q)
@@ -68,6 +78,9 @@ struct IntArith {
     __device__ __forceinline__ T from_mid(u64 raw) const { return raw; }
     __device__ __forceinline__ u64 to_mid(T v) const { return v; }
     typedef u64 W;
+    struct Word { u64 w, wp; };
+    __device__ __forceinline__ Word word(unsigned idx) const { return Word{*word_at(w, idx), *word_at(wp, idx)}; }
+    __device__ __forceinline__ void pair(const Word &x, W &a, W &b) const { a = x.w, b = x.wp; }
     __device__ __forceinline__ u64 mul_lazy(u64 a, u64 x, u64 xp) const {     // a x mod q in [0, 4q)
         const unsigned a0 = (unsigned)a, a1 = (unsigned)(a >> 32), p0 = (unsigned)xp, p1 = (unsigned)(xp >> 32);
         const u64 h = (u64)a1 * p1 + ((u64)__umulhi(a1, p0) + __umulhi(a0, p1));
@@ -95,12 +108,13 @@ struct IntArith {
             for (int k = 0; k < NV; k++) v[k] = fold(v[k]);
         }
     }
-    // stage a (3 first): the sums sit where bit 3 - a of the index is clear
-    __device__ __forceinline__ void after_inv(int a, T (&v)[16]) const {
-        if (!(a & 1) || tight) {
+    // stage s (the last one first): the sums sit where bit `half` of the index is clear
+    template <int NV>
+    __device__ __forceinline__ void after_inv(int s, int half, T (&v)[NV]) const {
+        if (!(s & 1) || tight) {
 #pragma unroll
-            for (int k = 0; k < 16; k++)
-                if (!(k & (8 >> a))) v[k] = fold(v[k]);
+            for (int k = 0; k < NV; k++)
+                if (!(k & half)) v[k] = fold(v[k]);
         }
     }
     __device__ __forceinline__ u64 to_rest_fwd(T v) const { return v >= q ? v - q : v; }
@@ -132,9 +146,13 @@ struct FpArith {
     __device__ __forceinline__ T from_mid(u64 raw) const { return __longlong_as_double((long long)raw); }
     __device__ __forceinline__ u64 to_mid(T v) const { return (u64)__double_as_longlong(v); }
     typedef double W;
+    typedef double Word;
+    __device__ __forceinline__ Word word(unsigned idx) const { return *word_at(w, idx); }
+    __device__ __forceinline__ void pair(Word x, W &a, W &b) const { a = x, b = x * qinv; }
     template <int NV>
     __device__ __forceinline__ void after_fwd(int, T (&)[NV]) const {}
-    __device__ __forceinline__ void after_inv(int, T (&)[16]) const {}
+    template <int NV>
+    __device__ __forceinline__ void after_inv(int, int, T (&)[NV]) const {}
     // With table twiddles (0 <= w < q, w/q correctly rounded) |r| <= 1.04 q; with generated ones
     // (|w| <= 0.9 q, w/q taken as w * (1/q)) |r| <= 1.2 q.  Either way every value stays below 2.1 q.
     __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {
@@ -164,32 +182,32 @@ struct FpArith {
 // them; FP64 limbs take the second factor w/q as w * (1/q), one multiplication instead
 // of a second table: the quotient estimate may then be off by one more unit, the product stays exact
 // (|r| <= 1.3 q for |y| <= 2.1 q).
-template <class A>
-struct TableTw;
-template <>
-struct TableTw<IntArith> {
-    u64 w[15], wp[15];
-    __device__ __forceinline__ TableTw(const IntArith &ar, u64 b0) {
+template <class A, int ST, int NB = 1>          // ST stages on NB adjacent blocks
+struct Tw {
+    const A &ar;
+    typename A::Word w[NB][(1 << ST) - 1];
+    __device__ __forceinline__ Tw(const A &a_, unsigned b0) : ar(a_) {
 #pragma unroll
-        for (int a = 0; a < 4; a++)
+        for (int b = 0; b < NB; b++)
 #pragma unroll
-            for (int g = 0; g < (1 << a); g++) w[(1 << a) - 1 + g] = ar.w[(b0 << a) + g], wp[(1 << a) - 1 + g] = ar.wp[(b0 << a) + g];
+            for (int a = 0; a < ST; a++)
+#pragma unroll
+                for (int g = 0; g < (1 << a); g++) w[b][(1 << a) - 1 + g] = ar.word(((b0 + b) << a) + g);
     }
-    __device__ __forceinline__ void get(int a, int g, u64 &w0, u64 &w1) const { w0 = w[(1 << a) - 1 + g], w1 = wp[(1 << a) - 1 + g]; }
+    __device__ __forceinline__ void get(int b, int a, int g, typename A::W &w0, typename A::W &w1) const {
+        ar.pair(w[b][(1 << a) - 1 + g], w0, w1);
+    }
 };
-template <>
-struct TableTw<FpArith> {
-    const FpArith &ar;
-    double w[15];
-    __device__ __forceinline__ TableTw(const FpArith &a_, u64 b0) : ar(a_) {
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int g = 0; g < (1 << a); g++) w[(1 << a) - 1 + g] = ar.w[(b0 << a) + g];
-    }
-    __device__ __forceinline__ void get(int a, int g, double &w0, double &w1) const {
-        w0 = w[(1 << a) - 1 + g];
-        w1 = w0 * ar.qinv;
+template <class A>
+using TableTw = Tw<A, 4>;
+// the same entries read where they are used, for kernels that have no registers to hold them
+template <class A, int ST, int NB = 1>
+struct LazyTw {
+    const A &ar;
+    unsigned b0;
+    __device__ __forceinline__ LazyTw(const A &a_, unsigned b0_) : ar(a_), b0(b0_) {}
+    __device__ __forceinline__ void get(int b, int a, int g, typename A::W &w0, typename A::W &w1) const {
+        ar.pair(ar.word(((b0 + b) << a) + g), w0, w1);
     }
 };
 // The same entries computed from ONE table word (FP64 limbs): with T_a = tw[base0 << a],
@@ -205,50 +223,60 @@ struct GenTw {
         T[1] = ar.mulmod(T[2], T[2], T[2] * ar.qinv);
         T[0] = ar.mulmod(T[1], T[1], T[1] * ar.qinv);
     }
-    __device__ __forceinline__ void get(int a, int g, double &w0, double &w1) const {
+    __device__ __forceinline__ void get(int, int a, int g, double &w0, double &w1) const {
         w0 = g ? ar.mulmod(T[a], ar.w[g], ar.wq[g]) : T[a];
         w1 = w0 * ar.qinv;
     }
 };
 
-// Four forward stages on 16 register values whose index k is the local position inside one
-// butterfly block of the first of these stages.
-template <class A, class TW>
-__device__ __forceinline__ void radix16_fwd_tw(typename A::T (&v)[16], const A &ar, const TW &tw) {
+// ST forward stages, the first of them stage S0 of the transform, on NB blocks of 2^ST register values whose index is the
+// local position inside one butterfly block of the first of these stages.
+template <int ST, int NB, int S0, class A, class TW>
+__device__ __forceinline__ void radix_fwd(typename A::T (&v)[NB << ST], const A &ar, const TW &tw) {
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
-        const int half = 8 >> a;
+    for (int a = 0; a < ST; a++) {
+        const int half = (1 << ST) >> (a + 1);
 #pragma unroll
-        for (int g = 0; g < (1 << a); g++) {
-            typename A::W w0, w1;
-            tw.get(a, g, w0, w1);
+        for (int b = 0; b < NB; b++)
 #pragma unroll
-            for (int j = 0; j < half; j++) {
-                int k = g * 2 * half + j;
-                ar.ct(v[k], v[k + half], w0, w1);
+            for (int g = 0; g < (1 << a); g++) {
+                typename A::W w0, w1;
+                tw.get(b, a, g, w0, w1);
+#pragma unroll
+                for (int j = 0; j < half; j++) {
+                    const int k = (b << ST) + g * 2 * half + j;
+                    ar.ct(v[k], v[k + half], w0, w1);
+                }
             }
-        }
-        ar.after_fwd(a, v);
+        ar.after_fwd(S0 + a, v);
     }
 }
-// The inverse of the above (stages in the opposite order).
 template <class A, class TW>
-__device__ __forceinline__ void radix16_inv_tw(typename A::T (&v)[16], const A &ar, const TW &tw) {
+__device__ __forceinline__ void radix16_fwd_tw(typename A::T (&v)[16], const A &ar, const TW &tw) {
+    radix_fwd<4, 1, 0>(v, ar, tw);
+}
+// The inverse of the above (stages in the opposite order).
+template <int ST, int S0, class A, class TW>
+__device__ __forceinline__ void radix_inv(typename A::T (&v)[1 << ST], const A &ar, const TW &tw) {
 #pragma unroll
-    for (int a = 3; a >= 0; a--) {
-        const int half = 8 >> a;
+    for (int a = ST - 1; a >= 0; a--) {
+        const int half = (1 << ST) >> (a + 1);
 #pragma unroll
         for (int g = 0; g < (1 << a); g++) {
             typename A::W w0, w1;
-            tw.get(a, g, w0, w1);
+            tw.get(0, a, g, w0, w1);
 #pragma unroll
             for (int j = 0; j < half; j++) {
-                int k = g * 2 * half + j;
+                const int k = g * 2 * half + j;
                 ar.gs(v[k], v[k + half], w0, w1);
             }
         }
-        ar.after_inv(a, v);
+        ar.after_inv(S0 + a, half, v);
     }
+}
+template <class A, class TW>
+__device__ __forceinline__ void radix16_inv_tw(typename A::T (&v)[16], const A &ar, const TW &tw) {
+    radix_inv<4, 0>(v, ar, tw);
 }
 // last four stages of the row pass: generated twiddles for FP64 limbs, table for the others
 __device__ __forceinline__ void radix16_fwd_last(double (&v)[16], const FpArith &ar, u64 base0) {
@@ -429,7 +457,10 @@ __device__ __forceinline__ void transpose16(typename A::T (&v)[16], const A &ar,
 }
 
 // The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of 4096 sit in LDS.
-__device__ __forceinline__ void finish_tail(const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
+// at(e): where word e of the chunk sits.
+template <int LANES, class AT>
+__device__ __forceinline__ void finish_tail(AT at, const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
+    constexpr int NW = 4096 / LANES;
     // this limb is NTT(conv) of item r, component c, limb l
     const int per = fb.ncomp * (fb.level + 1);
     const int r = limb / per, c = fb.comp0 + (limb % per) / (fb.level + 1), l = limb % (fb.level + 1);
@@ -442,56 +473,56 @@ __device__ __forceinline__ void finish_tail(const u64 *lds, const NttTables &t, 
     u64 *op = fb.out[r] + row + pos0;
     const unsigned g = fb.g[r];
     const int logn = 31 - __clz(n);
-    // All operands of the tail are loaded first, then combined: sixteen independent loads per stream are in flight at
+    // All operands of the tail are loaded first, then combined: NW independent loads per stream are in flight at
     // once instead of one load-wait-use chain per word.
-    u64 uu[16], aa[16], cc[16];
+    u64 uu[NW], aa[NW], cc[NW];
     if (fb.mul_pt) {
         // u = u[r] * (mul_pt through the Galois map mul_g[r]), formed here instead of being read
         const u64 qinv = t.modc[l].qinv;
         const u64 *mp = fb.mul_pt + (size_t)l * n;
         const unsigned mg = fb.mul_g[r];
 #pragma unroll
-        for (int k = 0; k < 16; k++) uu[k] = up[256 * k];
+        for (int k = 0; k < NW; k++) uu[k] = up[LANES * k];
         if (mg) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) aa[k] = mp[perm_src(pos0 + 256 * k, mg, logn)];
+            for (int k = 0; k < NW; k++) aa[k] = mp[perm_src(pos0 + LANES * k, mg, logn)];
         } else {
 #pragma unroll
-            for (int k = 0; k < 16; k++) aa[k] = mp[pos0 + 256 * k];
+            for (int k = 0; k < NW; k++) aa[k] = mp[pos0 + LANES * k];
         }
         if (ac) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) cc[k] = TAIL_LD(ac + 256 * k);
+            for (int k = 0; k < NW; k++) cc[k] = TAIL_LD(ac + LANES * k);
         }
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
+        for (int k = 0; k < NW; k++) {
             const u64 uv = redc((u128)uu[k] * aa[k], q, qinv);
-            u64 x = mul_shoup(submod(uv, lds[pad(threadIdx.x + 256 * k)], q), pi, pis, q);
+            u64 x = mul_shoup(submod(uv, lds[at(threadIdx.x + LANES * k)], q), pi, pis, q);
             if (ac) x = addmod(x, cc[k], q);
-            TAIL_ST(op + 256 * k, x);
+            TAIL_ST(op + LANES * k, x);
         }
         return;
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) uu[k] = up[256 * k];
+    for (int k = 0; k < NW; k++) uu[k] = up[LANES * k];
     if (ad && g) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) aa[k] = ad[perm_src(pos0 + 256 * k, g, logn)];
+        for (int k = 0; k < NW; k++) aa[k] = ad[perm_src(pos0 + LANES * k, g, logn)];
     } else if (ad) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) aa[k] = ad[pos0 + 256 * k];
+        for (int k = 0; k < NW; k++) aa[k] = ad[pos0 + LANES * k];
     }
     if (ac) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) cc[k] = ac[256 * k];
+        for (int k = 0; k < NW; k++) cc[k] = ac[LANES * k];
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        u64 d = submod(uu[k], lds[pad(threadIdx.x + 256 * k)], q);
+    for (int k = 0; k < NW; k++) {
+        u64 d = submod(uu[k], lds[at(threadIdx.x + LANES * k)], q);
         u64 x = mul_shoup(d, pi, pis, q);
         if (ad) x = addmod(x, aa[k], q);
         if (ac) x = addmod(x, cc[k], q);
-        op[256 * k] = x;
+        op[LANES * k] = x;
     }
 }
 
@@ -530,7 +561,7 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
         for (int k = 0; k < 16; k++) NTT_ST(p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
         return;
     }
-    finish_tail(lds, t, n, chunk, limb, fb);
+    finish_tail<NTT_THREADS>(pad, lds, t, n, chunk, limb, fb);
 }
 template <class A>
 __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
@@ -604,114 +635,143 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
 }
 
 // ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
-// The limb is one 256 x 16 tile: eight stages down the columns as above, then the last four on rows of 16 contiguous
-// words, one row per lane, all exchanges in LDS.  Bound by the chain of its twelve stages, not by bytes (32 KiB per
-// limb): the limb used to take two launches, a column and a row pass, and at 2 to 25 limbs a launch costs its few
-// microseconds whatever it moves.  With the ModDown / rescale tail in the same kernel a rotation of the 5 + 1 ring went
-// from 12 launches to 7, a 64 x 64 product on it (11 rotations) from 693 to 562 us.
+// 512 lanes with eight words each run the twelve stages as radix 8 x 8 x 8 x 8, all exchanges in LDS.  Bound by the chain of
+// its stages, not by bytes (32 KiB per limb): as a column and a row pass the limb took two launches, and at 2 to 25 limbs
+// a launch costs its few microseconds whatever it moves.  Eight words a lane keep two waves on every SIMD of the one
+// compute unit a limb has; with 256 lanes of sixteen words each wave is alone on its SIMD and waits out every latency.
+// A 64 x 64 product on the 5 + 1 ring (11 rotations): 693 us with two passes and separate conversion and tail, 562 us with
+// whole limbs and the tail, 483 us with eight words a lane and the conversion in front.
+#define FULL_THREADS 512
+#define FULL_LDS (4096 + 512)
+// one pad word per eight: lanes eight words apart, and runs of eight 64 words apart, hit distinct banks
+__device__ __forceinline__ int pad8(int e) { return e + (e >> 3); }
+// v[k] = word tid + 512 k
 template <class A, bool TAIL>
-__device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int limb,
+__device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&v)[8], const A &ar, const NttTables &t, int n, int limb,
                                               const FinishBatch &fb) {
-    A ar;
-    ar.init(t, mi, n);
-    const int tid = threadIdx.x, c = tid & 15, sub = tid >> 4;
-    typename A::T v[16];
-    u64 raw[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) raw[k] = ps[(sub + 16 * k) * 16 + c];
+    const int tid = threadIdx.x, h2 = tid >> 6, l2 = tid & 63, h3 = tid >> 3, l3 = tid & 7;
     {
-        const TableTw<A> tw(ar, 1);
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_rest(raw[k]);
-        radix16_fwd_tw(v, ar, tw);
+        const Tw<A, 3> tw(ar, 1);
+        radix_fwd<3, 1, 0>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad((sub + 16 * k) * 16 + c)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(k * 512 + tid)] = ar.to_mid(v[k]);
     {
-        const TableTw<A> tw(ar, 16 + sub);
+        const Tw<A, 3> tw(ar, 8 + h2);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
-        radix16_fwd_tw(v, ar, tw);
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h2 * 512 + k * 64 + l2)]);
+        radix_fwd<3, 1, 3>(v, ar, tw);
     }
-    // a lane writes back the words it read, then takes row tid
+    // every lane writes back the words it read, so one barrier per exchange is enough
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad((16 * sub + k) * 16 + c)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(h2 * 512 + k * 64 + l2)] = ar.to_mid(v[k]);
     {
-        const TableTw<A> tw(ar, 256 + tid);
+        const Tw<A, 3> tw(ar, 64 + h3);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(tid * 16 + k)]);
-        radix16_fwd_tw(v, ar, tw);
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h3 * 64 + k * 8 + l3)]);
+        radix_fwd<3, 1, 6>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad(tid * 16 + k)] = ar.to_rest_fwd(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(h3 * 64 + k * 8 + l3)] = ar.to_mid(v[k]);
+    {
+        const Tw<A, 3> tw(ar, 512 + tid);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(tid * 8 + k)]);
+        radix_fwd<3, 1, 9>(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) lds[pad8(tid * 8 + k)] = ar.to_rest_fwd(v[k]);
     __syncthreads();
     if (TAIL) {
-        finish_tail(lds, t, n, 0, limb, fb);
+        finish_tail<FULL_THREADS>(pad8, lds, t, n, 0, limb, fb);
         return;
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) p[tid + 256 * k] = lds[pad(tid + 256 * k)];
+    for (int k = 0; k < 8; k++) p[tid + 512 * k] = lds[pad8(tid + 512 * k)];
 }
 template <class A>
 __device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n) {
     A ar;
     ar.init(t, mi, n);
-    const int tid = threadIdx.x, c = tid & 15, sub = tid >> 4;
-    typename A::T v[16];
+    const int tid = threadIdx.x, h2 = tid >> 6, l2 = tid & 63, h3 = tid >> 3, l3 = tid & 7;
+    typename A::T v[8];
     {
         const int logn = 31 - __clz(n);
-        u64 w[16];
+        u64 w[8];
 #pragma unroll
-        for (int k = 0; k < 16; k++) w[k] = ps[g ? perm_src((unsigned)(tid + 256 * k), g, logn) : tid + 256 * k];
+        for (int k = 0; k < 8; k++) w[k] = ps[g ? perm_src((unsigned)(tid + 512 * k), g, logn) : tid + 512 * k];
 #pragma unroll
-        for (int k = 0; k < 16; k++) lds[pad(tid + 256 * k)] = w[k];
-        const TableTw<A> tw(ar, 256 + tid);
+        for (int k = 0; k < 8; k++) lds[pad8(tid + 512 * k)] = w[k];
+        const Tw<A, 3> tw(ar, 512 + tid);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_rest(lds[pad(tid * 16 + k)]);
-        radix16_inv_tw(v, ar, tw);
+        for (int k = 0; k < 8; k++) v[k] = ar.from_rest(lds[pad8(tid * 8 + k)]);
+        radix_inv<3, 9>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad(tid * 16 + k)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(tid * 8 + k)] = ar.to_mid(v[k]);
     {
-        const TableTw<A> tw(ar, 16 + sub);
+        const Tw<A, 3> tw(ar, 64 + h3);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
-        radix16_inv_tw(v, ar, tw);
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h3 * 64 + k * 8 + l3)]);
+        radix_inv<3, 6>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad((16 * sub + k) * 16 + c)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(h3 * 64 + k * 8 + l3)] = ar.to_mid(v[k]);
     {
-        const TableTw<A> tw(ar, 1);
+        const Tw<A, 3> tw(ar, 8 + h2);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((sub + 16 * k) * 16 + c)]);
-        radix16_inv_tw(v, ar, tw);
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h2 * 512 + k * 64 + l2)]);
+        radix_inv<3, 3>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 16; k++) p[(sub + 16 * k) * 16 + c] = ar.to_rest_inv(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(h2 * 512 + k * 64 + l2)] = ar.to_mid(v[k]);
+    {
+        const Tw<A, 3> tw(ar, 1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(k * 512 + tid)]);
+        radix_inv<3, 0>(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) p[k * 512 + tid] = ar.to_rest_inv(v[k]);
 }
 // grid.x = limbs.  The transform may run in place: every word is read before the first is written.
+template <class A, bool TAIL>
+__device__ __forceinline__ void full_fwd_load(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int limb,
+                                              const FinishBatch &fb) {
+    A ar;
+    ar.init(t, mi, n);
+    typename A::T v[8];
+    u64 raw[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) raw[k] = ps[threadIdx.x + 512 * k];
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = ar.from_rest(raw[k]);
+    full_fwd_body<A, TAIL>(lds, p, v, ar, t, n, limb, fb);
+}
 template <bool TAIL>
-__global__ __launch_bounds__(NTT_THREADS) void ntt_full_fwd(u64 *data, const u64 *src, const int *__restrict__ src_rows,
-                                                           const int *__restrict__ rows, const int *__restrict__ mod_idx,
-                                                           NttTables t, int n, FinishBatch fb) {
-    __shared__ u64 lds[LDS_WORDS];
+__global__ __launch_bounds__(FULL_THREADS) void ntt_full_fwd(u64 *data, const u64 *src, const int *__restrict__ src_rows,
+                                                            const int *__restrict__ rows, const int *__restrict__ mod_idx,
+                                                            NttTables t, int n, FinishBatch fb) {
+    __shared__ u64 lds[FULL_LDS];
     const int limb = blockIdx.x, mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p;
     if (t.fpq[mi].q != 0.0)
-        full_fwd_body<FpArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
+        full_fwd_load<FpArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
     else
-        full_fwd_body<IntArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
+        full_fwd_load<IntArith, TAIL>(lds, p, ps, t, mi, n, limb, fb);
 }
-__global__ __launch_bounds__(NTT_THREADS) void ntt_full_inv(u64 *data, const u64 *src, const int *__restrict__ src_rows,
-                                                           const int *__restrict__ rows, const int *__restrict__ mod_idx,
-                                                           NttTables t, int n, unsigned g) {
-    __shared__ u64 lds[LDS_WORDS];
+__global__ __launch_bounds__(FULL_THREADS) void ntt_full_inv(u64 *data, const u64 *src, const int *__restrict__ src_rows,
+                                                            const int *__restrict__ rows, const int *__restrict__ mod_idx,
+                                                            NttTables t, int n, unsigned g) {
+    __shared__ u64 lds[FULL_LDS];
     const int limb = blockIdx.x, mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p;
@@ -719,6 +779,301 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_full_inv(u64 *data, const u64
         full_inv_body<FpArith>(lds, p, ps, g, t, mi, n);
     else
         full_inv_body<IntArith>(lds, p, ps, g, t, mi, n);
+}
+
+// ---- fast base conversion, fused into the first pass of the forward transform of its results --------------------------
+// in rows in_rows[m] (coefficient domain, residues under the source moduli) -> out rows out_rows[r]:
+//   y_m = a_m * inv_hat_m mod q_m;  out_r = transform of sum_m y_m * hat_{m,r} mod q_r   (no correction term)
+// Batch item z: table (z % tab_period)*tab_step, input at (z / in_group)*in_stride, output at z*out_stride (the digits of
+// a raise use one table each and share the input; the two components of a ModDown share the table; a raise of several
+// polynomials runs its digits over z % period and its polynomials over z / in_group).  If own_src is given the source rows
+// of own_src (the evaluation-domain input, through the Galois map own_g if any) are copied to the same rows of the output.
+struct ConvArgs {
+    const ConvDev *tabs;
+    int tab_step, tab_period, in_group;
+    size_t in_stride, out_stride, own_stride;
+    const u64 *own_src;
+    unsigned own_g;
+    int tg, groups;               // targets per workgroup, workgroups that convert per (tile, item) (n = 65536)
+};
+// an empty statement that the compiler must take as a new value of x: values derived from x are not loop-invariant
+#define OPAQUE(x) asm volatile("" : "+v"(x))
+// The y_m of NV words.  Source moduli below 2^50 (the digits of a raise): exact integers in doubles; a product with a
+// weight under an FP64 target modulus is then the butterflies' product (6 instructions and an addition per term, no
+// carries), under a 60-bit one a split product (Acc50).  Larger sources (the special primes of a ModDown): 30 + 30 bit
+// halves against 25 + 25 bits of the weight, again without carry chains.  Otherwise 128-bit sums.
+// The integer sums are worked on one word after the other (sched_barrier): interleaving them costs more registers than a
+// wave has to spare.
+template <int NS, int NV>
+struct ConvY {
+    unsigned lo[NV][NS], hi[NV][NS];
+    __device__ __forceinline__ void set(const ConvDev &t, const u64 (&x)[NV][NS]) {
+        if (t.split == CONV_SPLIT_25) {
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                const double q = t.src_qd[m], w = t.inv_hat_d[m], wq = t.inv_hat_dq[m];
+#pragma unroll
+                for (int k = 0; k < NV; k++) {
+                    const double v = __longlong_as_double((long long)(x[k][m] | 0x4330000000000000ULL)) - TWO52;
+                    const double h = v * w, l = __builtin_fma(v, w, -h), c = __builtin_rint(v * wq);
+                    double y = __builtin_fma(-c, q, h) + l;                  // |y| < q
+                    y += y < 0.0 ? q : 0.0;
+                    lo[k][m] = (unsigned)__double2loint(y), hi[k][m] = (unsigned)__double2hiint(y);
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                const u64 y = mul_shoup(x[k][m], t.inv_hat[m], t.inv_hat_sh[m], t.src_q[m]);
+                lo[k][m] = (unsigned)y, hi[k][m] = (unsigned)(y >> 32);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ double yd(int k, int m) const { return __hiloint2double((int)hi[k][m], (int)lo[k][m]); }
+    // keep what is derived from the words (64-bit pairs of their halves) from being hoisted out of a loop over the targets
+    __device__ __forceinline__ void opaque() {
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                OPAQUE(lo[k][m]);
+                OPAQUE(hi[k][m]);
+            }
+    }
+    // targets below 2^50: |v| <= 0.6 q.  |y w - c q| <= 0.88 q per term (c off by three roundings of a value below 2^50), so
+    // the sum of eight terms stays below 2^53 and exact.
+    __device__ __forceinline__ void target_fp(const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
+        double w[NS], wq[NS];
+#pragma unroll
+        for (int m = 0; m < NS; m++) w[m] = o.w[m], wq[m] = w[m] * ar.qinv;
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            double s = ar.mulmod(yd(k, 0), w[0], wq[0]);
+#pragma unroll
+            for (int m = 1; m < NS; m++) s += ar.mulmod(yd(k, m), w[m], wq[m]);
+            v[k] = NS > 1 ? ar.norm(s) : s;
+        }
+    }
+    __device__ __forceinline__ void target_any(int split, const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
+        if (split == CONV_SPLIT_25) {
+            target_fp(o, ar, v);
+        } else {
+            u64 x[NV];
+            target(split, o, x);
+#pragma unroll
+            for (int k = 0; k < NV; k++) v[k] = ar.from_rest(x[k]);
+        }
+    }
+    __device__ __forceinline__ void target(int split, const ConvTarget &o, u64 (&out)[NV]) const {
+        u64 w[NS];
+        const u64 q = o.q, qinv = o.qinv;
+#pragma unroll
+        for (int m = 0; m < NS; m++) w[m] = o.wm[m];
+        if (split == CONV_SPLIT_25) {
+#pragma unroll
+            for (int k = 0; k < NV; k++) {
+                Acc50 acc;
+#pragma unroll
+                for (int m = 0; m < NS; m++) {
+                    const u64 y = (u64)__double_as_longlong(yd(k, m) + TWO52) & 0x000FFFFFFFFFFFFFULL;
+                    acc.mac((unsigned)y & LOW25, (unsigned)(y >> 25), w[m]);
+                }
+                out[k] = redc(acc.total(), q, qinv);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if (split == CONV_SPLIT_30) {
+            // every term below 2^55
+#pragma unroll
+            for (int k = 0; k < NV; k++) {
+                u64 t00 = 0, t01 = 0, t10 = 0, t11 = 0;
+#pragma unroll
+                for (int m = 0; m < NS; m++) {
+                    const u64 y = ((u64)hi[k][m] << 32) | lo[k][m];
+                    const unsigned y0 = (unsigned)y & LOW30, y1 = (unsigned)(y >> 30);
+                    const unsigned w0 = (unsigned)w[m] & LOW25, w1 = (unsigned)(w[m] >> 25);
+                    t00 += (u64)y0 * w0, t01 += (u64)y0 * w1, t10 += (u64)y1 * w0, t11 += (u64)y1 * w1;
+                }
+                out[k] = redc((u128)t00 + ((u128)t01 << 25) + ((u128)t10 << 30) + ((u128)t11 << 55), q, qinv);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < NV; k++) {
+                u128 T = 0;
+#pragma unroll
+                for (int m = 0; m < NS; m++) T += (u128)(((u64)hi[k][m] << 32) | lo[k][m]) * w[m];
+                out[k] = redc(T, q, qinv);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+};
+// n = 65536.  A workgroup of 512 lanes owns a column tile (256 rows x 8 columns) of one item: every lane loads four words
+// of each source, keeps the y_m in registers and runs over up to tg targets: conversion, then stages 0..7 as radix
+// 4 x 4 x 4 x 4, the exchanges through two LDS buffers in turn (one barrier each).  The converted limbs are never stored: a
+// raise used to write and re-read them between two launches.  Bound by the vector ALU and the latency of its barriers
+// (two workgroups per compute unit, about 100 registers for four sources); 16 columns x 1024 lanes (one workgroup per
+// compute unit) is 4 % slower on a product against the value cache, 4 columns (32-byte stores) 30 %, sixteen or eight
+// words a lane run out of registers.  Measured: 1104 limbs of eight raises 188 + 242 us (conversion, column pass) -> 362 us,
+// 144 limbs 28 + 37 -> 60 us, the 8 limbs of a ModDown at level 3 5.0 + 6.8 -> 8.6 us and a launch less.
+// tg: 8 targets a workgroup, so that the y_m (as much work as one target) are formed once for eight; halved while the
+// launch has fewer than CCF_FILL = 512 workgroups (two for each compute unit); 4 and 12 measured equal and 2 % slower.
+#define CCF_W 8
+#define CCF_THREADS (64 * CCF_W)
+#define CCF_TG 8
+#define CCF_FILL 512
+// LDS: row r of 8 words at row r ^ ((r >> 2) & 3): any four rows that a half-wave touches (neighbours, or four apart) then
+// cover all banks
+template <class A, template <class, int, int> class TW>
+__device__ __forceinline__ void ccf_body(u64 *lds, int buf, u64 *p, typename A::T (&v)[4], unsigned tid, const A &ar, int n2) {
+    const int c = tid % CCF_W, sub = tid / CCF_W;
+    u64 *A0 = lds + (buf ? 256 * CCF_W : 0) + c, *B0 = lds + (buf ? 0 : 256 * CCF_W) + c;
+    {
+        const TW<A, 2, 1> tw(ar, 1);
+        radix_fwd<2, 1, 0>(v, ar, tw);
+    }
+    const int sx = sub ^ ((sub >> 2) & 3);
+#pragma unroll
+    for (int k = 0; k < 4; k++) A0[(k * 64 + sx) * CCF_W] = ar.to_mid(v[k]);             // row 64 k + sub
+    {
+        const int hi = sub >> 4;
+        const TW<A, 2, 1> tw(ar, 4 + hi);
+        const int o = (hi * 64 + (sx & 15)) * CCF_W;                                     // row 64 hi + 16 k + lo
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = ar.from_mid(A0[o + k * 16 * CCF_W]);
+        radix_fwd<2, 1, 2>(v, ar, tw);
+#pragma unroll
+        for (int k = 0; k < 4; k++) B0[o + k * 16 * CCF_W] = ar.to_mid(v[k]);
+    }
+    {
+        const int hi = sub >> 2, lo = sub & 3;
+        const TW<A, 2, 1> tw(ar, 16 + hi);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = ar.from_mid(B0[(hi * 16 + k * 4 + (lo ^ k)) * CCF_W]);     // row 16 hi + 4 k + lo
+        radix_fwd<2, 1, 4>(v, ar, tw);
+#pragma unroll
+        for (int k = 0; k < 4; k++) A0[(hi * 16 + k * 4 + (lo ^ k)) * CCF_W] = ar.to_mid(v[k]);
+    }
+    {
+        const TW<A, 2, 1> tw(ar, 64 + sub);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = ar.from_mid(A0[(sub * 4 + (k ^ (sub & 3))) * CCF_W]);     // row 4 sub + k
+        radix_fwd<2, 1, 6>(v, ar, tw);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) NTT_ST(word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
+}
+// grid: x = column tile, y = target group (the last targets, those under the 60-bit primes, first), then the copies
+template <int NS>
+__global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a,
+                                                               NttTables t, int n, int logn) {
+    __shared__ u64 lds[2 * 256 * CCF_W];
+    const ConvDev &tab = a.tabs[(blockIdx.z % a.tab_period) * a.tab_step];
+    const int ns = tab.ns, nt = tab.nt, split = tab.split, n2 = n >> 8, tile = blockIdx.x;
+    out += blockIdx.z * a.out_stride;
+    if ((int)blockIdx.y == a.groups) {
+        const u64 *src = a.own_src + (blockIdx.z / a.in_group) * a.own_stride;
+        const unsigned i0 = (unsigned)tile * (256 * CCF_W) + threadIdx.x;
+        for (int m = 0; m < ns; m++) {
+            const size_t row = (size_t)tab.in_rows[m] * n;
+            u64 w[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) w[k] = src[row + (a.own_g ? perm_src(i0 + CCF_THREADS * k, a.own_g, logn) : i0 + CCF_THREADS * k)];
+#pragma unroll
+            for (int k = 0; k < 4; k++) NTT_ST(out + row + i0 + CCF_THREADS * k, w[k]);
+        }
+        return;
+    }
+    const int r0 = (a.groups - 1 - (int)blockIdx.y) * a.tg, r1 = min(r0 + a.tg, nt);
+    if (r0 >= nt) return;
+    const int c = threadIdx.x % CCF_W, sub = threadIdx.x / CCF_W;
+    in += (blockIdx.z / a.in_group) * a.in_stride + tile * CCF_W;
+    ConvY<NS, 4> y;
+    {
+        u64 x[4][NS];
+#pragma unroll
+        for (int m = 0; m < NS; m++) {
+            const u64 *row = in + (size_t)tab.in_rows[m] * n;
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k][m] = *word_at(row, (k * 64 + sub) * n2 + c);
+        }
+        y.set(tab, x);
+    }
+    unsigned tid = threadIdx.x;
+    int buf = 0;
+    for (int r = r0; r < r1; r++, buf ^= 1) {
+        OPAQUE(tid);                     // addresses are formed anew for every target (see ConvY)
+        const ConvTarget &o = tab.t[r];
+        u64 *p = out + (size_t)o.row * n + tile * CCF_W;
+        y.opaque();
+        if (o.qd != 0.0) {
+            FpArith ar;
+            ar.init(t, o.mod, n);
+            double v[4];
+            y.target_any(split, o, ar, v);
+            ccf_body<FpArith, Tw>(lds, buf, p, v, tid, ar, n2);
+        } else {
+            IntArith ar;
+            ar.init(t, o.mod, n);
+            u64 x[4];
+            y.target(split, o, x);
+            ccf_body<IntArith, Tw>(lds, buf, p, x, tid, ar, n2);
+        }
+    }
+}
+// n = 4096: one workgroup per target limb, conversion and the whole transform.  grid: x = target, then the own rows; y = item
+template <int NS, bool TAIL>
+__global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a, NttTables t,
+                                                             int n, int logn, FinishBatch fb) {
+    __shared__ u64 lds[FULL_LDS];
+    const int z = blockIdx.y, tid = threadIdx.x;
+    const ConvDev &tab = a.tabs[(z % a.tab_period) * a.tab_step];
+    const int ns = tab.ns, nt = tab.nt, r = blockIdx.x;
+    out += z * a.out_stride;
+    if (r >= nt) {
+        if (!a.own_src || r >= nt + ns) return;
+        const size_t row = (size_t)tab.in_rows[r - nt] * n;
+        const u64 *src = a.own_src + (z / a.in_group) * a.own_stride + row;
+        u64 w[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) w[k] = src[a.own_g ? perm_src((unsigned)(tid + 512 * k), a.own_g, logn) : tid + 512 * k];
+#pragma unroll
+        for (int k = 0; k < 8; k++) out[row + tid + 512 * k] = w[k];
+        return;
+    }
+    in += (z / a.in_group) * a.in_stride;
+    ConvY<NS, 8> y;
+    {
+        u64 x[8][NS];
+#pragma unroll
+        for (int m = 0; m < NS; m++)
+#pragma unroll
+            for (int k = 0; k < 8; k++) x[k][m] = in[(size_t)tab.in_rows[m] * n + tid + 512 * k];
+        y.set(tab, x);
+    }
+    const ConvTarget &o = tab.t[r];
+    const int limb = z * nt + r;                          // of the tail: item, component, limb
+    u64 *p = out + (size_t)o.row * n;
+    if (o.qd != 0.0) {
+        FpArith ar;
+        ar.init(t, o.mod, n);
+        double v[8];
+        y.target_any(tab.split, o, ar, v);
+        full_fwd_body<FpArith, TAIL>(lds, p, v, ar, t, n, limb, fb);
+    } else {
+        IntArith ar;
+        ar.init(t, o.mod, n);
+        u64 x[8];
+        y.target(tab.split, o, x);
+        full_fwd_body<IntArith, TAIL>(lds, p, x, ar, t, n, limb, fb);
+    }
 }
 
 static NttTables tables_of(const cm_ctx *ctx, bool inverse, int limbs) {
@@ -746,16 +1101,17 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
     const int n = ctx->n, n2 = n >> 8;
     dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
     const NttTables t = tables_of(ctx, inverse, limbs);
+    const dim3 full(FULL_THREADS);
     if (!inverse && n2 == 256) {
         hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, n2);
         hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, FinishBatch());
     } else if (!inverse) {
-        hipLaunchKernelGGL(ntt_full_fwd<false>, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, FinishBatch());
+        hipLaunchKernelGGL(ntt_full_fwd<false>, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, FinishBatch());
     } else if (n2 == 256) {
         hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
         hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
     } else {
-        hipLaunchKernelGGL(ntt_full_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
+        hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
     }
 }
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st, const u64 *src,
@@ -767,11 +1123,51 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
     const NttTables t = tables_of(ctx, false, limbs);
     const int *none = nullptr;
     if (n == 4096) {
-        hipLaunchKernelGGL(ntt_full_fwd<true>, grid, block, 0, st, conv, src, d_src_rows, none, d_mods, t, n, fb);
+        hipLaunchKernelGGL(ntt_full_fwd<true>, grid, dim3(FULL_THREADS), 0, st, conv, src, d_src_rows, none, d_mods, t, n, fb);
         return;
     }
     hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, conv, src, d_src_rows, none, d_mods, t, n, n >> 8);
     hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, conv, none, d_mods, t, n, fb);
+}
+void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
+                     int limbs, const FinishBatch *fb) {
+    const int n = ctx->n, ns = ctx->alpha > ctx->K ? ctx->alpha : ctx->K;       // bound of the source count, rounded up below
+    const NttTables t = tables_of(ctx, false, limbs);
+    ConvArgs a;
+    a.tabs = b.tabs, a.tab_step = b.tab_step, a.tab_period = b.tab_period ? b.tab_period : b.batch, a.in_group = b.in_group;
+    a.in_stride = b.in_stride, a.out_stride = b.out_stride, a.own_stride = b.own_stride;
+    a.own_src = b.own_src, a.own_g = b.own_g;
+    if (n == 4096) {
+        Prof prof_(ctx, CM_K_BASE_CONV, b.batch * b.max_nt, st);
+        const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
+#define FULL_LAUNCH(NS_)                                                                                                         \
+    if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb);        \
+    else hipLaunchKernelGGL((conv_full_fwd<NS_, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
+        if (ns <= 1) { FULL_LAUNCH(1); }
+        else if (ns <= 2) { FULL_LAUNCH(2); }
+        else if (ns <= 4) { FULL_LAUNCH(4); }
+        else { FULL_LAUNCH(8); }
+#undef FULL_LAUNCH
+        return;
+    }
+    {
+        Prof prof_(ctx, CM_K_BASE_CONV, b.batch * b.max_nt, st);
+        a.tg = CCF_TG;
+        while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
+        a.groups = (b.max_nt + a.tg - 1) / a.tg;
+        const dim3 grid(256 / CCF_W, a.groups + (b.own_src ? 1 : 0), b.batch);
+#define CCF_LAUNCH(NS_) hipLaunchKernelGGL((conv_cols_fwd<NS_>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn)
+        if (ns <= 1) CCF_LAUNCH(1);
+        else if (ns <= 2) CCF_LAUNCH(2);
+        else if (ns <= 4) CCF_LAUNCH(4);
+        else if (ns <= 6) CCF_LAUNCH(6);
+        else CCF_LAUNCH(8);
+#undef CCF_LAUNCH
+    }
+    Prof prof_(ctx, CM_K_NTT_FWD, limbs, st);
+    const dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
+    if (fb) hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, out, d_rows, d_mods, t, n, *fb);
+    else hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, out, d_rows, d_mods, t, n, FinishBatch());
 }
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs,
                      bool inverse, hipStream_t st) {

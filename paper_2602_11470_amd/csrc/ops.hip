@@ -80,16 +80,22 @@ static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector
     ConvDev d;
     memset(&d, 0, sizeof(d));
     d.ns = t.ns, d.nt = t.nt;
+    u64 smax = 0, tmax = 0;
     for (int m = 0; m < t.ns; m++) {
-        d.src_mod[m] = t.src[m], d.in_rows[m] = in_rows[m];
-        d.inv_hat[m] = t.inv_hat[m], d.inv_hat_sh[m] = t.inv_hat_sh[m];
-        d.src_q[m] = ctx->mod[t.src[m]];
+        d.in_rows[m] = in_rows[m];
+        d.inv_hat[m] = t.inv_hat[m], d.inv_hat_sh[m] = t.inv_hat_sh[m], d.src_q[m] = ctx->mod[t.src[m]];
+        d.src_qd[m] = (double)d.src_q[m], d.inv_hat_d[m] = (double)t.inv_hat[m], d.inv_hat_dq[m] = d.inv_hat_d[m] / d.src_qd[m];
+        smax = std::max(smax, d.src_q[m]);
     }
     for (int r = 0; r < t.nt; r++) {
-        d.dst_mod[r] = t.dst[r], d.out_rows[r] = out_rows[r];
-        d.dst_q[r] = ctx->modc[t.dst[r]].q, d.dst_qinv[r] = ctx->modc[t.dst[r]].qinv;
+        ConvTarget &o = d.t[r];
+        const ModC &mc = ctx->modc[t.dst[r]];
+        o.mod = t.dst[r], o.row = out_rows[r], o.q = mc.q, o.qinv = mc.qinv;
+        if (mc.q < (1ULL << 50)) o.qd = (double)mc.q, o.qinvd = 1.0 / (double)mc.q;
+        for (int m = 0; m < t.ns; m++) o.w[m] = (double)t.hat[(size_t)m * t.nt + r], o.wm[m] = t.hat_mont[(size_t)m * t.nt + r];
+        tmax = std::max(tmax, mc.q);
     }
-    for (size_t i = 0; i < t.hat_mont.size(); i++) d.hat_mont[i] = t.hat_mont[i];
+    d.split = smax < (1ULL << 50) ? CONV_SPLIT_25 : smax < (1ULL << 60) && tmax < (1ULL << 50) ? CONV_SPLIT_30 : CONV_SPLIT_NONE;
     return d;
 }
 static std::map<std::pair<cm_ctx *, int>, KsLevelFull> g_ks;
@@ -237,11 +243,21 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     // coefficient-domain copy of d (out of place), then all digits in one conversion launch; a
     // digit's own limbs are copied from d itself, which is already in the evaluation domain
     launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
-    launch_base_conv(ctx, k.d_modup, k.beta, 1, k.modup_max_nt, digits, A.ksin, 0, (size_t)k.ext * n, d, g, st);
-    launch_ntt_rows(ctx, digits, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt, false, st);
+    ConvBatch cb;
+    cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
+    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g;
+    launch_conv_ntt(ctx, cb, digits, A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
 }
 
+// second half of a ModDown of `batch` polynomials: their K special limbs (coefficient domain, at in + z*in_stride) converted
+// to q_0 .. q_level and transformed in `conv`, with the tail fb
+static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, int batch, u64 *conv, const u64 *in, size_t in_stride,
+                         const FinishBatch &fb, hipStream_t st) {
+    ConvBatch cb;
+    cb.tabs = tab, cb.batch = batch, cb.max_nt = k.level + 1, cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
+    launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
+}
 cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int addend_comps, u64 g, u64 *out,
                        const u64 *accum, hipStream_t st) {
     const KsLevelFull &k = ks_level_full(ctx, level);
@@ -249,12 +265,11 @@ cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int ad
     const size_t n = ctx->n;
     if (!addend) addend_comps = 0, g = 0;
     launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
-    launch_base_conv(ctx, k.d_moddown, 2, 0, level + 1, A.conv, u, (size_t)k.ext * n, (size_t)(level + 1) * n, nullptr, 0, st);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = addend_comps;
     fb.u[0] = u, fb.out[0] = out, fb.accum[0] = accum, fb.g[0] = (unsigned)g;
     fb.addend[0] = addend, fb.pinv = get_pinv(ctx, level);
-    launch_ntt_fwd_finish(ctx, A.conv, k.d_q_mods3, fb, st);
+    moddown_conv(ctx, k, k.d_moddown, 2, A.conv, u, (size_t)k.ext * n, fb, st);
     return CM_OK;
 }
 
@@ -312,8 +327,6 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
     const int level = k.level;
     const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n;
     launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
-    launch_base_conv(ctx, k.d_moddown, 2 * m, 0, level + 1, A.bconv, bu, (size_t)k.ext * n, (size_t)(level + 1) * n, nullptr,
-                     0, st);
     auto add_of = [&](int r) { return addends ? addends[r] : nullptr; };
     auto acc_of = [&](int r) { return accums ? accums[r] : nullptr; };
     FinishBatch fb;
@@ -324,7 +337,7 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
         fb.g[r] = add_of(r) && gs ? (unsigned)gs[r] : 0;
     }
     fb.pinv = get_pinv(ctx, level);
-    launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
+    moddown_conv(ctx, k, k.d_moddown, 2 * m, A.bconv, bu, (size_t)k.ext * n, fb, st);
 }
 cm_status moddown_batch_into(cm_ctx *ctx, u64 *us, int level, int m, const u64 *const *addends, int addend_comps, u64 g,
                              const u64 *const *accums, u64 *const *outs, hipStream_t st) {
@@ -354,14 +367,12 @@ cm_status moddown_many_second(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *con
         // special limbs of the second components to the coefficient domain, converted to q_0..q_level, transformed,
         // and the tail (u - conv) P^{-1} fused into the last pass of that transform
         launch_ntt_rows(ctx, bu, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st);
-        launch_base_conv(ctx, k.d_moddown, m, 0, level + 1, A.bconv, bu + (size_t)k.ext * n, ublk, (size_t)(level + 1) * n,
-                         nullptr, 0, st);
         FinishBatch fb;
         fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
         for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
         for (int r = 0; r < m; r++) fb.u[r] = bu + r * ublk, fb.out[r] = outs[base + r];
         fb.pinv = get_pinv(ctx, level);
-        launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
+        moddown_conv(ctx, k, k.d_moddown, m, A.bconv, bu + (size_t)k.ext * n, ublk, fb, st);
     }
     return CM_OK;
 }
@@ -372,12 +383,11 @@ cm_status moddown_second_keep(cm_ctx *ctx, const u64 *R, int level, u64 *out, hi
     const size_t n = ctx->n;
     // the K special limbs of the second component, to the coefficient domain in a buffer of their own
     launch_ntt_src(ctx, A.tmp[0], nullptr, R, k.d_sp1_rows, k.d_sp_mods, ctx->K, true, st, 0);
-    launch_base_conv(ctx, k.d_moddown0, 1, 0, level + 1, A.bconv, A.tmp[0], 0, 0, nullptr, 0, st);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     fb.u[0] = R, fb.out[0] = out, fb.pinv = get_pinv(ctx, level);
-    launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
+    moddown_conv(ctx, k, k.d_moddown0, 1, A.bconv, A.tmp[0], 0, fb, st);
     return CM_OK;
 }
 
@@ -389,14 +399,12 @@ cm_status moddown_second_keep_many(cm_ctx *ctx, const u64 *Rs, int level, int m,
     // the K special limbs of every second component, to the coefficient domain in a buffer of their own
     // (the three temporaries of the arena are contiguous: 9 (L+1) limbs, room for CM_KS_BATCH * K)
     launch_ntt_src(ctx, A.tmp[0], nullptr, Rs, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st, 0);
-    launch_base_conv(ctx, k.d_moddown0, m, 0, level + 1, A.bconv, A.tmp[0], (size_t)ctx->K * n, (size_t)(level + 1) * n, nullptr,
-                     0, st);
     FinishBatch fb;
     fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     for (int r = 0; r < m; r++) fb.u[r] = Rs + r * ublk, fb.out[r] = outs[r];
     fb.pinv = get_pinv(ctx, level);
-    launch_ntt_fwd_finish(ctx, A.bconv, k.d_bq_mods, fb, st);
+    moddown_conv(ctx, k, k.d_moddown0, m, A.bconv, A.tmp[0], (size_t)ctx->K * n, fb, st);
     return CM_OK;
 }
 
@@ -431,9 +439,11 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     const size_t n = ctx->n, ln = (size_t)(t.level + 1) * n;
     // the tables list the items in order, so the first m items are a prefix of every table
     launch_ntt_src(ctx, ksin, nullptr, cts, t.d_src_rows, t.d_in_mods, m * (t.level + 1), true, st, g);
-    launch_base_conv(ctx, k.d_modup, m * k.beta, 1, k.modup_max_nt, digits, ksin, ln, (size_t)k.ext * n,
-                     cts + (size_t)t.comp * ln, g, st, k.beta, k.beta, (size_t)t.ncomp * ln);
-    launch_ntt_rows(ctx, digits, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt, false, st);
+    ConvBatch cb;
+    cb.tabs = k.d_modup, cb.batch = m * k.beta, cb.tab_step = 1, cb.max_nt = k.modup_max_nt, cb.tab_period = k.beta, cb.in_group = k.beta;
+    cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
+    cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln;
+    launch_conv_ntt(ctx, cb, digits, ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
     return CM_OK;
 }
 
