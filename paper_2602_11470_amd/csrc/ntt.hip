@@ -17,9 +17,9 @@
 //              issues at full rate here, and a modular product is 6 instructions:
 //                  h = y*w; l = fma(y, w, -h)            (exact product h + l)
 //                  c = rint(y * (w/q)); r = fma(-c, q, h) + l
-//              exact because |h - c q| < 2^53 whenever |y| <= 2.1 q; r = y w (mod q), |r| <= 1.04 q.
-//              Values stay signed and lazy (|v| <= 1.54 q), one 3-instruction renormalisation per
-//              butterfly; ~11 instructions per butterfly.  Between the two kernels of a
+//              exact because |h - c q| < 2^53 whenever |y| < 8 q; r = y w (mod q).
+//              Values stay signed and lazy (below 8 q = 2^53); a forward butterfly is 8 instructions, an
+//              inverse one 11 (see FpArith).  Between the two kernels of a
 //              transform the words in memory are raw doubles; at rest they are u64 in [0, q).
 // Both give bit-identical results (all steps are exact integer arithmetic).
 #include "kernels.h"
@@ -75,6 +75,7 @@ struct IntArith {
         if (t.ninv) ni = t.ninv[mi], nip = t.ninvp[mi];
     }
     __device__ __forceinline__ T from_rest(u64 raw) const { return raw; }     // canonical [0, q)
+    __device__ __forceinline__ T from_lazy(u64 raw) const { return raw; }     // below 2q (a rescale's last limb under another modulus)
     __device__ __forceinline__ T from_mid(u64 raw) const { return raw; }
     __device__ __forceinline__ u64 to_mid(T v) const { return v; }
     typedef u64 W;
@@ -118,6 +119,21 @@ struct IntArith {
         }
     }
     __device__ __forceinline__ u64 to_rest_fwd(T v) const { return v >= q ? v - q : v; }
+    __device__ __forceinline__ u64 to_tail(T v) const { return to_rest_fwd(v); }
+    // (u - conv) pinv (+ a) (+ c), and (u pt - conv) pinv (+ c) with pt in multiplier form
+    struct Tail {
+        u64 pi, pis, qinv;
+        __device__ __forceinline__ Tail(const IntArith &, const NttTables &t, int mi, u64 p, u64 ps) : pi(p), pis(ps), qinv(t.modc[mi].qinv) {}
+        __device__ __forceinline__ u64 plain(const IntArith &ar, u64 u, u64 conv, bool has_a, u64 a, bool has_c, u64 c) const {
+            u64 x = mul_shoup(submod(u, conv, ar.q), pi, pis, ar.q);
+            if (has_a) x = addmod(x, a, ar.q);
+            if (has_c) x = addmod(x, c, ar.q);
+            return x;
+        }
+        __device__ __forceinline__ u64 masked(const IntArith &ar, u64 u, u64 pt, u64 conv, bool has_c, u64 c) const {
+            return plain(ar, redc((u128)u * pt, ar.q, qinv), conv, false, 0, has_c, c);
+        }
+    };
     __device__ __forceinline__ u64 to_rest_inv(T v) const { return mul_shoup(v, ni, nip, q); }
 };
 
@@ -143,20 +159,29 @@ struct FpArith {
     __device__ __forceinline__ T from_rest(u64 raw) const {
         return __longlong_as_double((long long)(raw | 0x4330000000000000ULL)) - TWO52;
     }
+    __device__ __forceinline__ T from_lazy(u64 raw) const { return norm(from_rest(raw)); }      // below 2q
     __device__ __forceinline__ T from_mid(u64 raw) const { return __longlong_as_double((long long)raw); }
     __device__ __forceinline__ u64 to_mid(T v) const { return (u64)__double_as_longlong(v); }
     typedef double W;
     typedef double Word;
     __device__ __forceinline__ Word word(unsigned idx) const { return *word_at(w, idx); }
     __device__ __forceinline__ void pair(Word x, W &a, W &b) const { a = x, b = x * qinv; }
+    // Products: |r| <= (1/2 + 3/8 B) q for |y| <= B q (the quotient comes from three roundings of a value below B 2^50).
+    // Forward: nothing is renormalised inside four stages; from B = 1 the values grow to 1.88, 3.08, 4.74, 7.02 q, below the
+    // 2^53 = 8 q up to which integers are exact, and are brought back to q / 2 after every fourth stage (3 instructions per
+    // word and four stages instead of 3 per butterfly).
+    // Inverse: sums double, so each is renormalised where it is formed.
     template <int NV>
-    __device__ __forceinline__ void after_fwd(int, T (&)[NV]) const {}
+    __device__ __forceinline__ void after_fwd(int s, T (&v)[NV]) const {
+        if ((s & 3) == 3) {
+#pragma unroll
+            for (int k = 0; k < NV; k++) v[k] = norm(v[k]);
+        }
+    }
     template <int NV>
     __device__ __forceinline__ void after_inv(int, int, T (&)[NV]) const {}
-    // With table twiddles (0 <= w < q, w/q correctly rounded) |r| <= 1.04 q; with generated ones
-    // (|w| <= 0.9 q, w/q taken as w * (1/q)) |r| <= 1.2 q.  Either way every value stays below 2.1 q.
     __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {
-        double x = norm(X), r = mulmod(Y, a, b);
+        const double x = X, r = mulmod(Y, a, b);
         X = x + r;
         Y = x - r;
     }
@@ -165,13 +190,36 @@ struct FpArith {
         X = norm(s);
         Y = mulmod(d, a, b);
     }
-    __device__ __forceinline__ u64 canon(double v) const {                     // |v| < 2^52  ->  [0, q)
-        double r = __builtin_fma(-__builtin_floor(v * qinv), q, v);
-        r = r < 0.0 ? r + q : r;
-        r = r >= q ? r - q : r;
-        return (u64)__double_as_longlong(r + TWO52) & 0x000FFFFFFFFFFFFFULL;
+    // |v| < q -> [0, q): q is added under the sign mask
+    __device__ __forceinline__ u64 lift(double v) const {
+        const int m = __double2hiint(v) >> 31;
+        const double a = __hiloint2double(__double2hiint(q) & m, __double2loint(q) & m);
+        return (u64)__double_as_longlong((v + a) + TWO52) & 0x000FFFFFFFFFFFFFULL;
     }
-    __device__ __forceinline__ u64 to_rest_fwd(T v) const { return canon(v); }
+    __device__ __forceinline__ u64 canon(double v) const { return lift(norm(v)); }       // |v| < 2^53 -> [0, q)
+    __device__ __forceinline__ u64 to_rest_fwd(T v) const { return lift(v); }           // after the last stage's norm
+    __device__ __forceinline__ u64 to_tail(T v) const { return to_mid(v); }
+    // The tails in FP64: |conv| <= q / 2, so |u - conv| <= 1.5 q, its product at most 1.07 q, and the sum of four terms
+    // below 5 q before the one reduction at the end.
+    struct Tail {
+        double pi, piq, rp, rpq;
+        __device__ __forceinline__ Tail(const FpArith &ar, const NttTables &t, int mi, u64 p, u64) {
+            pi = (double)p, piq = pi * ar.qinv;
+            rp = ar.mulmod(pi, t.fpq[mi].rinv, t.fpq[mi].rinvq), rpq = rp * ar.qinv;         // 2^-64 pinv
+        }
+        __device__ __forceinline__ u64 plain(const FpArith &ar, u64 u, u64 conv, bool has_a, u64 a, bool has_c, u64 c) const {
+            double x = ar.mulmod(ar.from_rest(u) - ar.from_mid(conv), pi, piq);
+            if (has_a) x += ar.from_rest(a);
+            if (has_c) x += ar.from_rest(c);
+            return ar.canon(x);
+        }
+        __device__ __forceinline__ u64 masked(const FpArith &ar, u64 u, u64 pt, u64 conv, bool has_c, u64 c) const {
+            const double a = ar.from_rest(pt);
+            double x = ar.mulmod(ar.mulmod(ar.from_rest(u), a, a * ar.qinv), rp, rpq) - ar.mulmod(ar.from_mid(conv), pi, piq);
+            if (has_c) x += ar.from_rest(c);
+            return ar.canon(x);
+        }
+    };
     __device__ __forceinline__ u64 to_rest_inv(T v) const { return canon(mulmod(v, ni, niq)); }
 };
 
@@ -305,7 +353,7 @@ __device__ __forceinline__ int pad(int e) { return e + (e >> 4); }
 
 // ---- column passes: stages 0..7; tile = rows 0..255 of 16 adjacent columns ---------------------------
 template <class A>
-__device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int n2) {
+__device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, bool lazy, const NttTables &t, int mi, int n, int n2) {
     A ar;
     ar.init(t, mi, n);
     const int c = threadIdx.x & 15, sub = threadIdx.x >> 4;
@@ -321,7 +369,7 @@ __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, c
     {
         const TableTw<A> tw(ar, 1);                 // in flight together with the data
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = ar.from_rest(raw[k]);
+        for (int k = 0; k < 16; k++) v[k] = lazy ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
         radix16_fwd_tw(v, ar, tw);
     }
 #pragma unroll
@@ -378,9 +426,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_fwd(u64 *__restrict__ da
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n + c0 : p;
     if (t.fpq[mi].q != 0.0)
-        cols_fwd_body<FpArith>(lds, p, ps, t, mi, n, n2);
+        cols_fwd_body<FpArith>(lds, p, ps, src != nullptr, t, mi, n, n2);
     else
-        cols_fwd_body<IntArith>(lds, p, ps, t, mi, n, n2);
+        cols_fwd_body<IntArith>(lds, p, ps, src != nullptr, t, mi, n, n2);
 }
 __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_inv(u64 *__restrict__ data, const int *__restrict__ rows,
                                                            const int *__restrict__ mod_idx, NttTables t, int n,
@@ -396,75 +444,24 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_inv(u64 *__restrict__ da
         cols_inv_body<IntArith>(lds, p, t, mi, n, n2);
 }
 
-// ---- 16 x 16 transpose inside a row of 16 lanes, by cross-lane moves instead of a trip through LDS -----------------
-// lane s, register k  <->  lane k, register s: four exchange stages with the partner lane s ^ b (b = 8, 4, 2, 1); in the
-// stage of b the pair of registers (k, k | b) trades one member with the partner.  b = 8 and 4 are DPP row moves that
-// write only the banks (groups of four lanes) on one side; b = 2 and 1 are quad permutations with selects around them:
-// 96 DPP moves and 96 selects per lane.  The row passes use it for the exchange between their two radix-16 groups
-// (the sixteen lanes that share a block of 256 words); measured against the LDS exchange it replaces (32 LDS
-// instructions and a barrier) it is time-neutral, within 2 % either way from 24 to 1008 limbs per launch.
-template <int CTRL, int BANKS>
-__device__ __forceinline__ u64 dpp_merge(u64 old, u64 src) {
-    const int lo = __builtin_amdgcn_update_dpp((int)old, (int)src, CTRL, 0xF, BANKS, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(old >> 32), (int)(src >> 32), CTRL, 0xF, BANKS, false);
-    return ((u64)(unsigned)hi << 32) | (unsigned)lo;
+// The exchange between the two radix-16 groups of a row pass stays among the sixteen lanes that share a block of 256 words,
+// i.e. inside a wave: LDS operations of a wave are in order, so no barrier is needed (only the compiler has to keep them
+// in order).  Cross-lane (DPP) moves in place of the trip cost 192 vector ALU instructions per lane in passes that are
+// bound by that unit (up to 86 % busy).  With the LDS trip instead, four stages between renormalisations and the tails in
+// FP64: 1112 limbs 248 -> 216 us, 368 limbs with the ModDown tail 157 -> 136 us.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
-template <int CTRL>
-__device__ __forceinline__ u64 dpp_all(u64 src) {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)src, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(src >> 32), CTRL, 0xF, 0xF, false);
-    return ((u64)(unsigned)hi << 32) | (unsigned)lo;
-}
-__device__ __forceinline__ void transpose16(u64 (&x)[16], int s) {
-#pragma unroll
-    for (int k = 0; k < 16; k++)
-        if (!(k & 8)) {
-            const u64 a = x[k], b = x[k | 8];
-            x[k] = dpp_merge<0x128, 0xC>(a, b);          // lanes 8..15 take the partner's upper register (row_ror:8)
-            x[k | 8] = dpp_merge<0x128, 0x3>(b, a);      // lanes 0..7 take the partner's lower register
-        }
-#pragma unroll
-    for (int k = 0; k < 16; k++)
-        if (!(k & 4)) {
-            const u64 a = x[k], b = x[k | 4];
-            x[k] = dpp_merge<0x114, 0xA>(a, b);          // row_shr:4 into the banks with bit 2 set
-            x[k | 4] = dpp_merge<0x104, 0x5>(b, a);      // row_shl:4 into the others
-        }
-    const bool h2 = s & 2, h1 = s & 1;
-#pragma unroll
-    for (int k = 0; k < 16; k++)
-        if (!(k & 2)) {
-            const u64 a = x[k], b = x[k | 2];
-            const u64 r = dpp_all<0x4E>(h2 ? a : b);     // quad_perm [2, 3, 0, 1]
-            x[k] = h2 ? r : a, x[k | 2] = h2 ? b : r;
-        }
-#pragma unroll
-    for (int k = 0; k < 16; k++)
-        if (!(k & 1)) {
-            const u64 a = x[k], b = x[k | 1];
-            const u64 r = dpp_all<0xB1>(h1 ? a : b);     // quad_perm [1, 0, 3, 2]
-            x[k] = h1 ? r : a, x[k | 1] = h1 ? b : r;
-        }
-}
-template <class A>
-__device__ __forceinline__ void transpose16(typename A::T (&v)[16], const A &ar, int s) {
-    u64 x[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) x[k] = ar.to_mid(v[k]);
-    transpose16(x, s);
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = ar.from_mid(x[k]);
-}
-
 // The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of 4096 sit in LDS.
 // at(e): where word e of the chunk sits.
-template <int LANES, class AT>
-__device__ __forceinline__ void finish_tail(AT at, const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
+template <int LANES, class AT, class A>
+__device__ __forceinline__ void finish_tail(AT at, const A &ar, const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
     constexpr int NW = 4096 / LANES;
     // this limb is NTT(conv) of item r, component c, limb l
     const int per = fb.ncomp * (fb.level + 1);
     const int r = limb / per, c = fb.comp0 + (limb % per) / (fb.level + 1), l = limb % (fb.level + 1);
-    const u64 q = t.modc[l].q, pi = fb.pinv[2 * l], pis = fb.pinv[2 * l + 1];
+    const u64 pi = fb.pinv[2 * l], pis = fb.pinv[2 * l + 1];
     const unsigned pos0 = (unsigned)chunk * 4096 + threadIdx.x;
     const size_t row = ((size_t)c * (fb.level + 1) + l) * n;
     const u64 *up = fb.u[r] + ((size_t)c * fb.ext + l) * n + pos0;
@@ -478,7 +475,7 @@ __device__ __forceinline__ void finish_tail(AT at, const u64 *lds, const NttTabl
     u64 uu[NW], aa[NW], cc[NW];
     if (fb.mul_pt) {
         // u = u[r] * (mul_pt through the Galois map mul_g[r]), formed here instead of being read
-        const u64 qinv = t.modc[l].qinv;
+        const typename A::Tail tl(ar, t, l, pi, pis);
         const u64 *mp = fb.mul_pt + (size_t)l * n;
         const unsigned mg = fb.mul_g[r];
 #pragma unroll
@@ -496,13 +493,12 @@ __device__ __forceinline__ void finish_tail(AT at, const u64 *lds, const NttTabl
         }
 #pragma unroll
         for (int k = 0; k < NW; k++) {
-            const u64 uv = redc((u128)uu[k] * aa[k], q, qinv);
-            u64 x = mul_shoup(submod(uv, lds[at(threadIdx.x + LANES * k)], q), pi, pis, q);
-            if (ac) x = addmod(x, cc[k], q);
+            const u64 x = tl.masked(ar, uu[k], aa[k], lds[at(threadIdx.x + LANES * k)], ac != nullptr, cc[k]);
             TAIL_ST(op + LANES * k, x);
         }
         return;
     }
+    const typename A::Tail tl(ar, t, l, pi, pis);
 #pragma unroll
     for (int k = 0; k < NW; k++) uu[k] = up[LANES * k];
     if (ad && g) {
@@ -518,10 +514,7 @@ __device__ __forceinline__ void finish_tail(AT at, const u64 *lds, const NttTabl
     }
 #pragma unroll
     for (int k = 0; k < NW; k++) {
-        u64 d = submod(uu[k], lds[at(threadIdx.x + LANES * k)], q);
-        u64 x = mul_shoup(d, pi, pis, q);
-        if (ad) x = addmod(x, aa[k], q);
-        if (ac) x = addmod(x, cc[k], q);
+        const u64 x = tl.plain(ar, uu[k], lds[at(threadIdx.x + LANES * k)], ad != nullptr, aa[k], ac != nullptr, cc[k]);
         op[LANES * k] = x;
     }
 }
@@ -549,19 +542,23 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
         for (int k = 0; k < 16; k++) v[k] = ar.from_mid(raw[k]);
         radix16_fwd_tw(v, ar, tw);
     }
-    transpose16(v, ar, sub);           // word sub + 16 k of the block -> word 16 sub + k
-    radix16_fwd_last(v, ar, 4096 + B * 16 + sub);
-    // Each lane now owns 16 contiguous words.  A trip through LDS (the only one of this pass) hands every lane the
-    // words tid, tid + 256, ... of the tile instead, so that all global traffic below is coalesced.
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + 16 * sub + k)] = ar.to_rest_fwd(v[k]);
+    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + sub + 16 * k)] = ar.to_mid(v[k]);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(blk * 256 + 16 * sub + k)]);
+    radix16_fwd_last(v, ar, 4096 + B * 16 + sub);
+    // Each lane now owns 16 contiguous words.  A trip through LDS hands every lane the words tid, tid + 256, ... of the tile
+    // instead, so that all global traffic below is coalesced.  A tail takes the values as they are.
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + 16 * sub + k)] = TAIL ? ar.to_tail(v[k]) : ar.to_rest_fwd(v[k]);
     __syncthreads();
     if (!TAIL) {
 #pragma unroll
         for (int k = 0; k < 16; k++) NTT_ST(p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
         return;
     }
-    finish_tail<NTT_THREADS>(pad, lds, t, n, chunk, limb, fb);
+    finish_tail<NTT_THREADS>(pad, ar, lds, t, n, chunk, limb, fb);
 }
 template <class A>
 __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
@@ -595,7 +592,11 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
     }
     radix16_inv_last(v, ar, 4096 + B * 16 + sub);
     const TableTw<A> tw2(ar, 256 + B);
-    transpose16(v, ar, sub);           // word 16 sub + k of the block -> word sub + 16 k
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[pad(blk * 256 + 16 * sub + k)] = ar.to_mid(v[k]);       // the words it read
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(blk * 256 + sub + 16 * k)]);
     radix16_inv_tw(v, ar, tw2);
 #pragma unroll
     for (int k = 0; k < 16; k++) NTT_ST(p + blk * 256 + sub + 16 * k, ar.to_mid(v[k]));
@@ -683,10 +684,10 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
         radix_fwd<3, 1, 9>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 8; k++) lds[pad8(tid * 8 + k)] = ar.to_rest_fwd(v[k]);
+    for (int k = 0; k < 8; k++) lds[pad8(tid * 8 + k)] = TAIL ? ar.to_tail(v[k]) : ar.to_rest_fwd(v[k]);
     __syncthreads();
     if (TAIL) {
-        finish_tail<FULL_THREADS>(pad8, lds, t, n, 0, limb, fb);
+        finish_tail<FULL_THREADS>(pad8, ar, lds, t, n, 0, limb, fb);
         return;
     }
 #pragma unroll
@@ -752,7 +753,7 @@ __device__ __forceinline__ void full_fwd_load(u64 *lds, u64 *p, const u64 *ps, c
 #pragma unroll
     for (int k = 0; k < 8; k++) raw[k] = ps[threadIdx.x + 512 * k];
 #pragma unroll
-    for (int k = 0; k < 8; k++) v[k] = ar.from_rest(raw[k]);
+    for (int k = 0; k < 8; k++) v[k] = ps != p ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
     full_fwd_body<A, TAIL>(lds, p, v, ar, t, n, limb, fb);
 }
 template <bool TAIL>

@@ -38,6 +38,28 @@ def test_lazy_product_stays_below_4q():
             assert 0 <= r < 4 * q and r % q == a * w % q
 
 
+def test_fp64_products_stay_exact_over_four_stages_without_renormalisation():
+    """FpArith: from |y| <= B q a product with a twiddle below q, its quotient taken with w (1/q), lies within (1/2 + 3/8 B) q,
+    so four forward stages from B = 1 stay below 8 q = 2^53, where integers are exact."""
+    rng = np.random.default_rng(11)
+    q = _moduli(50, 65536, 1)[0]
+    qinv = 1.0 / float(q)
+    bound = 1.0
+    for _ in range(4):
+        r_max = 0.5 + 0.375 * bound
+        lim = int(bound * q)
+        for i in range(3000):
+            y = int(rng.integers(-lim, lim + 1)) if i % 7 else (lim if i % 2 else -lim)
+            w = int(rng.integers(0, q)) if i % 5 else q - 1 - i
+            c = round(float(y) * (float(w) * qinv))                  # rint of the three rounded operations
+            r = y * w - c * q
+            assert abs(r) <= r_max * q
+            h = float(y) * float(w)
+            assert abs(int(h) - c * q) < 1 << 53 and abs(y * w - int(h)) < 1 << 53      # both steps of the product are exact
+        bound += r_max
+    assert bound < 8.0
+
+
 def _brev(n):
     logn = n.bit_length() - 1
     i = np.arange(n, dtype=np.uint32)
