@@ -514,7 +514,7 @@ __global__ __launch_bounds__(TPB) void k_inner_product_batch(IpBatch b, const Mo
 // Galois map; extra[z] ([2][ext][n], may be out[z] itself) is added, which lets several launches with
 // different keys accumulate into one output.
 #define IP_SHARED_MAX_BETA 8
-template <bool SA>
+template <bool SA, int NB>
 __global__ __launch_bounds__(TPB) void k_inner_product_shared_key(IpBatch b, const ModC *__restrict__ modc, int beta,
                                                                   int ext, int level, int L, int nmod, int n, int logn,
                                                                   unsigned g, EvkA eva, const u64 *__restrict__ ubound) {
@@ -526,11 +526,11 @@ __global__ __launch_bounds__(TPB) void k_inner_product_shared_key(IpBatch b, con
     const unsigned src = g ? perm_src(i2, g, logn) : i2;
     const unsigned base = src & ~1u;
     const bool swap = src & 1u;
-    ulonglong2 eb[IP_SHARED_MAX_BETA], ea[IP_SHARED_MAX_BETA];
+    ulonglong2 eb[NB], ea[NB];
     const u64 *key = b.it[0].key;
     const u64 bound = ubound[mi], cg0 = ((u64)i2 + 1) * GOLD, cg1 = cg0 + GOLD;
 #pragma unroll
-    for (int j = 0; j < IP_SHARED_MAX_BETA; j++) {
+    for (int j = 0; j < NB; j++) {
         if (j < beta) {
             const u64 *kb = key + ((size_t)j * nmod + mi) * n + i2;
             eb[j].x = __builtin_nontemporal_load(kb), eb[j].y = __builtin_nontemporal_load(kb + 1);
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(TPB) void k_inner_product_shared_key(IpBatch b, con
         const u64 *dig = b.it[z].dig;
         u128 a0 = 0, a1 = 0, b0 = 0, b1 = 0;
 #pragma unroll
-        for (int j = 0; j < IP_SHARED_MAX_BETA; j++) {
+        for (int j = 0; j < NB; j++) {
             if (j < beta) {
                 ulonglong2 d = *reinterpret_cast<const ulonglong2 *>(dig + ((size_t)j * ext + r) * n + base);
                 const u64 dx = swap ? d.y : d.x, dy = swap ? d.x : d.y;
@@ -577,20 +577,31 @@ void launch_inner_product_shared_key(cm_ctx *ctx, const IpBatch &b, int beta, in
         return;
     }
     Prof prof_(ctx, CM_K_INNER_PRODUCT, b.nz, st);
-    if (ctx->evk_stored_a)
-        hipLaunchKernelGGL(k_inner_product_shared_key<true>, dim3(ctx->n / (2 * TPB), ext), dim3(TPB), 0, st, b, ctx->d_modc, beta,
-                           ext, level, ctx->L, ctx->nmod, ctx->n, ctx->logn, (unsigned)g, evk_a_of(ctx), ctx->d_ubound);
-    else
-        hipLaunchKernelGGL(k_inner_product_shared_key<false>, dim3(ctx->n / (2 * TPB), ext), dim3(TPB), 0, st, b, ctx->d_modc, beta,
-                           ext, level, ctx->L, ctx->nmod, ctx->n, ctx->logn, (unsigned)g, evk_a_of(ctx), ctx->d_ubound);
+    // NB as in the fan-out kernel: registers for the digits there are
+#define SHARED_LAUNCH(SA_, NB_)                                                                                                  \
+    hipLaunchKernelGGL((k_inner_product_shared_key<SA_, NB_>), dim3(ctx->n / (2 * TPB), ext), dim3(TPB), 0, st, b, ctx->d_modc, beta, \
+                       ext, level, ctx->L, ctx->nmod, ctx->n, ctx->logn, (unsigned)g, evk_a_of(ctx), ctx->d_ubound)
+    if (ctx->evk_stored_a) {
+        if (beta <= 4) SHARED_LAUNCH(true, 4);
+        else SHARED_LAUNCH(true, 8);
+    } else if (beta <= 2) SHARED_LAUNCH(false, 2);
+    else if (beta <= 3) SHARED_LAUNCH(false, 3);
+    else if (beta <= 4) SHARED_LAUNCH(false, 4);
+    else if (beta <= 6) SHARED_LAUNCH(false, 6);
+    else SHARED_LAUNCH(false, 8);
+#undef SHARED_LAUNCH
 }
 // One digit array, many keys, one output per key (the hoisted rotations of ONE ciphertext, each kept on its own): a lane
 // keeps the digit words of two SOURCE positions (and the first component's) in registers and walks over the keys; for
 // key a it writes its result at the position the Galois map sends its source to (the inverse map; pairs go to pairs,
 // aligned runs of 64 to aligned runs of 64, so key reads and result writes stay coalesced).  Same sums as
 // k_inner_product_batch, but the digits are read once per IP_FAN_CHUNK keys instead of once per key.
+// NB = compile-time bound of the digit count: registers for eight digits leave three waves a SIMD, each with the two or three
+// loads in flight that a low level has; sized for its digits the kernel runs four to eight waves.  Bound by memory (one half
+// to two thirds reads): the 63 baby steps of a 4096 x 4096 product at level 4 (two digits) 328 -> 290 us, the 127 of an MLP
+// projection at level 3 499 -> 400 us.  Requesting the next rotation's words ahead as well changed nothing.
 #define IP_FAN_CHUNK 8
-template <bool SA>
+template <bool SA, int NB>
 __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64 *__restrict__ dig, const u64 *__restrict__ c0,
                                                               int c0_ext, const ModC *__restrict__ modc, int beta, int ext,
                                                               int level, int L, int nmod, int n, int logn,
@@ -612,9 +623,11 @@ __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64
     const ModC m = modc[mi];
     const u64 bound = ubound[mi];
     const bool small = m.q < (1ULL << 50);
-    ulonglong2 d[IP_SHARED_MAX_BETA];
+    const int a0_ = (int)bz * IP_FAN_CHUNK, a_end = min(f.n, a0_ + IP_FAN_CHUNK);
+    struct Words { u64x2 b[NB], a[NB]; };
+    ulonglong2 d[NB];
 #pragma unroll
-    for (int j = 0; j < IP_SHARED_MAX_BETA; j++)
+    for (int j = 0; j < NB; j++)
         if (j < beta) d[j] = *reinterpret_cast<const ulonglong2 *>(dig + ((size_t)j * ext + r) * n + s2);
     // the first component's contribution to the first output component: sigma(c0) as it is (extended basis) or
     // P sigma(c0) on the ciphertext limbs
@@ -627,54 +640,49 @@ __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64
             cv.x = redc((u128)cv.x * pm, m.q, m.qinv), cv.y = redc((u128)cv.y * pm, m.q, m.qinv);
         }
     }
-    const int a_end = min(f.n, (int)(bz + 1) * IP_FAN_CHUNK);
     // The generator stream keys of this chunk's (key, digit) pairs: lane 8 a' + j of every wave fetches one, and the loop
     // below broadcasts it with a lane read, so that no draw waits for a load of its own.
     u64 my_sk = 0;
     if (!SA) {
         const int la = (threadIdx.x & 63) >> 3, lj = threadIdx.x & 7;
         static_assert(IP_FAN_CHUNK * IP_SHARED_MAX_BETA == 64, "one lane per (key, digit) of a chunk");
-        if ((int)bz * IP_FAN_CHUNK + la < a_end && lj < beta)
-            my_sk = f.key[bz * IP_FAN_CHUNK + la][(size_t)eva.kdig * nmod * n + (size_t)lj * nmod + mi];
+        if (a0_ + la < a_end && lj < beta) my_sk = f.key[a0_ + la][(size_t)eva.kdig * nmod * n + (size_t)lj * nmod + mi];
     }
-    for (int a = bz * IP_FAN_CHUNK; a < a_end; a++) {
+    for (int a = a0_; a < a_end; a++) {
         const unsigned dst = perm_src(s2, f.ginv[a], logn);       // where this rotation puts source s2; s2 + 1 goes to dst ^ 1
         const unsigned base = dst & ~1u;
         const bool swap = dst & 1u;
-        const u64 *key = f.key[a];
         const u64 cg0 = ((u64)base + 1) * GOLD, cg1 = cg0 + GOLD;
+        Words w;
         // every key word of this rotation is requested before the first is used
-        ulonglong2 eb[IP_SHARED_MAX_BETA], ea[IP_SHARED_MAX_BETA];
+        const u64 *key = f.key[a] + (size_t)mi * n + base;
 #pragma unroll
-        for (int j = 0; j < IP_SHARED_MAX_BETA; j++)
+        for (int j = 0; j < NB; j++)
             if (j < beta) {
-                const u64 *kb = key + ((size_t)j * nmod + mi) * n + base;
-                eb[j].x = __builtin_nontemporal_load(kb), eb[j].y = __builtin_nontemporal_load(kb + 1);
-                if (SA) {
-                    const u64 *ka = kb + eva.a_off;
-                    ea[j].x = __builtin_nontemporal_load(ka), ea[j].y = __builtin_nontemporal_load(ka + 1);
-                }
+                const u64 *kb = key + (size_t)j * nmod * n;
+                w.b[j] = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(kb));
+                if (SA) w.a[j] = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(kb + eva.a_off));
             }
         if (!SA) {
             // attempt 0 of every draw in straight-line code; the rejected ones (a 2^-14 chance under a 50-bit modulus,
             // up to 1/16 under a 60-bit one) are redone in one branch behind them
-            const int l0 = (a - (int)bz * IP_FAN_CHUNK) * 8;
+            const int l0 = (a - a0_) * 8;
             bool rej = false;
 #pragma unroll
-            for (int j = 0; j < IP_SHARED_MAX_BETA; j++)
+            for (int j = 0; j < NB; j++)
                 if (j < beta) {
                     const u64 sk_ = ((u64)__builtin_amdgcn_readlane((int)(my_sk >> 32), l0 + j) << 32) |
                                     (unsigned)__builtin_amdgcn_readlane((int)my_sk, l0 + j);
-                    ea[j].x = mix64(sk_ + cg0), ea[j].y = mix64(sk_ + cg1);
-                    rej |= (ea[j].x >= bound) | (ea[j].y >= bound);
+                    w.a[j].x = mix64(sk_ + cg0), w.a[j].y = mix64(sk_ + cg1);
+                    rej |= (w.a[j].x >= bound) | (w.a[j].y >= bound);
                 }
             if (rej) {
 #pragma unroll
-                for (int j = 0; j < IP_SHARED_MAX_BETA; j++)
+                for (int j = 0; j < NB; j++)
                     if (j < beta) {
                         const u64 sk_ = ((u64)__builtin_amdgcn_readlane((int)(my_sk >> 32), l0 + j) << 32) |
                                         (unsigned)__builtin_amdgcn_readlane((int)my_sk, l0 + j);
-                        ea[j].x = evk_a_draw(sk_, cg0, base, bound), ea[j].y = evk_a_draw(sk_, cg1, base + 1, bound);
+                        w.a[j].x = evk_a_draw(sk_, cg0, base, bound), w.a[j].y = evk_a_draw(sk_, cg1, base + 1, bound);
                     }
             }
         }
@@ -682,24 +690,24 @@ __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64
         if (small) {
             Acc50 A0, A1, B0, B1;
 #pragma unroll
-            for (int j = 0; j < IP_SHARED_MAX_BETA; j++) {
+            for (int j = 0; j < NB; j++) {
                 if (j < beta) {
                     const u64 dx = swap ? d[j].y : d[j].x, dy = swap ? d[j].x : d[j].y;      // sources of positions base, base + 1
                     const unsigned x0 = (unsigned)dx & LOW25, x1 = (unsigned)(dx >> 25), y0 = (unsigned)dy & LOW25, y1 = (unsigned)(dy >> 25);
-                    B0.mac(x0, x1, eb[j].x), B1.mac(y0, y1, eb[j].y);
-                    A0.mac(x0, x1, ea[j].x), A1.mac(y0, y1, ea[j].y);
+                    B0.mac(x0, x1, w.b[j].x), B1.mac(y0, y1, w.b[j].y);
+                    A0.mac(x0, x1, w.a[j].x), A1.mac(y0, y1, w.a[j].y);
                 }
             }
             a0 = A0.total(), a1 = A1.total(), b0 = B0.total(), b1 = B1.total();
         } else {
 #pragma unroll
-            for (int j = 0; j < IP_SHARED_MAX_BETA; j++) {
+            for (int j = 0; j < NB; j++) {
                 if (j < beta) {
                     const u64 dx = swap ? d[j].y : d[j].x, dy = swap ? d[j].x : d[j].y;
-                    b0 += (u128)dx * eb[j].x;
-                    b1 += (u128)dy * eb[j].y;
-                    a0 += (u128)dx * ea[j].x;
-                    a1 += (u128)dy * ea[j].y;
+                    b0 += (u128)dx * w.b[j].x;
+                    b1 += (u128)dy * w.b[j].y;
+                    a0 += (u128)dx * w.a[j].x;
+                    a1 += (u128)dy * w.a[j].y;
                 }
             }
         }
@@ -718,12 +726,19 @@ bool launch_inner_product_fanout(cm_ctx *ctx, const IpFan &f, const u64 *dig, co
     Prof prof_(ctx, CM_K_INNER_PRODUCT, f.n, st);
     const int ext = level + 1 + ctx->K;
     const dim3 grid(ctx->n / (2 * TPB), ext, (f.n + IP_FAN_CHUNK - 1) / IP_FAN_CHUNK);
-    if (ctx->evk_stored_a)
-        hipLaunchKernelGGL(k_inner_product_fanout<true>, grid, dim3(TPB), 0, st, f, dig, c0, c0_ext ? 1 : 0, ctx->d_modc, beta, ext,
-                           level, ctx->L, ctx->nmod, ctx->n, ctx->logn, ctx->d_pmont, evk_a_of(ctx), ctx->d_ubound);
-    else
-        hipLaunchKernelGGL(k_inner_product_fanout<false>, grid, dim3(TPB), 0, st, f, dig, c0, c0_ext ? 1 : 0, ctx->d_modc, beta, ext,
-                           level, ctx->L, ctx->nmod, ctx->n, ctx->logn, ctx->d_pmont, evk_a_of(ctx), ctx->d_ubound);
+#define FAN_LAUNCH(SA_, NB_)                                                                                                       \
+    hipLaunchKernelGGL((k_inner_product_fanout<SA_, NB_>), grid, dim3(TPB), 0, st, f, dig, c0, c0_ext ? 1 : 0, ctx->d_modc, beta, \
+                       ext, level, ctx->L, ctx->nmod, ctx->n, ctx->logn, ctx->d_pmont, evk_a_of(ctx), ctx->d_ubound)
+    if (ctx->evk_stored_a) {
+        if (beta <= 4) FAN_LAUNCH(true, 4);
+        else FAN_LAUNCH(true, 8);
+    } else if (beta <= 1) FAN_LAUNCH(false, 1);
+    else if (beta <= 2) FAN_LAUNCH(false, 2);
+    else if (beta <= 3) FAN_LAUNCH(false, 3);
+    else if (beta <= 4) FAN_LAUNCH(false, 4);
+    else if (beta <= 6) FAN_LAUNCH(false, 6);
+    else FAN_LAUNCH(false, 8);
+#undef FAN_LAUNCH
     return true;
 }
 // NA keys (rotation amounts) applied to the same nz digit arrays, summed: out[z] = extra[z] + sum_a [ sum_j
