@@ -215,11 +215,11 @@ struct MacFp {
     __device__ __forceinline__ static double from_u64(u64 raw) {                 // raw < 2^52
         return __longlong_as_double((long long)(raw | 0x4330000000000000ULL)) - 4503599627370496.0;
     }
-    __device__ __forceinline__ u64 canon(double v) const {                       // |v| < 2^52 -> [0, q)
-        double r = __builtin_fma(-__builtin_floor(v * qinv), q, v);
-        r = r < 0.0 ? r + q : r;
-        r = r >= q ? r - q : r;
-        return (u64)__double_as_longlong(r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFULL;
+    __device__ __forceinline__ u64 canon(double v) const {                       // |v| < 2^53 -> [0, q)
+        const double r = norm(v);                                                // |r| < q: q is added under the sign mask
+        const int m = __double2hiint(r) >> 31;
+        const double a = __hiloint2double(__double2hiint(q) & m, __double2loint(q) & m);
+        return (u64)__double_as_longlong((r + a) + 4503599627370496.0) & 0x000FFFFFFFFFFFFFULL;
     }
 };
 // out[z][3][limbs][n] = sum_{j < cnt} a[j] (x) b[z*gs + j*ts]: a and b stacked at stride 2*limbs*n (gs, ts = the distance of
@@ -1262,7 +1262,8 @@ void launch_mask_circulant(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *M, int 
 // The same sums through a length-E transform along the copy index: for one coefficient A[k] = sum_c t[c] m[(c + k) mod E]
 // is a cyclic correlation, so with t'[c] = t[(-c) mod E] and F the length-E number-theoretic transform (E divides
 // q - 1), A = F^-1( F(m) . F(t') ): E (log2 E + 1) products per coefficient instead of nk * shared, exact like the direct sum.
-// MODE 0 (set-up): rows M[E][limbs][n] -> Mhat = F(m) / E, kept in the order the forward pass leaves (bit-reversed);
+// MODE 0 (set-up): rows M[E][limbs][n] -> Mhat = F(m) / E, kept in the order the forward pass leaves (bit-reversed), in
+// multiplier form (nk != 0) or as plain residues (nk = 0);
 // MODE 1: T[nk] stacked ciphertexts -> A[shared].  A workgroup owns CO coefficients of one limb and one component and
 // keeps the E x CO words in LDS; the forward pass is decimation in frequency, the inverse one decimation in time, so
 // no reordering is needed.  tw[limbs][2][E/2][2]: omega^e and omega^-e with their companions; einv[limbs]: E^-1 in
@@ -1298,8 +1299,10 @@ __global__ __launch_bounds__(TPB) void k_mask_ntt(u64 *__restrict__ out, const u
     }
     if (MODE == 0) {
         const u64 s = einv[l];
-        for (int e = threadIdx.x; e < E * CO; e += TPB)
-            out[(size_t)(e >> logCO) * cs + o + (e & (CO - 1))] = redc((u128)X[e] * s, q, m.qinv);
+        for (int e = threadIdx.x; e < E * CO; e += TPB) {
+            const u64 x = redc((u128)X[e] * s, q, m.qinv);
+            out[(size_t)(e >> logCO) * cs + o + (e & (CO - 1))] = nk ? x : redc((u128)x, q, m.qinv);
+        }
         return;
     }
     for (int e = threadIdx.x; e < E * CO; e += TPB)
@@ -1320,6 +1323,130 @@ __global__ __launch_bounds__(TPB) void k_mask_ntt(u64 *__restrict__ out, const u
     for (int e = threadIdx.x; e < shared * CO; e += TPB)
         out[(size_t)(e >> logCO) * ctw + comp * cs + o + (e & (CO - 1))] = X[e];
 }
+// The same sums on limbs below 2^50 in FP64 and registers, for E = 2^(L1 + L2) = 16 .. 256: a lane holds 2^L1 rows of one
+// coefficient, the forward pass is L1 stages, an exchange through LDS and L2 stages; the product with Mhat and the first L2
+// inverse stages happen on the same registers, one more exchange, L1 stages.  The workgroups of the two components are
+// neighbours, so that Mhat comes from HBM about once.
+// Bound by memory (T and A once, Mhat once): the integer form above walks through LDS and a barrier at every one of its
+// 2 log2 E stages.  Measured, 126 ciphertexts of 12 limbs, E = 128: 3.69 -> 1.11 ms (4 GB; with
+// both components in one workgroup and its Mhat words kept over them 1.52 ms, two waves a SIMD).
+// Bounds in units of q (products: 1/2 + 3/8 B): forward sums are renormalised, differences stay below 4, products below 2;
+// from the product with Mhat (1.25, renormalised where L2 = 4) three inverse stages reach 5.4, are renormalised, and four
+// or fewer more reach 5.2.
+template <int L1, int L2>
+__global__ __launch_bounds__(TPB) void k_mask_ntt_fp(u64 *__restrict__ out, const u64 *__restrict__ in, const u64 *__restrict__ Mhat,
+                                                     const u64 *__restrict__ tw, const FpQ *__restrict__ fpq, int nk, int shared,
+                                                     int limbs, int n) {
+    constexpr int E = 1 << (L1 + L2), NV = 1 << L1, NB = 1 << (L1 - L2), BL = 1 << L2, CO = TPB >> L2;
+    __shared__ double X[E * CO];
+    __shared__ double wt[2][E / 2];
+    const int l = blockIdx.y, comp = blockIdx.x & 1, i0 = (blockIdx.x >> 1) * CO, co = threadIdx.x & (CO - 1), s = threadIdx.x / CO;
+    const FpQ fq = fpq[l];
+    const MacFp F{fq.q, fq.qinv};
+    const size_t cs = (size_t)limbs * n, ctw = 2 * cs, o = (size_t)l * n + i0 + co;
+    for (int e = threadIdx.x; e < E; e += TPB) wt[e / (E / 2)][e % (E / 2)] = MacFp::from_u64(tw[(size_t)l * 2 * E + 2 * e]);
+    double v[NV];
+    {
+        u64 raw[NV];
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const int c = (E - (k * BL + s)) & (E - 1);
+            raw[k] = c < nk ? __builtin_nontemporal_load(in + (size_t)c * ctw + comp * cs + o) : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NV; k++) v[k] = MacFp::from_u64(raw[k]);
+    }
+    // forward, decimation in frequency: rows k BL + s
+#pragma unroll
+    for (int a = 0; a < L1; a++) {
+        const int half = NV >> (a + 1);
+#pragma unroll
+        for (int j = 0; j < half; j++) {
+            const double w = wt[0][(j * BL + s) << a], wq = w * F.qinv;
+#pragma unroll
+            for (int g = 0; g < (1 << a); g++) {
+                const int k = g * 2 * half + j;
+                const double u = v[k], y = v[k + half];
+                v[k] = F.norm(u + y), v[k + half] = F.mulmod(u - y, w, wq);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NV; k++) X[(k * BL + s) * CO + co] = v[k];
+    u64 mh[NV];                               // in flight across the exchange
+#pragma unroll
+    for (int x = 0; x < NV; x++) mh[x] = Mhat[(size_t)((s * NB + x / BL) * BL + x % BL) * cs + o];
+    __syncthreads();
+    // rows (s NB + b) BL + k
+#pragma unroll
+    for (int x = 0; x < NV; x++) v[x] = X[((s * NB + x / BL) * BL + x % BL) * CO + co];
+#pragma unroll
+    for (int a = 0; a < L2; a++) {
+        const int half = BL >> (a + 1);
+#pragma unroll
+        for (int j = 0; j < half; j++) {
+            const double w = wt[0][j << (L1 + a)], wq = w * F.qinv;
+#pragma unroll
+            for (int g = 0; g < (NB << a); g++) {
+                const int k = g * 2 * half + j;
+                const double u = v[k], y = v[k + half];
+                v[k] = F.norm(u + y), v[k + half] = F.mulmod(u - y, w, wq);
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < NV; x++) {
+        const double m = MacFp::from_u64(mh[x]);
+        v[x] = F.mulmod(v[x], m, m * F.qinv);
+        if (L2 > 3) v[x] = F.norm(v[x]);
+    }
+    // inverse, decimation in time
+#pragma unroll
+    for (int a = L2 - 1; a >= 0; a--) {
+        const int half = BL >> (a + 1);
+#pragma unroll
+        for (int j = 0; j < half; j++) {
+            const double w = wt[1][j << (L1 + a)], wq = w * F.qinv;
+#pragma unroll
+            for (int g = 0; g < (NB << a); g++) {
+                const int k = g * 2 * half + j;
+                const double u = v[k], y = F.mulmod(v[k + half], w, wq);
+                v[k] = u + y, v[k + half] = u - y;
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < NV; x++) X[((s * NB + x / BL) * BL + x % BL) * CO + co] = F.norm(v[x]);       // the words it read
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; k++) v[k] = X[(k * BL + s) * CO + co];
+#pragma unroll
+    for (int a = L1 - 1; a >= 0; a--) {
+        const int half = NV >> (a + 1);
+#pragma unroll
+        for (int j = 0; j < half; j++) {
+            const double w = wt[1][(j * BL + s) << a], wq = w * F.qinv;
+#pragma unroll
+            for (int g = 0; g < (1 << a); g++) {
+                const int k = g * 2 * half + j;
+                const double u = v[k], y = F.mulmod(v[k + half], w, wq);
+                v[k] = u + y, v[k + half] = u - y;
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NV; k++) {
+        const int c = k * BL + s;
+        if (c < shared) __builtin_nontemporal_store(F.canon(v[k]), out + (size_t)c * ctw + comp * cs + o);
+    }
+}
+// where the FP64 form runs (its Mhat is kept as plain residues, the integer form's in multiplier form)
+static bool mask_ntt_fp(const cm_ctx *ctx, int E, int limbs) {
+    bool fp = E >= 16 && E <= 256;
+    for (int l = 0; l < limbs; l++) fp = fp && ctx->mod[l] < (1ULL << 50);
+    return fp;
+}
 // CO = min(64, 4096 / E) coefficients per workgroup (32 KiB of LDS at most); 8 <= E <= 512
 static int mask_ntt_log_co(int E) {
     int lg = 6;
@@ -1332,13 +1459,25 @@ void launch_mask_ntt_setup(cm_ctx *ctx, u64 *Mhat, const u64 *M, const u64 *tw, 
     while ((1 << logE) < E) logE++;
     const int lg = mask_ntt_log_co(E);
     hipLaunchKernelGGL(k_mask_ntt<0>, dim3(ctx->n >> lg, limbs, 1), dim3(TPB), ((size_t)E << lg) * 8, st, Mhat, M, nullptr, tw, einv,
-                       ctx->d_modc, E, E, logE, E, limbs, ctx->n, lg);
+                       ctx->d_modc, mask_ntt_fp(ctx, E, limbs) ? 0 : E, E, logE, E, limbs, ctx->n, lg);
 }
 void launch_mask_ntt(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *Mhat, const u64 *tw, const u64 *einv, int nk, int E, int shared,
                      int limbs, hipStream_t st) {
     Prof prof_(ctx, CM_K_ELEMENTWISE, (double)E * 2 * limbs, st);
     int logE = 0;
     while ((1 << logE) < E) logE++;
+    if (mask_ntt_fp(ctx, E, limbs)) {
+#define MASK_FP(L1_, L2_)                                                                                                        \
+    hipLaunchKernelGGL((k_mask_ntt_fp<L1_, L2_>), dim3(2 * ctx->n / (TPB >> L2_), limbs), dim3(TPB), 0, st, A, T, Mhat, tw, ctx->d_fpq, nk, \
+                       shared, limbs, ctx->n)
+        if (logE == 4) MASK_FP(2, 2);
+        else if (logE == 5) MASK_FP(3, 2);
+        else if (logE == 6) MASK_FP(3, 3);
+        else if (logE == 7) MASK_FP(4, 3);
+        else MASK_FP(4, 4);
+#undef MASK_FP
+        return;
+    }
     const int lg = mask_ntt_log_co(E);
     hipLaunchKernelGGL(k_mask_ntt<1>, dim3(ctx->n >> lg, limbs, 2), dim3(TPB), ((size_t)E << lg) * 8, st, A, T, Mhat, tw, einv,
                        ctx->d_modc, nk, E, logE, shared, limbs, ctx->n, lg);

@@ -59,3 +59,31 @@ def test_key_switches_match_the_oracle(n, n_q, n_p, alpha, q0_bits, qi_bits, p_b
             same(octx.rescale(orl), gctx.rescale(grl))
     finally:
         gctx.close()
+
+
+def test_masked_sums_of_32_copies_against_float64():
+    """q K^T through the FP64 transform of length 32 (radix 8 x 4; the other lengths are compared limb for limb elsewhere),
+    with the last ciphertext partly filled and half of the rows written, against float64 and the printed order."""
+    from oracle import packing
+    from paper_2602_11470_amd import binding as B, inputs
+    gctx = B.config1()
+    try:
+        H, E, lv = 8, 32, gctx.L - 1
+        lay = packing.KvLayout(gctx.S, H, E)
+        nk = 32
+        ntok = nk * lay.t - 3
+        q, K, _, _ = inputs.attention_inputs(23, H, 2, E, ntok)
+        q = q * 0.3
+        sk = gctx.keygen_secret(1)
+        enc = lambda v, seed: gctx.level_drop(gctx.encrypt(sk, gctx.encode(v, gctx.L), seed), lv)
+        want = np.einsum("he,nhe->hn", q, K)
+        for shared in (32, 16):                              # nk * shared >= 16 E: the transform
+            kv = gctx.kv_create(H, E, lv, unrolled_ladders=True, shared_dims=shared)
+            keys = gctx.keygen_rotations(sk, kv.steps(), 2, with_relin=True)
+            for c in range(nk):
+                kv.load(B.CM_QK, c, enc(lay.pack_k(K, c), 100 + c))
+            kv.set_tokens(ntok)
+            got = gctx.decrypt(sk, gctx.vmm_kv(keys, kv, B.CM_QK, enc(lay.pack_vec(q), 10))).real
+            assert np.abs(lay.unpack_scores(got, ntok) - want).max() < 1e-4
+    finally:
+        gctx.close()
