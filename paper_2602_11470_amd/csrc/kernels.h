@@ -97,8 +97,10 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // pts: all r_i*r_o plaintexts in the blocked layout written by launch_pt_block
 void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
                     size_t ct_stride, int k0, int k1, hipStream_t st);
+// words of the blocked array
+size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level);
 // copies plaintext (j,k) from plain[limbs][n] into the blocked array (to_blocked) or back
-void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int r_i, int r_o, int j, int k, bool to_blocked,
+void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int level, int r_i, int r_o, int j, int k, bool to_blocked,
                      hipStream_t st);
 
 // Tail of a ModDown fused into the last pass of the forward transform of its converted limbs:

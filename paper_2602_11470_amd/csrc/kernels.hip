@@ -598,8 +598,8 @@ void launch_inner_product_shared_key(cm_ctx *ctx, const IpBatch &b, int beta, in
 // k_inner_product_batch, but the digits are read once per IP_FAN_CHUNK keys instead of once per key.
 // NB = compile-time bound of the digit count: registers for eight digits leave three waves a SIMD, each with the two or three
 // loads in flight that a low level has; sized for its digits the kernel runs four to eight waves.  Bound by memory (one half
-// to two thirds reads): the 63 baby steps of a 4096 x 4096 product at level 4 (two digits) 328 -> 290 us, the 127 of an MLP
-// projection at level 3 499 -> 400 us.  Requesting the next rotation's words ahead as well changed nothing.
+// to two thirds reads): the 63 baby steps of a 4096 x 4096 product at level 4 (two digits) 328 -> 243 us, the 127 of a
+// 16384 x 4096 one at level 3 499 -> 361 us.  Requesting the next rotation's words ahead as well changed nothing.
 #define IP_FAN_CHUNK 8
 template <bool SA, int NB>
 __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64 *__restrict__ dig, const u64 *__restrict__ c0,
@@ -986,10 +986,9 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // ---- packed product: inner_k = sum_j baby_j * p_{j,k} ---------------------------------------------------
 // babies: r_i ciphertexts [2][limbs][n] at stride ct_stride; out: r_o ciphertexts at stride
 // ct_stride; pts: the r_i*r_o plaintexts in multiplier form, blocked for streaming:
-//     word c of chunk ch (64 coefficients) of limb l of plaintext (j,k) at
-//     (((l*(n/64) + ch)*r_o + k)*r_i + j)*64 + c
-// so that the workgroup that owns (l, ch) reads one contiguous run of r_o*r_i*512 bytes, and the
-// wave that owns k one run of r_i*512 bytes.  Limb l has
+//     the words of plaintexts (0 .. r_i-1, k) of chunk ch (64 coefficients) of limb l are one contiguous run
+// (MacLayout), the runs of a chunk follow each other in k: the workgroup that owns (l, ch) reads one contiguous
+// stretch, the wave that owns k one run of it.  Limb l has
 // modulus index l up to `level`, and the special primes follow when limbs = level + 1 + K (sums
 // kept in the extended basis).
 // The baby ciphertexts are staged in LDS: a workgroup owns 64 coefficients of
@@ -1009,18 +1008,73 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // sums are renormalised every four terms (|sum| < 4.6 q < 2^53 stays exact).  That is 8.5
 // instructions per product against 17 for the 128-bit integer form.  The plaintexts are stored in
 // multiplier form (times 2^64), so the finished sum is multiplied by 2^-64 mod q.
-// With an even number of baby steps the words of plaintexts (2j', k) and (2j'+1, k) are interleaved
+// Limbs below 2^50 are stored packed where there are at least eight baby steps: the eight words of plaintexts (8g .. 8g+7, k)
+// of a coefficient as their low 32 bits (two 16-byte lane words, 1 KiB a wave each), the next 16 bits (one) and the top two
+// bits (one halfword): 50 bytes instead of 64, all loads aligned, whole lines a wave.  Unpacking takes three more
+// instructions a word in a kernel that waits for memory.  Fewer than eight baby steps and the integer limbs keep
+// 64-bit words.  Measured per kernel, unpacked -> packed: a 4096 x 4096 product at level 23 1681 -> 1588 us, at level 4
+// 540 -> 519, a 16384 x 4096 product at level 3 1713 -> 1623,
+// 32 tokens of 1024 x 1024 at level 9 1567 -> 1441; two or three groups
+// in flight instead of one (100 and more VGPRs a lane, half the waves) cost 3 to 5% of a product.
+// Otherwise, with an even number of baby steps, the words of plaintexts (2j', k) and (2j'+1, k) are interleaved
 // (word c of the pair at 2c, 2c+1 of a 128-word row), so that a lane reads both with one 16-byte load and a
 // wavefront instruction covers 1 KiB of the stream.
-__host__ __device__ __forceinline__ size_t mac_pt_index(int n, int r_i, int r_o, int l, int ch, int k, int j, int c) {
-    const size_t row = (((size_t)l * (n / MAC_CO) + ch) * r_o + k) * r_i;
-    return (r_i & 1) ? (row + j) * MAC_CO + c : (row + (j & ~1)) * MAC_CO + 2 * c + (j & 1);
+#define MAC_PACK_WORDS 400                     // 64-bit words of a packed group: 64 coefficients x 8 plaintexts
+struct MacLayout {
+    int n, r_i, r_o;
+    u64 packed;                                // bit l: limb l is packed
+    __host__ __device__ __forceinline__ bool is_packed(int l) const { return (packed >> l) & 1; }
+    // words of limb l, first word of limb l, first word of the run of (limb, chunk, k)
+    __host__ __device__ __forceinline__ size_t limb_words(int l) const {
+        return (size_t)(n / MAC_CO) * r_o * (is_packed(l) ? (size_t)(r_i / 8) * MAC_PACK_WORDS : (size_t)r_i * MAC_CO);
+    }
+    __host__ __device__ __forceinline__ size_t limb_base(int l) const {
+        const int below = __builtin_popcountll(packed & ((1ULL << l) - 1));
+        const size_t rows = (size_t)(n / MAC_CO) * r_o;
+        return rows * ((size_t)below * (r_i / 8) * MAC_PACK_WORDS + (size_t)(l - below) * r_i * MAC_CO);
+    }
+    __host__ __device__ __forceinline__ size_t run(int l, int ch, int k) const {
+        return limb_base(l) + ((size_t)ch * r_o + k) * (is_packed(l) ? (size_t)(r_i / 8) * MAC_PACK_WORDS : (size_t)r_i * MAC_CO);
+    }
+    // unpacked limbs: word (j, c) of a run
+    __host__ __device__ __forceinline__ size_t word(int j, int c) const {
+        return (r_i & 1) ? (size_t)j * MAC_CO + c : (size_t)(j & ~1) * MAC_CO + 2 * c + (j & 1);
+    }
+};
+static MacLayout mac_layout(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level) {
+    MacLayout m{ctx->n, r_i, r_o, 0};
+    if (r_i % 8 == 0)
+        for (int l = 0; l < limbs; l++)
+            if (ctx->mod[l <= level ? l : ctx->L + (l - level)] < (1ULL << 50)) m.packed |= 1ULL << l;
+    return m;
+}
+size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level) {
+    const MacLayout m = mac_layout(ctx, r_i, r_o, limbs, level);
+    size_t w = 0;
+    for (int l = 0; l < limbs; l++) w += m.limb_words(l);
+    return w;
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+struct MacGroup { u32x4 lo0, lo1, mid; unsigned top; };       // a lane's eight packed words
+__device__ __forceinline__ MacGroup mac_load_packed(const u64 *grp, int co) {
+    MacGroup g;
+    const u32x4 *v = reinterpret_cast<const u32x4 *>(grp);
+    g.lo0 = __builtin_nontemporal_load(v + co), g.lo1 = __builtin_nontemporal_load(v + 64 + co);
+    g.mid = __builtin_nontemporal_load(v + 128 + co);
+    g.top = __builtin_nontemporal_load(reinterpret_cast<const unsigned short *>(v + 192) + co);
+    return g;
+}
+__device__ __forceinline__ double mac_word(const MacGroup &g, int jj) {       // word jj as an exact double
+    const unsigned lo = jj < 4 ? g.lo0[jj & 3] : g.lo1[jj & 3], m = g.mid[jj >> 1];
+    const unsigned hi = ((((g.top >> (2 * jj)) & 3u) << 16) | ((jj & 1) ? m >> 16 : m & 0xFFFFu)) | 0x43300000u;
+    return __hiloint2double((int)hi, (int)lo) - 4503599627370496.0;
 }
 __global__ __launch_bounds__(TPB) void k_vmm_mac_lds(u64 *__restrict__ out, const u64 *__restrict__ babies,
                                                      const u64 *__restrict__ pts, const ModC *__restrict__ modc,
-                                                     const FpQ *__restrict__ fpq, int r_i, int r_o, int limbs, int n,
+                                                     const FpQ *__restrict__ fpq, MacLayout lay, int limbs, int n,
                                                      size_t ct_stride, int k0, int k1, int level, int L) {
     __shared__ u64 sb[MAC_JC * 2 * MAC_CO];
+    const int r_i = lay.r_i;
     // the limbs of the special primes (integer products, the slowest workgroups) are dispatched first, not last
     const int nsp = limbs - (level + 1), y = blockIdx.y;
     const int l = y < nsp ? level + 1 + y : y - nsp, ch = blockIdx.x, i0 = ch * MAC_CO;
@@ -1028,11 +1082,10 @@ __global__ __launch_bounds__(TPB) void k_vmm_mac_lds(u64 *__restrict__ out, cons
     const int mi = l <= level ? l : L + 1 + (l - level - 1);
     const ModC m = modc[mi];
     const FpQ fq = fpq[mi];
-    const bool fp = fq.q != 0.0;
+    const bool fp = fq.q != 0.0, packed = lay.is_packed(l);
     const bool pair = !(r_i & 1);
     const MacFp F{fq.q, fq.qinv};
     const size_t o = (size_t)l * n + i0, cs = (size_t)limbs * n;
-    const u64 *pblk = pts + ((size_t)l * (n / MAC_CO) + ch) * r_o * r_i * MAC_CO;
     // up to MAC_KW giant steps per wave keep their running sums in registers across the passes over the baby steps
     // (otherwise every pass after the first re-reads and re-writes the output)
     u64 acc0[MAC_KW], acc1[MAC_KW];
@@ -1061,52 +1114,64 @@ __global__ __launch_bounds__(TPB) void k_vmm_mac_lds(u64 *__restrict__ out, cons
         // A sum of products is reduced when one more group of 8 could pass q * 2^64 (the bound of
         // REDC): after every group for the 60-bit special primes.
         for (int k = k0 + kq; k < k1; k += 4) {
-            const u64 *pk = pblk + ((size_t)k * r_i + j0) * MAC_CO;
-            // words of plaintexts j0 + j8 .. j0 + j8 + MAC_G - 1 for this lane's coefficient (zero past the end)
-            auto load_group = [&](int j8, u64 (&w)[MAC_G]) {
-                if (pair) {
-#pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj += 2) {
-                        u64x2 v = {0, 0};
-                        if (j8 + jj < jn) v = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(pk + (size_t)(j8 + jj) * MAC_CO) + co);
-                        w[jj] = v.x, w[jj + 1] = v.y;
-                    }
-                } else {
-#pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj++) w[jj] = j8 + jj < jn ? __builtin_nontemporal_load(pk + (size_t)(j8 + jj) * MAC_CO + co) : 0;
-                }
-            };
-            u64 p[MAC_G], pn[MAC_G];
-            load_group(0, p);
+            const u64 *run = pts + lay.run(l, ch, k);
             u64 v0, v1;
-            if (fp) {
+            if (packed) {
+                const u64 *pk = run + (size_t)(j0 / 8) * MAC_PACK_WORDS;
+                MacGroup p = mac_load_packed(pk, co), pn = p;
                 double s0 = 0.0, s1 = 0.0;
-                for (int j8 = 0; j8 < jn; j8 += MAC_G) {
+                for (int j8 = 0; j8 < jn; j8 += 8) {
                     // the next group is in flight while this one is multiplied
-                    load_group(j8 + MAC_G, pn);
+                    if (j8 + 8 < jn) pn = mac_load_packed(pk + (size_t)(j8 / 8 + 1) * MAC_PACK_WORDS, co);
 #pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj++) {
-                        if (j8 + jj < jn) {
-                            const double a = MacFp::from_u64(p[jj]), aq = a * F.qinv;
-                            s0 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 0) * MAC_CO + co]), a, aq);
-                            s1 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 1) * MAC_CO + co]), a, aq);
-                        }
+                    for (int jj = 0; jj < 8; jj++) {
+                        const double a = mac_word(p, jj), aq = a * F.qinv;
+                        s0 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 0) * MAC_CO + co]), a, aq);
+                        s1 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 1) * MAC_CO + co]), a, aq);
                         if ((jj & 3) == 3) s0 = F.norm(s0), s1 = F.norm(s1);
                     }
-#pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj++) p[jj] = pn[jj];
+                    p = pn;
                 }
                 v0 = F.canon(F.mulmod(s0, fq.rinv, fq.rinvq));
                 v1 = F.canon(F.mulmod(s1, fq.rinv, fq.rinvq));
             } else {
-                v0 = v1 = 0;
-                for (int j8 = 0; j8 < jn; j8 += MAC_G) {
-                    load_group(j8 + MAC_G, pn);
+                const u64 *pk = run + (size_t)j0 * MAC_CO;
+                // words of plaintexts j0 + j8 .. j0 + j8 + MAC_G - 1 for this lane's coefficient (zero past the end)
+                auto load_group = [&](int j8, u64 (&w)[MAC_G]) {
+                    if (pair) {
 #pragma unroll
-                    for (int h = 0; h < MAC_G; h += 8) {
+                        for (int jj = 0; jj < MAC_G; jj += 2) {
+                            u64x2 v = {0, 0};
+                            if (j8 + jj < jn) v = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(pk + (size_t)(j8 + jj) * MAC_CO) + co);
+                            w[jj] = v.x, w[jj + 1] = v.y;
+                        }
+                    } else {
+#pragma unroll
+                        for (int jj = 0; jj < MAC_G; jj++) w[jj] = j8 + jj < jn ? __builtin_nontemporal_load(pk + (size_t)(j8 + jj) * MAC_CO + co) : 0;
+                    }
+                };
+                u64 p[MAC_G], pn[MAC_G];
+                load_group(0, p);
+                if (fp) {                      // fewer than eight baby steps
+                    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                    for (int jj = 0; jj < MAC_G; jj++) {
+                        if (jj < jn) {
+                            const double a = MacFp::from_u64(p[jj]), aq = a * F.qinv;
+                            s0 += F.mulmod(__longlong_as_double((long long)sb[(jj * 2 + 0) * MAC_CO + co]), a, aq);
+                            s1 += F.mulmod(__longlong_as_double((long long)sb[(jj * 2 + 1) * MAC_CO + co]), a, aq);
+                        }
+                        if ((jj & 3) == 3) s0 = F.norm(s0), s1 = F.norm(s1);
+                    }
+                    v0 = F.canon(F.mulmod(s0, fq.rinv, fq.rinvq));
+                    v1 = F.canon(F.mulmod(s1, fq.rinv, fq.rinvq));
+                } else {
+                    v0 = v1 = 0;
+                    for (int j8 = 0; j8 < jn; j8 += MAC_G) {
+                        load_group(j8 + MAC_G, pn);
                         u128 s0 = 0, s1 = 0;
 #pragma unroll
-                        for (int jj = h; jj < h + 8; jj++) {
+                        for (int jj = 0; jj < MAC_G; jj++) {
                             if (j8 + jj < jn) {
                                 s0 += (u128)sb[((j8 + jj) * 2 + 0) * MAC_CO + co] * p[jj];
                                 s1 += (u128)sb[((j8 + jj) * 2 + 1) * MAC_CO + co] * p[jj];
@@ -1114,9 +1179,9 @@ __global__ __launch_bounds__(TPB) void k_vmm_mac_lds(u64 *__restrict__ out, cons
                         }
                         v0 = addmod(v0, redc(s0, m.q, m.qinv), m.q);
                         v1 = addmod(v1, redc(s1, m.q, m.qinv), m.q);
-                    }
 #pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj++) p[jj] = pn[jj];
+                        for (int jj = 0; jj < MAC_G; jj++) p[jj] = pn[jj];
+                    }
                 }
             }
             u64 *dst = out + (size_t)k * ct_stride + o + co;
@@ -1146,7 +1211,7 @@ void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, in
                     size_t ct_stride, int k0, int k1, hipStream_t st) {
     Prof prof_(ctx, CM_K_VMM_MAC, r_i * (k1 - k0), st);
     hipLaunchKernelGGL(k_vmm_mac_lds, dim3(ctx->n / MAC_CO, limbs), dim3(TPB), 0, st, out, babies, pts, ctx->d_modc,
-                       ctx->d_fpq, r_i, r_o, limbs, ctx->n, ct_stride, k0, k1, level, ctx->L);
+                       ctx->d_fpq, mac_layout(ctx, r_i, r_o, limbs, level), limbs, ctx->n, ct_stride, k0, k1, level, ctx->L);
 }
 // ---- masks before the shared rotations of query-times-K --------------------------------------------------
 // A[k] = sum_{c < nk} T[c] * M[(c + k) mod E] for k < shared: T the nk key-ciphertext sums [2][limbs][n] (stacked),
@@ -1482,16 +1547,32 @@ void launch_mask_ntt(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *Mhat, const u
     hipLaunchKernelGGL(k_mask_ntt<1>, dim3(ctx->n >> lg, limbs, 2), dim3(TPB), ((size_t)E << lg) * 8, st, A, T, Mhat, tw, einv,
                        ctx->d_modc, nk, E, logE, shared, limbs, ctx->n, lg);
 }
-// plaintext (j,k) between its plain form src[limbs][n] and its place in the blocked array
-__global__ void k_pt_block(u64 *blocked, u64 *plain, int n, int r_i, int r_o, int j, int k, int to_blocked) {
-    const int i = blockIdx.x * TPB + threadIdx.x, l = blockIdx.y;
-    const size_t b = mac_pt_index(n, r_i, r_o, l, i / MAC_CO, k, j, i % MAC_CO);
+// plaintext (j,k) between its plain form src[limbs][n] and its place in the blocked array.  The top bits of a packed group
+// share a halfword: a launch writes one plaintext, so a lane reads and writes its halfword alone.
+__global__ void k_pt_block(u64 *blocked, u64 *plain, MacLayout lay, int n, int j, int k, int to_blocked) {
+    const int i = blockIdx.x * TPB + threadIdx.x, l = blockIdx.y, co = i % MAC_CO;
+    u64 *run = blocked + lay.run(l, i / MAC_CO, k);
     const size_t p = (size_t)l * n + i;
-    if (to_blocked) blocked[b] = plain[p];
-    else plain[p] = blocked[b];
+    if (!lay.is_packed(l)) {
+        const size_t b = lay.word(j, co);
+        if (to_blocked) run[b] = plain[p];
+        else plain[p] = run[b];
+        return;
+    }
+    const int jj = j & 7;
+    char *grp = (char *)(run + (size_t)(j / 8) * MAC_PACK_WORDS);
+    unsigned *lo = (unsigned *)(grp + (jj / 4) * 1024) + co * 4 + (jj & 3);
+    unsigned short *mid = (unsigned short *)(grp + 2048) + co * 8 + jj, *top = (unsigned short *)(grp + 3072) + co;
+    if (to_blocked) {
+        const u64 v = plain[p];
+        *lo = (unsigned)v, *mid = (unsigned short)(v >> 32);
+        *top = (unsigned short)((*top & ~(3u << (2 * jj))) | ((unsigned)(v >> 48) << (2 * jj)));
+    } else {
+        plain[p] = (u64)*lo | ((u64)*mid << 32) | ((u64)((*top >> (2 * jj)) & 3u) << 48);
+    }
 }
-void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int r_i, int r_o, int j, int k, bool to_blocked,
+void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int level, int r_i, int r_o, int j, int k, bool to_blocked,
                      hipStream_t st) {
-    hipLaunchKernelGGL(k_pt_block, dim3(ctx->n / TPB, limbs), dim3(TPB), 0, st, blocked, plain, ctx->n, r_i, r_o, j, k,
-                       to_blocked ? 1 : 0);
+    hipLaunchKernelGGL(k_pt_block, dim3(ctx->n / TPB, limbs), dim3(TPB), 0, st, blocked, plain, mac_layout(ctx, r_i, r_o, limbs, level),
+                       ctx->n, j, k, to_blocked ? 1 : 0);
 }

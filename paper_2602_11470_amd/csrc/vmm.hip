@@ -33,7 +33,7 @@ struct cm_vmm_plan {
     u64 *d_many = nullptr;     // direct: r_o - 1 ciphertexts, their coefficient-domain c1 and their raised digits
     int pt_limbs;              // level+1, or level+1+K when raised
     int *d_pt_mods = nullptr;  // modulus index of every plaintext limb
-    u64 *d_pts = nullptr;      // r_i*r_o plaintexts of pt_limbs limbs, multiplier form, blocked by 64 coefficients
+    u64 *d_pts = nullptr;      // r_i*r_o plaintexts of pt_limbs limbs, multiplier form, blocked by 64 coefficients and packed
     u64 *d_work = nullptr;     // r_i baby + r_o inner ciphertexts of 2*pt_limbs limbs, 3 temporary ciphertexts, one more sum
 };
 
@@ -155,7 +155,8 @@ static cm_status plan_alloc(cm_vmm_plan *p, bool raised, bool direct, bool unrol
     const size_t n = ctx->n, ptw = (size_t)p->pt_limbs * n, ctw = 2 * (size_t)(p->level + 1) * n;
     if (hipMalloc((void **)&p->d_pt_mods, mods.size() * sizeof(int)) != hipSuccess) return CM_E_NOMEM;
     if (hipMemcpy(p->d_pt_mods, mods.data(), mods.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) return CM_E_HIP;
-    if (hipMalloc((void **)&p->d_pts, (size_t)p->M * ptw * 8) != hipSuccess) return CM_E_NOMEM;
+    const size_t pts_bytes = vmm_pts_words(ctx, p->r_i, p->r_o, p->pt_limbs, p->level) * 8;
+    if (hipMalloc((void **)&p->d_pts, pts_bytes) != hipSuccess) return CM_E_NOMEM;
     // r_i baby + r_o inner ciphertexts, 3 temporaries on the ciphertext limbs, one more on the plaintext limbs
     if (hipMalloc((void **)&p->d_work, ((size_t)(p->r_i + p->r_o + 1) * 2 * ptw + 3 * ctw) * 8) != hipSuccess) return CM_E_NOMEM;
     if (direct && p->r_o > 1) {
@@ -176,7 +177,7 @@ static cm_status plan_load_diag(cm_vmm_plan *p, int idx, const int64_t *coeffs) 
     launch_reduce_i64(ctx, plain, (const long long *)stage, p->d_pt_mods, p->pt_limbs, 0);
     launch_ntt_rows(ctx, plain, nullptr, p->d_pt_mods, p->pt_limbs, false, 0);
     launch_to_mont(ctx, plain, p->d_pt_mods, p->pt_limbs, 0);
-    launch_pt_block(ctx, p->d_pts, plain, p->pt_limbs, p->r_i, p->r_o, idx / p->r_o, idx % p->r_o, true, 0);
+    launch_pt_block(ctx, p->d_pts, plain, p->pt_limbs, p->level, p->r_i, p->r_o, idx / p->r_o, idx % p->r_o, true, 0);
     HIPCHK(hipDeviceSynchronize());
     return CM_OK;
 }
@@ -294,7 +295,7 @@ extern "C" cm_status cm_vmm_plan_diag_export(cm_ctx *ctx, const cm_vmm_plan *p, 
     u64 *tmp = nullptr;
     HIPCHK(hipDeviceSynchronize());
     if (hipMalloc((void **)&tmp, words * 8) != hipSuccess) return CM_E_NOMEM;
-    launch_pt_block(ctx, p->d_pts, tmp, p->pt_limbs, p->r_i, p->r_o, j, k, false, 0);
+    launch_pt_block(ctx, p->d_pts, tmp, p->pt_limbs, p->level, p->r_i, p->r_o, j, k, false, 0);
     launch_from_mont(ctx, tmp, tmp, p->d_pt_mods, p->pt_limbs, 0);
     launch_ntt_rows(ctx, tmp, nullptr, p->d_pt_mods, p->pt_limbs, true, 0);
     hipError_t e = hipMemcpy(out, tmp, words * 8, hipMemcpyDeviceToHost);
