@@ -92,6 +92,7 @@ struct FpQ {
 #define CM_MAX_DIGITS 16
 #define CM_GAUSS_K 19
 #define CM_KS_BATCH 8      // hoisted rotations whose ModDown runs as one batch
+#define CM_MASK_BATCH 32   // masked products of a cache append in one batch, at most (rescale_masked_batch)
 #define CM_NTT_MAX_LIMBS 1024
 
 struct ConvTable {            // fast base conversion src -> dst (all indices into the modulus list)

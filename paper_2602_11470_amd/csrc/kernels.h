@@ -8,10 +8,10 @@ void launch_to_mont(cm_ctx *ctx, u64 *data, const int *d_mod_idx, int limbs, hip
 void launch_from_mont(cm_ctx *ctx, u64 *out, const u64 *in, const int *d_mod_idx, int limbs, hipStream_t st);
 void launch_add(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int ncomp, int limbs, hipStream_t st);
 void launch_mul_pt(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *pt_mont, int ncomp, int limbs, hipStream_t st);
-// out[z][2][limbs][n] = src[z] * (pt rotated by the Galois element g[z]) for z < cnt <= CM_KS_BATCH
+// out[z][2][limbs][n] = src[z] * (pt rotated by the Galois element g[z]) for z < cnt <= CM_MASK_BATCH
 struct MulPtBatch {
-    const u64 *src[CM_KS_BATCH];
-    unsigned g[CM_KS_BATCH];
+    const u64 *src[CM_MASK_BATCH];
+    unsigned g[CM_MASK_BATCH];
 };
 void launch_mul_pt_rot_batch(cm_ctx *ctx, u64 *out, const MulPtBatch &b, int cnt, const u64 *pt_mont, int limbs, hipStream_t st);
 // the same products on the last of the `limbs` limbs only: out[z][2][n]
@@ -109,16 +109,16 @@ void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int level
 struct FinishBatch {
     int items = 0, level = 0, ext = 0, addend_comps = 0;
     int ncomp = 2, comp0 = 0;         // components handled per item, and the first of them (1, 1: second component only)
-    const u64 *u[CM_KS_BATCH];        // [2][ext][n] per item (evaluation domain)
-    u64 *out[CM_KS_BATCH];            // [2][level+1][n] per item
-    const u64 *accum[CM_KS_BATCH];    // nullable; may alias out
-    unsigned g[CM_KS_BATCH];
-    const u64 *addend[CM_KS_BATCH];   // [2][level+1][n] per item, nullable; must not alias any out
+    const u64 *u[CM_MASK_BATCH];        // [2][ext][n] per item (evaluation domain)
+    u64 *out[CM_MASK_BATCH];            // [2][level+1][n] per item
+    const u64 *accum[CM_MASK_BATCH];    // nullable; may alias out
+    unsigned g[CM_MASK_BATCH];
+    const u64 *addend[CM_MASK_BATCH];   // [2][level+1][n] per item, nullable; must not alias any out
     const u64 *pinv = nullptr;        // [level+1][2]: P^{-1} mod q_l and its Shoup companion
     // u_r is not stored but formed on the fly as u[r] * (mul_pt read through the Galois map mul_g[r]): the masked
     // products of a cache append, whose rescale is this tail (mul_pt[ext][n], multiplier form; nullable)
     const u64 *mul_pt = nullptr;
-    unsigned mul_g[CM_KS_BATCH] = {};
+    unsigned mul_g[CM_MASK_BATCH] = {};
 };
 // forward transform of conv[items*ncomp*(level+1)][n] (mods 0..level repeating) with that tail
 // with src: the first pass reads row d_src_rows[i] of src for limb i (words below twice that limb's modulus) instead of conv
@@ -140,6 +140,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
                      int limbs, const FinishBatch *fb = nullptr);
 
 // ops.hip internals shared with vmm.hip
+int rescale_masked_batch(cm_ctx *ctx, int level, size_t words);
 bool rescale_masked_into(cm_ctx *ctx, const MulPtBatch &mb, int cnt, const u64 *pt, int level, u64 *out, hipStream_t st,
                          u64 *last, u64 *red, bool accumulate);
 struct KsLevel {            // cached per level: which rows of the digit array are converted / transformed

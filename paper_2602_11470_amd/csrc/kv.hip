@@ -380,29 +380,32 @@ static cm_status kv_append(cm_ctx *ctx, const cm_evk *evk, cm_kv *kv, const cm_c
         }
         CMCHK(ks_apply_many(ctx, digits, lv, kv->r_o - 1, keys.data(), gs.data(), v_new->dev, dst.data(), st));
     }
-    // CM_KS_BATCH value ciphertexts at a time: their masked products in one launch, one stacked rescale,
-    // one stacked addition (consecutive value ciphertexts are contiguous)
-    u64 *prods = shifted + (size_t)(kv->r_o > 1 ? kv->r_o - 1 : 0) * ctw_up, *ress = prods + (size_t)CM_KS_BATCH * ctw_up;
-    u64 *last = ress + (size_t)CM_KS_BATCH * ctw, *red = last + (size_t)CM_KS_BATCH * 2 * n;
-    for (int kb = 0; kb < kv->E; kb += CM_KS_BATCH) {
-        const int m = kv->E - kb < CM_KS_BATCH ? kv->E - kb : CM_KS_BATCH;
-        MulPtBatch mb;
-        for (int r = 0; r < m; r++) {
-            const int k = kb + r, g = k / kv->r_i;
-            long long a = (long long)(((c - k) % kv->E + kv->E) % kv->E) * kv->H * kv->t + tau +
-                          (long long)g * kv->r_i * kv->H * kv->t;
-            mb.src[r] = g == 0 ? v_new->dev : shifted + (size_t)(g - 1) * ctw_up;
-            mb.g[r] = (unsigned)rot_g(kv, -a);
+    // dst[k] += rescale(mask through the Galois map g(k) * src(k)) for the E ciphertexts of dst (contiguous: the rescale adds
+    // its result onto a run of them), as many per launch as the work area has room for, or, where the rescale does not
+    // form the products itself, CM_KS_BATCH in two steps
+    const u64 *vmask = group ? kv->d_mask_vg : kv->d_mask_v;
+    auto add_masked = [&](u64 *dst, u64 *work, auto src, auto g) -> cm_status {
+        const int fused = rescale_masked_batch(ctx, lv, kv->d_work + kv->work_words - work), B = fused ? fused : CM_KS_BATCH;
+        u64 *last = work, *red = last + (size_t)B * 2 * n, *prods = red + (size_t)B * 2 * lv * n;
+        for (int kb = 0; kb < kv->E; kb += B) {
+            const int m = kv->E - kb < B ? kv->E - kb : B;
+            MulPtBatch mb;
+            for (int r = 0; r < m; r++) mb.src[r] = src(kb + r), mb.g[r] = (unsigned)g(kb + r);
+            if (rescale_masked_into(ctx, mb, m, vmask, lv, dst + (size_t)kb * ctw, st, last, red, true)) continue;
+            launch_mul_pt_rot_batch(ctx, prods, mb, m, vmask, lv + 1, st);
+            CMCHK(rescale_into(ctx, prods, 2 * m, lv, dst + (size_t)kb * ctw, st, last, red, true));
         }
-        // consecutive value ciphertexts are contiguous: the rescale adds its result onto them
-        const u64 *vmask = group ? kv->d_mask_vg : kv->d_mask_v;
-        if (rescale_masked_into(ctx, mb, m, vmask, lv, kv->d_v + (size_t)kb * ctw, st, last, red, true)) continue;
-        launch_mul_pt_rot_batch(ctx, prods, mb, m, vmask, lv + 1, st);
-        CMCHK(rescale_into(ctx, prods, 2 * m, lv, kv->d_v + (size_t)kb * ctw, st, last, red, true));
-    }
+        return CM_OK;
+    };
+    CMCHK(add_masked(kv->d_v, shifted + (size_t)(kv->r_o > 1 ? kv->r_o - 1 : 0) * ctw_up,
+                     [&](int k) { return k < kv->r_i ? v_new->dev : shifted + (size_t)(k / kv->r_i - 1) * ctw_up; },
+                     [&](int k) {
+                         return rot_g(kv, -((long long)(((c - k) % kv->E + kv->E) % kv->E) * kv->H * kv->t + tau +
+                                            (long long)(k / kv->r_i) * kv->r_i * kv->H * kv->t));
+                     }));
     if (kv->indexed) {
         // index: X_{g r_i + j} += rescale(mask * Rot(k_new, j B)), mask = copy (c + g r_i) mod E at residue tau (a group: the
-        // whole copy); the baby rotations of the new key are hoisted, the masked products go eight per launch
+        // whole copy); the baby rotations of the new key are hoisted
         if (kv->r_i > 1) {
             u64 *digits = arena_digits(ctx);
             CMCHK(ks_raise(ctx, k_new->dev + (size_t)(lv + 1) * n, lv, digits, st));
@@ -415,22 +418,10 @@ static cm_status kv_append(cm_ctx *ctx, const cm_evk *evk, cm_kv *kv, const cm_c
             }
             CMCHK(ks_apply_many(ctx, digits, lv, kv->r_i - 1, keys.data(), gs.data(), k_new->dev, dst.data(), st));
         }
-        u64 *xp = shifted + (size_t)(kv->r_i > 1 ? kv->r_i - 1 : 0) * ctw_up, *xr = xp + (size_t)CM_KS_BATCH * ctw_up;
-        u64 *xl = xr + (size_t)CM_KS_BATCH * ctw, *xd = xl + (size_t)CM_KS_BATCH * 2 * n;
-        for (int kb = 0; kb < kv->E; kb += CM_KS_BATCH) {
-            const int m = kv->E - kb < CM_KS_BATCH ? kv->E - kb : CM_KS_BATCH;
-            MulPtBatch mb;
-            for (int r = 0; r < m; r++) {
-                const int place = kb + r, j = place / kv->r_o, g = place % kv->r_o;      // index ciphertext g r_i + j
-                const long long a = (long long)((c + g * kv->r_i) % kv->E) * kv->H * kv->t + tau;
-                mb.src[r] = j == 0 ? k_new->dev : shifted + (size_t)(j - 1) * ctw_up;
-                mb.g[r] = (unsigned)rot_g(kv, -a);
-            }
-            const u64 *xmask = group ? kv->d_mask_vg : kv->d_mask_v;
-            if (rescale_masked_into(ctx, mb, m, xmask, lv, kv->d_x + (size_t)kb * ctw, st, xl, xd, true)) continue;
-            launch_mul_pt_rot_batch(ctx, xp, mb, m, xmask, lv + 1, st);
-            CMCHK(rescale_into(ctx, xp, 2 * m, lv, kv->d_x + (size_t)kb * ctw, st, xl, xd, true));
-        }
+        // place j r_o + g holds index ciphertext g r_i + j
+        CMCHK(add_masked(kv->d_x, shifted + (size_t)(kv->r_i > 1 ? kv->r_i - 1 : 0) * ctw_up,
+                         [&](int k) { return k < kv->r_o ? k_new->dev : shifted + (size_t)(k / kv->r_o - 1) * ctw_up; },
+                         [&](int k) { return rot_g(kv, -((long long)((c + k % kv->r_o * kv->r_i) % kv->E) * kv->H * kv->t + tau)); }));
     }
     kv->ntok += group ? kv->t : 1;
     kv->scale = k_new->scale * (double)ctx->mod[lv] / (double)ctx->mod[lv];

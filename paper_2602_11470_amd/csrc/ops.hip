@@ -56,7 +56,7 @@ static cm_status sync_begin() {
 
 struct KsLevelFull : KsLevel {
     int *d_q_mods3 = nullptr;   // 0..level repeated three times
-    int *d_last_mods = nullptr; // level, repeated for up to RESCALE_MAX_COMPS components
+    int *d_last_mods = nullptr; // level, repeated for up to 2 CM_MASK_BATCH components
     int *d_red_mods = nullptr;  // 0..level-1, repeated likewise
     int *d_red_src = nullptr;   // the component each of those limbs belongs to (its row in the stacked last limbs)
     bool last_fits = false;     // the last modulus is below twice every other one (and below 2^52): its residues can enter
@@ -161,7 +161,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
     k.d_ntt_mods = up(ntt_mods);
     k.h_ntt_rows = ntt_rows, k.h_ntt_mods = ntt_mods;
     k.n_ntt = (int)ntt_rows.size();
-    std::vector<int> sp_rows, sp_mods, q_rows, q3, last(RESCALE_MAX_COMPS, level), red;
+    std::vector<int> sp_rows, sp_mods, q_rows, q3, last(2 * CM_MASK_BATCH, level), red;
     for (int c = 0; c < 2; c++)
         for (int s = 0; s < ctx->K; s++) {
             sp_rows.push_back(c * k.ext + level + 1 + s);
@@ -171,7 +171,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
     for (int c = 0; c < 3; c++)
         for (int i = 0; i <= level; i++) q3.push_back(i);
     std::vector<int> red_src;
-    for (int c = 0; c < RESCALE_MAX_COMPS; c++)
+    for (int c = 0; c < 2 * CM_MASK_BATCH; c++)
         for (int i = 0; i < level; i++) red.push_back(i), red_src.push_back(c);
     if (red.empty()) red.push_back(0), red_src.push_back(0);
     k.last_fits = ctx->mod[level] < (1ULL << 52);
@@ -331,7 +331,7 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
     auto acc_of = [&](int r) { return accums ? accums[r] : nullptr; };
     FinishBatch fb;
     fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = addends ? addend_comps : 0;
-    for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr;
+    for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr;
     for (int r = 0; r < m; r++) {
         fb.u[r] = bu + r * ublk, fb.out[r] = outs[r], fb.accum[r] = acc_of(r), fb.addend[r] = add_of(r);
         fb.g[r] = add_of(r) && gs ? (unsigned)gs[r] : 0;
@@ -369,7 +369,7 @@ cm_status moddown_many_second(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *con
         launch_ntt_rows(ctx, bu, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st);
         FinishBatch fb;
         fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
-        for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+        for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
         for (int r = 0; r < m; r++) fb.u[r] = bu + r * ublk, fb.out[r] = outs[base + r];
         fb.pinv = get_pinv(ctx, level);
         moddown_conv(ctx, k, k.d_moddown, m, A.bconv, bu + (size_t)k.ext * n, ublk, fb, st);
@@ -385,7 +385,7 @@ cm_status moddown_second_keep(cm_ctx *ctx, const u64 *R, int level, u64 *out, hi
     launch_ntt_src(ctx, A.tmp[0], nullptr, R, k.d_sp1_rows, k.d_sp_mods, ctx->K, true, st, 0);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
-    for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+    for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     fb.u[0] = R, fb.out[0] = out, fb.pinv = get_pinv(ctx, level);
     moddown_conv(ctx, k, k.d_moddown0, 1, A.bconv, A.tmp[0], 0, fb, st);
     return CM_OK;
@@ -401,7 +401,7 @@ cm_status moddown_second_keep_many(cm_ctx *ctx, const u64 *Rs, int level, int m,
     launch_ntt_src(ctx, A.tmp[0], nullptr, Rs, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st, 0);
     FinishBatch fb;
     fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
-    for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+    for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     for (int r = 0; r < m; r++) fb.u[r] = Rs + r * ublk, fb.out[r] = outs[r];
     fb.pinv = get_pinv(ctx, level);
     moddown_conv(ctx, k, k.d_moddown0, m, A.bconv, A.tmp[0], (size_t)ctx->K * n, fb, st);
@@ -859,7 +859,7 @@ static cm_status rescale_core(cm_ctx *ctx, const RescaleTabs &k, const u64 *in, 
         // ModDown's, with `level` output rows and level+1 input rows per component and q_level^{-1} for P^{-1}
         FinishBatch fb;
         fb.items = ncomp / 2, fb.level = level - 1, fb.ext = level + 1, fb.addend_comps = 0, fb.ncomp = 2, fb.comp0 = 0;
-        for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+        for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
         for (int r = 0; r < fb.items; r++) {
             fb.u[r] = in + (size_t)r * 2 * (level + 1) * ctx->n, fb.out[r] = out + (size_t)r * 2 * level * ctx->n;
             fb.accum[r] = accumulate ? fb.out[r] : nullptr;
@@ -885,6 +885,16 @@ cm_status rescale_into(cm_ctx *ctx, const u64 *in, int ncomp, int level, u64 *ou
     const RescaleTabs t{k.d_last_rows, k.d_last_mods, k.d_red_mods, k.d_red_src, get_qlinv(ctx, level), k.last_fits};
     return rescale_core(ctx, t, in, ncomp, level, out, st, last, red, accumulate);
 }
+// How many masked products one rescale_masked_into call takes where `words` are free for last and red (0: it would refuse,
+// the caller then works in two steps of CM_KS_BATCH).  The five launches of a batch are short: at eight products a batch
+// they are as many workgroups as the chip holds at once, so every launch pays its ramp and its last wave.  A decode step
+// (32 heads of 128, append of 256 masked products and the attention) with 8 / 16 / 32 a batch: level 3 4183 / 3875 /
+// 3649 us, level 8 7330 / 7033 / 6926.
+int rescale_masked_batch(cm_ctx *ctx, int level, size_t words) {
+    if (!ks_level_full(ctx, level).last_fits || ctx->two_step_masks) return 0;
+    const size_t fit = words / (2 * (size_t)(level + 1) * ctx->n);
+    return fit < CM_MASK_BATCH ? (int)fit : CM_MASK_BATCH;
+}
 // out[r] (+)= rescale(src_r * (pt through the Galois map g_r)) for r < cnt, src_r = mb.src[r] ([2][level+1][n]), out
 // stacked at stride 2*level*n: the products are never stored; only their last limbs are formed (for the inverse
 // transform), the others inside the tail of the forward transform.  Only where rescale_into would take its fused path
@@ -892,13 +902,13 @@ cm_status rescale_into(cm_ctx *ctx, const u64 *in, int ncomp, int level, u64 *ou
 bool rescale_masked_into(cm_ctx *ctx, const MulPtBatch &mb, int cnt, const u64 *pt, int level, u64 *out, hipStream_t st,
                          u64 *last, u64 *red, bool accumulate) {
     const KsLevelFull &k = ks_level_full(ctx, level);
-    if (!k.last_fits || cnt < 1 || cnt > CM_KS_BATCH || !last || !red) return false;
+    if (!k.last_fits || cnt < 1 || cnt > CM_MASK_BATCH || !last || !red) return false;
     if (ctx->two_step_masks) return false;                  // CM_OPT_TWO_STEP_MASKS: multiply, store, then rescale
     launch_mul_pt_rot_last(ctx, last, mb, cnt, pt, level + 1, st);
     launch_ntt(ctx, last, k.d_last_mods, 2 * cnt, true, st);
     FinishBatch fb;
     fb.items = cnt, fb.level = level - 1, fb.ext = level + 1, fb.addend_comps = 0, fb.ncomp = 2, fb.comp0 = 0;
-    for (int r = 0; r < CM_KS_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+    for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     for (int r = 0; r < cnt; r++) {
         fb.u[r] = mb.src[r], fb.out[r] = out + (size_t)r * 2 * level * ctx->n, fb.mul_g[r] = mb.g[r];
         fb.accum[r] = accumulate ? fb.out[r] : nullptr;
