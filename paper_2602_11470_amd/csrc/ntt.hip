@@ -248,16 +248,6 @@ struct Tw {
 };
 template <class A>
 using TableTw = Tw<A, 4>;
-// the same entries read where they are used, for kernels that have no registers to hold them
-template <class A, int ST, int NB = 1>
-struct LazyTw {
-    const A &ar;
-    unsigned b0;
-    __device__ __forceinline__ LazyTw(const A &a_, unsigned b0_) : ar(a_), b0(b0_) {}
-    __device__ __forceinline__ void get(int b, int a, int g, typename A::W &w0, typename A::W &w1) const {
-        ar.pair(ar.word(((b0 + b) << a) + g), w0, w1);
-    }
-};
 // The same entries computed from ONE table word (FP64 limbs): with T_a = tw[base0 << a],
 //   T_2 = T_3^2, T_1 = T_2^2, T_0 = T_1^2      (the exponent brev(base0) >> a doubles each time)
 //   tw[(base0 << a) + g] = T_a * tw[g]          (the low bits g reverse into the top of the exponent)
@@ -453,16 +443,16 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-// The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of 4096 sit in LDS.
+// The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of CH sit in LDS.
 // at(e): where word e of the chunk sits.
-template <int LANES, class AT, class A>
+template <int LANES, int CH = 4096, class AT, class A>
 __device__ __forceinline__ void finish_tail(AT at, const A &ar, const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
-    constexpr int NW = 4096 / LANES;
+    constexpr int NW = CH / LANES;
     // this limb is NTT(conv) of item r, component c, limb l
     const int per = fb.ncomp * (fb.level + 1);
     const int r = limb / per, c = fb.comp0 + (limb % per) / (fb.level + 1), l = limb % (fb.level + 1);
     const u64 pi = fb.pinv[2 * l], pis = fb.pinv[2 * l + 1];
-    const unsigned pos0 = (unsigned)chunk * 4096 + threadIdx.x;
+    const unsigned pos0 = (unsigned)chunk * CH + threadIdx.x;
     const size_t row = ((size_t)c * (fb.level + 1) + l) * n;
     const u64 *up = fb.u[r] + ((size_t)c * fb.ext + l) * n + pos0;
     const u64 *ad = (fb.addend[r] && c < fb.addend_comps) ? fb.addend[r] + row : nullptr;
@@ -633,6 +623,194 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
         rows256_inv_body<FpArith>(lds, p, ps, psrow, g, t, mi, n, chunk);
     else
         rows256_inv_body<IntArith>(lds, p, ps, psrow, g, t, mi, n, chunk);
+}
+
+// ---- passes of a few limbs (n = 65536): four words a lane --------------------------------------------------------------
+// With few limbs a pass takes as long as one lane's chain of loads, butterflies and exchanges: with sixteen words a lane that is
+// 64 butterflies one after the other in a wave alone on its SIMD.  Here 512 lanes own 2048 words as radix 4 x 4 x 4 x 4: a
+// quarter of the chain, two waves on every SIMD, twice the workgroups, for two exchanges more.  Sixteen words -> four, in us:
+// 8 limbs under 60-bit primes, inverse rows 8.6 -> 6.1, columns 9.7 -> 8.4; 4 limbs below 2^50, inverse 6.4 -> 4.2 and
+// 6.4 -> 5.6, forward rows 8.9 -> 5.6; 8 limbs with the ModDown tail 10.5 -> 7.4; columns of 6 limbs forward 6.7 -> 5.4.
+// A rotary embedding at level 3 (three key switches): 168 -> 138 us.
+// The limits: SMALL_COLS, because 64-byte segments cost columns more than the chain once there is work for every compute unit
+// (14 limbs inverse 6.9 -> 11.1; sixteen columns and 1024 lanes: 9.3, and slower below); SMALL_PLAIN for forward rows
+// (13 limbs 9.7 -> 8.0, 28 limbs 13.5 -> 14.0, 58 limbs 16.5 -> 18.4); SMALL_ROWS for inverse rows and forward rows with a tail
+// (35 limbs inverse 14.7 -> 11.3; 64 limbs 20.0 -> 18.9 and 30.3 -> 26.5; 80 limbs with a tail the same).
+#define SMALL_COLS 8
+#define SMALL_PLAIN 16
+#define SMALL_ROWS 64
+#define SMALL_CW 8                // columns of a workgroup
+#define SMALL_THREADS 512
+#define SMALL_CHUNK 2048
+// A column (or a row) of 256 words is shared by 64 lanes.  v[k] = word 64 k + sub on one side, 4 sub + k on the other;
+// at(e): LDS place of word e; R: 1 for the columns (stages 0..7), 256 + row for the rows (stages 8..15).
+template <class A, class AT, class S>
+__device__ __forceinline__ void small_fwd(u64 *lds, typename A::T (&v)[4], const A &ar, unsigned R, int sub, AT at, S sync) {
+    const int hi1 = sub >> 4, lo1 = sub & 15, hi2 = sub >> 2, lo2 = sub & 3;
+    const Tw<A, 2> t1(ar, 4 * R + hi1), t2(ar, 16 * R + hi2), t3(ar, 64 * R + sub);
+    radix_fwd<2, 1, 0>(v, ar, Tw<A, 2>(ar, R));
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(64 * k + sub)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + 16 * k + lo1)]);
+    radix_fwd<2, 1, 2>(v, ar, t1);
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + 16 * k + lo1)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + 4 * k + lo2)]);
+    radix_fwd<2, 1, 4>(v, ar, t2);
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + 4 * k + lo2)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(4 * sub + k)]);
+    radix_fwd<2, 1, 6>(v, ar, t3);
+}
+template <class A, class AT, class S>
+__device__ __forceinline__ void small_inv(u64 *lds, typename A::T (&v)[4], const A &ar, unsigned R, int sub, AT at, S sync) {
+    const int hi1 = sub >> 4, lo1 = sub & 15, hi2 = sub >> 2, lo2 = sub & 3;
+    const Tw<A, 2> t0(ar, R), t1(ar, 4 * R + hi1), t2(ar, 16 * R + hi2);
+    radix_inv<2, 6>(v, ar, Tw<A, 2>(ar, 64 * R + sub));
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(4 * sub + k)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + 4 * k + lo2)]);
+    radix_inv<2, 4>(v, ar, t2);
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + 4 * k + lo2)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + 16 * k + lo1)]);
+    radix_inv<2, 2>(v, ar, t1);
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + 16 * k + lo1)] = ar.to_mid(v[k]);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * k + sub)]);
+    radix_inv<2, 0>(v, ar, t0);
+}
+// SMALL_CW columns of 256 words; the rows that a half-wave touches (neighbours, or four apart) cover all banks
+struct SmallCol {
+    int c;
+    __device__ __forceinline__ int operator()(int e) const { return SMALL_CW * (e ^ ((e >> 2) & (32 / SMALL_CW - 1))) + c; }
+};
+struct SmallRow {
+    int base;
+    __device__ __forceinline__ int operator()(int e) const { return pad(base + e); }
+};
+struct GroupSync {
+    __device__ __forceinline__ void operator()() const { __syncthreads(); }
+};
+struct WaveSync {
+    __device__ __forceinline__ void operator()() const { wave_sync(); }
+};
+template <class A>
+__device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, bool lazy, const NttTables &t, int mi, int n) {
+    A ar;
+    ar.init(t, mi, n);
+    const int n2 = n >> 8, c = threadIdx.x % SMALL_CW, sub = threadIdx.x / SMALL_CW;
+    u64 raw[4];
+    typename A::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) raw[k] = ps[(64 * k + sub) * n2 + c];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = lazy ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
+    small_fwd(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
+#pragma unroll
+    for (int k = 0; k < 4; k++) NTT_ST(p + (4 * sub + k) * n2 + c, ar.to_mid(v[k]));
+}
+template <class A>
+__device__ __forceinline__ void small_cols_inv_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n) {
+    A ar;
+    ar.init(t, mi, n);
+    const int n2 = n >> 8, c = threadIdx.x % SMALL_CW, sub = threadIdx.x / SMALL_CW;
+    typename A::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(p[(4 * sub + k) * n2 + c]);
+    small_inv(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
+#pragma unroll
+    for (int k = 0; k < 4; k++) NTT_ST(p + (64 * k + sub) * n2 + c, ar.to_rest_inv(v[k]));
+}
+// eight rows, a wave each: the exchanges stay inside it
+template <class A, bool TAIL>
+__device__ __forceinline__ void small_rows_fwd_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int chunk, int limb,
+                                                    const FinishBatch &fb) {
+    A ar;
+    ar.init(t, mi, n);
+    const int sub = threadIdx.x & 63, row = threadIdx.x >> 6;
+    p += row * 256;
+    typename A::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(p[64 * k + sub]);
+    small_fwd(lds, v, ar, 256 + 8 * chunk + row, sub, SmallRow{row * 256}, WaveSync());
+#pragma unroll
+    for (int k = 0; k < 4; k++) lds[pad(row * 256 + 4 * sub + k)] = TAIL ? ar.to_tail(v[k]) : ar.to_rest_fwd(v[k]);
+    if (!TAIL) {
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < 4; k++) NTT_ST(p + 64 * k + sub, lds[pad(row * 256 + 64 * k + sub)]);
+        return;
+    }
+    __syncthreads();
+    finish_tail<SMALL_THREADS, SMALL_CHUNK>(pad, ar, lds, t, n, chunk, limb, fb);
+}
+template <class A>
+__device__ __forceinline__ void small_rows_inv_body(u64 *lds, u64 *p, const u64 *psrow, unsigned g, const NttTables &t, int mi, int n,
+                                                    int chunk) {
+    A ar;
+    ar.init(t, mi, n);
+    const int sub = threadIdx.x & 63, row = threadIdx.x >> 6, logn = 31 - __clz(n);
+    const unsigned pos0 = (unsigned)chunk * SMALL_CHUNK + row * 256 + 4 * sub;
+    u64 raw[4];
+    typename A::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) raw[k] = psrow[g ? perm_src(pos0 + k, g, logn) : pos0 + k];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ar.from_rest(raw[k]);
+    small_inv(lds, v, ar, 256 + 8 * chunk + row, sub, SmallRow{row * 256}, WaveSync());
+#pragma unroll
+    for (int k = 0; k < 4; k++) NTT_ST(p + row * 256 + 64 * k + sub, ar.to_mid(v[k]));
+}
+// grid.x = limbs * n / 2048
+__global__ __launch_bounds__(64 * SMALL_CW) void small_cols_fwd(u64 *__restrict__ data, const u64 *__restrict__ src,
+                                                               const int *__restrict__ src_rows, const int *__restrict__ rows,
+                                                               const int *__restrict__ mod_idx, NttTables t, int n) {
+    __shared__ u64 lds[256 * SMALL_CW];
+    const int per = n / (256 * SMALL_CW), limb = blockIdx.x / per, c0 = (blockIdx.x % per) * SMALL_CW, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
+    const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n + c0 : p;
+    if (t.fpq[mi].q != 0.0) small_cols_fwd_body<FpArith>(lds, p, ps, src != nullptr, t, mi, n);
+    else small_cols_fwd_body<IntArith>(lds, p, ps, src != nullptr, t, mi, n);
+}
+__global__ __launch_bounds__(64 * SMALL_CW) void small_cols_inv(u64 *__restrict__ data, const int *__restrict__ rows,
+                                                               const int *__restrict__ mod_idx, NttTables t, int n) {
+    __shared__ u64 lds[256 * SMALL_CW];
+    const int per = n / (256 * SMALL_CW), limb = blockIdx.x / per, c0 = (blockIdx.x % per) * SMALL_CW, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
+    if (t.fpq[mi].q != 0.0) small_cols_inv_body<FpArith>(lds, p, t, mi, n);
+    else small_cols_inv_body<IntArith>(lds, p, t, mi, n);
+}
+template <bool TAIL>
+__global__ __launch_bounds__(SMALL_THREADS) void small_rows_fwd(u64 *__restrict__ data, const int *__restrict__ rows,
+                                                               const int *__restrict__ mod_idx, NttTables t, int n, FinishBatch fb) {
+    __shared__ u64 lds[SMALL_CHUNK + SMALL_CHUNK / 16];
+    const int per = n / SMALL_CHUNK, limb = blockIdx.x / per, chunk = blockIdx.x % per, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + (size_t)chunk * SMALL_CHUNK;
+    if (t.fpq[mi].q != 0.0) small_rows_fwd_body<FpArith, TAIL>(lds, p, t, mi, n, chunk, limb, fb);
+    else small_rows_fwd_body<IntArith, TAIL>(lds, p, t, mi, n, chunk, limb, fb);
+}
+__global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict__ data, const u64 *__restrict__ src,
+                                                               const int *__restrict__ src_rows, const int *__restrict__ rows,
+                                                               const int *__restrict__ mod_idx, NttTables t, int n, unsigned g) {
+    __shared__ u64 lds[SMALL_CHUNK + SMALL_CHUNK / 16];
+    const int per = n / SMALL_CHUNK, limb = blockIdx.x / per, chunk = blockIdx.x % per, mi = mod_idx[limb];
+    u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + (size_t)chunk * SMALL_CHUNK;
+    const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - (size_t)chunk * SMALL_CHUNK;
+    if (t.fpq[mi].q != 0.0) small_rows_inv_body<FpArith>(lds, p, psrow, g, t, mi, n, chunk);
+    else small_rows_inv_body<IntArith>(lds, p, psrow, g, t, mi, n, chunk);
 }
 
 // ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
@@ -1090,6 +1268,21 @@ static NttTables tables_of(const cm_ctx *ctx, bool inverse, int limbs) {
     }
     return t;
 }
+static void launch_cols_fwd(u64 *data, const u64 *src, const int *d_src_rows, const int *d_rows, const int *d_mods, const NttTables &t,
+                            int n, int limbs, hipStream_t st) {
+    if (limbs <= SMALL_COLS)
+        hipLaunchKernelGGL(small_cols_fwd, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, src, d_src_rows, d_rows, d_mods, t, n);
+    else
+        hipLaunchKernelGGL(ntt_cols_fwd, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, src, d_src_rows, d_rows, d_mods, t, n, n >> 8);
+}
+template <bool TAIL>
+static void launch_rows_fwd(u64 *data, const int *d_rows, const int *d_mods, const NttTables &t, int n, int limbs, const FinishBatch &fb,
+                            hipStream_t st) {
+    if (limbs <= (TAIL ? SMALL_ROWS : SMALL_PLAIN))
+        hipLaunchKernelGGL(small_rows_fwd<TAIL>, dim3(limbs * (n / SMALL_CHUNK)), dim3(SMALL_THREADS), 0, st, data, d_rows, d_mods, t, n, fb);
+    else
+        hipLaunchKernelGGL(ntt_rows256_fwd<TAIL>, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, d_rows, d_mods, t, n, fb);
+}
 // data rows d_rows[i] (or i) are transformed in place; with src != nullptr the first pass reads row
 // src_rows[i] (or i) of src instead, so the transform is out of place and src is left untouched.
 // With g != 0 (inverse, out of place only) the source is read through the Galois permutation, i.e.
@@ -1103,14 +1296,19 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
     dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
     const NttTables t = tables_of(ctx, inverse, limbs);
     const dim3 full(FULL_THREADS);
-    if (!inverse && n2 == 256) {
-        hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, n2);
-        hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, FinishBatch());
+    if (n2 == 256 && !inverse) {
+        launch_cols_fwd(data, src, d_src_rows, d_rows, d_mod_idx, t, n, limbs, st);
+        launch_rows_fwd<false>(data, d_rows, d_mod_idx, t, n, limbs, FinishBatch(), st);
     } else if (!inverse) {
         hipLaunchKernelGGL(ntt_full_fwd<false>, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, FinishBatch());
     } else if (n2 == 256) {
-        hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
-        hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
+        if (limbs <= SMALL_ROWS)
+            hipLaunchKernelGGL(small_rows_inv, dim3(limbs * (n / SMALL_CHUNK)), dim3(SMALL_THREADS), 0, st, data, src, d_src_rows, d_rows,
+                               d_mod_idx, t, n, (unsigned)g);
+        else hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
+        if (limbs <= SMALL_COLS)
+            hipLaunchKernelGGL(small_cols_inv, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, d_rows, d_mod_idx, t, n);
+        else hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
     } else {
         hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
     }
@@ -1120,15 +1318,14 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
     const int limbs = fb.items * fb.ncomp * (fb.level + 1), n = ctx->n;
     if (limbs <= 0) return;
     Prof prof_(ctx, CM_K_NTT_FWD, limbs, st);
-    dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
     const NttTables t = tables_of(ctx, false, limbs);
     const int *none = nullptr;
     if (n == 4096) {
-        hipLaunchKernelGGL(ntt_full_fwd<true>, grid, dim3(FULL_THREADS), 0, st, conv, src, d_src_rows, none, d_mods, t, n, fb);
+        hipLaunchKernelGGL(ntt_full_fwd<true>, dim3(limbs), dim3(FULL_THREADS), 0, st, conv, src, d_src_rows, none, d_mods, t, n, fb);
         return;
     }
-    hipLaunchKernelGGL(ntt_cols_fwd, grid, block, 0, st, conv, src, d_src_rows, none, d_mods, t, n, n >> 8);
-    hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, conv, none, d_mods, t, n, fb);
+    launch_cols_fwd(conv, src, d_src_rows, none, d_mods, t, n, limbs, st);
+    launch_rows_fwd<true>(conv, none, d_mods, t, n, limbs, fb, st);
 }
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb) {
@@ -1166,9 +1363,8 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 #undef CCF_LAUNCH
     }
     Prof prof_(ctx, CM_K_NTT_FWD, limbs, st);
-    const dim3 grid((unsigned)limbs * (n >> 12)), block(NTT_THREADS);
-    if (fb) hipLaunchKernelGGL(ntt_rows256_fwd<true>, grid, block, 0, st, out, d_rows, d_mods, t, n, *fb);
-    else hipLaunchKernelGGL(ntt_rows256_fwd<false>, grid, block, 0, st, out, d_rows, d_mods, t, n, FinishBatch());
+    if (fb) launch_rows_fwd<true>(out, d_rows, d_mods, t, n, limbs, *fb, st);
+    else launch_rows_fwd<false>(out, d_rows, d_mods, t, n, limbs, FinishBatch(), st);
 }
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs,
                      bool inverse, hipStream_t st) {
