@@ -127,11 +127,12 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
 
 // Base conversion of `batch` items and the forward transform of the results.  Item z: table (z % tab_period)*tab_step
 // (tab_period 0 = batch), input (z / in_group)*in_stride, output z*out_stride; own_src: the items' own source rows are
-// copied from it (through the Galois map own_g if non-zero).  d_rows, d_mods: the converted limbs as rows of `out` with
+// copied from it (through the Galois map own_g if non-zero).  ns: the most sources a table has (the digit size of a raise, the
+// special primes of a ModDown).  d_rows, d_mods: the converted limbs as rows of `out` with
 // their modulus indices (d_rows null: 0, 1, 2, ..), with fb: that transform ends in the tail.
 struct ConvBatch {
     const ConvDev *tabs = nullptr;
-    int batch = 1, tab_step = 0, max_nt = 0, tab_period = 0, in_group = 1;
+    int batch = 1, tab_step = 0, ns = 0, max_nt = 0, tab_period = 0, in_group = 1;
     size_t in_stride = 0, out_stride = 0, own_stride = 0;
     const u64 *own_src = nullptr;
     unsigned own_g = 0;

@@ -1329,7 +1329,7 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
 }
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb) {
-    const int n = ctx->n, ns = ctx->alpha > ctx->K ? ctx->alpha : ctx->K;       // bound of the source count, rounded up below
+    const int n = ctx->n, ns = b.ns;              // rounded up to an instantiated bound below
     const NttTables t = tables_of(ctx, false, limbs);
     ConvArgs a;
     a.tabs = b.tabs, a.tab_step = b.tab_step, a.tab_period = b.tab_period ? b.tab_period : b.batch, a.in_group = b.in_group;
@@ -1341,6 +1341,8 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 #define FULL_LAUNCH(NS_)                                                                                                         \
     if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb);        \
     else hipLaunchKernelGGL((conv_full_fwd<NS_, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
+        // the instantiation for eight spills 31 of 256 registers and still takes less than conversion and transform in two launches
+        // (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us; five sources 66 -> 56
         if (ns <= 1) { FULL_LAUNCH(1); }
         else if (ns <= 2) { FULL_LAUNCH(2); }
         else if (ns <= 4) { FULL_LAUNCH(4); }
@@ -1354,11 +1356,16 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
         while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
         a.groups = (b.max_nt + a.tg - 1) / a.tg;
         const dim3 grid(256 / CCF_W, a.groups + (b.own_src ? 1 : 0), b.batch);
+        // Eight sources spill twelve registers (128 for two workgroups per compute unit), seven do not: with seven special
+        // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
+        // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
+        // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
 #define CCF_LAUNCH(NS_) hipLaunchKernelGGL((conv_cols_fwd<NS_>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn)
         if (ns <= 1) CCF_LAUNCH(1);
         else if (ns <= 2) CCF_LAUNCH(2);
         else if (ns <= 4) CCF_LAUNCH(4);
         else if (ns <= 6) CCF_LAUNCH(6);
+        else if (ns <= 7) CCF_LAUNCH(7);
         else CCF_LAUNCH(8);
 #undef CCF_LAUNCH
     }

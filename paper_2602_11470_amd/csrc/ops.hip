@@ -244,7 +244,7 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     // digit's own limbs are copied from d itself, which is already in the evaluation domain
     launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     ConvBatch cb;
-    cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
+    cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
     cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g;
     launch_conv_ntt(ctx, cb, digits, A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
@@ -255,7 +255,8 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
 static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, int batch, u64 *conv, const u64 *in, size_t in_stride,
                          const FinishBatch &fb, hipStream_t st) {
     ConvBatch cb;
-    cb.tabs = tab, cb.batch = batch, cb.max_nt = k.level + 1, cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
+    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1;
+    cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
     launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
 }
 cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int addend_comps, u64 g, u64 *out,
@@ -440,7 +441,8 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     // the tables list the items in order, so the first m items are a prefix of every table
     launch_ntt_src(ctx, ksin, nullptr, cts, t.d_src_rows, t.d_in_mods, m * (t.level + 1), true, st, g);
     ConvBatch cb;
-    cb.tabs = k.d_modup, cb.batch = m * k.beta, cb.tab_step = 1, cb.max_nt = k.modup_max_nt, cb.tab_period = k.beta, cb.in_group = k.beta;
+    cb.tabs = k.d_modup, cb.batch = m * k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt;
+    cb.tab_period = k.beta, cb.in_group = k.beta;
     cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
     cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln;
     launch_conv_ntt(ctx, cb, digits, ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);

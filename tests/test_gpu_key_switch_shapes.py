@@ -26,10 +26,17 @@ def _both(n, n_q, n_p, alpha, q0_bits, qi_bits, p_bits):
     (4096, 9, 8, 8, 50, 50, 60, (8, 4)),                     # eight sources
     (4096, 4, 2, 2, 58, 54, 60, (3, 1)),                     # no FP64 modulus: 128-bit sums in the conversion
     (4096, 4, 2, 2, 50, 40, 61, (3, 2)),                     # 61-bit special primes
+    (4096, 9, 3, 7, 50, 50, 60, (8, 6)),                     # more sources in a raise than in a ModDown
+    (4096, 5, 6, 2, 50, 49, 60, (4,)),                       # and fewer
+    (4096, 5, 2, 2, 58, 49, 60, (4, 2, 1)),                  # a digit of one integer and one FP64 modulus
+    (4096, 4, 2, 2, 40, 49, 60, (3, 1)),                     # a last modulus far above the first: reduced before it is transformed
     (65536, 3, 1, 1, 50, 50, 60, (2,)),
     (65536, 4, 2, 2, 50, 49, 60, (3, 2)),
     (65536, 9, 8, 8, 50, 50, 60, (8,)),
     (65536, 3, 2, 2, 55, 52, 60, (2,)),
+    (65536, 8, 7, 7, 50, 49, 60, (7, 6)),                    # seven sources
+    (65536, 4, 7, 2, 50, 49, 50, (3,)),                      # seven FP64 special primes, digits of two
+    (65536, 6, 2, 5, 50, 49, 60, (5,)),
 ])
 def test_key_switches_match_the_oracle(n, n_q, n_p, alpha, q0_bits, qi_bits, p_bits, levels):
     octx, gctx = _both(n, n_q, n_p, alpha, q0_bits, qi_bits, p_bits)
