@@ -432,10 +432,12 @@ cm_status cm_keyswitch(cm_ctx *ctx, const cm_evk *evk, int32_t step, int32_t rel
 
 /* Per-kernel-family timing: while enabled, every launch of the listed families is bracketed by
  * HIP events on its own stream.  cm_profile_enable(ctx, 1) clears the records and starts,
- * (ctx, 0) stops; cm_profile_get sums launches, work units (limbs for the NTTs, written limbs for
- * base conversion and element-wise kernels, 1 otherwise) and milliseconds of one family.  A base conversion ends in the
- * first pass (n = 4096: in the whole) of the forward transform of its results, so CM_K_NTT_FWD holds their remaining
- * pass only; the ModDown tail runs inside a transform, so CM_K_MODDOWN_FINISH stays empty. */
+ * (ctx, 0) stops; cm_profile_get sums launches, work units (limbs for the transforms, written limbs for
+ * base conversion and element-wise kernels, 1 otherwise) and milliseconds of one family; the passes of one transform
+ * count as one launch.  A base conversion is one kernel with the start (n = 4096: the whole) of the forward transform of its
+ * results: CM_K_BASE_CONV holds the conversions with those transforms from the first pass to the last, CM_K_NTT_FWD the other
+ * forward transforms, so that milliseconds over units is the time of a limb in either.  The ModDown tail runs inside
+ * a transform: CM_K_MODDOWN_FINISH stays empty. */
 enum {
     CM_K_NTT_FWD = 0, CM_K_NTT_INV = 1, CM_K_BASE_CONV = 2, CM_K_INNER_PRODUCT = 3,
     CM_K_MODDOWN_FINISH = 4, CM_K_VMM_MAC = 5, CM_K_ELEMENTWISE = 6, CM_K_RESCALE = 7,

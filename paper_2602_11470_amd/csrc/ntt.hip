@@ -1335,8 +1335,8 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     a.tabs = b.tabs, a.tab_step = b.tab_step, a.tab_period = b.tab_period ? b.tab_period : b.batch, a.in_group = b.in_group;
     a.in_stride = b.in_stride, a.out_stride = b.out_stride, a.own_stride = b.own_stride;
     a.own_src = b.own_src, a.own_g = b.own_g;
+    Prof prof_(ctx, CM_K_BASE_CONV, limbs, st);
     if (n == 4096) {
-        Prof prof_(ctx, CM_K_BASE_CONV, b.batch * b.max_nt, st);
         const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
 #define FULL_LAUNCH(NS_)                                                                                                         \
     if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb);        \
@@ -1350,26 +1350,22 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 #undef FULL_LAUNCH
         return;
     }
-    {
-        Prof prof_(ctx, CM_K_BASE_CONV, b.batch * b.max_nt, st);
-        a.tg = CCF_TG;
-        while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
-        a.groups = (b.max_nt + a.tg - 1) / a.tg;
-        const dim3 grid(256 / CCF_W, a.groups + (b.own_src ? 1 : 0), b.batch);
-        // Eight sources spill twelve registers (128 for two workgroups per compute unit), seven do not: with seven special
-        // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
-        // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
-        // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
+    a.tg = CCF_TG;
+    while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
+    a.groups = (b.max_nt + a.tg - 1) / a.tg;
+    const dim3 grid(256 / CCF_W, a.groups + (b.own_src ? 1 : 0), b.batch);
+    // Eight sources spill twelve registers (128 for two workgroups per compute unit), seven do not: with seven special
+    // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
+    // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
+    // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
 #define CCF_LAUNCH(NS_) hipLaunchKernelGGL((conv_cols_fwd<NS_>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn)
-        if (ns <= 1) CCF_LAUNCH(1);
-        else if (ns <= 2) CCF_LAUNCH(2);
-        else if (ns <= 4) CCF_LAUNCH(4);
-        else if (ns <= 6) CCF_LAUNCH(6);
-        else if (ns <= 7) CCF_LAUNCH(7);
-        else CCF_LAUNCH(8);
+    if (ns <= 1) CCF_LAUNCH(1);
+    else if (ns <= 2) CCF_LAUNCH(2);
+    else if (ns <= 4) CCF_LAUNCH(4);
+    else if (ns <= 6) CCF_LAUNCH(6);
+    else if (ns <= 7) CCF_LAUNCH(7);
+    else CCF_LAUNCH(8);
 #undef CCF_LAUNCH
-    }
-    Prof prof_(ctx, CM_K_NTT_FWD, limbs, st);
     if (fb) launch_rows_fwd<true>(out, d_rows, d_mods, t, n, limbs, *fb, st);
     else launch_rows_fwd<false>(out, d_rows, d_mods, t, n, limbs, FinishBatch(), st);
 }
