@@ -354,10 +354,9 @@ def test_prompt_phase_attention_of_a_query_group_on_the_full_ring(ring2):
 
 
 def test_appends_with_the_masked_product_inside_the_rescale_equal_the_two_step_appends(ring2):
-    """At n = 2^16 an append forms its masked products inside the tail of the rescale's transform; with the
-    context option CM_OPT_TWO_STEP_MASKS it multiplies, stores and rescales (the path the small-ring tests
-    check limb for limb against the oracle).  Same cache, same key index, bit for bit: one token group and
-    two single tokens."""
+    """An append forms its masked products inside the tail of the rescale's transform (the small-ring tests check that form limb
+    for limb against the oracle); with the context option CM_OPT_TWO_STEP_MASKS it multiplies, stores and rescales.  Same cache,
+    same key index, bit for bit: one token group and two single tokens."""
     from oracle import packing
     B, octx, gctx, prm = ring2
     H, E, lv = 32, 128, 4

@@ -69,8 +69,9 @@ def test_key_switches_match_the_oracle(n, n_q, n_p, alpha, q0_bits, qi_bits, p_b
 
 
 def test_masked_sums_of_32_copies_against_float64():
-    """q K^T through the FP64 transform of length 32 (radix 8 x 4; the other lengths are compared limb for limb elsewhere),
-    with the last ciphertext partly filled and half of the rows written, against float64 and the printed order."""
+    """q K^T through the FP64 transform of length 32 (radix 8 x 4) with every key ciphertext there, the last one partly filled,
+    and half of the rows written: scores against float64 (limbs are compared with the oracle's at 20 of 32 ciphertexts, where the
+    shared-dim rotations are tested)."""
     from oracle import packing
     from paper_2602_11470_amd import binding as B, inputs
     gctx = B.config1()
