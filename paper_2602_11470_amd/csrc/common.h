@@ -14,7 +14,7 @@ typedef uint64_t u64;
 typedef unsigned __int128 u128;
 
 // ---- 64-bit modular arithmetic -----------------------------------------------------------
-// All moduli are below 2^62.  Three multiplier forms are used:
+// All moduli are below 2^61 (the lazy sums of the transforms use up to 8 q of a word).  Three multiplier forms are used:
 //   Shoup:      constant w with companion wp = floor(w 2^64 / q); result in [0, 2q) (lazy).
 //   Montgomery: one operand pre-multiplied by 2^64 mod q; products are accumulated in 128
 //               bits and reduced once (REDC), result in [0, q).
@@ -114,7 +114,7 @@ enum { CONV_SPLIT_25 = 0, CONV_SPLIT_30 = 1, CONV_SPLIT_NONE = 2 };
 // one target modulus: everything the conversion to it reads, in one record
 struct ConvTarget {
     int mod, row;                 // modulus index, output row
-    double qd, qinvd;             // the modulus and its inverse as doubles, qd = 0 from 2^50 on (integer arithmetic)
+    double qd;                    // the modulus as a double, 0 from 2^50 on (integer arithmetic)
     double w[CONV_MAX_SRC];       // hat_m mod q (exact for moduli below 2^50)
     u64 q, qinv;                  // modulus, q^{-1} mod 2^64
     u64 wm[CONV_MAX_SRC];         // hat_m mod q in multiplier form
@@ -124,7 +124,7 @@ struct ConvDev {
     int in_rows[CONV_MAX_SRC];
     u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC], src_q[CONV_MAX_SRC];
     double src_qd[CONV_MAX_SRC], inv_hat_d[CONV_MAX_SRC], inv_hat_dq[CONV_MAX_SRC];   // q_m, inv_hat_m, inv_hat_m / q_m as doubles
-    ConvTarget t[CONV_MAX_DST + 1];          // one past the end may be read ahead
+    ConvTarget t[CONV_MAX_DST];
 };
 
 // per-kernel-family timing with HIP events on the launching stream (off unless enabled)

@@ -79,7 +79,7 @@ void launch_mul_pt(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *pt_mont, int 
     hipLaunchKernelGGL(k_mul_pt, dim3(ctx->n / TPB, ncomp * limbs), dim3(TPB), 0, st, out, a, pt_mont, ctx->d_modc, limbs, ctx->n);
 }
 
-// out[z][2][limbs][n] = src_z * perm_{g_z}(pt): up to 8 ciphertexts times slot rotations of one
+// out[z][2][limbs][n] = src_z * perm_{g_z}(pt): up to CM_MASK_BATCH ciphertexts times slot rotations of one
 // plaintext (the rotation is the Galois permutation of its evaluation-domain words), one launch
 __global__ void k_mul_pt_rot_batch(u64 *__restrict__ out, MulPtBatch b, const u64 *__restrict__ pt_mont,
                                    const ModC *__restrict__ modc, int limbs, int n, int logn) {
@@ -598,8 +598,8 @@ void launch_inner_product_shared_key(cm_ctx *ctx, const IpBatch &b, int beta, in
 // k_inner_product_batch, but the digits are read once per IP_FAN_CHUNK keys instead of once per key.
 // NB = compile-time bound of the digit count: registers for eight digits leave three waves a SIMD, each with the two or three
 // loads in flight that a low level has; sized for its digits the kernel runs four to eight waves.  Bound by memory (one half
-// to two thirds reads): the 63 baby steps of a 4096 x 4096 product at level 4 (two digits) 328 -> 243 us, the 127 of a
-// 16384 x 4096 one at level 3 499 -> 361 us.  Requesting the next rotation's words ahead as well changed nothing.
+// to two thirds reads): the 63 baby steps of a 4096 x 4096 product at level 4 (two digits) 326 -> 252 us, the 127 of a
+// 16384 x 4096 one at level 3 (one digit) 471 -> 362 us.  Requesting the next rotation's words ahead as well changed nothing.
 #define IP_FAN_CHUNK 8
 template <bool SA, int NB>
 __global__ __launch_bounds__(TPB) void k_inner_product_fanout(IpFan f, const u64 *__restrict__ dig, const u64 *__restrict__ c0,
@@ -1013,9 +1013,10 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // bits (one halfword): 50 bytes instead of 64, all loads aligned, whole lines a wave.  Unpacking takes three more
 // instructions a word in a kernel that waits for memory.  Fewer than eight baby steps and the integer limbs keep
 // 64-bit words.  Measured per kernel, unpacked -> packed: a 4096 x 4096 product at level 23 1681 -> 1588 us, at level 4
-// 540 -> 519, a 16384 x 4096 product at level 3 1713 -> 1623,
-// 32 tokens of 1024 x 1024 at level 9 1567 -> 1441; two or three groups
-// in flight instead of one (100 and more VGPRs a lane, half the waves) cost 3 to 5% of a product.
+// 540 -> 519, a 16384 x 4096 product at level 3 1713 -> 1623, 32 tokens of 1024 x 1024 at level 9 1567 -> 1441: 0.75 of the
+// rate that a plain kernel reads at.  The kernel takes 168 registers (three waves a SIMD), which the 128-bit sums of the integer
+// limbs set (the packed branch by itself 126), and a run of a wave starts with a load that nothing hides, once in four
+// groups at 32 baby steps a pass.  Two or three groups in flight instead of one, in as many waves, cost 3 to 5 % of a product.
 // Otherwise, with an even number of baby steps, the words of plaintexts (2j', k) and (2j'+1, k) are interleaved
 // (word c of the pair at 2c, 2c+1 of a 128-word row), so that a lane reads both with one 16-byte load and a
 // wavefront instruction covers 1 KiB of the stream.

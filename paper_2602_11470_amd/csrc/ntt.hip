@@ -229,22 +229,18 @@ struct FpArith {
 // loads overlap the data loads or the LDS exchange in front of them).  Integer limbs read the Shoup companions with
 // them; FP64 limbs take the second factor w/q as w * (1/q), one multiplication instead
 // of a second table: the quotient estimate may then be off by one more unit, the product stays exact
-// (|r| <= 1.3 q for |y| <= 2.1 q).
-template <class A, int ST, int NB = 1>          // ST stages on NB adjacent blocks
+// (|r| <= (1/2 + 3/8 B) q for |y| <= B q, see FpArith).
+template <class A, int ST>                      // ST stages
 struct Tw {
     const A &ar;
-    typename A::Word w[NB][(1 << ST) - 1];
+    typename A::Word w[(1 << ST) - 1];
     __device__ __forceinline__ Tw(const A &a_, unsigned b0) : ar(a_) {
 #pragma unroll
-        for (int b = 0; b < NB; b++)
+        for (int a = 0; a < ST; a++)
 #pragma unroll
-            for (int a = 0; a < ST; a++)
-#pragma unroll
-                for (int g = 0; g < (1 << a); g++) w[b][(1 << a) - 1 + g] = ar.word(((b0 + b) << a) + g);
+            for (int g = 0; g < (1 << a); g++) w[(1 << a) - 1 + g] = ar.word((b0 << a) + g);
     }
-    __device__ __forceinline__ void get(int b, int a, int g, typename A::W &w0, typename A::W &w1) const {
-        ar.pair(w[b][(1 << a) - 1 + g], w0, w1);
-    }
+    __device__ __forceinline__ void get(int a, int g, typename A::W &w0, typename A::W &w1) const { ar.pair(w[(1 << a) - 1 + g], w0, w1); }
 };
 template <class A>
 using TableTw = Tw<A, 4>;
@@ -261,37 +257,35 @@ struct GenTw {
         T[1] = ar.mulmod(T[2], T[2], T[2] * ar.qinv);
         T[0] = ar.mulmod(T[1], T[1], T[1] * ar.qinv);
     }
-    __device__ __forceinline__ void get(int, int a, int g, double &w0, double &w1) const {
+    __device__ __forceinline__ void get(int a, int g, double &w0, double &w1) const {
         w0 = g ? ar.mulmod(T[a], ar.w[g], ar.wq[g]) : T[a];
         w1 = w0 * ar.qinv;
     }
 };
 
-// ST forward stages, the first of them stage S0 of the transform, on NB blocks of 2^ST register values whose index is the
-// local position inside one butterfly block of the first of these stages.
-template <int ST, int NB, int S0, class A, class TW>
-__device__ __forceinline__ void radix_fwd(typename A::T (&v)[NB << ST], const A &ar, const TW &tw) {
+// ST forward stages, the first of them stage S0 of the transform, on 2^ST register values whose index is the local position
+// inside one butterfly block of the first of these stages.
+template <int ST, int S0, class A, class TW>
+__device__ __forceinline__ void radix_fwd(typename A::T (&v)[1 << ST], const A &ar, const TW &tw) {
 #pragma unroll
     for (int a = 0; a < ST; a++) {
         const int half = (1 << ST) >> (a + 1);
 #pragma unroll
-        for (int b = 0; b < NB; b++)
+        for (int g = 0; g < (1 << a); g++) {
+            typename A::W w0, w1;
+            tw.get(a, g, w0, w1);
 #pragma unroll
-            for (int g = 0; g < (1 << a); g++) {
-                typename A::W w0, w1;
-                tw.get(b, a, g, w0, w1);
-#pragma unroll
-                for (int j = 0; j < half; j++) {
-                    const int k = (b << ST) + g * 2 * half + j;
-                    ar.ct(v[k], v[k + half], w0, w1);
-                }
+            for (int j = 0; j < half; j++) {
+                const int k = g * 2 * half + j;
+                ar.ct(v[k], v[k + half], w0, w1);
             }
+        }
         ar.after_fwd(S0 + a, v);
     }
 }
 template <class A, class TW>
 __device__ __forceinline__ void radix16_fwd_tw(typename A::T (&v)[16], const A &ar, const TW &tw) {
-    radix_fwd<4, 1, 0>(v, ar, tw);
+    radix_fwd<4, 0>(v, ar, tw);
 }
 // The inverse of the above (stages in the opposite order).
 template <int ST, int S0, class A, class TW>
@@ -302,7 +296,7 @@ __device__ __forceinline__ void radix_inv(typename A::T (&v)[1 << ST], const A &
 #pragma unroll
         for (int g = 0; g < (1 << a); g++) {
             typename A::W w0, w1;
-            tw.get(0, a, g, w0, w1);
+            tw.get(a, g, w0, w1);
 #pragma unroll
             for (int j = 0; j < half; j++) {
                 const int k = g * 2 * half + j;
@@ -635,7 +629,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
 // The limits: SMALL_COLS, because 64-byte segments cost columns more than the chain once there is work for every compute unit
 // (14 limbs inverse 6.9 -> 11.1; sixteen columns and 1024 lanes: 9.3, and slower below); SMALL_PLAIN for forward rows
 // (13 limbs 9.7 -> 8.0, 28 limbs 13.5 -> 14.0, 58 limbs 16.5 -> 18.4); SMALL_ROWS for inverse rows and forward rows with a tail
-// (35 limbs inverse 14.7 -> 11.3; 64 limbs 20.0 -> 18.9 and 30.3 -> 26.5; 80 limbs with a tail the same).
+// (35 limbs inverse 14.7 -> 11.3; 64 limbs 20.0 -> 18.9 and 30.3 -> 26.5; 80 limbs with a tail the same).  All tails were
+// ModDowns; full batches of an append's masked products (64 limbs a level) are past the limit and were not timed in this form.
 #define SMALL_COLS 8
 #define SMALL_PLAIN 16
 #define SMALL_ROWS 64
@@ -648,25 +643,25 @@ template <class A, class AT, class S>
 __device__ __forceinline__ void small_fwd(u64 *lds, typename A::T (&v)[4], const A &ar, unsigned R, int sub, AT at, S sync) {
     const int hi1 = sub >> 4, lo1 = sub & 15, hi2 = sub >> 2, lo2 = sub & 3;
     const Tw<A, 2> t1(ar, 4 * R + hi1), t2(ar, 16 * R + hi2), t3(ar, 64 * R + sub);
-    radix_fwd<2, 1, 0>(v, ar, Tw<A, 2>(ar, R));
+    radix_fwd<2, 0>(v, ar, Tw<A, 2>(ar, R));
 #pragma unroll
     for (int k = 0; k < 4; k++) lds[at(64 * k + sub)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + 16 * k + lo1)]);
-    radix_fwd<2, 1, 2>(v, ar, t1);
+    radix_fwd<2, 2>(v, ar, t1);
 #pragma unroll
     for (int k = 0; k < 4; k++) lds[at(64 * hi1 + 16 * k + lo1)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + 4 * k + lo2)]);
-    radix_fwd<2, 1, 4>(v, ar, t2);
+    radix_fwd<2, 4>(v, ar, t2);
 #pragma unroll
     for (int k = 0; k < 4; k++) lds[at(16 * hi2 + 4 * k + lo2)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(4 * sub + k)]);
-    radix_fwd<2, 1, 6>(v, ar, t3);
+    radix_fwd<2, 6>(v, ar, t3);
 }
 template <class A, class AT, class S>
 __device__ __forceinline__ void small_inv(u64 *lds, typename A::T (&v)[4], const A &ar, unsigned R, int sub, AT at, S sync) {
@@ -831,7 +826,7 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
     const int tid = threadIdx.x, h2 = tid >> 6, l2 = tid & 63, h3 = tid >> 3, l3 = tid & 7;
     {
         const Tw<A, 3> tw(ar, 1);
-        radix_fwd<3, 1, 0>(v, ar, tw);
+        radix_fwd<3, 0>(v, ar, tw);
     }
 #pragma unroll
     for (int k = 0; k < 8; k++) lds[pad8(k * 512 + tid)] = ar.to_mid(v[k]);
@@ -840,7 +835,7 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h2 * 512 + k * 64 + l2)]);
-        radix_fwd<3, 1, 3>(v, ar, tw);
+        radix_fwd<3, 3>(v, ar, tw);
     }
     // every lane writes back the words it read, so one barrier per exchange is enough
 #pragma unroll
@@ -850,7 +845,7 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(h3 * 64 + k * 8 + l3)]);
-        radix_fwd<3, 1, 6>(v, ar, tw);
+        radix_fwd<3, 6>(v, ar, tw);
     }
 #pragma unroll
     for (int k = 0; k < 8; k++) lds[pad8(h3 * 64 + k * 8 + l3)] = ar.to_mid(v[k]);
@@ -859,7 +854,7 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(tid * 8 + k)]);
-        radix_fwd<3, 1, 9>(v, ar, tw);
+        radix_fwd<3, 9>(v, ar, tw);
     }
 #pragma unroll
     for (int k = 0; k < 8; k++) lds[pad8(tid * 8 + k)] = TAIL ? ar.to_tail(v[k]) : ar.to_rest_fwd(v[k]);
@@ -1023,8 +1018,9 @@ struct ConvY {
                 OPAQUE(hi[k][m]);
             }
     }
-    // targets below 2^50: |v| <= 0.6 q.  |y w - c q| <= 0.88 q per term (c off by three roundings of a value below 2^50), so
-    // the sum of eight terms stays below 2^53 and exact.
+    // targets below 2^50: |v| <= q, all that the forward stages ask (0.6 q where several sources are summed and reduced, 0.88 q
+    // for one).  |y w - c q| <= 0.88 q per term (c off by three roundings of a value below 2^50), so the sum of eight terms
+    // stays below 2^53 and exact.
     __device__ __forceinline__ void target_fp(const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
         double w[NS], wq[NS];
 #pragma unroll
@@ -1107,44 +1103,44 @@ struct ConvY {
 #define CCF_FILL 512
 // LDS: row r of 8 words at row r ^ ((r >> 2) & 3): any four rows that a half-wave touches (neighbours, or four apart) then
 // cover all banks
-template <class A, template <class, int, int> class TW>
+template <class A>
 __device__ __forceinline__ void ccf_body(u64 *lds, int buf, u64 *p, typename A::T (&v)[4], unsigned tid, const A &ar, int n2) {
     const int c = tid % CCF_W, sub = tid / CCF_W;
     u64 *A0 = lds + (buf ? 256 * CCF_W : 0) + c, *B0 = lds + (buf ? 0 : 256 * CCF_W) + c;
     {
-        const TW<A, 2, 1> tw(ar, 1);
-        radix_fwd<2, 1, 0>(v, ar, tw);
+        const Tw<A, 2> tw(ar, 1);
+        radix_fwd<2, 0>(v, ar, tw);
     }
     const int sx = sub ^ ((sub >> 2) & 3);
 #pragma unroll
     for (int k = 0; k < 4; k++) A0[(k * 64 + sx) * CCF_W] = ar.to_mid(v[k]);             // row 64 k + sub
     {
         const int hi = sub >> 4;
-        const TW<A, 2, 1> tw(ar, 4 + hi);
+        const Tw<A, 2> tw(ar, 4 + hi);
         const int o = (hi * 64 + (sx & 15)) * CCF_W;                                     // row 64 hi + 16 k + lo
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = ar.from_mid(A0[o + k * 16 * CCF_W]);
-        radix_fwd<2, 1, 2>(v, ar, tw);
+        radix_fwd<2, 2>(v, ar, tw);
 #pragma unroll
         for (int k = 0; k < 4; k++) B0[o + k * 16 * CCF_W] = ar.to_mid(v[k]);
     }
     {
         const int hi = sub >> 2, lo = sub & 3;
-        const TW<A, 2, 1> tw(ar, 16 + hi);
+        const Tw<A, 2> tw(ar, 16 + hi);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = ar.from_mid(B0[(hi * 16 + k * 4 + (lo ^ k)) * CCF_W]);     // row 16 hi + 4 k + lo
-        radix_fwd<2, 1, 4>(v, ar, tw);
+        radix_fwd<2, 4>(v, ar, tw);
 #pragma unroll
         for (int k = 0; k < 4; k++) A0[(hi * 16 + k * 4 + (lo ^ k)) * CCF_W] = ar.to_mid(v[k]);
     }
     {
-        const TW<A, 2, 1> tw(ar, 64 + sub);
+        const Tw<A, 2> tw(ar, 64 + sub);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = ar.from_mid(A0[(sub * 4 + (k ^ (sub & 3))) * CCF_W]);     // row 4 sub + k
-        radix_fwd<2, 1, 6>(v, ar, tw);
+        radix_fwd<2, 6>(v, ar, tw);
     }
 #pragma unroll
     for (int k = 0; k < 4; k++) NTT_ST(word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
@@ -1197,13 +1193,13 @@ __global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict_
             ar.init(t, o.mod, n);
             double v[4];
             y.target_any(split, o, ar, v);
-            ccf_body<FpArith, Tw>(lds, buf, p, v, tid, ar, n2);
+            ccf_body<FpArith>(lds, buf, p, v, tid, ar, n2);
         } else {
             IntArith ar;
             ar.init(t, o.mod, n);
             u64 x[4];
             y.target(split, o, x);
-            ccf_body<IntArith, Tw>(lds, buf, p, x, tid, ar, n2);
+            ccf_body<IntArith>(lds, buf, p, x, tid, ar, n2);
         }
     }
 }

@@ -91,7 +91,7 @@ static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector
         ConvTarget &o = d.t[r];
         const ModC &mc = ctx->modc[t.dst[r]];
         o.mod = t.dst[r], o.row = out_rows[r], o.q = mc.q, o.qinv = mc.qinv;
-        if (mc.q < (1ULL << 50)) o.qd = (double)mc.q, o.qinvd = 1.0 / (double)mc.q;
+        if (mc.q < (1ULL << 50)) o.qd = (double)mc.q;
         for (int m = 0; m < t.ns; m++) o.w[m] = (double)t.hat[(size_t)m * t.nt + r], o.wm[m] = t.hat_mont[(size_t)m * t.nt + r];
         tmax = std::max(tmax, mc.q);
     }
