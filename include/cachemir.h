@@ -420,7 +420,8 @@ cm_status cm_inner_rot_create(cm_ctx *ctx, int32_t t, int32_t delta, int32_t lev
 /* ---- building blocks exposed for measurement and parity -------------------------------- */
 /* Forward / inverse negacyclic NTT of `limbs` limbs in place (device), limb i under modulus
  * index mod_idx[i] (host array, read before the call returns; indices into q_0..q_L,p_0..);
- * 1 <= limbs <= 1024.  Enqueues only (a list that is not a run of consecutive indices is written into
+ * 1 <= limbs <= 1024.  Input words are any representatives below 4 q_i (forward) or 2 q_i (inverse), results lie in [0, q_i).
+ * Enqueues only (a list that is not a run of consecutive indices is written into
  * a per-context staging array by a small kernel: two such calls on different streams must be ordered). */
 cm_status cm_ntt(cm_ctx *ctx, uint64_t *dev, const int32_t *mod_idx, int32_t limbs,
                  int32_t inverse, void *stream);

@@ -55,7 +55,7 @@ __device__ __forceinline__ const T *word_at(const T *base, unsigned idx) {
 // Every second stage all values (forward) or the sums (inverse) are folded: with 2^(b-1) < q = 2^b - c < 2^b,
 // v = (v mod 2^b) + (v >> b) c < q + 17 c < 2q, three instructions.  (The primes of a context are the first ones below
 // 2^b in steps of 2n, so c is below 2^32 by far.)  Bounds, in units of q:
-//   forward  2 -> 6 -> 10 -> fold < 2 (two stages), 61-bit: 2 -> 6 -> fold
+//   forward  2 (input: 4) -> 6 (8) -> 10 (12) -> fold < 2 (two stages), 61-bit: 2 (4) -> 6 (8) -> fold
 //   inverse  4 -> 8 (sum), 4 (product) -> 16 (sum, folded), 4; 61-bit: 4 -> 8 (sum, folded), 4
 // Measured against exact quotients with a conditional subtraction per butterfly (32 instructions) and twiddles read
 // where they are used: 8 limbs under 60-bit primes 11.1 + 10.6 -> 9.3 + 9.8 us (inverse rows + columns), 64 limbs
@@ -74,8 +74,8 @@ struct IntArith {
         ni = nip = 0;
         if (t.ninv) ni = t.ninv[mi], nip = t.ninvp[mi];
     }
-    __device__ __forceinline__ T from_rest(u64 raw) const { return raw; }     // canonical [0, q)
-    __device__ __forceinline__ T from_lazy(u64 raw) const { return raw; }     // below 2q (a rescale's last limb under another modulus)
+    __device__ __forceinline__ T from_rest(u64 raw) const { return raw; }     // inverse: below 2q
+    __device__ __forceinline__ T from_lazy(u64 raw) const { return raw; }     // forward: below 4q
     __device__ __forceinline__ T from_mid(u64 raw) const { return raw; }
     __device__ __forceinline__ u64 to_mid(T v) const { return v; }
     typedef u64 W;
@@ -156,10 +156,12 @@ struct FpArith {
         return __builtin_fma(-c, q, h) + l;
     }
     __device__ __forceinline__ double norm(double x) const { return __builtin_fma(-__builtin_rint(x * qinv), q, x); }
-    __device__ __forceinline__ T from_rest(u64 raw) const {
+    __device__ __forceinline__ T from_rest(u64 raw) const {                                     // below 2^52, i.e. 4q
         return __longlong_as_double((long long)(raw | 0x4330000000000000ULL)) - TWO52;
     }
-    __device__ __forceinline__ T from_lazy(u64 raw) const { return norm(from_rest(raw)); }      // below 2q
+    // What comes into a forward transform need not be reduced (a caller's words, a rescale's last limb under another
+    // modulus): brought to q / 2 here, since four stages from 4q would pass 2^53 (three instructions of about 90 a word).
+    __device__ __forceinline__ T from_lazy(u64 raw) const { return norm(from_rest(raw)); }
     __device__ __forceinline__ T from_mid(u64 raw) const { return __longlong_as_double((long long)raw); }
     __device__ __forceinline__ u64 to_mid(T v) const { return (u64)__double_as_longlong(v); }
     typedef double W;
@@ -337,7 +339,7 @@ __device__ __forceinline__ int pad(int e) { return e + (e >> 4); }
 
 // ---- column passes: stages 0..7; tile = rows 0..255 of 16 adjacent columns ---------------------------
 template <class A>
-__device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, bool lazy, const NttTables &t, int mi, int n, int n2) {
+__device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int n2) {
     A ar;
     ar.init(t, mi, n);
     const int c = threadIdx.x & 15, sub = threadIdx.x >> 4;
@@ -353,7 +355,7 @@ __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, b
     {
         const TableTw<A> tw(ar, 1);                 // in flight together with the data
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = lazy ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
+        for (int k = 0; k < 16; k++) v[k] = ar.from_lazy(raw[k]);
         radix16_fwd_tw(v, ar, tw);
     }
 #pragma unroll
@@ -410,9 +412,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_fwd(u64 *__restrict__ da
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n + c0 : p;
     if (t.fpq[mi].q != 0.0)
-        cols_fwd_body<FpArith>(lds, p, ps, src != nullptr, t, mi, n, n2);
+        cols_fwd_body<FpArith>(lds, p, ps, t, mi, n, n2);
     else
-        cols_fwd_body<IntArith>(lds, p, ps, src != nullptr, t, mi, n, n2);
+        cols_fwd_body<IntArith>(lds, p, ps, t, mi, n, n2);
 }
 __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_inv(u64 *__restrict__ data, const int *__restrict__ rows,
                                                            const int *__restrict__ mod_idx, NttTables t, int n,
@@ -703,7 +705,7 @@ struct WaveSync {
     __device__ __forceinline__ void operator()() const { wave_sync(); }
 };
 template <class A>
-__device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, bool lazy, const NttTables &t, int mi, int n) {
+__device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n) {
     A ar;
     ar.init(t, mi, n);
     const int n2 = n >> 8, c = threadIdx.x % SMALL_CW, sub = threadIdx.x / SMALL_CW;
@@ -712,7 +714,7 @@ __device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 
 #pragma unroll
     for (int k = 0; k < 4; k++) raw[k] = ps[(64 * k + sub) * n2 + c];
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = lazy ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_lazy(raw[k]);
     small_fwd(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
 #pragma unroll
     for (int k = 0; k < 4; k++) NTT_ST(p + (4 * sub + k) * n2 + c, ar.to_mid(v[k]));
@@ -777,8 +779,8 @@ __global__ __launch_bounds__(64 * SMALL_CW) void small_cols_fwd(u64 *__restrict_
     const int per = n / (256 * SMALL_CW), limb = blockIdx.x / per, c0 = (blockIdx.x % per) * SMALL_CW, mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n + c0 : p;
-    if (t.fpq[mi].q != 0.0) small_cols_fwd_body<FpArith>(lds, p, ps, src != nullptr, t, mi, n);
-    else small_cols_fwd_body<IntArith>(lds, p, ps, src != nullptr, t, mi, n);
+    if (t.fpq[mi].q != 0.0) small_cols_fwd_body<FpArith>(lds, p, ps, t, mi, n);
+    else small_cols_fwd_body<IntArith>(lds, p, ps, t, mi, n);
 }
 __global__ __launch_bounds__(64 * SMALL_CW) void small_cols_inv(u64 *__restrict__ data, const int *__restrict__ rows,
                                                                const int *__restrict__ mod_idx, NttTables t, int n) {
@@ -926,7 +928,7 @@ __device__ __forceinline__ void full_fwd_load(u64 *lds, u64 *p, const u64 *ps, c
 #pragma unroll
     for (int k = 0; k < 8; k++) raw[k] = ps[threadIdx.x + 512 * k];
 #pragma unroll
-    for (int k = 0; k < 8; k++) v[k] = ps != p ? ar.from_lazy(raw[k]) : ar.from_rest(raw[k]);
+    for (int k = 0; k < 8; k++) v[k] = ar.from_lazy(raw[k]);
     full_fwd_body<A, TAIL>(lds, p, v, ar, t, n, limb, fb);
 }
 template <bool TAIL>

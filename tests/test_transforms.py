@@ -99,3 +99,60 @@ def test_transform_matches_the_oracle(n, q0_bits, qi_bits, p_bits):
         gctx.ntt(dev, idx, inverse=True)
         assert np.array_equal(dev.cpu().numpy().view(np.uint64), a)
     gctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,bits,limb_counts", [(4096, (50, 49, 60), (3, 30)), (4096, (61, 51, 61), (3,)), (65536, (50, 49, 60), (3, 9, 17)),
+                                                (65536, (61, 51, 61), (3, 17))])
+def test_words_need_not_be_reduced(n, bits, limb_counts):
+    """cm_ntt on representatives below 4q (forward) and 2q (inverse): the transform of the residues they stand for."""
+    import torch
+    from paper_2602_11470_amd import binding as B
+    gctx = B.Context(n, 2, 1, 1, *bits, 2.0 ** 30)
+    try:
+        mods = np.array([int(q) for q in gctx.moduli()], dtype=np.uint64)
+        rng = np.random.default_rng(n)
+
+        def run(a, idx, inverse):
+            dev = torch.from_numpy(a.view(np.int64)).cuda()
+            gctx.ntt(dev, idx, inverse=inverse)
+            return dev.cpu().numpy().view(np.uint64)
+
+        for limbs in limb_counts:
+            idx = [i % 3 for i in range(limbs)]
+            q = mods[idx][:, None]
+            a = np.stack([rng.integers(0, int(x), n, dtype=np.uint64) for x in mods[idx]])
+            a[-1] = mods[idx[-1]] - np.uint64(1)
+            for inverse, reps in ((False, 4), (True, 2)):
+                lazy = a + q * rng.integers(0, reps, a.shape, dtype=np.uint64)
+                lazy[0], lazy[-1] = a[0] + np.uint64(reps - 1) * q[0], a[-1] + np.uint64(reps - 1) * q[-1]
+                assert np.array_equal(run(lazy, idx, inverse), run(a, idx, inverse)), (limbs, inverse)
+    finally:
+        gctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("limbs", [1, 9])
+def test_unreduced_words_that_add_up(limbs):
+    """Sixteen words below 4q, 4096 apart under the fourth 50-bit prime, whose first four forward stages reach 8.36 q, past the
+    2^53 up to which doubles hold integers, if they start from the words as they are (found by a search over the rounding of
+    the stages' quotients): reduced on the way in they stay exact."""
+    import torch
+    from paper_2602_11470_amd import binding as B
+    words = [4503599545581571, 4199760826192367, 4471848604929594, 4241931004056753, 4479579066880186, 4220889704009987,
+             4129894886765134, 4372344326500026, 4501524114183561, 4455057803063279, 4219648474230283, 4284223482568811,
+             4352827221761171, 4057168962167838, 4223436928134148, 4077454602415467]
+    gctx = B.Context(65536, 4, 1, 1, 50, 50, 60, 2.0 ** 30)
+    try:
+        q = int(gctx.moduli()[3])
+        assert q == 1125899886395393 and max(words) < 4 * q
+        a = np.random.default_rng(3).integers(0, q, (limbs, 65536), dtype=np.uint64)
+        a[:, 77::4096] = np.array(words, dtype=np.uint64)
+        outs = []
+        for x in (a, a % np.uint64(q)):
+            dev = torch.from_numpy(x.view(np.int64)).cuda()
+            gctx.ntt(dev, [3] * limbs)
+            outs.append(dev.cpu().numpy().view(np.uint64))
+        assert np.array_equal(*outs)
+    finally:
+        gctx.close()
