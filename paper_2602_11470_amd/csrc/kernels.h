@@ -96,7 +96,7 @@ void launch_encrypt(cm_ctx *ctx, u64 *c0, const u64 *a, const u64 *e, const u64 
 void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int ncomp, int ct_limbs, int limbs, hipStream_t st);
 // pts: all r_i*r_o plaintexts in the blocked layout written by launch_pt_block
 void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
-                    size_t ct_stride, int k0, int k1, hipStream_t st);
+                    size_t ct_stride, hipStream_t st);
 // words of the blocked array
 size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level);
 // copies plaintext (j,k) from plain[limbs][n] into the blocked array (to_blocked) or back

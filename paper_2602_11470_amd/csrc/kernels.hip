@@ -202,7 +202,9 @@ void launch_mac_pt_rot_batch(cm_ctx *ctx, u64 *acc, const u64 *src, const MulPtB
     hipLaunchKernelGGL(k_mac_pt_rot_batch, dim3(ctx->n / TPB, 2 * limbs), dim3(TPB), 0, st, acc, src, b, cnt, pt_mont,
                        ctx->d_modc, limbs, ctx->n, ctx->logn, accumulate);
 }
-// FP64 modular products for limbs whose modulus is below 2^50 (the arithmetic is explained at k_vmm_mac_lds)
+// FP64 modular products for limbs whose modulus is below 2^50: residues as exact integers in doubles, a product
+//     h = y a;  l = fma(y, a, -h);  c = rint(y (a / q));  r = fma(-c, q, h) + l        (|r| < q)
+// with a / q taken as a * (1 / q); four terms may be summed before a sum is renormalised (|sum| < 4.6 q < 2^53 stays exact)
 struct MacFp {
     double q, qinv;
     __device__ __forceinline__ double mulmod(double y, double a, double aq) const {
@@ -986,67 +988,62 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // ---- packed product: inner_k = sum_j baby_j * p_{j,k} ---------------------------------------------------
 // babies: r_i ciphertexts [2][limbs][n] at stride ct_stride; out: r_o ciphertexts at stride
 // ct_stride; pts: the r_i*r_o plaintexts in multiplier form, blocked for streaming:
-//     the words of plaintexts (0 .. r_i-1, k) of chunk ch (64 coefficients) of limb l are one contiguous run
-// (MacLayout), the runs of a chunk follow each other in k: the workgroup that owns (l, ch) reads one contiguous
-// stretch, the wave that owns k one run of it.  Limb l has
-// modulus index l up to `level`, and the special primes follow when limbs = level + 1 + K (sums
+//     the words of plaintexts (8g .. 8g+7, k) of chunk ch (64 coefficients) of limb l are one group, the groups follow each
+// other in k, g, ch, l: a wave that takes some k of one g, and the workgroup that owns (l, ch), read contiguous stretches.
+// Limb l has modulus index l up to `level`, and the special primes follow when limbs = level + 1 + K (sums
 // kept in the extended basis).
-// The baby ciphertexts are staged in LDS: a workgroup owns 64 coefficients of
-// one limb; its four waves take the k = k0 + wave, k0 + wave + 4, ... and every lane sums over all
-// j for its k, so each output is written once and each plaintext word is read once.  Up to 32
-// baby ciphertexts per pass (32 KiB of LDS).
 #define MAC_CO 64
-// the baby ciphertexts are read once per launch, like the plaintexts: non-temporal loads (2 % off the kernel)
-#define MAC_LD(ptr) __builtin_nontemporal_load(ptr)
-#define MAC_JC 32
-#define MAC_KW 4      // giant steps per wave whose sums stay in registers over the passes
-#define MAC_G 8       // plaintext words a lane keeps in flight per group (the next group is loaded while one is multiplied; 16 and 32 measured slower)
-// Limbs whose modulus is below 2^50 run the products in FP64 (the arithmetic of the transforms'
-// butterflies): residues as exact integers in doubles, a modular product
-//     h = y a;  l = fma(y, a, -h);  c = rint(y (a / q));  r = fma(-c, q, h) + l        (|r| < q)
-// with a / q taken as a * (1 / q), once per plaintext word for both ciphertext components; partial
-// sums are renormalised every four terms (|sum| < 4.6 q < 2^53 stays exact).  That is 8.5
-// instructions per product against 17 for the 128-bit integer form.  The plaintexts are stored in
-// multiplier form (times 2^64), so the finished sum is multiplied by 2^-64 mod q.
-// Limbs below 2^50 are stored packed where there are at least eight baby steps: the eight words of plaintexts (8g .. 8g+7, k)
-// of a coefficient as their low 32 bits (two 16-byte lane words, 1 KiB a wave each), the next 16 bits (one) and the top two
-// bits (one halfword): 50 bytes instead of 64, all loads aligned, whole lines a wave.  Unpacking takes three more
-// instructions a word in a kernel that waits for memory.  Fewer than eight baby steps and the integer limbs keep
-// 64-bit words.  Measured per kernel, unpacked -> packed: a 4096 x 4096 product at level 23 1681 -> 1588 us, at level 4
-// 540 -> 519, a 16384 x 4096 product at level 3 1713 -> 1623, 32 tokens of 1024 x 1024 at level 9 1567 -> 1441: 0.75 of the
-// rate that a plain kernel reads at.  The kernel takes 168 registers (three waves a SIMD), which the 128-bit sums of the integer
-// limbs set (the packed branch by itself 126), and a run of a wave starts with a load that nothing hides, once in four
-// groups at 32 baby steps a pass.  Two or three groups in flight instead of one, in as many waves, cost 3 to 5 % of a product.
-// Otherwise, with an even number of baby steps, the words of plaintexts (2j', k) and (2j'+1, k) are interleaved
-// (word c of the pair at 2c, 2c+1 of a 128-word row), so that a lane reads both with one 16-byte load and a
-// wavefront instruction covers 1 KiB of the stream.
-#define MAC_PACK_WORDS 400                     // 64-bit words of a packed group: 64 coefficients x 8 plaintexts
+#define MAC_G 8       // plaintexts of a group: what a lane loads at once for one giant step
+// Bound by HBM, and by what writes do to a read stream there: plain kernels read 7.1 TB/s with non-temporal loads (6.4 without
+// them), but 5 GB read with 3 % of stores sprinkled over the launch take 924 us instead of 744, whatever the stores' size or
+// placement; 881 if the stores go through to memory at once (agent scope) instead of leaving the L2 when it evicts them.
+// Arithmetic, LDS reads and barriers are hidden: without them, the plaintext stream and the stores alone take as long.
+// So bytes count: the packed groups, and the stores at agent scope.  Per launch, before (FP64 products on the limbs below
+// 2^50, 128-bit sums and 64-bit words on the others, plain stores) -> now: 64 x 8 products at level 23 1597 -> 1419 us, at
+// level 4 540 -> 471, 128 x 16 at level 3 1644 -> 1365, 64 x 16 (32 tokens of 1024 x 1024) at level 9 1438 -> 1278.
+// Sums of a wave that keeps all baby words of a group in registers (no LDS, no barriers), two or three groups in flight, FP64
+// or integer: within 2 % of this or slower.
+// Where there are at least eight baby steps the groups of limbs below 2^60 are packed, so that all loads are aligned and cover
+// whole lines a wave:
+//   below 2^50: eight words of a coefficient as their low 32 bits (two 16-byte lane words, 1 KiB a wave each), the next 16
+//               bits (one) and the top two bits (one halfword), 50 bytes instead of 64;
+//   below 2^60: the sixteen 30-bit halves in fifteen 32-bit words (three 16-byte lane words and one of 12), the last half in
+//               the top two bits of each, 60 bytes.
+// Fewer baby steps and larger moduli keep 64-bit words: with an even number of baby steps, the words of plaintexts (2j', k) and
+// (2j'+1, k) are interleaved (word c of the pair at 2c, 2c+1 of a 128-word row), so that a lane reads both with one 16-byte load.
+#define MAC_PACK50_WORDS 400                   // 64-bit words of a packed group: 64 coefficients x 8 plaintexts
+#define MAC_PACK60_WORDS 480
 struct MacLayout {
     int n, r_i, r_o;
-    u64 packed;                                // bit l: limb l is packed
-    __host__ __device__ __forceinline__ bool is_packed(int l) const { return (packed >> l) & 1; }
-    // words of limb l, first word of limb l, first word of the run of (limb, chunk, k)
-    __host__ __device__ __forceinline__ size_t limb_words(int l) const {
-        return (size_t)(n / MAC_CO) * r_o * (is_packed(l) ? (size_t)(r_i / 8) * MAC_PACK_WORDS : (size_t)r_i * MAC_CO);
+    u64 packed50, packed60;                    // bit l: how limb l is packed
+    __host__ __device__ __forceinline__ bool is50(int l) const { return (packed50 >> l) & 1; }
+    __host__ __device__ __forceinline__ bool is60(int l) const { return (packed60 >> l) & 1; }
+    __host__ __device__ __forceinline__ int per_group() const { return r_i % MAC_G ? r_i : MAC_G; }     // plaintexts of a group
+    __host__ __device__ __forceinline__ int group_words(int l) const {
+        return is50(l) ? MAC_PACK50_WORDS : is60(l) ? MAC_PACK60_WORDS : per_group() * MAC_CO;
     }
-    __host__ __device__ __forceinline__ size_t limb_base(int l) const {
-        const int below = __builtin_popcountll(packed & ((1ULL << l) - 1));
-        const size_t rows = (size_t)(n / MAC_CO) * r_o;
-        return rows * ((size_t)below * (r_i / 8) * MAC_PACK_WORDS + (size_t)(l - below) * r_i * MAC_CO);
+    __host__ __device__ __forceinline__ size_t groups() const { return (size_t)(n / MAC_CO) * r_o * (r_i / per_group()); }     // of a limb
+    __host__ __device__ __forceinline__ size_t limb_words(int l) const { return groups() * group_words(l); }
+    // first word of group g (baby steps 8 g ..) of giant step k of chunk ch of limb l
+    __host__ __device__ __forceinline__ size_t group(int l, int ch, int g, int k) const {
+        const u64 below = (1ULL << l) - 1;
+        const int b50 = __builtin_popcountll(packed50 & below), b60 = __builtin_popcountll(packed60 & below);
+        return groups() * ((size_t)b50 * MAC_PACK50_WORDS + (size_t)b60 * MAC_PACK60_WORDS + (size_t)(l - b50 - b60) * per_group() * MAC_CO) +
+               (((size_t)ch * (r_i / per_group()) + g) * r_o + k) * group_words(l);
     }
-    __host__ __device__ __forceinline__ size_t run(int l, int ch, int k) const {
-        return limb_base(l) + ((size_t)ch * r_o + k) * (is_packed(l) ? (size_t)(r_i / 8) * MAC_PACK_WORDS : (size_t)r_i * MAC_CO);
-    }
-    // unpacked limbs: word (j, c) of a run
-    __host__ __device__ __forceinline__ size_t word(int j, int c) const {
-        return (r_i & 1) ? (size_t)j * MAC_CO + c : (size_t)(j & ~1) * MAC_CO + 2 * c + (j & 1);
+    // unpacked limbs: word (j, c) of a group
+    __host__ __device__ __forceinline__ int word(int j, int c) const {
+        return (r_i & 1) ? j * MAC_CO + c : (j & ~1) * MAC_CO + 2 * c + (j & 1);
     }
 };
 static MacLayout mac_layout(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level) {
-    MacLayout m{ctx->n, r_i, r_o, 0};
-    if (r_i % 8 == 0)
-        for (int l = 0; l < limbs; l++)
-            if (ctx->mod[l <= level ? l : ctx->L + (l - level)] < (1ULL << 50)) m.packed |= 1ULL << l;
+    MacLayout m{ctx->n, r_i, r_o, 0, 0};
+    if (r_i % MAC_G == 0)
+        for (int l = 0; l < limbs; l++) {
+            const u64 q = ctx->mod[l <= level ? l : ctx->L + (l - level)];
+            if (q < (1ULL << 50)) m.packed50 |= 1ULL << l;
+            else if (q < (1ULL << 60)) m.packed60 |= 1ULL << l;
+        }
     return m;
 }
 size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level) {
@@ -1056,163 +1053,203 @@ size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level) 
     return w;
 }
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-struct MacGroup { u32x4 lo0, lo1, mid; unsigned top; };       // a lane's eight packed words
-__device__ __forceinline__ MacGroup mac_load_packed(const u64 *grp, int co) {
-    MacGroup g;
-    const u32x4 *v = reinterpret_cast<const u32x4 *>(grp);
-    g.lo0 = __builtin_nontemporal_load(v + co), g.lo1 = __builtin_nontemporal_load(v + 64 + co);
-    g.mid = __builtin_nontemporal_load(v + 128 + co);
-    g.top = __builtin_nontemporal_load(reinterpret_cast<const unsigned short *>(v + 192) + co);
-    return g;
-}
-__device__ __forceinline__ double mac_word(const MacGroup &g, int jj) {       // word jj as an exact double
-    const unsigned lo = jj < 4 ? g.lo0[jj & 3] : g.lo1[jj & 3], m = g.mid[jj >> 1];
-    const unsigned hi = ((((g.top >> (2 * jj)) & 3u) << 16) | ((jj & 1) ? m >> 16 : m & 0xFFFFu)) | 0x43300000u;
-    return __hiloint2double((int)hi, (int)lo) - 4503599627370496.0;
-}
-__global__ __launch_bounds__(TPB) void k_vmm_mac_lds(u64 *__restrict__ out, const u64 *__restrict__ babies,
-                                                     const u64 *__restrict__ pts, const ModC *__restrict__ modc,
-                                                     const FpQ *__restrict__ fpq, MacLayout lay, int limbs, int n,
-                                                     size_t ct_stride, int k0, int k1, int level, int L) {
-    __shared__ u64 sb[MAC_JC * 2 * MAC_CO];
-    const int r_i = lay.r_i;
-    // the limbs of the special primes (integer products, the slowest workgroups) are dispatched first, not last
-    const int nsp = limbs - (level + 1), y = blockIdx.y;
-    const int l = y < nsp ? level + 1 + y : y - nsp, ch = blockIdx.x, i0 = ch * MAC_CO;
-    const int co = threadIdx.x & (MAC_CO - 1), kq = threadIdx.x >> 6;
-    const int mi = l <= level ? l : L + 1 + (l - level - 1);
-    const ModC m = modc[mi];
-    const FpQ fq = fpq[mi];
-    const bool fp = fq.q != 0.0, packed = lay.is_packed(l);
-    const bool pair = !(r_i & 1);
-    const MacFp F{fq.q, fq.qinv};
-    const size_t o = (size_t)l * n + i0, cs = (size_t)limbs * n;
-    // up to MAC_KW giant steps per wave keep their running sums in registers across the passes over the baby steps
-    // (otherwise every pass after the first re-reads and re-writes the output)
-    u64 acc0[MAC_KW], acc1[MAC_KW];
+// Both factors of a product are split, so that it is four 32 x 32 -> 64-bit multiply-adds into three accumulators without
+// carries: T = t0 + 2^B t1 + 2^2B t2 with B = 25 under the 50-bit primes, 30 under the others.
+struct MacAcc {
+    u64 t0 = 0, t1 = 0, t2 = 0;
+    __device__ __forceinline__ void mac(unsigned b0, unsigned b1, unsigned w0, unsigned w1) {
+        t0 += (u64)b0 * w0, t1 += (u64)b0 * w1, t1 += (u64)b1 * w0, t2 += (u64)b1 * w1;
+    }
+    template <int B>
+    __device__ __forceinline__ u64 reduce(const ModC &m) const {
+        return redc((u128)t0 + ((u128)t1 << B) + ((u128)t2 << (2 * B)), m.q, m.qinv);
+    }
+};
+// A lane's eight words of a group; B: bits of the lower half; TERMS: products that the accumulators hold (t1 takes two a term).
+struct MacPacked50 {
+    static constexpr int GROUP_WORDS = MAC_PACK50_WORDS, B = 25, TERMS = 1 << 13;
+    u32x4 lo0, lo1, mid;
+    unsigned top;
+    __device__ __forceinline__ void load(const u64 *grp, int co) {
+        const u32x4 *v = reinterpret_cast<const u32x4 *>(grp);
+        lo0 = __builtin_nontemporal_load(v + co), lo1 = __builtin_nontemporal_load(v + 64 + co);
+        mid = __builtin_nontemporal_load(v + 128 + co);
+        top = __builtin_nontemporal_load(reinterpret_cast<const unsigned short *>(v + 192) + co);
+    }
+    __device__ __forceinline__ void word(int j, unsigned &w0, unsigned &w1) const {
+        const unsigned lo = j < 4 ? lo0[j & 3] : lo1[j & 3], m = mid[j >> 1];
+        const unsigned hi = (((top >> (2 * j)) & 3u) << 16) | ((j & 1) ? m >> 16 : m & 0xFFFFu);
+        w0 = lo & LOW25, w1 = __builtin_amdgcn_alignbit(hi, lo, 25);
+    }
+};
+typedef unsigned u32x3 __attribute__((ext_vector_type(3), aligned(4)));
+struct MacPacked60 {
+    static constexpr int GROUP_WORDS = MAC_PACK60_WORDS, B = 30, TERMS = 8;
+    u32x4 a[3];
+    u32x3 b;
+    unsigned last;
+    __device__ __forceinline__ void load(const u64 *grp, int co) {
+        const u32x4 *v = reinterpret_cast<const u32x4 *>(grp);
 #pragma unroll
-    for (int x = 0; x < MAC_KW; x++) acc0[x] = acc1[x] = 0;
-    const bool keep = k1 - k0 <= 4 * MAC_KW;
-    for (int j0 = 0; j0 < r_i; j0 += MAC_JC) {
-        const int jn = r_i - j0 < MAC_JC ? r_i - j0 : MAC_JC;
-        __syncthreads();
-        {
-            // a lane stages word `co` of rows kq, kq + 4, ...: all its loads are issued before the first is used
-            constexpr int ROWS = MAC_JC * 2 * MAC_CO / TPB;
-            u64 w[ROWS];
+        for (int i = 0; i < 3; i++) a[i] = __builtin_nontemporal_load(v + 64 * i + co);
+        b = __builtin_nontemporal_load(reinterpret_cast<const u32x3 *>((const char *)grp + 3072 + 12 * co));
+    }
+    __device__ __forceinline__ unsigned d(int i) const { return i < 12 ? a[i / 4][i % 4] : b[i % 4]; }
+    __device__ __forceinline__ void word(int j, unsigned &w0, unsigned &w1) const {
+        w0 = d(2 * j) & LOW30;
+        if (j < 7) {
+            w1 = d(2 * j + 1) & LOW30;
+        } else {
+            w1 = 0;
 #pragma unroll
-            for (int it = 0; it < ROWS; it++) {
-                const int jc = kq + 4 * it;
-                w[it] = jc < 2 * jn ? MAC_LD(babies + (size_t)(j0 + (jc >> 1)) * ct_stride + (jc & 1) * cs + o + co) : 0;
-            }
-#pragma unroll
-            for (int it = 0; it < ROWS; it++) {
-                const int jc = kq + 4 * it;
-                if (jc < 2 * jn) sb[jc * MAC_CO + co] = fp ? (u64)__double_as_longlong(MacFp::from_u64(w[it])) : w[it];
-            }
+            for (int i = 0; i < 15; i++) w1 = __builtin_amdgcn_alignbit(w1, d(i), 30);
         }
-        __syncthreads();
-        // A sum of products is reduced when one more group of 8 could pass q * 2^64 (the bound of
-        // REDC): after every group for the 60-bit special primes.
-        for (int k = k0 + kq; k < k1; k += 4) {
-            const u64 *run = pts + lay.run(l, ch, k);
-            u64 v0, v1;
-            if (packed) {
-                const u64 *pk = run + (size_t)(j0 / 8) * MAC_PACK_WORDS;
-                MacGroup p = mac_load_packed(pk, co), pn = p;
-                double s0 = 0.0, s1 = 0.0;
-                for (int j8 = 0; j8 < jn; j8 += 8) {
+    }
+};
+struct MacWords {                              // 64-bit words, pairs interleaved: moduli from 2^60 up to 2^61
+    static constexpr int GROUP_WORDS = MAC_G * MAC_CO, B = 30, TERMS = 4;
+    u64x2 w[MAC_G / 2];
+    __device__ __forceinline__ void load(const u64 *grp, int co) {
+#pragma unroll
+        for (int i = 0; i < MAC_G / 2; i++) w[i] = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(grp) + 64 * i + co);
+    }
+    __device__ __forceinline__ void word(int j, unsigned &w0, unsigned &w1) const {
+        const u64 v = (j & 1) ? w[j / 2].y : w[j / 2].x;
+        w0 = (unsigned)v & LOW30, w1 = (unsigned)(v >> 30);
+    }
+};
+// A workgroup owns 64 coefficients of one limb; its four waves take KW giant steps each.  The baby words are staged in LDS as
+// two halves, sixteen baby steps a pass (16 KiB, so that registers set the occupancy: four waves a SIMD; thirty-two measured
+// the same), the first group of a pass requested before them.  The sums stay in registers over the passes and are written once.
+#define MAC_JC 16
+template <int KW, class G>
+__device__ __forceinline__ void mac_body(uint2 *sb, u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
+                                         const ModC &m, const MacLayout &lay, int l, int ch, size_t cs, size_t ct_stride) {
+    const int co = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t o = (size_t)l * lay.n + ch * MAC_CO;          // uniform: lanes differ by co alone
+    for (int k0 = 0; k0 < lay.r_o; k0 += 4 * KW) {
+        const int kb = k0 + wave * KW;
+        const bool active = kb < lay.r_o;                     // uniform in a wave
+        u64 s[KW][2];
+#pragma unroll
+        for (int k = 0; k < KW; k++) s[k][0] = s[k][1] = 0;
+        for (int j0 = 0; j0 < lay.r_i; j0 += MAC_JC) {
+            const int groups = min(MAC_JC, lay.r_i - j0) / MAC_G, rows = 2 * MAC_G * groups;
+            const u64 *p = pts + lay.group(l, ch, j0 / MAC_G, kb);
+            G q;
+            if (active) q.load(p, co);                        // in flight across the staging
+            {
+                // a lane stages word `co` of rows wave, wave + 4, ...: all its loads are issued before the first is used
+                constexpr int ROWS = MAC_JC * 2 / 4;
+                u64 x[ROWS];
+#pragma unroll
+                for (int it = 0; it < ROWS; it++) {
+                    const int r = min(wave + 4 * it, rows - 1);             // past the last row: one more time, never used
+                    x[it] = __builtin_nontemporal_load(babies + (size_t)(j0 + (r >> 1)) * ct_stride + (r & 1) * cs + o + co);
+                }
+                if (j0 || k0) __syncthreads();
+#pragma unroll
+                for (int it = 0; it < ROWS; it++)
+                    sb[(wave + 4 * it) * MAC_CO + co] = make_uint2((unsigned)x[it] & ((1u << G::B) - 1), (unsigned)(x[it] >> G::B));
+                __syncthreads();
+            }
+            if (!active) continue;
+#pragma unroll
+            for (int k = 0; k < KW; k++) {
+                MacAcc t[2];
+#pragma unroll 1
+                for (int g = 0; g < groups; g++) {
+                    G nx = q;
                     // the next group is in flight while this one is multiplied
-                    if (j8 + 8 < jn) pn = mac_load_packed(pk + (size_t)(j8 / 8 + 1) * MAC_PACK_WORDS, co);
+                    if (g + 1 < groups) nx.load(p + ((size_t)(g + 1) * lay.r_o + k) * G::GROUP_WORDS, co);
+                    else if (k + 1 < KW) nx.load(p + (size_t)(k + 1) * G::GROUP_WORDS, co);
 #pragma unroll
-                    for (int jj = 0; jj < 8; jj++) {
-                        const double a = mac_word(p, jj), aq = a * F.qinv;
-                        s0 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 0) * MAC_CO + co]), a, aq);
-                        s1 += F.mulmod(__longlong_as_double((long long)sb[((j8 + jj) * 2 + 1) * MAC_CO + co]), a, aq);
-                        if ((jj & 3) == 3) s0 = F.norm(s0), s1 = F.norm(s1);
-                    }
-                    p = pn;
-                }
-                v0 = F.canon(F.mulmod(s0, fq.rinv, fq.rinvq));
-                v1 = F.canon(F.mulmod(s1, fq.rinv, fq.rinvq));
-            } else {
-                const u64 *pk = run + (size_t)j0 * MAC_CO;
-                // words of plaintexts j0 + j8 .. j0 + j8 + MAC_G - 1 for this lane's coefficient (zero past the end)
-                auto load_group = [&](int j8, u64 (&w)[MAC_G]) {
-                    if (pair) {
+                    for (int j = 0; j < MAC_G; j++) {
+                        unsigned w0, w1;
+                        q.word(j, w0, w1);
 #pragma unroll
-                        for (int jj = 0; jj < MAC_G; jj += 2) {
-                            u64x2 v = {0, 0};
-                            if (j8 + jj < jn) v = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(pk + (size_t)(j8 + jj) * MAC_CO) + co);
-                            w[jj] = v.x, w[jj + 1] = v.y;
+                        for (int c = 0; c < 2; c++) {
+                            const uint2 b = sb[((g * MAC_G + j) * 2 + c) * MAC_CO + co];
+                            t[c].mac(b.x, b.y, w0, w1);
                         }
-                    } else {
+                        if (G::TERMS <= MAC_G && (j + 1) % G::TERMS == 0) {
 #pragma unroll
-                        for (int jj = 0; jj < MAC_G; jj++) w[jj] = j8 + jj < jn ? __builtin_nontemporal_load(pk + (size_t)(j8 + jj) * MAC_CO + co) : 0;
-                    }
-                };
-                u64 p[MAC_G], pn[MAC_G];
-                load_group(0, p);
-                if (fp) {                      // fewer than eight baby steps
-                    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-                    for (int jj = 0; jj < MAC_G; jj++) {
-                        if (jj < jn) {
-                            const double a = MacFp::from_u64(p[jj]), aq = a * F.qinv;
-                            s0 += F.mulmod(__longlong_as_double((long long)sb[(jj * 2 + 0) * MAC_CO + co]), a, aq);
-                            s1 += F.mulmod(__longlong_as_double((long long)sb[(jj * 2 + 1) * MAC_CO + co]), a, aq);
+                            for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q), t[c] = MacAcc();
                         }
-                        if ((jj & 3) == 3) s0 = F.norm(s0), s1 = F.norm(s1);
                     }
-                    v0 = F.canon(F.mulmod(s0, fq.rinv, fq.rinvq));
-                    v1 = F.canon(F.mulmod(s1, fq.rinv, fq.rinvq));
-                } else {
-                    v0 = v1 = 0;
-                    for (int j8 = 0; j8 < jn; j8 += MAC_G) {
-                        load_group(j8 + MAC_G, pn);
-                        u128 s0 = 0, s1 = 0;
-#pragma unroll
-                        for (int jj = 0; jj < MAC_G; jj++) {
-                            if (j8 + jj < jn) {
-                                s0 += (u128)sb[((j8 + jj) * 2 + 0) * MAC_CO + co] * p[jj];
-                                s1 += (u128)sb[((j8 + jj) * 2 + 1) * MAC_CO + co] * p[jj];
-                            }
-                        }
-                        v0 = addmod(v0, redc(s0, m.q, m.qinv), m.q);
-                        v1 = addmod(v1, redc(s1, m.q, m.qinv), m.q);
-#pragma unroll
-                        for (int jj = 0; jj < MAC_G; jj++) p[jj] = pn[jj];
-                    }
+                    q = nx;
                 }
-            }
-            u64 *dst = out + (size_t)k * ct_stride + o + co;
-            if (keep) {
-                // the sums of this wave's giant steps stay in registers over the passes and are written once
-                const int ki = (k - k0 - kq) >> 2;
-                const bool last = j0 + MAC_JC >= r_i;
+                if (G::TERMS > MAC_G) {
 #pragma unroll
-                for (int x = 0; x < MAC_KW; x++)
-                    if (x == ki) {
-                        if (j0) v0 = addmod(v0, acc0[x], m.q), v1 = addmod(v1, acc1[x], m.q);
-                        acc0[x] = v0, acc1[x] = v1;
-                    }
-                if (last) dst[0] = v0, dst[cs] = v1;
-            } else {
-                if (j0) {
-                    v0 = addmod(v0, dst[0], m.q);
-                    v1 = addmod(v1, dst[cs], m.q);
+                    for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q);
                 }
-                dst[0] = v0;
-                dst[cs] = v1;
             }
         }
+        if (!active) continue;
+#pragma unroll
+        for (int k = 0; k < KW; k++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) 
+                __hip_atomic_store(out + (size_t)(kb + k) * ct_stride + c * cs + o + co, s[k][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+template <int KW>
+__global__ __launch_bounds__(TPB) void k_vmm_mac(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
+                                                   const ModC *__restrict__ modc, MacLayout lay, int limbs, size_t ct_stride, int level, int L) {
+    __shared__ uint2 sb[MAC_JC * 2 * MAC_CO];
+    // the limbs of the special primes (64-bit words, the slowest workgroups) are dispatched first, not last
+    const int nsp = limbs - (level + 1), y = blockIdx.y;
+    const int l = y < nsp ? level + 1 + y : y - nsp, mi = l <= level ? l : L + 1 + (l - level - 1);
+    const ModC m = modc[mi];
+    const size_t cs = (size_t)limbs * lay.n;
+    if (lay.is50(l)) mac_body<KW, MacPacked50>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
+    else if (lay.is60(l)) mac_body<KW, MacPacked60>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
+    else mac_body<KW, MacWords>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
+}
+// fewer than eight baby steps (1, 2 or 4): a lane keeps its baby words and runs over some giant steps
+#define MAC_FEW_K 8
+__global__ __launch_bounds__(TPB) void k_vmm_mac_few(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
+                                                    const ModC *__restrict__ modc, MacLayout lay, int limbs, size_t ct_stride, int level,
+                                                    int L) {
+    const int l = blockIdx.y, i = blockIdx.x * TPB + threadIdx.x, mi = l <= level ? l : L + 1 + (l - level - 1);
+    const ModC m = modc[mi];
+    const size_t o = (size_t)l * lay.n + i, cs = (size_t)limbs * lay.n;
+    u64 b[4][2];
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+        for (int c = 0; c < 2; c++) b[j][c] = j < lay.r_i ? babies[j * ct_stride + c * cs + o] : 0;
+    const int k0 = blockIdx.z * MAC_FEW_K, k1 = min(k0 + MAC_FEW_K, lay.r_o);
+    for (int k = k0; k < k1; k++) {
+        const u64 *run = pts + lay.group(l, i / MAC_CO, 0, k);
+        u128 s0 = 0, s1 = 0;                   // four products: below q 2^64 for all moduli
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            if (j < lay.r_i) {
+                const u64 w = __builtin_nontemporal_load(run + lay.word(j, i % MAC_CO));
+                s0 += (u128)b[j][0] * w, s1 += (u128)b[j][1] * w;
+            }
+        }
+        out[k * ct_stride + o] = redc(s0, m.q, m.qinv);
+        out[k * ct_stride + cs + o] = redc(s1, m.q, m.qinv);
     }
 }
 void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
-                    size_t ct_stride, int k0, int k1, hipStream_t st) {
-    Prof prof_(ctx, CM_K_VMM_MAC, r_i * (k1 - k0), st);
-    hipLaunchKernelGGL(k_vmm_mac_lds, dim3(ctx->n / MAC_CO, limbs), dim3(TPB), 0, st, out, babies, pts, ctx->d_modc,
-                       ctx->d_fpq, mac_layout(ctx, r_i, r_o, limbs, level), limbs, ctx->n, ct_stride, k0, k1, level, ctx->L);
+                    size_t ct_stride, hipStream_t st) {
+    Prof prof_(ctx, CM_K_VMM_MAC, r_i * r_o, st);
+    const MacLayout lay = mac_layout(ctx, r_i, r_o, limbs, level);
+    if (r_i % 8) {
+        hipLaunchKernelGGL(k_vmm_mac_few, dim3(ctx->n / TPB, limbs, (r_o + MAC_FEW_K - 1) / MAC_FEW_K), dim3(TPB), 0, st, out, babies, pts,
+                           ctx->d_modc, lay, limbs, ct_stride, level, ctx->L);
+        return;
+    }
+    const dim3 grid(ctx->n / MAC_CO, limbs), block(TPB);
+#define MAC_LAUNCH(KW_)                                                                                                            \
+    hipLaunchKernelGGL(k_vmm_mac<KW_>, grid, block, 0, st, out, babies, pts, ctx->d_modc, lay, limbs, ct_stride, level, ctx->L)
+    if (r_o <= 4) MAC_LAUNCH(1);
+    else if (r_o <= 8) MAC_LAUNCH(2);
+    else MAC_LAUNCH(4);
+#undef MAC_LAUNCH
 }
 // ---- masks before the shared rotations of query-times-K --------------------------------------------------
 // A[k] = sum_{c < nk} T[c] * M[(c + k) mod E] for k < shared: T the nk key-ciphertext sums [2][limbs][n] (stacked),
@@ -1548,28 +1585,42 @@ void launch_mask_ntt(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *Mhat, const u
     hipLaunchKernelGGL(k_mask_ntt<1>, dim3(ctx->n >> lg, limbs, 2), dim3(TPB), ((size_t)E << lg) * 8, st, A, T, Mhat, tw, einv,
                        ctx->d_modc, nk, E, logE, shared, limbs, ctx->n, lg);
 }
-// plaintext (j,k) between its plain form src[limbs][n] and its place in the blocked array.  The top bits of a packed group
-// share a halfword: a launch writes one plaintext, so a lane reads and writes its halfword alone.
+// plaintext (j,k) between its plain form src[limbs][n] and its place in the blocked array.  The words of a packed group share
+// some bits' places: a launch writes one plaintext, so a lane reads and writes the places of its coefficient alone.
 __global__ void k_pt_block(u64 *blocked, u64 *plain, MacLayout lay, int n, int j, int k, int to_blocked) {
     const int i = blockIdx.x * TPB + threadIdx.x, l = blockIdx.y, co = i % MAC_CO;
-    u64 *run = blocked + lay.run(l, i / MAC_CO, k);
+    u64 *grp = blocked + lay.group(l, i / MAC_CO, j / lay.per_group(), k);
+    const int jj = j % lay.per_group();
     const size_t p = (size_t)l * n + i;
-    if (!lay.is_packed(l)) {
-        const size_t b = lay.word(j, co);
-        if (to_blocked) run[b] = plain[p];
-        else plain[p] = run[b];
-        return;
-    }
-    const int jj = j & 7;
-    char *grp = (char *)(run + (size_t)(j / 8) * MAC_PACK_WORDS);
-    unsigned *lo = (unsigned *)(grp + (jj / 4) * 1024) + co * 4 + (jj & 3);
-    unsigned short *mid = (unsigned short *)(grp + 2048) + co * 8 + jj, *top = (unsigned short *)(grp + 3072) + co;
-    if (to_blocked) {
-        const u64 v = plain[p];
-        *lo = (unsigned)v, *mid = (unsigned short)(v >> 32);
-        *top = (unsigned short)((*top & ~(3u << (2 * jj))) | ((unsigned)(v >> 48) << (2 * jj)));
+    unsigned *dw = (unsigned *)grp;
+    if (lay.is50(l)) {
+        unsigned *lo = dw + (jj / 4) * 256 + co * 4 + (jj & 3);
+        unsigned short *mid = (unsigned short *)(dw + 512) + co * 8 + jj, *top = (unsigned short *)(dw + 768) + co;
+        if (to_blocked) {
+            const u64 v = plain[p];
+            *lo = (unsigned)v, *mid = (unsigned short)(v >> 32);
+            *top = (unsigned short)((*top & ~(3u << (2 * jj))) | ((unsigned)(v >> 48) << (2 * jj)));
+        } else {
+            plain[p] = (u64)*lo | ((u64)*mid << 32) | ((u64)((*top >> (2 * jj)) & 3u) << 48);
+        }
+    } else if (lay.is60(l)) {
+        auto d = [&](int i) -> unsigned & { return i < 12 ? dw[(i / 4) * 256 + co * 4 + i % 4] : dw[768 + co * 3 + i % 4]; };
+        auto put = [&](int h, unsigned v) {
+            if (h < 15) d(h) = (d(h) & ~LOW30) | v;
+            else for (int i = 0; i < 15; i++) d(i) = (d(i) & LOW30) | (((v >> (28 - 2 * i)) & 3u) << 30);
+        };
+        auto get = [&](int h) {
+            unsigned v = 0;
+            if (h < 15) v = d(h) & LOW30;
+            else for (int i = 0; i < 15; i++) v = (v << 2) | (d(i) >> 30);
+            return v;
+        };
+        if (to_blocked) put(2 * jj, (unsigned)plain[p] & LOW30), put(2 * jj + 1, (unsigned)(plain[p] >> 30));
+        else plain[p] = (u64)get(2 * jj) | ((u64)get(2 * jj + 1) << 30);
     } else {
-        plain[p] = (u64)*lo | ((u64)*mid << 32) | ((u64)((*top >> (2 * jj)) & 3u) << 48);
+        const int b = lay.word(jj, co);
+        if (to_blocked) grp[b] = plain[p];
+        else plain[p] = grp[b];
     }
 }
 void launch_pt_block(cm_ctx *ctx, u64 *blocked, u64 *plain, int limbs, int level, int r_i, int r_o, int j, int k, bool to_blocked,

@@ -395,7 +395,7 @@ static cm_status vmm_raised_finish(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_
     u64 *inner = p->d_work + (size_t)p->r_i * rw, *t0 = inner + (size_t)p->r_o * rw;
     u64 *t1 = t0 + ctw, *t2 = t1 + ctw;
     const int r_o = p->r_o;
-    launch_vmm_mac(ctx, inner, babies, p->d_pts, p->r_i, r_o, ext, level, rw, 0, r_o, st);
+    launch_vmm_mac(ctx, inner, babies, p->d_pts, p->r_i, r_o, ext, level, rw, st);
     u64 *acc = t1, *other = t2;
     if (p->direct) {
         // giant steps unrolled: the second component of inner_k is divided by P and raised digit by digit
@@ -537,7 +537,7 @@ extern "C" cm_status cm_vmm_pt(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_plan
     }
     //    multiply-accumulate: inner_k = sum_j baby_j * p_{j,k}; streams every weight plaintext once
     const int r_o = p->r_o;
-    launch_vmm_mac(ctx, inner, babies, p->d_pts, p->r_i, r_o, limbs, level, ctw, 0, r_o, st);
+    launch_vmm_mac(ctx, inner, babies, p->d_pts, p->r_i, r_o, limbs, level, ctw, st);
     //    giant steps, Horner form
     u64 *acc = inner + (size_t)(r_o - 1) * ctw;
     for (int k = r_o - 2; k >= 0; k--) {
