@@ -35,7 +35,12 @@ struct NttTables {
     const FpQ *fpq;               // [nmod] q and 1/q as doubles; q = 0 where the limb must use IntArith
     // Large launches (256 limbs and more) read with non-temporal loads: their input was written long before and is read
     // once.  Small launches find theirs in the caches and read plainly (a single key switch is 3 % slower otherwise).
-    int stream_loads;
+    // A limb is read again only by a later kernel.  Large launches write with non-temporal stores (after hundreds of MiB of
+    // other limbs have gone by; 1 % off the transforms of a step against plain stores), small ones at agent scope, through to
+    // memory at once instead of when the L2 evicts or a kernel ends.  Against non-temporal stores: ciphertext product at level
+    // 13 158.5 -> 154.2 us, rotary embedding at level 3 138.0 -> 134.9, 4096 x 4096 product at level 4 1154 -> 1140; for large
+    // launches agent scope is 2 to 5 % slower (attention, product at level 23), plain stores 1 to 4 %.
+    int large;
 };
 
 // element idx of a uniform array by a 32-bit byte offset (one register and the scalar base, no 64-bit address arithmetic)
@@ -326,14 +331,15 @@ __device__ __forceinline__ void radix16_inv_last(u64 (&v)[16], const IntArith &a
     radix16_inv_tw(v, ar, TableTw<IntArith>(ar, base0));
 }
 
-// LDS index with one pad word per 16 so that lanes reading words 16 apart hit distinct banks
-// The passes write with non-temporal stores: a limb is read again only by a later kernel, after hundreds of MiB of other
-// limbs have gone by (measured: 1 % off the transforms of a step against plain stores).
-#define NTT_ST(ptr, val) __builtin_nontemporal_store((u64)(val), (ptr))
+__device__ __forceinline__ void ntt_store(int large, u64 *p, u64 v) {
+    if (large) __builtin_nontemporal_store(v, p);
+    else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // the masked products of a cache append read the cached ciphertext they add to and write it back past the caches (the
 // cache is gigabytes; 3 % off an append)
 #define TAIL_LD(ptr) __builtin_nontemporal_load(ptr)
 #define TAIL_ST(ptr, val) __builtin_nontemporal_store((u64)(val), (ptr))
+// LDS index with one pad word per 16 so that lanes reading words 16 apart hit distinct banks
 __device__ __forceinline__ int pad(int e) { return e + (e >> 4); }
 #define LDS_WORDS (4096 + 256)
 
@@ -345,7 +351,7 @@ __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, c
     const int c = threadIdx.x & 15, sub = threadIdx.x >> 4;
     typename A::T v[16];
     u64 raw[16];
-    if (t.stream_loads) {
+    if (t.large) {
 #pragma unroll
         for (int k = 0; k < 16; k++) raw[k] = __builtin_nontemporal_load(ps + (unsigned)((sub + 16 * k) * n2 + c));
     } else {
@@ -366,7 +372,7 @@ __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, c
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
     radix16_fwd_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) NTT_ST(p + (unsigned)((16 * sub + k) * n2 + c), ar.to_mid(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(t.large, p + (unsigned)((16 * sub + k) * n2 + c), ar.to_mid(v[k]));
 }
 template <class A>
 __device__ __forceinline__ void cols_inv_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int n2) {
@@ -375,7 +381,7 @@ __device__ __forceinline__ void cols_inv_body(u64 *lds, u64 *p, const NttTables 
     const int c = threadIdx.x & 15, sub = threadIdx.x >> 4;
     typename A::T v[16];
     u64 raw[16];
-    if (t.stream_loads) {
+    if (t.large) {
 #pragma unroll
         for (int k = 0; k < 16; k++) raw[k] = __builtin_nontemporal_load(p + (unsigned)((16 * sub + k) * n2 + c));
     } else {
@@ -396,7 +402,7 @@ __device__ __forceinline__ void cols_inv_body(u64 *lds, u64 *p, const NttTables 
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((sub + 16 * k) * 16 + c)]);
     radix16_inv_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) NTT_ST(p + (unsigned)((sub + 16 * k) * n2 + c), ar.to_rest_inv(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(t.large, p + (unsigned)((sub + 16 * k) * n2 + c), ar.to_rest_inv(v[k]));
 }
 
 // grid.x = limbs * (n2/16)
@@ -515,7 +521,7 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
     const u64 B = (u64)chunk * 16 + blk;
     typename A::T v[16];
     u64 raw[16];
-    if (t.stream_loads) {
+    if (t.large) {
 #pragma unroll
         for (int k = 0; k < 16; k++) raw[k] = __builtin_nontemporal_load(p + blk * 256 + sub + 16 * k);
     } else {
@@ -541,7 +547,7 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
     __syncthreads();
     if (!TAIL) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) NTT_ST(p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
+        for (int k = 0; k < 16; k++) ntt_store(t.large, p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
         return;
     }
     finish_tail<NTT_THREADS>(pad, ar, lds, t, n, chunk, limb, fb);
@@ -563,7 +569,7 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
         if (g) {
 #pragma unroll
             for (int k = 0; k < 16; k++) w[k] = psrow[perm_src(pos0 + 256 * k, g, logn)];
-        } else if (t.stream_loads) {
+        } else if (t.large) {
 #pragma unroll
             for (int k = 0; k < 16; k++) w[k] = __builtin_nontemporal_load(ps + threadIdx.x + 256 * k);
         } else {
@@ -585,7 +591,7 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(blk * 256 + sub + 16 * k)]);
     radix16_inv_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) NTT_ST(p + blk * 256 + sub + 16 * k, ar.to_mid(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(t.large, p + blk * 256 + sub + 16 * k, ar.to_mid(v[k]));
 }
 // grid.x = limbs * n/4096; TAIL: the fused ModDown / rescale tail (a kernel of its own, so that the registers its
 // operands take do not lower the occupancy of the plain transform)
@@ -717,7 +723,7 @@ __device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 
     for (int k = 0; k < 4; k++) v[k] = ar.from_lazy(raw[k]);
     small_fwd(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
 #pragma unroll
-    for (int k = 0; k < 4; k++) NTT_ST(p + (4 * sub + k) * n2 + c, ar.to_mid(v[k]));
+    for (int k = 0; k < 4; k++) ntt_store(0, p + (4 * sub + k) * n2 + c, ar.to_mid(v[k]));
 }
 template <class A>
 __device__ __forceinline__ void small_cols_inv_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n) {
@@ -729,7 +735,7 @@ __device__ __forceinline__ void small_cols_inv_body(u64 *lds, u64 *p, const NttT
     for (int k = 0; k < 4; k++) v[k] = ar.from_mid(p[(4 * sub + k) * n2 + c]);
     small_inv(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
 #pragma unroll
-    for (int k = 0; k < 4; k++) NTT_ST(p + (64 * k + sub) * n2 + c, ar.to_rest_inv(v[k]));
+    for (int k = 0; k < 4; k++) ntt_store(0, p + (64 * k + sub) * n2 + c, ar.to_rest_inv(v[k]));
 }
 // eight rows, a wave each: the exchanges stay inside it
 template <class A, bool TAIL>
@@ -748,7 +754,7 @@ __device__ __forceinline__ void small_rows_fwd_body(u64 *lds, u64 *p, const NttT
     if (!TAIL) {
         wave_sync();
 #pragma unroll
-        for (int k = 0; k < 4; k++) NTT_ST(p + 64 * k + sub, lds[pad(row * 256 + 64 * k + sub)]);
+        for (int k = 0; k < 4; k++) ntt_store(0, p + 64 * k + sub, lds[pad(row * 256 + 64 * k + sub)]);
         return;
     }
     __syncthreads();
@@ -769,7 +775,7 @@ __device__ __forceinline__ void small_rows_inv_body(u64 *lds, u64 *p, const u64 
     for (int k = 0; k < 4; k++) v[k] = ar.from_rest(raw[k]);
     small_inv(lds, v, ar, 256 + 8 * chunk + row, sub, SmallRow{row * 256}, WaveSync());
 #pragma unroll
-    for (int k = 0; k < 4; k++) NTT_ST(p + row * 256 + 64 * k + sub, ar.to_mid(v[k]));
+    for (int k = 0; k < 4; k++) ntt_store(0, p + row * 256 + 64 * k + sub, ar.to_mid(v[k]));
 }
 // grid.x = limbs * n / 2048
 __global__ __launch_bounds__(64 * SMALL_CW) void small_cols_fwd(u64 *__restrict__ data, const u64 *__restrict__ src,
@@ -1106,7 +1112,7 @@ struct ConvY {
 // LDS: row r of 8 words at row r ^ ((r >> 2) & 3): any four rows that a half-wave touches (neighbours, or four apart) then
 // cover all banks
 template <class A>
-__device__ __forceinline__ void ccf_body(u64 *lds, int buf, u64 *p, typename A::T (&v)[4], unsigned tid, const A &ar, int n2) {
+__device__ __forceinline__ void ccf_body(u64 *lds, int buf, int large, u64 *p, typename A::T (&v)[4], unsigned tid, const A &ar, int n2) {
     const int c = tid % CCF_W, sub = tid / CCF_W;
     u64 *A0 = lds + (buf ? 256 * CCF_W : 0) + c, *B0 = lds + (buf ? 0 : 256 * CCF_W) + c;
     {
@@ -1145,7 +1151,7 @@ __device__ __forceinline__ void ccf_body(u64 *lds, int buf, u64 *p, typename A::
         radix_fwd<2, 6>(v, ar, tw);
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++) NTT_ST(word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
+    for (int k = 0; k < 4; k++) ntt_store(large, word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
 }
 // grid: x = column tile, y = target group (the last targets, those under the 60-bit primes, first), then the copies
 template <int NS>
@@ -1164,7 +1170,7 @@ __global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict_
 #pragma unroll
             for (int k = 0; k < 4; k++) w[k] = src[row + (a.own_g ? perm_src(i0 + CCF_THREADS * k, a.own_g, logn) : i0 + CCF_THREADS * k)];
 #pragma unroll
-            for (int k = 0; k < 4; k++) NTT_ST(out + row + i0 + CCF_THREADS * k, w[k]);
+            for (int k = 0; k < 4; k++) ntt_store(t.large, out + row + i0 + CCF_THREADS * k, w[k]);
         }
         return;
     }
@@ -1195,13 +1201,13 @@ __global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict_
             ar.init(t, o.mod, n);
             double v[4];
             y.target_any(split, o, ar, v);
-            ccf_body<FpArith>(lds, buf, p, v, tid, ar, n2);
+            ccf_body<FpArith>(lds, buf, t.large, p, v, tid, ar, n2);
         } else {
             IntArith ar;
             ar.init(t, o.mod, n);
             u64 x[4];
             y.target(split, o, x);
-            ccf_body<IntArith>(lds, buf, p, x, tid, ar, n2);
+            ccf_body<IntArith>(lds, buf, t.large, p, x, tid, ar, n2);
         }
     }
 }
@@ -1256,7 +1262,7 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
 static NttTables tables_of(const cm_ctx *ctx, bool inverse, int limbs) {
     NttTables t;
     t.modc = ctx->d_modc, t.fpq = ctx->d_fpq;
-    t.stream_loads = limbs >= 256;
+    t.large = limbs >= 256;
     if (!inverse) {
         t.tw = ctx->d_tw, t.twp = ctx->d_twp, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
         t.ninv = t.ninvp = nullptr, t.ninvd = t.ninvqd = nullptr;
