@@ -118,6 +118,8 @@ struct ConvTarget {
     double w[CONV_MAX_SRC];       // hat_m mod q (exact for moduli below 2^50)
     u64 q, qinv;                  // modulus, q^{-1} mod 2^64
     u64 wm[CONV_MAX_SRC];         // hat_m mod q in multiplier form
+    double wl;                    // the same of the weight of a folded last limb (ConvFold): P mod q
+    u64 wlm;
 };
 struct ConvDev {
     int ns, nt, split;
@@ -125,6 +127,13 @@ struct ConvDev {
     u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC], src_q[CONV_MAX_SRC];
     double src_qd[CONV_MAX_SRC], inv_hat_d[CONV_MAX_SRC], inv_hat_dq[CONV_MAX_SRC];   // q_m, inv_hat_m, inv_hat_m / q_m as doubles
     ConvTarget t[CONV_MAX_DST];
+    // ModDown and rescale in one (ks_drop): one more source, the limb x of row `row` under q_level, enters as
+    // (x - sum_m y_m hat_m) P^-1 mod q_level with the weight P
+    struct {
+        int row;
+        ConvTarget t;             // the conversion to q_level
+        u64 pinv, pinv_sh;        // P^{-1} mod q_level
+    } fold;
 };
 
 // per-kernel-family timing with HIP events on the launching stream (off unless enabled)

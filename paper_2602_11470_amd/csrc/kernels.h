@@ -51,6 +51,9 @@ struct IpItem {
 };
 struct IpBatch {
     int nz = 0, nsum = 1;
+    // the special limbs of the nsum items are not summed but stored one item after the other: out[z] and extra[z] are
+    // [2][level + 1 + nsum K][n]
+    bool apart = false;
     IpItem it[IP_MAX_ITEMS];
     u64 *out[IP_MAX_ITEMS] = {};
     const u64 *extra[IP_MAX_ITEMS] = {};      // nullable; the kernels test it, so it must never be left unset
@@ -115,6 +118,10 @@ struct FinishBatch {
     unsigned g[CM_MASK_BATCH];
     const u64 *addend[CM_MASK_BATCH];   // [2][level+1][n] per item, nullable; must not alias any out
     const u64 *pinv = nullptr;        // [level+1][2]: P^{-1} mod q_l and its Shoup companion
+    // ModDown and rescale in one (ks_drop): pinv holds (P q_{level+1})^-1, addend and accum are multiplied by ainv = q_{level+1}^-1
+    // (same layout) and have in_rows limbs a component (0: level + 1, like out)
+    const u64 *ainv = nullptr;
+    int in_rows = 0;
     // u_r is not stored but formed on the fly as u[r] * (mul_pt read through the Galois map mul_g[r]): the masked
     // products of a cache append, whose rescale is this tail (mul_pt[ext][n], multiplier form; nullable)
     const u64 *mul_pt = nullptr;
@@ -136,6 +143,17 @@ struct ConvBatch {
     size_t in_stride = 0, out_stride = 0, own_stride = 0;
     const u64 *own_src = nullptr;
     unsigned own_g = 0;
+    bool fold = false;                // the tables' folded limb is a source (ConvDev)
+};
+// What joins the folded limbs of a ks_drop on their way into the inverse transform: of every `per` consecutive limbs of the
+// launch (one component) the first becomes u + P (sigma_g(add) + acc).  Row of component c of item z in add, acc: z*stride +
+// (c*rows + rows - 1)*n; add on the first add_comps components only.
+struct FoldIn {
+    int per = 0, rows = 0, add_comps = 0;          // per = 0: nothing joins
+    unsigned g = 0;
+    const u64 *add = nullptr, *acc = nullptr;
+    size_t add_stride = 0, acc_stride = 0;
+    u64 pm = 0, q = 0, qinv = 0;                   // P mod q_level in multiplier form, q_level
 };
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb = nullptr);
@@ -205,6 +223,20 @@ cm_status ks_apply_many_raised(cm_ctx *ctx, const u64 *digits, int level, int cn
 cm_status rescale_into(cm_ctx *ctx, const u64 *in, int ncomp, int level, u64 *out, hipStream_t st, u64 *last = nullptr,
                        u64 *red = nullptr, bool accumulate = false);
 u64 *arena_digits(const cm_ctx *ctx);
+size_t arena_digits_words(const cm_ctx *ctx);
+// ModDown and rescale in one: out[r][2][level][n] = rescale(sum_s ModDown(u_r,s) + perm_g(add_r) + acc_r) for r < m stacked sums
+// us + r*2*ext'*n, ext' = level + 1 + sets*K, whose special limbs of s = 0 .. sets-1 follow each other and whose ciphertext limbs
+// are summed over s; add_r = add + r*add_stride (on the first add_comps components), acc_r = acc + r*acc_stride ([2][level+1][n],
+// nullable).  One forward transform per output limb instead of two, and four launches fewer than one after the other.  Rows
+// level .. of us are overwritten.  ks_drop_fits: whether the kernels cover this level and count (otherwise: two steps).
+bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m);
+cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *add, size_t add_stride, int add_comps, u64 g,
+                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st);
+// out[2][level][n] = rescale(ModDown(u[2][ext][n])), in one where ks_drop_fits, through tmp[2][level+1][n] otherwise
+cm_status moddown_rescale_into(cm_ctx *ctx, u64 *u, int level, u64 *tmp, u64 *out, hipStream_t st);
+// out[2][level][n] = rescale(Rot(in) + accum) (+ extra as rotate_into), likewise
+cm_status rotate_rescale_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64 g, u64 *tmp, u64 *out, hipStream_t st,
+                              const u64 *accum = nullptr, const u64 *extra = nullptr);
 // room for CM_KS_BATCH key-switch sums [2][L+1+K][n] (what moddown_batch_into consumes)
 u64 *arena_batch_sums(const cm_ctx *ctx);
 cm_status ks_apply_many(cm_ctx *ctx, const u64 *digits, int level, int cnt, const u64 *const *keys, const u64 *gs,
@@ -214,5 +246,5 @@ const u64 *find_key(const cm_evk *evk, u64 g);
 bool evk_fits(const cm_ctx *ctx, const cm_evk *evk);
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mods, int limbs, bool inverse, hipStream_t st);
 void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, const int *d_src_rows,
-                    const int *d_mods, int limbs, bool inverse, hipStream_t st, u64 g = 0);
+                    const int *d_mods, int limbs, bool inverse, hipStream_t st, u64 g = 0, const FoldIn &fi = FoldIn());
 void decode_host(const cm_ctx *ctx, const std::vector<double> &m, double *re, double *im, size_t nslots);

@@ -471,11 +471,12 @@ __global__ __launch_bounds__(TPB) void k_inner_product_batch(IpBatch b, const Mo
     const int mi = r <= level ? r : L + 1 + (r - level - 1);
     const ModC m = modc[mi];
     const size_t o = (size_t)r * n + i2;
+    const int special = ext - level - 1, out_rows = b.apart ? ext + (b.nsum - 1) * special : ext;
     const u64 bound = ubound[mi], cg0 = ((u64)i2 + 1) * GOLD, cg1 = cg0 + GOLD;
     ulonglong2 r0 = make_ulonglong2(0, 0), r1 = make_ulonglong2(0, 0);
     if (b.extra[z]) {
         r0 = *reinterpret_cast<const ulonglong2 *>(b.extra[z] + o);
-        r1 = *reinterpret_cast<const ulonglong2 *>(b.extra[z] + (size_t)ext * n + o);
+        r1 = *reinterpret_cast<const ulonglong2 *>(b.extra[z] + (size_t)out_rows * n + o);
     }
     for (int s = 0; s < b.nsum; s++) {
         const IpItem it = b.it[z * b.nsum + s];
@@ -506,9 +507,16 @@ __global__ __launch_bounds__(TPB) void k_inner_product_batch(IpBatch b, const Mo
         }
         r0.x = addmod(r0.x, redc(b0, m.q, m.qinv), m.q), r0.y = addmod(r0.y, redc(b1, m.q, m.qinv), m.q);
         r1.x = addmod(r1.x, evk_a_reduce<SA>(a0, m), m.q), r1.y = addmod(r1.y, evk_a_reduce<SA>(a1, m), m.q);
+        if (b.apart && r > level) {          // this item's special limb by itself
+            u64 *dst = b.out[z] + (size_t)s * special * n + o;
+            *reinterpret_cast<ulonglong2 *>(dst) = r0;
+            *reinterpret_cast<ulonglong2 *>(dst + (size_t)out_rows * n) = r1;
+            r0 = r1 = make_ulonglong2(0, 0);
+        }
     }
+    if (b.apart && r > level) return;
     *reinterpret_cast<ulonglong2 *>(b.out[z] + o) = r0;
-    *reinterpret_cast<ulonglong2 *>(b.out[z] + (size_t)ext * n + o) = r1;
+    *reinterpret_cast<ulonglong2 *>(b.out[z] + (size_t)out_rows * n + o) = r1;
 }
 // The same key applied to nz digit arrays: a lane keeps its key words in registers and runs over the
 // arrays, so the key is read from HBM once per launch.  With g != 0 the digits (and the optional

@@ -491,10 +491,14 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
             adds[r] = TB + r * 3 * ln, outs[r] = PB + r * ctw;
         }
         launch_inner_product_shared_key(ctx, ip, kl.beta, lv, st);
-        CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st));
         // with shared rotations the sums of the key ciphertexts are kept (d_T) until all of them are there
         u64 *r0 = kv->shared > 1 ? kv->d_T + (size_t)c0 * ctw1 : RB0, *r1 = RB1;
-        CMCHK(rescale_into(ctx, PB, 2 * m, lv, r0, st, last, red));        // stacked: [m][2][lv+1] -> [m][2][lv]
+        if (ks_drop_fits(ctx, lv, 1, m)) {
+            CMCHK(ks_drop(ctx, bu, lv, 1, m, TB, 3 * ln, 2, 0, nullptr, 0, r0, st));
+        } else {
+            CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st));
+            CMCHK(rescale_into(ctx, PB, 2 * m, lv, r0, st, last, red));        // stacked: [m][2][lv+1] -> [m][2][lv]
+        }
         const size_t ublk1 = 2 * (size_t)kl1.ext * n, dblk1 = (size_t)kl1.beta * kl1.ext * n;
         if (kv->unrolled && !kv->dim_groups.empty()) {
             // sum over the E dims in the extended basis: R = (P c0, P c1); every run adds the hoisted rotations of R by
@@ -580,9 +584,10 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
             launch_inner_product_batch(ctx, b, kl1.beta, lv - 1, st);
             std::swap(cur, nxt);
         }
-        CMCHK(moddown_into(ctx, cur, lv - 1, nullptr, 0, 0, acc, nullptr, st));
+        CMCHK(moddown_rescale_into(ctx, cur, lv - 1, acc, out->dev, st));
+    } else {
+        CMCHK(rescale_into(ctx, acc, 2, lv - 1, out->dev, st));
     }
-    CMCHK(rescale_into(ctx, acc, 2, lv - 1, out->dev, st));
     out->level = lv - 2, out->ncomp = 2;
     out->scale = in->scale * kv->scale / (double)ctx->mod[lv];      // the mask scale cancels the second rescale
     RETURN_LAUNCH_STATUS();
@@ -694,8 +699,7 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
             launch_inner_product_batch(ctx, b, kl.beta, lv, st);
             std::swap(cur, nxt);
         }
-        CMCHK(moddown_into(ctx, cur, lv, nullptr, 0, 0, tmp, nullptr, st));
-        CMCHK(rescale_into(ctx, tmp, 2, lv, out->dev, st));
+        CMCHK(moddown_rescale_into(ctx, cur, lv, tmp, out->dev, st));
         out->level = lv - 1, out->ncomp = 2;
         out->scale = in->scale * kv->scale / (double)ctx->mod[lv];
         RETURN_LAUNCH_STATUS();
@@ -704,10 +708,11 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
     for (int g = kv->r_o - 2; g >= 0; g--) {
         u64 gg = rot_g(kv, kv->r_i * Ht);
         u64 *nxt = inner + (size_t)g * ctw;                      // inner_g + Rot(acc), written over inner_g
-        CMCHK(rotate_into(ctx, find_key(evk, gg), acc, lv, gg, nxt, st, nxt));
+        if (g == 0) CMCHK(rotate_rescale_into(ctx, find_key(evk, gg), acc, lv, gg, nxt, R, st, nxt));
+        else CMCHK(rotate_into(ctx, find_key(evk, gg), acc, lv, gg, nxt, st, nxt));
         acc = nxt;
     }
-    CMCHK(rescale_into(ctx, acc, 2, lv, R, st));
+    if (kv->r_o == 1) CMCHK(rescale_into(ctx, acc, 2, lv, R, st));
     for (int l = 0; l < ilog2(kv->t) && reduce; l++) {
         u64 g = rot_g(kv, 1 << l);
         CMCHK(rotate_into(ctx, find_key(evk, g), R, lv - 1, g, tmp, st, R));

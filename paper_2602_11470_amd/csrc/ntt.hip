@@ -129,6 +129,10 @@ struct IntArith {
     struct Tail {
         u64 pi, pis, qinv;
         __device__ __forceinline__ Tail(const IntArith &, const NttTables &t, int mi, u64 p, u64 ps) : pi(p), pis(ps), qinv(t.modc[mi].qinv) {}
+        // (u - conv) pinv + (a + c) ainv
+        __device__ __forceinline__ u64 drop(const IntArith &ar, u64 u, u64 conv, u64 a, u64 c, u64 ai, u64 ais) const {
+            return addmod(mul_shoup(submod(u, conv, ar.q), pi, pis, ar.q), mul_shoup(a + c, ai, ais, ar.q), ar.q);
+        }
         __device__ __forceinline__ u64 plain(const IntArith &ar, u64 u, u64 conv, bool has_a, u64 a, bool has_c, u64 c) const {
             u64 x = mul_shoup(submod(u, conv, ar.q), pi, pis, ar.q);
             if (has_a) x = addmod(x, a, ar.q);
@@ -219,6 +223,11 @@ struct FpArith {
             if (has_a) x += ar.from_rest(a);
             if (has_c) x += ar.from_rest(c);
             return ar.canon(x);
+        }
+        __device__ __forceinline__ u64 drop(const FpArith &ar, u64 u, u64 conv, u64 a, u64 c, u64 ai, u64) const {
+            const double w = (double)ai;
+            return ar.canon(ar.mulmod(ar.from_rest(u) - ar.from_mid(conv), pi, piq) +
+                            ar.mulmod(ar.from_rest(a) + ar.from_rest(c), w, w * ar.qinv));
         }
         __device__ __forceinline__ u64 masked(const FpArith &ar, u64 u, u64 pt, u64 conv, bool has_c, u64 c) const {
             const double a = ar.from_rest(pt);
@@ -455,10 +464,10 @@ __device__ __forceinline__ void finish_tail(AT at, const A &ar, const u64 *lds, 
     const int r = limb / per, c = fb.comp0 + (limb % per) / (fb.level + 1), l = limb % (fb.level + 1);
     const u64 pi = fb.pinv[2 * l], pis = fb.pinv[2 * l + 1];
     const unsigned pos0 = (unsigned)chunk * CH + threadIdx.x;
-    const size_t row = ((size_t)c * (fb.level + 1) + l) * n;
+    const size_t row = ((size_t)c * (fb.level + 1) + l) * n, in_row = fb.in_rows ? ((size_t)c * fb.in_rows + l) * n : row;
     const u64 *up = fb.u[r] + ((size_t)c * fb.ext + l) * n + pos0;
-    const u64 *ad = (fb.addend[r] && c < fb.addend_comps) ? fb.addend[r] + row : nullptr;
-    const u64 *ac = fb.accum[r] ? fb.accum[r] + row + pos0 : nullptr;
+    const u64 *ad = (fb.addend[r] && c < fb.addend_comps) ? fb.addend[r] + in_row : nullptr;
+    const u64 *ac = fb.accum[r] ? fb.accum[r] + in_row + pos0 : nullptr;
     u64 *op = fb.out[r] + row + pos0;
     const unsigned g = fb.g[r];
     const int logn = 31 - __clz(n);
@@ -504,10 +513,35 @@ __device__ __forceinline__ void finish_tail(AT at, const A &ar, const u64 *lds, 
 #pragma unroll
         for (int k = 0; k < NW; k++) cc[k] = ac[LANES * k];
     }
+    if (fb.ainv && (ad || ac)) {
+        const u64 ai = fb.ainv[2 * l], ais = fb.ainv[2 * l + 1];
+#pragma unroll
+        for (int k = 0; k < NW; k++)
+            op[LANES * k] = tl.drop(ar, uu[k], lds[at(threadIdx.x + LANES * k)], ad ? aa[k] : 0, ac ? cc[k] : 0, ai, ais);
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < NW; k++) {
         const u64 x = tl.plain(ar, uu[k], lds[at(threadIdx.x + LANES * k)], ad != nullptr, aa[k], ac != nullptr, cc[k]);
         op[LANES * k] = x;
+    }
+}
+
+// the words of limb `limb` (positions pos(k)) that a FoldIn turns into u + P (sigma_g(add) + acc)
+template <int NW, class P>
+__device__ __forceinline__ void fold_in(const FoldIn &fi, int limb, int n, int logn, u64 (&w)[NW], P pos) {
+    if (!fi.per || limb % fi.per) return;
+    const int c = limb / fi.per & 1, z = limb / (2 * fi.per);
+    const size_t row = ((size_t)c * fi.rows + fi.rows - 1) * n;
+    if (fi.add && c < fi.add_comps) {
+        const u64 *a = fi.add + z * fi.add_stride + row;
+#pragma unroll
+        for (int k = 0; k < NW; k++) w[k] = addmod(w[k], redc((u128)a[fi.g ? perm_src(pos(k), fi.g, logn) : pos(k)] * fi.pm, fi.q, fi.qinv), fi.q);
+    }
+    if (fi.acc) {
+        const u64 *a = fi.acc + z * fi.acc_stride + row;
+#pragma unroll
+        for (int k = 0; k < NW; k++) w[k] = addmod(w[k], redc((u128)a[pos(k)] * fi.pm, fi.q, fi.qinv), fi.q);
     }
 }
 
@@ -554,7 +588,7 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
 }
 template <class A>
 __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
-                                                 const NttTables &t, int mi, int n, int chunk) {
+                                                 const NttTables &t, int mi, int n, int chunk, int limb, const FoldIn &fi) {
     A ar;
     ar.init(t, mi, n);
     const int sub = threadIdx.x & 15, blk = threadIdx.x >> 4;
@@ -576,6 +610,7 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
 #pragma unroll
             for (int k = 0; k < 16; k++) w[k] = ps[threadIdx.x + 256 * k];
         }
+        fold_in(fi, limb, n, logn, w, [&](int k) { return pos0 + 256 * k; });
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[pad(threadIdx.x + 256 * k)] = w[k];
         __syncthreads();
@@ -613,7 +648,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
                                                               const int *__restrict__ src_rows,
                                                               const int *__restrict__ rows,
                                                               const int *__restrict__ mod_idx, NttTables t, int n,
-                                                              unsigned g) {
+                                                              unsigned g, FoldIn fi) {
     __shared__ u64 lds[LDS_WORDS];
     const int per = n >> 12;
     const int limb = blockIdx.x / per, chunk = blockIdx.x % per;
@@ -622,9 +657,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
     const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - (size_t)chunk * 4096;
     const u64 *ps = psrow + (size_t)chunk * 4096;
     if (t.fpq[mi].q != 0.0)
-        rows256_inv_body<FpArith>(lds, p, ps, psrow, g, t, mi, n, chunk);
+        rows256_inv_body<FpArith>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
     else
-        rows256_inv_body<IntArith>(lds, p, ps, psrow, g, t, mi, n, chunk);
+        rows256_inv_body<IntArith>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
 }
 
 // ---- passes of a few limbs (n = 65536): four words a lane --------------------------------------------------------------
@@ -762,7 +797,7 @@ __device__ __forceinline__ void small_rows_fwd_body(u64 *lds, u64 *p, const NttT
 }
 template <class A>
 __device__ __forceinline__ void small_rows_inv_body(u64 *lds, u64 *p, const u64 *psrow, unsigned g, const NttTables &t, int mi, int n,
-                                                    int chunk) {
+                                                    int chunk, int limb, const FoldIn &fi) {
     A ar;
     ar.init(t, mi, n);
     const int sub = threadIdx.x & 63, row = threadIdx.x >> 6, logn = 31 - __clz(n);
@@ -771,6 +806,7 @@ __device__ __forceinline__ void small_rows_inv_body(u64 *lds, u64 *p, const u64 
     typename A::T v[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) raw[k] = psrow[g ? perm_src(pos0 + k, g, logn) : pos0 + k];
+    fold_in(fi, limb, n, logn, raw, [&](int k) { return pos0 + k; });
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_rest(raw[k]);
     small_inv(lds, v, ar, 256 + 8 * chunk + row, sub, SmallRow{row * 256}, WaveSync());
@@ -807,13 +843,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_fwd(u64 *__restrict_
 }
 __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict__ data, const u64 *__restrict__ src,
                                                                const int *__restrict__ src_rows, const int *__restrict__ rows,
-                                                               const int *__restrict__ mod_idx, NttTables t, int n, unsigned g) {
+                                                               const int *__restrict__ mod_idx, NttTables t, int n, unsigned g, FoldIn fi) {
     __shared__ u64 lds[SMALL_CHUNK + SMALL_CHUNK / 16];
     const int per = n / SMALL_CHUNK, limb = blockIdx.x / per, chunk = blockIdx.x % per, mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + (size_t)chunk * SMALL_CHUNK;
     const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - (size_t)chunk * SMALL_CHUNK;
-    if (t.fpq[mi].q != 0.0) small_rows_inv_body<FpArith>(lds, p, psrow, g, t, mi, n, chunk);
-    else small_rows_inv_body<IntArith>(lds, p, psrow, g, t, mi, n, chunk);
+    if (t.fpq[mi].q != 0.0) small_rows_inv_body<FpArith>(lds, p, psrow, g, t, mi, n, chunk, limb, fi);
+    else small_rows_inv_body<IntArith>(lds, p, psrow, g, t, mi, n, chunk, limb, fi);
 }
 
 // ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
@@ -875,7 +911,8 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
     for (int k = 0; k < 8; k++) p[tid + 512 * k] = lds[pad8(tid + 512 * k)];
 }
 template <class A>
-__device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n) {
+__device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n, int limb,
+                                              const FoldIn &fi) {
     A ar;
     ar.init(t, mi, n);
     const int tid = threadIdx.x, h2 = tid >> 6, l2 = tid & 63, h3 = tid >> 3, l3 = tid & 7;
@@ -885,6 +922,7 @@ __device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, u
         u64 w[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) w[k] = ps[g ? perm_src((unsigned)(tid + 512 * k), g, logn) : tid + 512 * k];
+        fold_in(fi, limb, n, logn, w, [&](int k) { return (unsigned)(tid + 512 * k); });
 #pragma unroll
         for (int k = 0; k < 8; k++) lds[pad8(tid + 512 * k)] = w[k];
         const Tw<A, 3> tw(ar, 512 + tid);
@@ -952,15 +990,15 @@ __global__ __launch_bounds__(FULL_THREADS) void ntt_full_fwd(u64 *data, const u6
 }
 __global__ __launch_bounds__(FULL_THREADS) void ntt_full_inv(u64 *data, const u64 *src, const int *__restrict__ src_rows,
                                                             const int *__restrict__ rows, const int *__restrict__ mod_idx,
-                                                            NttTables t, int n, unsigned g) {
+                                                            NttTables t, int n, unsigned g, FoldIn fi) {
     __shared__ u64 lds[FULL_LDS];
     const int limb = blockIdx.x, mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p;
     if (t.fpq[mi].q != 0.0)
-        full_inv_body<FpArith>(lds, p, ps, g, t, mi, n);
+        full_inv_body<FpArith>(lds, p, ps, g, t, mi, n, limb, fi);
     else
-        full_inv_body<IntArith>(lds, p, ps, g, t, mi, n);
+        full_inv_body<IntArith>(lds, p, ps, g, t, mi, n, limb, fi);
 }
 
 // ---- fast base conversion, fused into the first pass of the forward transform of its results --------------------------
@@ -986,9 +1024,10 @@ struct ConvArgs {
 // halves against 25 + 25 bits of the weight, again without carry chains.  Otherwise 128-bit sums.
 // The integer sums are worked on one word after the other (sched_barrier): interleaving them costs more registers than a
 // wave has to spare.
-template <int NS, int NV>
+// FOLD: one more source, the folded last limb (ConvDev::fold).
+template <int NS, int NV, bool FOLD>
 struct ConvY {
-    unsigned lo[NV][NS], hi[NV][NS];
+    unsigned lo[NV][NS], hi[NV][NS], flo[NV], fhi[NV];
     __device__ __forceinline__ void set(const ConvDev &t, const u64 (&x)[NV][NS]) {
         if (t.split == CONV_SPLIT_25) {
 #pragma unroll
@@ -1015,6 +1054,20 @@ struct ConvY {
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    // x: the words of the folded limb, below q_level (itself below 2^50 where the sources are)
+    __device__ __forceinline__ void fold(const ConvDev &t, const u64 (&x)[NV]) {
+        u64 c[NV];
+        const u64 q = t.fold.t.q;
+        target<false>(t.split, t.fold.t, c);
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const u64 y = mul_shoup(submod(x[k], c[k], q), t.fold.pinv, t.fold.pinv_sh, q);
+            const double d = __longlong_as_double((long long)(y | 0x4330000000000000ULL)) - TWO52;
+            flo[k] = t.split == CONV_SPLIT_25 ? (unsigned)__double2loint(d) : (unsigned)y;
+            fhi[k] = t.split == CONV_SPLIT_25 ? (unsigned)__double2hiint(d) : (unsigned)(y >> 32);
+        }
+    }
+    __device__ __forceinline__ double fd(int k) const { return __hiloint2double((int)fhi[k], (int)flo[k]); }
     __device__ __forceinline__ double yd(int k, int m) const { return __hiloint2double((int)hi[k][m], (int)lo[k][m]); }
     // keep what is derived from the words (64-bit pairs of their halves) from being hoisted out of a loop over the targets
     __device__ __forceinline__ void opaque() {
@@ -1025,10 +1078,17 @@ struct ConvY {
                 OPAQUE(lo[k][m]);
                 OPAQUE(hi[k][m]);
             }
+        if (FOLD) {
+#pragma unroll
+            for (int k = 0; k < NV; k++) {
+                OPAQUE(flo[k]);
+                OPAQUE(fhi[k]);
+            }
+        }
     }
     // targets below 2^50: |v| <= q, all that the forward stages ask (0.6 q where several sources are summed and reduced, 0.88 q
-    // for one).  |y w - c q| <= 0.88 q per term (c off by three roundings of a value below 2^50), so the sum of eight terms
-    // stays below 2^53 and exact.
+    // for one).  |y w - c q| <= 0.88 q per term (c off by three roundings of a value below 2^50), so the sum of nine terms
+    // (the folded limb among them) stays below 2^53 and exact.
     __device__ __forceinline__ void target_fp(const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
         double w[NS], wq[NS];
 #pragma unroll
@@ -1038,7 +1098,8 @@ struct ConvY {
             double s = ar.mulmod(yd(k, 0), w[0], wq[0]);
 #pragma unroll
             for (int m = 1; m < NS; m++) s += ar.mulmod(yd(k, m), w[m], wq[m]);
-            v[k] = NS > 1 ? ar.norm(s) : s;
+            if (FOLD) s += ar.mulmod(fd(k), o.wl, o.wl * ar.qinv);
+            v[k] = NS > 1 || FOLD ? ar.norm(s) : s;
         }
     }
     __device__ __forceinline__ void target_any(int split, const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
@@ -1051,6 +1112,7 @@ struct ConvY {
             for (int k = 0; k < NV; k++) v[k] = ar.from_rest(x[k]);
         }
     }
+    template <bool WITH = FOLD>
     __device__ __forceinline__ void target(int split, const ConvTarget &o, u64 (&out)[NV]) const {
         u64 w[NS];
         const u64 q = o.q, qinv = o.qinv;
@@ -1065,6 +1127,10 @@ struct ConvY {
                     const u64 y = (u64)__double_as_longlong(yd(k, m) + TWO52) & 0x000FFFFFFFFFFFFFULL;
                     acc.mac((unsigned)y & LOW25, (unsigned)(y >> 25), w[m]);
                 }
+                if (WITH) {
+                    const u64 y = (u64)__double_as_longlong(fd(k) + TWO52) & 0x000FFFFFFFFFFFFFULL;
+                    acc.mac((unsigned)y & LOW25, (unsigned)(y >> 25), o.wlm);
+                }
                 out[k] = redc(acc.total(), q, qinv);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1074,10 +1140,10 @@ struct ConvY {
             for (int k = 0; k < NV; k++) {
                 u64 t00 = 0, t01 = 0, t10 = 0, t11 = 0;
 #pragma unroll
-                for (int m = 0; m < NS; m++) {
-                    const u64 y = ((u64)hi[k][m] << 32) | lo[k][m];
+                for (int m = 0; m < NS + (WITH ? 1 : 0); m++) {
+                    const u64 y = m < NS ? ((u64)hi[k][m] << 32) | lo[k][m] : ((u64)fhi[k] << 32) | flo[k], wm = m < NS ? w[m] : o.wlm;
                     const unsigned y0 = (unsigned)y & LOW30, y1 = (unsigned)(y >> 30);
-                    const unsigned w0 = (unsigned)w[m] & LOW25, w1 = (unsigned)(w[m] >> 25);
+                    const unsigned w0 = (unsigned)wm & LOW25, w1 = (unsigned)(wm >> 25);
                     t00 += (u64)y0 * w0, t01 += (u64)y0 * w1, t10 += (u64)y1 * w0, t11 += (u64)y1 * w1;
                 }
                 out[k] = redc((u128)t00 + ((u128)t01 << 25) + ((u128)t10 << 30) + ((u128)t11 << 55), q, qinv);
@@ -1089,6 +1155,7 @@ struct ConvY {
                 u128 T = 0;
 #pragma unroll
                 for (int m = 0; m < NS; m++) T += (u128)(((u64)hi[k][m] << 32) | lo[k][m]) * w[m];
+                if (WITH) T += (u128)(((u64)fhi[k] << 32) | flo[k]) * o.wlm;
                 out[k] = redc(T, q, qinv);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1154,8 +1221,8 @@ __device__ __forceinline__ void ccf_body(u64 *lds, int buf, int large, u64 *p, t
     for (int k = 0; k < 4; k++) ntt_store(large, word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
 }
 // grid: x = column tile, y = target group (the last targets, those under the 60-bit primes, first), then the copies
-template <int NS>
-__global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a,
+template <int NS, bool FOLD>
+__global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a,
                                                                NttTables t, int n, int logn) {
     __shared__ u64 lds[2 * 256 * CCF_W];
     const ConvDev &tab = a.tabs[(blockIdx.z % a.tab_period) * a.tab_step];
@@ -1178,16 +1245,22 @@ __global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict_
     if (r0 >= nt) return;
     const int c = threadIdx.x % CCF_W, sub = threadIdx.x / CCF_W;
     in += (blockIdx.z / a.in_group) * a.in_stride + tile * CCF_W;
-    ConvY<NS, 4> y;
+    ConvY<NS, 4, FOLD> y;
     {
-        u64 x[4][NS];
+        u64 x[4][NS], xf[4];
 #pragma unroll
         for (int m = 0; m < NS; m++) {
             const u64 *row = in + (size_t)tab.in_rows[m] * n;
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k][m] = *word_at(row, (k * 64 + sub) * n2 + c);
         }
+        if (FOLD) {
+            const u64 *row = in + (size_t)tab.fold.row * n;
+#pragma unroll
+            for (int k = 0; k < 4; k++) xf[k] = *word_at(row, (k * 64 + sub) * n2 + c);
+        }
         y.set(tab, x);
+        if (FOLD) y.fold(tab, xf);
     }
     unsigned tid = threadIdx.x;
     int buf = 0;
@@ -1212,7 +1285,7 @@ __global__ __launch_bounds__(CCF_THREADS, 4) void conv_cols_fwd(u64 *__restrict_
     }
 }
 // n = 4096: one workgroup per target limb, conversion and the whole transform.  grid: x = target, then the own rows; y = item
-template <int NS, bool TAIL>
+template <int NS, bool TAIL, bool FOLD>
 __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a, NttTables t,
                                                              int n, int logn, FinishBatch fb) {
     __shared__ u64 lds[FULL_LDS];
@@ -1232,14 +1305,19 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
         return;
     }
     in += (z / a.in_group) * a.in_stride;
-    ConvY<NS, 8> y;
+    ConvY<NS, 8, FOLD> y;
     {
-        u64 x[8][NS];
+        u64 x[8][NS], xf[8];
 #pragma unroll
         for (int m = 0; m < NS; m++)
 #pragma unroll
             for (int k = 0; k < 8; k++) x[k][m] = in[(size_t)tab.in_rows[m] * n + tid + 512 * k];
+        if (FOLD) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) xf[k] = in[(size_t)tab.fold.row * n + tid + 512 * k];
+        }
         y.set(tab, x);
+        if (FOLD) y.fold(tab, xf);
     }
     const ConvTarget &o = tab.t[r];
     const int limb = z * nt + r;                          // of the tail: item, component, limb
@@ -1292,7 +1370,7 @@ static void launch_rows_fwd(u64 *data, const int *d_rows, const int *d_mods, con
 // With g != 0 (inverse, out of place only) the source is read through the Galois permutation, i.e.
 // the result is the coefficient form of the mapped polynomial.
 void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, const int *d_src_rows,
-                    const int *d_mod_idx, int limbs, bool inverse, hipStream_t st, u64 g) {
+                    const int *d_mod_idx, int limbs, bool inverse, hipStream_t st, u64 g, const FoldIn &fi) {
     if (limbs <= 0) return;
     if (g && (!inverse || !src || src == data)) g = 0;
     Prof prof_(ctx, inverse ? CM_K_NTT_INV : CM_K_NTT_FWD, limbs, st);
@@ -1308,13 +1386,13 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
     } else if (n2 == 256) {
         if (limbs <= SMALL_ROWS)
             hipLaunchKernelGGL(small_rows_inv, dim3(limbs * (n / SMALL_CHUNK)), dim3(SMALL_THREADS), 0, st, data, src, d_src_rows, d_rows,
-                               d_mod_idx, t, n, (unsigned)g);
-        else hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
+                               d_mod_idx, t, n, (unsigned)g, fi);
+        else hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g, fi);
         if (limbs <= SMALL_COLS)
             hipLaunchKernelGGL(small_cols_inv, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, d_rows, d_mod_idx, t, n);
         else hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
     } else {
-        hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g);
+        hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g, fi);
     }
 }
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st, const u64 *src,
@@ -1343,8 +1421,9 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     if (n == 4096) {
         const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
 #define FULL_LAUNCH(NS_)                                                                                                         \
-    if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb);        \
-    else hipLaunchKernelGGL((conv_full_fwd<NS_, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
+    if (b.fold) hipLaunchKernelGGL((conv_full_fwd<NS_, true, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
+    else if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
+    else hipLaunchKernelGGL((conv_full_fwd<NS_, false, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
         // the instantiation for eight spills 31 of 256 registers and still takes less than conversion and transform in two launches
         // (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us; five sources 66 -> 56
         if (ns <= 1) { FULL_LAUNCH(1); }
@@ -1362,7 +1441,11 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
     // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
     // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
-#define CCF_LAUNCH(NS_) hipLaunchKernelGGL((conv_cols_fwd<NS_>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn)
+#define CCF_LAUNCH(NS_)                                                                                                          \
+    do {                                                                                                                         \
+        if (b.fold) hipLaunchKernelGGL((conv_cols_fwd<NS_, true>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);   \
+        else hipLaunchKernelGGL((conv_cols_fwd<NS_, false>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);         \
+    } while (0)
     if (ns <= 1) CCF_LAUNCH(1);
     else if (ns <= 2) CCF_LAUNCH(2);
     else if (ns <= 4) CCF_LAUNCH(4);

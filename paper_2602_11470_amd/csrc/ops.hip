@@ -68,6 +68,11 @@ struct KsLevelFull : KsLevel {
     ConvDev *d_moddown0 = nullptr;                      // the ModDown conversion reading its K input limbs from rows 0..K-1
     int *d_bq_mods = nullptr;                           // 0..level repeated 2*CM_KS_BATCH times
     std::vector<int> h_ntt_rows, h_ntt_mods;            // host copies of d_ntt_rows / d_ntt_mods
+    // ks_drop with one and with two sets of special limbs: tables, rows (the last limb and the special ones of every component of
+    // up to CM_KS_BATCH sums, of one with two sets) with their moduli, (P q_level)^-1 mod q_i with companions
+    ConvDev *d_drop[2] = {nullptr, nullptr};
+    int *d_drop_rows[2] = {nullptr, nullptr}, *d_drop_mods[2] = {nullptr, nullptr};
+    u64 *d_pqinv = nullptr;
     ConvDev *d_modup = nullptr; // one table per digit
     ConvDev *d_moddown = nullptr;
     int modup_max_nt = 0;
@@ -98,10 +103,36 @@ static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector
     d.split = smax < (1ULL << 50) ? CONV_SPLIT_25 : smax < (1ULL << 60) && tmax < (1ULL << 50) ? CONV_SPLIT_30 : CONV_SPLIT_NONE;
     return d;
 }
+// the conversion of a ks_drop: `sets` times the special limbs (rows level + 1 ..), the folded limb in row `level`, targets q_0 .. q_{level-1}
+static ConvDev drop_dev(cm_ctx *ctx, int level, int sets) {
+    const ConvTable &t = get_moddown(ctx, level);
+    const int K = t.ns;
+    ConvTable w;
+    w.ns = sets * K, w.nt = level + 1, w.dst = t.dst;
+    std::vector<int> in_rows, out_rows;
+    for (int m = 0; m < w.ns; m++) {
+        w.src.push_back(t.src[m % K]), w.inv_hat.push_back(t.inv_hat[m % K]), w.inv_hat_sh.push_back(t.inv_hat_sh[m % K]);
+        in_rows.push_back(level + 1 + m);
+        for (int r = 0; r <= level; r++) w.hat.push_back(t.hat[(size_t)(m % K) * t.nt + r]), w.hat_mont.push_back(t.hat_mont[(size_t)(m % K) * t.nt + r]);
+    }
+    for (int r = 0; r <= level; r++) out_rows.push_back(r);
+    ConvDev d = conv_dev(ctx, w, in_rows, out_rows);
+    for (int r = 0; r <= level; r++) {
+        const u64 q = ctx->mod[r];
+        u64 P = 1;
+        for (int k = 0; k < ctx->K; k++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + k] % q, q);
+        d.t[r].wl = (double)P, d.t[r].wlm = h_mulmod(P, (u64)(((u128)1 << 64) % q), q);
+        if (r == level) d.fold.pinv = h_invmod(P, q), d.fold.pinv_sh = h_shoup(d.fold.pinv, q);
+    }
+    d.fold.row = level, d.fold.t = d.t[level], d.nt = level;
+    return d;
+}
 static std::map<std::pair<cm_ctx *, int>, KsLevelFull> g_ks;
 
 static void free_ks(KsLevelFull &k) {
     hipFree(k.d_modup); hipFree(k.d_moddown); hipFree(k.d_bsp_rows); hipFree(k.d_bsp1_rows); hipFree(k.d_sp1_rows); hipFree(k.d_moddown0); hipFree(k.d_bsp_mods); hipFree(k.d_bq_mods);
+    for (int i = 0; i < 2; i++) hipFree(k.d_drop[i]), hipFree(k.d_drop_rows[i]), hipFree(k.d_drop_mods[i]);
+    hipFree(k.d_pqinv);
     hipFree(k.d_last_rows);
     hipFree(k.d_ntt_rows); hipFree(k.d_ntt_mods); hipFree(k.d_sp_rows); hipFree(k.d_sp_mods);
     hipFree(k.d_q_rows); hipFree(k.d_q_mods3); hipFree(k.d_last_mods); hipFree(k.d_red_mods); hipFree(k.d_red_src);
@@ -215,6 +246,25 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
         k.d_moddown0 = up(md0);
         k.d_sp1_rows = up(sp1);
     }
+    for (int sets = 1; sets <= 2; sets++) {
+        if (!ks_drop_fits(ctx, level, sets, 1)) continue;
+        std::vector<ConvDev> dd(1, drop_dev(ctx, level, sets));
+        std::vector<int> rows, mods;
+        for (int c = 0; c < (sets == 1 ? 2 * CM_KS_BATCH : 2); c++)
+            for (int j = 0; j <= sets * ctx->K; j++) {
+                rows.push_back(c * (level + 1 + sets * ctx->K) + level + j);
+                mods.push_back(j ? ctx->L + 1 + (j - 1) % ctx->K : level);
+            }
+        k.d_drop[sets - 1] = up(dd), k.d_drop_rows[sets - 1] = up(rows), k.d_drop_mods[sets - 1] = up(mods);
+    }
+    std::vector<u64> pq;
+    for (int i = 0; i < level; i++) {
+        const u64 q = ctx->mod[i];
+        u64 P = ctx->mod[level] % q;
+        for (int m = 0; m < ctx->K; m++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + m] % q, q);
+        pq.push_back(h_invmod(P, q)), pq.push_back(h_shoup(pq.back(), q));
+    }
+    k.d_pqinv = up(pq);
     get_pinv(ctx, level);
     get_qlinv(ctx, level);
 }
@@ -281,6 +331,60 @@ cm_status ks_apply(cm_ctx *ctx, const u64 *digits, const u64 *evk, int level, u6
     launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, digits, evk, k.beta, level, g, st);
     return moddown_into(ctx, A.u, level, addend, addend_comps, g, out, accum, st);
 }
+// A ModDown with a rescale behind it transforms every limb that stays twice, and the two are linear modulo each of those limbs:
+// with x = ModDown's limb under q_level, in coefficients, both are (u - NTT(conv + P x)) (P q_level)^-1, and x comes out of
+// the same inverse transforms and the same conversion.  Bound like a ModDown (transforms; at the low levels its launches).
+// Measured: query times K at level 12 (125 relinearisations) 18350 -> 17060 us, q / k / v at level 13 3310 -> 3280, 4096 x 4096 at
+// level 4 1148 -> 1137, grouped-query attention at level 9 14690 -> 14095; with the rotary embedding's two rotations and rescale
+// in one (two sets) that takes 83 us at level 3 instead of 134.
+// The product forms of the conversion hold one more term below 2^50 (or below 2^60, split in 30 bits) where the split ones
+// apply, and up to seven below 2^61 as 128-bit sums.  One set of seven or eight special primes stays with two steps: the folded
+// limb's registers come on top of an instantiation that spills.
+bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m) {
+    const int ns = sets * ctx->K;
+    if (level < 1 || m < 1 || ns > CONV_MAX_SRC || (sets == 1 ? m > CM_KS_BATCH || ns > 6 : m > 1)) return false;
+    u64 pmax = 0, qmax = 0;
+    for (int k = 0; k < ctx->K; k++) pmax = std::max(pmax, ctx->mod[ctx->L + 1 + k]);
+    for (int i = 0; i <= level; i++) qmax = std::max(qmax, ctx->mod[i]);
+    if (pmax < (1ULL << 50)) return ctx->mod[level] < (1ULL << 50);
+    return (pmax < (1ULL << 60) && qmax < (1ULL << 50)) || ns + 1 <= 7;
+}
+cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *add, size_t add_stride, int add_comps, u64 g,
+                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st) {
+    if (!ks_drop_fits(ctx, level, sets, m)) return CM_E_INVAL;
+    const KsLevelFull &k = ks_level_full(ctx, level);
+    Arena A = arena_of(ctx);
+    const size_t n = ctx->n;
+    const int ns = sets * ctx->K, ext = level + 1 + ns;
+    FoldIn fi;
+    if (add || acc) {
+        const ModC &mc = ctx->modc[level];
+        u64 P = 1;
+        for (int i = 0; i < ctx->K; i++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + i] % mc.q, mc.q);
+        fi.per = ns + 1, fi.rows = level + 1, fi.add_comps = add_comps, fi.g = (unsigned)g;
+        fi.add = add, fi.acc = acc, fi.add_stride = add_stride, fi.acc_stride = acc_stride;
+        fi.pm = h_mulmod(P, (u64)(((u128)1 << 64) % mc.q), mc.q), fi.q = mc.q, fi.qinv = mc.qinv;
+    }
+    launch_ntt_src(ctx, us, k.d_drop_rows[sets - 1], nullptr, nullptr, k.d_drop_mods[sets - 1], 2 * m * (ns + 1), true, st, 0, fi);
+    FinishBatch fb;
+    fb.items = m, fb.level = level - 1, fb.ext = ext, fb.addend_comps = add ? add_comps : 0, fb.in_rows = level + 1;
+    for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
+    for (int r = 0; r < m; r++) {
+        fb.u[r] = us + (size_t)r * 2 * ext * n, fb.out[r] = out + (size_t)r * 2 * level * n, fb.g[r] = (unsigned)g;
+        fb.addend[r] = add ? add + r * add_stride : nullptr, fb.accum[r] = acc ? acc + r * acc_stride : nullptr;
+    }
+    fb.pinv = k.d_pqinv, fb.ainv = get_qlinv(ctx, level);
+    ConvBatch cb;
+    cb.tabs = k.d_drop[sets - 1], cb.batch = 2 * m, cb.ns = ns, cb.max_nt = level, cb.fold = true;
+    cb.in_stride = (size_t)ext * n, cb.out_stride = (size_t)level * n;
+    launch_conv_ntt(ctx, cb, A.bconv, us, st, nullptr, k.d_red_mods, 2 * m * level, &fb);
+    return CM_OK;
+}
+cm_status moddown_rescale_into(cm_ctx *ctx, u64 *u, int level, u64 *tmp, u64 *out, hipStream_t st) {
+    if (ks_drop_fits(ctx, level, 1, 1)) return ks_drop(ctx, u, level, 1, 1, nullptr, 0, 0, 0, nullptr, 0, out, st);
+    CMCHK(moddown_into(ctx, u, level, nullptr, 0, 0, tmp, nullptr, st));
+    return rescale_into(ctx, tmp, 2, level, out, st);
+}
 // inverse of the odd g modulo the power of two 2n (Newton's iteration doubles the correct low bits)
 static unsigned galois_inverse(const cm_ctx *ctx, u64 g) {
     const u64 two_n = 2 * (u64)ctx->n;
@@ -318,6 +422,8 @@ cm_status ks_apply_many_raised(cm_ctx *ctx, const u64 *digits, int level, int cn
     return CM_OK;
 }
 u64 *arena_digits(const cm_ctx *ctx) { return arena_of(ctx).digits; }
+// words from there on that a call may use which needs neither u, conv nor the temporaries
+size_t arena_digits_words(const cm_ctx *ctx) { return arena_of(ctx).misc - arena_of(ctx).digits; }
 u64 *arena_batch_sums(const cm_ctx *ctx) { return arena_of(ctx).bu; }
 
 // ModDown of m <= CM_KS_BATCH stacked sums bu[r][2][ext][n] in one batch of launches:
@@ -1039,6 +1145,18 @@ cm_status rotate_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64
     const KsLevelFull &k = ks_level_full(ctx, level);
     launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
     return moddown_into(ctx, A.u, level, in, 1, g, out, accum, st);
+}
+cm_status rotate_rescale_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64 g, u64 *tmp, u64 *out, hipStream_t st,
+                              const u64 *accum, const u64 *extra) {
+    if (!ks_drop_fits(ctx, level, 1, 1)) {
+        CMCHK(rotate_into(ctx, key, in, level, g, tmp, st, accum, extra));
+        return rescale_into(ctx, tmp, 2, level, out, st);
+    }
+    Arena A = arena_of(ctx);
+    CMCHK(ks_raise(ctx, in + (size_t)(level + 1) * ctx->n, level, A.digits, st, g));
+    const KsLevelFull &k = ks_level_full(ctx, level);
+    launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
+    return ks_drop(ctx, A.u, level, 1, 1, in, 0, 1, g, accum, 0, out, st);
 }
 extern "C" cm_status cm_rotate(cm_ctx *ctx, const cm_evk *evk, const cm_ct *in, int32_t step, cm_ct *out, void *stream) {
     (void)hipGetLastError();          // stale errors of earlier calls are not this call's

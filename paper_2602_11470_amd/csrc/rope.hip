@@ -22,6 +22,7 @@ struct cm_rope {
     double base;
     u64 *d_pts = nullptr;      // [3][level+1][n], multiplier form
     u64 *d_work = nullptr;     // three ciphertexts
+    KsManyTables tabs;         // raise of the two rotated second components at once
 };
 
 static bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -36,6 +37,26 @@ __global__ void k_mul_pt3(u64 *out0, u64 *out1, u64 *out2, const u64 *__restrict
     out0[o] = redc((u128)v * pts[po], m.q, m.qinv);
     out1[o] = redc((u128)v * pts[ps + po], m.q, m.qinv);
     out2[o] = redc((u128)v * pts[2 * ps + po], m.q, m.qinv);
+}
+
+// The same products, the second and third already rotated (read through their Galois maps) and, of the first components,
+// summed: sum[2][limbs][n] = (a0 p0 + sigma_u(a0 p2) + sigma_d(a0 p1), a1 p0), rot[2][limbs][n] = sigma_u(a1 p2), sigma_d(a1 p1)
+__global__ void k_mul_pt3_rot(u64 *__restrict__ sum, u64 *__restrict__ rot, const u64 *__restrict__ a, const u64 *__restrict__ pts,
+                              const ModC *__restrict__ modc, int limbs, int n, int logn, unsigned gu, unsigned gd) {
+    const unsigned i = blockIdx.x * 256 + threadIdx.x, iu = perm_src(i, gu, logn), id = perm_src(i, gd, logn);
+    const int r = blockIdx.y, l = r % limbs;
+    const ModC m = modc[l];
+    const size_t row = (size_t)r * n, po = (size_t)l * n, ps = (size_t)limbs * n;
+    const u64 v = redc((u128)a[row + i] * pts[po + i], m.q, m.qinv);
+    const u64 u = redc((u128)a[row + iu] * pts[2 * ps + po + iu], m.q, m.qinv);
+    const u64 d = redc((u128)a[row + id] * pts[ps + po + id], m.q, m.qinv);
+    if (r < limbs) {
+        sum[row + i] = addmod(addmod(v, u, m.q), d, m.q);
+    } else {
+        sum[row + i] = v;
+        rot[po + i] = u;
+        rot[ps + po + i] = d;
+    }
 }
 
 extern "C" cm_status cm_rope_create(cm_ctx *ctx, int32_t heads, int32_t dim, int32_t level, int32_t token, int32_t tau,
@@ -54,6 +75,10 @@ extern "C" cm_status cm_rope_create(cm_ctx *ctx, int32_t heads, int32_t dim, int
     r->step_up = heads * t, r->step_dn = -(heads * t);
     const size_t n = ctx->n, ln = (size_t)(level + 1) * n;
     if (hipMalloc((void **)&r->d_pts, 3 * ln * 8) != hipSuccess || hipMalloc((void **)&r->d_work, 6 * ln * 8) != hipSuccess) {
+        cm_rope_destroy(r);
+        return CM_E_NOMEM;
+    }
+    if (ks_many_tables_create(ctx, level, 2, &r->tabs, 1, 0) != CM_OK) {
         cm_rope_destroy(r);
         return CM_E_NOMEM;
     }
@@ -105,6 +130,10 @@ extern "C" cm_status cm_inner_rot_create(cm_ctx *ctx, int32_t t, int32_t delta, 
         cm_rope_destroy(r);
         return CM_E_NOMEM;
     }
+    if (ks_many_tables_create(ctx, level, 2, &r->tabs, 1, 0) != CM_OK) {
+        cm_rope_destroy(r);
+        return CM_E_NOMEM;
+    }
     const double scale = (double)ctx->mod[level];
     std::vector<double> p[3];
     for (auto &v : p) v.assign(S, 0.0);
@@ -126,6 +155,7 @@ extern "C" cm_status cm_inner_rot_create(cm_ctx *ctx, int32_t t, int32_t delta, 
 }
 extern "C" void cm_rope_destroy(cm_rope *r) {
     if (!r) return;
+    ks_many_tables_destroy(&r->tabs);
     hipFree(r->d_pts);
     hipFree(r->d_work);
     delete r;
@@ -148,8 +178,28 @@ extern "C" cm_status cm_rope_apply(cm_ctx *ctx, const cm_evk *evk, const cm_rope
     const u64 g_up = galois_of_step(ctx, r->step_up), g_dn = galois_of_step(ctx, r->step_dn);
     const u64 *k_up = find_key(evk, g_up), *k_dn = find_key(evk, g_dn);
     if (!k_up || !k_dn) return CM_E_NOKEY;
-    const size_t ctw = 2 * (size_t)limbs * ctx->n;
+    const size_t n = ctx->n, ctw = 2 * (size_t)limbs * n;
     u64 *a = r->d_work, *b = a + ctw, *c = b + ctw;
+    const KsLevel &kl = ks_level(ctx, level);
+    const size_t dblk = (size_t)kl.beta * kl.ext * n;
+    if (ks_drop_fits(ctx, level, 2, 1) && 2 * dblk <= arena_digits_words(ctx)) {
+        // Both rotations and the rescale in one go, ten launches instead of twenty-three (each takes its 4 to 8 us at the low
+        // levels): products rotated as they are formed, one raise and one inner product for both, and since the two ModDowns
+        // and the rescale are sums of conversions, one forward transform for all of them (ks_drop with two sets).
+        u64 *digits = arena_digits(ctx);
+        hipLaunchKernelGGL(k_mul_pt3_rot, dim3(n / 256, 2 * limbs), dim3(256), 0, st, a, b, x->dev, r->d_pts, ctx->d_modc, limbs, (int)n,
+                           ctx->logn, (unsigned)g_up, (unsigned)g_dn);
+        CMCHK(ks_raise_many(ctx, r->tabs, b, c, digits, st));
+        IpBatch ip;
+        ip.nz = 1, ip.nsum = 2, ip.apart = true;
+        ip.it[0].dig = digits, ip.it[0].key = k_up, ip.it[1].dig = digits + dblk, ip.it[1].key = k_dn;
+        ip.out[0] = arena_batch_sums(ctx);
+        launch_inner_product_batch(ctx, ip, kl.beta, level, st);
+        CMCHK(ks_drop(ctx, ip.out[0], level, 2, 1, nullptr, 0, 0, 0, a, 0, y->dev, st));
+        y->level = level - 1, y->ncomp = 2;
+        y->scale = x->scale;                                      // plaintext scale = the prime just removed
+        RETURN_LAUNCH_STATUS();
+    }
     hipLaunchKernelGGL(k_mul_pt3, dim3(ctx->n / 256, 2 * limbs), dim3(256), 0, st, a, c, b, x->dev, r->d_pts, ctx->d_modc, limbs,
                        ctx->n);                                   // a = x p0, c = x p1, b = x p2
     CMCHK(rotate_into(ctx, k_up, b, level, g_up, a, st, a));      // a += Rot(x p2, step_up)

@@ -440,23 +440,29 @@ static cm_status vmm_raised_finish(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_
                 std::swap(total, nxt);
             }
         }
-        CMCHK(moddown_into(ctx, total, level, nullptr, 0, 0, acc, nullptr, st));
+        if (p->unrolled || p->reduce_steps.empty()) CMCHK(moddown_rescale_into(ctx, total, level, acc, y->dev, st));
+        else CMCHK(moddown_into(ctx, total, level, nullptr, 0, 0, acc, nullptr, st));
+    } else if (r_o == 1 && p->reduce_steps.empty()) {
+        CMCHK(moddown_rescale_into(ctx, inner, level, acc, y->dev, st));
     } else {
         // giant steps, Horner form: acc <- Rot(acc) + ModDown-ed inner_k in one key switch
         CMCHK(moddown_into(ctx, inner + (size_t)(r_o - 1) * rw, level, nullptr, 0, 0, acc, nullptr, st));
         for (int k = r_o - 2; k >= 0; k--) {
-            CMCHK(rotate_into(ctx, key_of(p->giant_step), acc, level, galois_of_step(ctx, p->giant_step), other, st,
-                              nullptr, inner + (size_t)k * rw));
+            const u64 g = galois_of_step(ctx, p->giant_step), *key = key_of(p->giant_step), *extra = inner + (size_t)k * rw;
+            if (k == 0 && p->reduce_steps.empty())
+                CMCHK(rotate_rescale_into(ctx, key, acc, level, g, other, y->dev, st, nullptr, extra));
+            else CMCHK(rotate_into(ctx, key, acc, level, g, other, st, nullptr, extra));
             std::swap(acc, other);
         }
     }
-    // 3. reduce inside the ciphertext
-    for (int r : p->reduce_steps) {
-        if (p->unrolled) break;                               // done above, before the ModDown
-        CMCHK(rotate_into(ctx, key_of(r), acc, level, galois_of_step(ctx, r), other, st, acc));
+    // 3. reduce inside the ciphertext (unrolled: done above, before the ModDown); the last rotation ends in the rescale
+    for (size_t i = 0; i < p->reduce_steps.size() && !p->unrolled; i++) {
+        const int r = p->reduce_steps[i];
+        const u64 g = galois_of_step(ctx, r);
+        if (i + 1 == p->reduce_steps.size()) CMCHK(rotate_rescale_into(ctx, key_of(r), acc, level, g, other, y->dev, st, acc));
+        else CMCHK(rotate_into(ctx, key_of(r), acc, level, g, other, st, acc));
         std::swap(acc, other);
     }
-    CMCHK(rescale_into(ctx, acc, 2, level, y->dev, st));
     y->level = level - 1, y->ncomp = 2;
     y->scale = x->scale * p->pt_scale / (double)ctx->mod[level];
     RETURN_LAUNCH_STATUS();
@@ -541,17 +547,22 @@ extern "C" cm_status cm_vmm_pt(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_plan
     //    giant steps, Horner form
     u64 *acc = inner + (size_t)(r_o - 1) * ctw;
     for (int k = r_o - 2; k >= 0; k--) {
+        const u64 g = galois_of_step(ctx, p->giant_step), *key = key_of(p->giant_step);
         u64 *nxt = inner + (size_t)k * ctw;                  // inner_k + Rot(acc), written over inner_k
-        CMCHK(rotate_into(ctx, key_of(p->giant_step), acc, level, galois_of_step(ctx, p->giant_step), nxt, st, nxt));
+        if (k == 0 && p->reduce_steps.empty()) CMCHK(rotate_rescale_into(ctx, key, acc, level, g, nxt, y->dev, st, nxt));
+        else CMCHK(rotate_into(ctx, key, acc, level, g, nxt, st, nxt));
         acc = nxt;
     }
-    // 3. reduce inside the ciphertext (two buffers again; baby slot 0 is free by now)
+    // 3. reduce inside the ciphertext (two buffers again; baby slot 0 is free by now); the last rotation ends in the rescale
     other = acc == babies ? tmp : babies;
-    for (int r : p->reduce_steps) {
-        CMCHK(rotate_into(ctx, key_of(r), acc, level, galois_of_step(ctx, r), other, st, acc));
+    for (size_t i = 0; i < p->reduce_steps.size(); i++) {
+        const int r = p->reduce_steps[i];
+        const u64 g = galois_of_step(ctx, r);
+        if (i + 1 == p->reduce_steps.size()) CMCHK(rotate_rescale_into(ctx, key_of(r), acc, level, g, other, y->dev, st, acc));
+        else CMCHK(rotate_into(ctx, key_of(r), acc, level, g, other, st, acc));
         std::swap(acc, other);
     }
-    CMCHK(rescale_into(ctx, acc, 2, level, y->dev, st));
+    if (r_o == 1 && p->reduce_steps.empty()) CMCHK(rescale_into(ctx, acc, 2, level, y->dev, st));
     y->level = level - 1, y->ncomp = 2;
     y->scale = x->scale * p->pt_scale / (double)ctx->mod[level];
     RETURN_LAUNCH_STATUS();
