@@ -2,6 +2,29 @@
 #pragma once
 #include "common.h"
 
+// The counter-based generator (its finaliser; the streams are defined with the samplers in kernels.hip).
+#define GOLD 0x9E3779B97F4A7C15ULL
+__host__ __device__ __forceinline__ u64 mix64(u64 z) {
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
+    return z ^ (z >> 31);
+}
+// An evaluation key in HBM is its b half only: b_j in multiplier form, [digit][nmod][n], followed by the [digit][nmod]
+// keys of the generator streams of a_j.  The uniform half is drawn directly in the evaluation domain, so word i of
+// limb mi of a_j is draw i of that stream (rejected at or above bound = q floor(2^64/q), then taken mod q): the inner
+// products regenerate it instead of reading it, which takes a third off their traffic.  The draw enters the sums as
+// the raw 64-bit word v (v = a mod q): sum_j d_j v_j < beta q 2^64 fits 128 bits, REDC gives (sum 2^-64) mod q below
+// (beta + 1) q, and a second REDC against 2^128 mod q gives sum mod q in [0, q) -- two reductions per output instead of
+// one per key word.  ctr_gold = (i + 1) GOLD is the counter term of attempt 0, shared by all digits of a lane.
+__device__ __forceinline__ u64 evk_a_draw(u64 stream_key, u64 ctr_gold, unsigned i, u64 bound) {
+    u64 v = mix64(stream_key + ctr_gold);
+    for (u64 att = 1; v >= bound; att++) v = mix64(stream_key + (((att << 32) | (u64)i) + 1) * GOLD);
+    return v;
+}
+__device__ __forceinline__ u64 redc_raw(u128 T, const ModC &m) {
+    return redc((u128)redc(T, m.q, m.qinv) * m.r2, m.q, m.qinv);
+}
+
 void launch_set_idx(int *d_dst, const int *h_src, int count, hipStream_t st);
 void launch_reduce_i64(cm_ctx *ctx, u64 *out, const long long *d_coeffs, const int *d_mod_idx, int limbs, hipStream_t st);
 void launch_to_mont(cm_ctx *ctx, u64 *data, const int *d_mod_idx, int limbs, hipStream_t st);
@@ -37,6 +60,16 @@ bool mask_ntt_supported(int E);
 void launch_mask_ntt_setup(cm_ctx *ctx, u64 *Mhat, const u64 *M, const u64 *tw, const u64 *einv, int E, int limbs, hipStream_t st);
 void launch_mask_ntt(cm_ctx *ctx, u64 *A, const u64 *T, const u64 *Mhat, const u64 *tw, const u64 *einv, int nk, int E, int shared,
                      int limbs, hipStream_t st);
+// What joins the folded limbs of a ks_drop on their way into the inverse transform: of every `per` consecutive limbs of the
+// launch (one component) the first becomes u + P (sigma_g(add) + acc).  Row of component c of item z in add, acc: z*stride +
+// (c*rows + rows - 1)*n; add on the first add_comps components only.
+struct FoldIn {
+    int per = 0, rows = 0, add_comps = 0;          // per = 0: nothing joins
+    unsigned g = 0;
+    const u64 *add = nullptr, *acc = nullptr;
+    size_t add_stride = 0, acc_stride = 0;
+    u64 pm = 0, q = 0, qinv = 0;                   // P mod q_level in multiplier form, q_level
+};
 // (u0, u1)[ext][n] = sum_j perm_g(dig_j) * evk_j  [+ P * perm_g(c0) on the ciphertext limbs of u0]  [+ extra[2][ext][n]]
 void launch_inner_product(cm_ctx *ctx, u64 *u0, u64 *u1, const u64 *dig, const u64 *evk, int beta, int level, u64 g,
                           hipStream_t st, const u64 *c0 = nullptr, const u64 *extra = nullptr);
@@ -46,6 +79,8 @@ void launch_inner_product(cm_ctx *ctx, u64 *u0, u64 *u1, const u64 *dig, const u
 #define IP_MAX_ITEMS 32
 struct IpItem {
     const u64 *dig = nullptr, *key = nullptr, *c0 = nullptr;
+    const u64 *own = nullptr;         // launch_rows_ip: [level+1][n], the raised polynomial itself, evaluation domain
+    unsigned own_g = 0;               //                 read through that Galois map (g = 0 then)
     unsigned g = 0;
     unsigned c0_ext = 0;      // c0 is already in the extended basis ([ext][n], all limbs): added as it is, no factor P
 };
@@ -59,6 +94,11 @@ struct IpBatch {
     const u64 *extra[IP_MAX_ITEMS] = {};      // nullable; the kernels test it, so it must never be left unset
 };
 void launch_inner_product_batch(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st);
+// The same sums from half-transformed digits (ConvBatch::half): the row pass of every digit, the inner products and, for the rows
+// from inv_from on (0: none), the row pass of the inverse transform in one launch (n = 65536, keys without stored halves:
+// rows_ip_fits).  What fi describes (one output a component pair, row `level`) joins before that.
+bool rows_ip_fits(const cm_ctx *ctx, int beta, int nsum);
+void launch_rows_ip(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st, int inv_from = 0, const FoldIn &fi = FoldIn());
 // na = 2 or 3 keys (Galois elements g[a] != 0) applied to the nz digit arrays b.it[z].dig and summed into out[z] together with
 // extra[z] and, per key, the first component b.it[z].c0 (extended basis) through that key's Galois map.  Returns false
 // (nothing launched) if the lane cannot hold the keys: more than 6 digits.
@@ -127,6 +167,7 @@ struct FinishBatch {
     const u64 *mul_pt = nullptr;
     unsigned mul_g[CM_MASK_BATCH] = {};
 };
+void launch_cols_inv(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs, hipStream_t st);
 // forward transform of conv[items*ncomp*(level+1)][n] (mods 0..level repeating) with that tail
 // with src: the first pass reads row d_src_rows[i] of src for limb i (words below twice that limb's modulus) instead of conv
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st,
@@ -144,16 +185,7 @@ struct ConvBatch {
     const u64 *own_src = nullptr;
     unsigned own_g = 0;
     bool fold = false;                // the tables' folded limb is a source (ConvDev)
-};
-// What joins the folded limbs of a ks_drop on their way into the inverse transform: of every `per` consecutive limbs of the
-// launch (one component) the first becomes u + P (sigma_g(add) + acc).  Row of component c of item z in add, acc: z*stride +
-// (c*rows + rows - 1)*n; add on the first add_comps components only.
-struct FoldIn {
-    int per = 0, rows = 0, add_comps = 0;          // per = 0: nothing joins
-    unsigned g = 0;
-    const u64 *add = nullptr, *acc = nullptr;
-    size_t add_stride = 0, acc_stride = 0;
-    u64 pm = 0, q = 0, qinv = 0;                   // P mod q_level in multiplier form, q_level
+    bool half = false;                // n = 65536: column pass only, own rows not copied (launch_rows_ip does the rest)
 };
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb = nullptr);
@@ -174,19 +206,21 @@ struct KsLevel {            // cached per level: which rows of the digit array a
 const KsLevel &ks_level(cm_ctx *ctx, int level);
 // digits[beta][ext][n] (evaluation domain) from evaluation-domain d[level+1][n]
 // with g != 0: digits of the Galois-mapped polynomial (d is read through the permutation)
-cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_t st, u64 g = 0);
-// (out0, out1) = ModDown(sum_j perm_g(digits_j) * evk_j) [+ perm_g(addend) on component 0]; out = [2][level+1][n]
-// addend_comps: 0 none, 1 component 0 only (rotation), 2 both (relinearisation)
-cm_status ks_apply(cm_ctx *ctx, const u64 *digits, const u64 *evk, int level, u64 g, const u64 *addend,
-                   int addend_comps, u64 *out, hipStream_t st, const u64 *accum = nullptr);
+// half: for launch_rows_ip
+cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_t st, u64 g = 0, bool half = false);
+// one key switch of d[level+1][n] (through the Galois map g if non-zero): raise, inner product, ModDown, with the addends of
+// moddown_into and `extra` ([2][ext][n]) joining the sum before the ModDown
+cm_status ks_one(cm_ctx *ctx, const u64 *d, const u64 *key, int level, u64 g, const u64 *addend, int addend_comps, u64 *out, hipStream_t st,
+                 const u64 *accum = nullptr, const u64 *extra = nullptr);
 // out = Rot(in) (+ accum); out may alias in or accum
 // extra: a [2][ext][n] sum in the extended basis that joins the key-switch sum before its ModDown
 cm_status rotate_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64 g, u64 *out, hipStream_t st,
                       const u64 *accum = nullptr, const u64 *extra = nullptr);
 // out[2][level+1][n] = ModDown(u[2][ext][n]) (+ perm_g(addend) on the first addend_comps components) (+ accum);
 // the special limbs of u are overwritten
+// rows_done: the row pass of the inverse transform of the special limbs has been done (launch_rows_ip)
 cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int addend_comps, u64 g, u64 *out,
-                       const u64 *accum, hipStream_t st);
+                       const u64 *accum, hipStream_t st, bool rows_done = false);
 // Tables for raising component `comp` of cnt stacked ciphertexts of ncomp components at one level in
 // single launches.
 struct KsManyTables {
@@ -199,7 +233,7 @@ void ks_many_tables_destroy(KsManyTables *t);
 // digits[k][beta][ext][n] (evaluation domain) of component t.comp of cts[k][t.ncomp][level+1][n] for k < m <= t.cnt
 // (through the Galois map g if g != 0); ksin: m*(level+1) limbs of scratch
 cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 *ksin, u64 *digits, hipStream_t st,
-                        int m = -1, u64 g = 0);
+                        int m = -1, u64 g = 0, bool half = false);
 // outs[r][2][level+1][n] = ModDown(us + r*2*ext*n) for r < cnt (any cnt; runs in batches); special limbs of us are overwritten
 // second components only: outs[r] + (level+1)*n <- ModDown(us[r][1]); the first components of us (all their limbs)
 // and of outs are left as they are
@@ -213,7 +247,7 @@ cm_status moddown_many(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *const *out
 // one batch (m <= CM_KS_BATCH): outs[r] = ModDown(us + r*2*ext*n) + perm_g(addends[r]) on the first addend_comps
 // components (+ accums[r]); addends / accums nullable arrays of nullable pointers
 cm_status moddown_batch_into(cm_ctx *ctx, u64 *us, int level, int m, const u64 *const *addends, int addend_comps, u64 g,
-                             const u64 *const *accums, u64 *const *outs, hipStream_t st);
+                             const u64 *const *accums, u64 *const *outs, hipStream_t st, bool rows_done = false);
 // raised[r][2][ext][n] = sum_j perm_{g_r}(digits_j) * key_r + P * perm_{g_r}(in.c0): hoisted rotations left in the
 // extended basis
 cm_status ks_apply_many_raised(cm_ctx *ctx, const u64 *digits, int level, int cnt, const u64 *const *keys,
@@ -231,7 +265,9 @@ size_t arena_digits_words(const cm_ctx *ctx);
 // level .. of us are overwritten.  ks_drop_fits: whether the kernels cover this level and count (otherwise: two steps).
 bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m);
 cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *add, size_t add_stride, int add_comps, u64 g,
-                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st);
+                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st, bool rows_done = false);
+// what joins row `level` of a ks_drop (launch_rows_ip does it where it does the inverse row pass: inv_from = level)
+FoldIn ks_drop_fold(cm_ctx *ctx, int level, int sets, const u64 *add, size_t add_stride, int add_comps, u64 g, const u64 *acc, size_t acc_stride);
 // out[2][level][n] = rescale(ModDown(u[2][ext][n])), in one where ks_drop_fits, through tmp[2][level+1][n] otherwise
 cm_status moddown_rescale_into(cm_ctx *ctx, u64 *u, int level, u64 *tmp, u64 *out, hipStream_t st);
 // out[2][level][n] = rescale(Rot(in) + accum) (+ extra as rotate_into), likewise

@@ -352,28 +352,6 @@ void launch_automorphism(cm_ctx *ctx, u64 *out, const u64 *in, int rows, u64 g, 
 // rotations).  Two adjacent coefficients per lane (16-byte accesses); the permutation keeps
 // aligned pairs together (it maps i^1 to src^1).
 // `extra` may be the output itself (a running sum): every lane reads its own words before it writes them.
-// The counter-based generator (its finaliser; the streams are defined with the samplers below).
-#define GOLD 0x9E3779B97F4A7C15ULL
-__host__ __device__ __forceinline__ u64 mix64(u64 z) {
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
-    return z ^ (z >> 31);
-}
-// An evaluation key in HBM is its b half only: b_j in multiplier form, [digit][nmod][n], followed by the [digit][nmod]
-// keys of the generator streams of a_j.  The uniform half is drawn directly in the evaluation domain, so word i of
-// limb mi of a_j is draw i of that stream (rejected at or above bound = q floor(2^64/q), then taken mod q): the inner
-// products regenerate it instead of reading it, which takes a third off their traffic.  The draw enters the sums as
-// the raw 64-bit word v (v = a mod q): sum_j d_j v_j < beta q 2^64 fits 128 bits, REDC gives (sum 2^-64) mod q below
-// (beta + 1) q, and a second REDC against 2^128 mod q gives sum mod q in [0, q) -- two reductions per output instead of
-// one per key word.  ctr_gold = (i + 1) GOLD is the counter term of attempt 0, shared by all digits of a lane.
-__device__ __forceinline__ u64 evk_a_draw(u64 stream_key, u64 ctr_gold, unsigned i, u64 bound) {
-    u64 v = mix64(stream_key + ctr_gold);
-    for (u64 att = 1; v >= bound; att++) v = mix64(stream_key + (((att << 32) | (u64)i) + 1) * GOLD);
-    return v;
-}
-__device__ __forceinline__ u64 redc_raw(u128 T, const ModC &m) {
-    return redc((u128)redc(T, m.q, m.qinv) * m.r2, m.q, m.qinv);
-}
 // Where the two words of a_j for positions (i, i + 1) of limb mi come from.  Keys generated with both halves stored
 // carry a_j in multiplier form like b_j (word offset a_off inside the key): the kernels read it, one REDC per sum.
 // Otherwise it is regenerated from its stream (raw draws, two REDCs per sum).  Both give the same residues.

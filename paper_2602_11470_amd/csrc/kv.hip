@@ -481,22 +481,27 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         u64 *outs[CM_KS_BATCH];
         // tensor products, relinearised together
         launch_tensor_batch(ctx, TB, cq, kv->d_k + (size_t)c0 * ctw, m, limbs, st);
-        CMCHK(ks_raise_many(ctx, kv->relin_tabs, TB, ksin, digits, st, m, 0));
+        const bool half = rows_ip_fits(ctx, kl.beta, 1), drop = ks_drop_fits(ctx, lv, 1, m);
+        CMCHK(ks_raise_many(ctx, kv->relin_tabs, TB, ksin, digits, st, m, 0, half));
         const size_t ublk = 2 * (size_t)kl.ext * n, dblk = (size_t)kl.beta * kl.ext * n;
         IpBatch ip;
         ip.nz = m, ip.nsum = 1;
         for (int r = 0; r < m; r++) {
             ip.it[r].dig = digits + r * dblk, ip.it[r].key = relin, ip.it[r].c0 = nullptr, ip.it[r].g = 0;
             ip.out[r] = bu + r * ublk, ip.extra[r] = nullptr;
+            ip.it[r].own = TB + r * 3 * ln + 2 * ln;
             adds[r] = TB + r * 3 * ln, outs[r] = PB + r * ctw;
         }
-        launch_inner_product_shared_key(ctx, ip, kl.beta, lv, st);
+        if (half)
+            launch_rows_ip(ctx, ip, kl.beta, lv, st, drop ? lv : lv + 1,
+                           drop ? ks_drop_fold(ctx, lv, 1, TB, 3 * ln, 2, 0, nullptr, 0) : FoldIn());
+        else launch_inner_product_shared_key(ctx, ip, kl.beta, lv, st);
         // with shared rotations the sums of the key ciphertexts are kept (d_T) until all of them are there
         u64 *r0 = kv->shared > 1 ? kv->d_T + (size_t)c0 * ctw1 : RB0, *r1 = RB1;
-        if (ks_drop_fits(ctx, lv, 1, m)) {
-            CMCHK(ks_drop(ctx, bu, lv, 1, m, TB, 3 * ln, 2, 0, nullptr, 0, r0, st));
+        if (drop) {
+            CMCHK(ks_drop(ctx, bu, lv, 1, m, TB, 3 * ln, 2, 0, nullptr, 0, r0, st, half));
         } else {
-            CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st));
+            CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st, half));
             CMCHK(rescale_into(ctx, PB, 2 * m, lv, r0, st, last, red));        // stacked: [m][2][lv+1] -> [m][2][lv]
         }
         const size_t ublk1 = 2 * (size_t)kl1.ext * n, dblk1 = (size_t)kl1.beta * kl1.ext * n;
@@ -572,16 +577,18 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         launch_raise_by_P(ctx, cur, kv->d_A, lv - 1, st, 1);
         for (int k0 = 1; k0 < kv->shared; k0 += CM_KS_BATCH) {
             const int m = kv->shared - k0 < CM_KS_BATCH ? kv->shared - k0 : CM_KS_BATCH;
-            CMCHK(ks_raise_many(ctx, kv->rot_tabs, kv->d_A + (size_t)k0 * ctw1, ksin, digits, st, m, 0));
+            const bool half = rows_ip_fits(ctx, kl1.beta, m);
+            CMCHK(ks_raise_many(ctx, kv->rot_tabs, kv->d_A + (size_t)k0 * ctw1, ksin, digits, st, m, 0, half));
             IpBatch b;
             b.nz = 1, b.nsum = m;
             for (int r = 0; r < m; r++) {
                 const u64 gal = rot_g(kv, (long long)(k0 + r) * kv->H * kv->t);
                 b.it[r].dig = digits + r * dblk1, b.it[r].key = find_key(evk, gal), b.it[r].g = (unsigned)gal;
-                b.it[r].c0 = kv->d_A + (size_t)(k0 + r) * ctw1, b.it[r].c0_ext = 0;
+                b.it[r].c0 = kv->d_A + (size_t)(k0 + r) * ctw1, b.it[r].c0_ext = 0, b.it[r].own = b.it[r].c0 + ln1;
             }
             b.out[0] = nxt, b.extra[0] = cur;
-            launch_inner_product_batch(ctx, b, kl1.beta, lv - 1, st);
+            if (half) launch_rows_ip(ctx, b, kl1.beta, lv - 1, st);
+            else launch_inner_product_batch(ctx, b, kl1.beta, lv - 1, st);
             std::swap(cur, nxt);
         }
         CMCHK(moddown_rescale_into(ctx, cur, lv - 1, acc, out->dev, st));
@@ -650,7 +657,8 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         const int m = kv->r_o - g0 < CM_KS_BATCH ? kv->r_o - g0 : CM_KS_BATCH;
         if (array == kv->d_x) launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * ctw, kv->r_i, m, limbs, st, 1, kv->r_o);
         else launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * kv->r_i * ctw, kv->r_i, m, limbs, st);
-        CMCHK(ks_raise_many(ctx, kv->relin_tabs, T, ksin, bdigits, st, m, 0));
+        const bool half = rows_ip_fits(ctx, kl.beta, 1);
+        CMCHK(ks_raise_many(ctx, kv->relin_tabs, T, ksin, bdigits, st, m, 0, half));
         u64 *bu = arena_batch_sums(ctx);
         IpBatch ip;
         ip.nz = m, ip.nsum = 1;
@@ -659,10 +667,11 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         for (int r = 0; r < m; r++) {
             ip.it[r].dig = bdigits + r * dblk, ip.it[r].key = relin, ip.it[r].c0 = nullptr, ip.it[r].g = 0;
             ip.out[r] = bu + r * ublk, ip.extra[r] = nullptr;
-            adds[r] = T + (size_t)r * 3 * ln, outs[r] = inner + (size_t)(g0 + r) * ctw;
+            adds[r] = T + (size_t)r * 3 * ln, outs[r] = inner + (size_t)(g0 + r) * ctw, ip.it[r].own = adds[r] + 2 * ln;
         }
-        launch_inner_product_shared_key(ctx, ip, kl.beta, lv, st);
-        CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st));
+        if (half) launch_rows_ip(ctx, ip, kl.beta, lv, st, lv + 1);
+        else launch_inner_product_shared_key(ctx, ip, kl.beta, lv, st);
+        CMCHK(moddown_batch_into(ctx, bu, lv, m, adds, 2, 0, nullptr, outs, st, half));
     }
     if (kv->unrolled) {
         // sum_g Rot(inner_g, g G) next to P inner_0, then the ladder over the residues, all in the extended basis;
@@ -672,16 +681,18 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         launch_raise_by_P(ctx, cur, inner, lv, st);
         for (int g0 = 1; g0 < kv->r_o; g0 += CM_KS_BATCH) {
             const int m = kv->r_o - g0 < CM_KS_BATCH ? kv->r_o - g0 : CM_KS_BATCH;
-            CMCHK(ks_raise_many(ctx, kv->giant_tabs, inner + (size_t)g0 * ctw, ksin, bdigits, st, m, 0));
+            const bool half = rows_ip_fits(ctx, kl.beta, m);
+            CMCHK(ks_raise_many(ctx, kv->giant_tabs, inner + (size_t)g0 * ctw, ksin, bdigits, st, m, 0, half));
             IpBatch b;
             b.nz = 1, b.nsum = m;
             for (int r = 0; r < m; r++) {
                 const u64 gal = rot_g(kv, (long long)(g0 + r) * kv->r_i * Ht);
                 b.it[r].dig = bdigits + r * dblk, b.it[r].key = find_key(evk, gal), b.it[r].g = (unsigned)gal;
-                b.it[r].c0 = inner + (size_t)(g0 + r) * ctw, b.it[r].c0_ext = 0;
+                b.it[r].c0 = inner + (size_t)(g0 + r) * ctw, b.it[r].c0_ext = 0, b.it[r].own = b.it[r].c0 + ln;
             }
             b.out[0] = nxt, b.extra[0] = cur;
-            launch_inner_product_batch(ctx, b, kl.beta, lv, st);
+            if (half) launch_rows_ip(ctx, b, kl.beta, lv, st);
+            else launch_inner_product_batch(ctx, b, kl.beta, lv, st);
             std::swap(cur, nxt);
         }
         for (const auto &grp : kv->res_groups) {

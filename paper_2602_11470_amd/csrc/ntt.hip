@@ -681,29 +681,34 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
 #define SMALL_THREADS 512
 #define SMALL_CHUNK 2048
 // A column (or a row) of 256 words is shared by 64 lanes.  v[k] = word 64 k + sub on one side, 4 sub + k on the other;
-// at(e): LDS place of word e; R: 1 for the columns (stages 0..7), 256 + row for the rows (stages 8..15).
+// at(base, step, k): LDS place of word base + step k; R: 1 for the columns (stages 0..7), 256 + row for the rows (stages 8..15).
+template <class A>
+struct SmallTw {
+    const Tw<A, 2> t0, t1, t2, t3;
+    __device__ __forceinline__ SmallTw(const A &ar, unsigned R, int sub) : t0(ar, R), t1(ar, 4 * R + (sub >> 4)), t2(ar, 16 * R + (sub >> 2)), t3(ar, 64 * R + sub) {}
+};
 template <class A, class AT, class S>
-__device__ __forceinline__ void small_fwd(u64 *lds, typename A::T (&v)[4], const A &ar, unsigned R, int sub, AT at, S sync) {
+__device__ __forceinline__ void small_fwd(u64 *lds, typename A::T (&v)[4], const A &ar, const SmallTw<A> &tw, int sub, AT at, S sync) {
     const int hi1 = sub >> 4, lo1 = sub & 15, hi2 = sub >> 2, lo2 = sub & 3;
-    const Tw<A, 2> t1(ar, 4 * R + hi1), t2(ar, 16 * R + hi2), t3(ar, 64 * R + sub);
-    radix_fwd<2, 0>(v, ar, Tw<A, 2>(ar, R));
+    const Tw<A, 2> &t1 = tw.t1, &t2 = tw.t2, &t3 = tw.t3;
+    radix_fwd<2, 0>(v, ar, tw.t0);
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(64 * k + sub)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(sub, 64, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + 16 * k + lo1)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + lo1, 16, k)]);
     radix_fwd<2, 2>(v, ar, t1);
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + 16 * k + lo1)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + lo1, 16, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + 4 * k + lo2)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + lo2, 4, k)]);
     radix_fwd<2, 4>(v, ar, t2);
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + 4 * k + lo2)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + lo2, 4, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(4 * sub + k)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(4 * sub, 1, k)]);
     radix_fwd<2, 6>(v, ar, t3);
 }
 template <class A, class AT, class S>
@@ -712,32 +717,35 @@ __device__ __forceinline__ void small_inv(u64 *lds, typename A::T (&v)[4], const
     const Tw<A, 2> t0(ar, R), t1(ar, 4 * R + hi1), t2(ar, 16 * R + hi2);
     radix_inv<2, 6>(v, ar, Tw<A, 2>(ar, 64 * R + sub));
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(4 * sub + k)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(4 * sub, 1, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + 4 * k + lo2)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(16 * hi2 + lo2, 4, k)]);
     radix_inv<2, 4>(v, ar, t2);
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + 4 * k + lo2)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(16 * hi2 + lo2, 4, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + 16 * k + lo1)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * hi1 + lo1, 16, k)]);
     radix_inv<2, 2>(v, ar, t1);
 #pragma unroll
-    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + 16 * k + lo1)] = ar.to_mid(v[k]);
+    for (int k = 0; k < 4; k++) lds[at(64 * hi1 + lo1, 16, k)] = ar.to_mid(v[k]);
     sync();
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(64 * k + sub)]);
+    for (int k = 0; k < 4; k++) v[k] = ar.from_mid(lds[at(sub, 64, k)]);
     radix_inv<2, 0>(v, ar, t0);
 }
 // SMALL_CW columns of 256 words; the rows that a half-wave touches (neighbours, or four apart) cover all banks
 struct SmallCol {
     int c;
-    __device__ __forceinline__ int operator()(int e) const { return SMALL_CW * (e ^ ((e >> 2) & (32 / SMALL_CW - 1))) + c; }
+    __device__ __forceinline__ int operator()(int base, int step, int k) const {
+        const int e = base + step * k;
+        return SMALL_CW * (e ^ ((e >> 2) & (32 / SMALL_CW - 1))) + c;
+    }
 };
 struct SmallRow {
-    int base;
-    __device__ __forceinline__ int operator()(int e) const { return pad(base + e); }
+    int row;                      // first word of the row, a multiple of 16; no step carries from below a multiple of 16 past it
+    __device__ __forceinline__ int operator()(int base, int step, int k) const { return pad(row + base) + pad(step * k); }
 };
 struct GroupSync {
     __device__ __forceinline__ void operator()() const { __syncthreads(); }
@@ -756,7 +764,7 @@ __device__ __forceinline__ void small_cols_fwd_body(u64 *lds, u64 *p, const u64 
     for (int k = 0; k < 4; k++) raw[k] = ps[(64 * k + sub) * n2 + c];
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_lazy(raw[k]);
-    small_fwd(lds, v, ar, 1, sub, SmallCol{c}, GroupSync());
+    small_fwd(lds, v, ar, SmallTw<A>(ar, 1, sub), sub, SmallCol{c}, GroupSync());
 #pragma unroll
     for (int k = 0; k < 4; k++) ntt_store(0, p + (4 * sub + k) * n2 + c, ar.to_mid(v[k]));
 }
@@ -783,7 +791,7 @@ __device__ __forceinline__ void small_rows_fwd_body(u64 *lds, u64 *p, const NttT
     typename A::T v[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = ar.from_mid(p[64 * k + sub]);
-    small_fwd(lds, v, ar, 256 + 8 * chunk + row, sub, SmallRow{row * 256}, WaveSync());
+    small_fwd(lds, v, ar, SmallTw<A>(ar, 256 + 8 * chunk + row, sub), sub, SmallRow{row * 256}, WaveSync());
 #pragma unroll
     for (int k = 0; k < 4; k++) lds[pad(row * 256 + 4 * sub + k)] = TAIL ? ar.to_tail(v[k]) : ar.to_rest_fwd(v[k]);
     if (!TAIL) {
@@ -850,6 +858,207 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict_
     const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - (size_t)chunk * SMALL_CHUNK;
     if (t.fpq[mi].q != 0.0) small_rows_inv_body<FpArith>(lds, p, psrow, g, t, mi, n, chunk, limb, fi);
     else small_rows_inv_body<IntArith>(lds, p, psrow, g, t, mi, n, chunk, limb, fi);
+}
+
+// an empty statement that the compiler must take as a new value of x: values derived from x are not loop-invariant
+#define OPAQUE(x) asm volatile("" : "+v"(x))
+
+// ---- row pass of the digits and inner product with the keys in one launch (n = 65536) -----------------------------------------
+// A wave owns one row of 256 words of one limb of one output: for every item and digit it does the digit's row pass (four words a
+// lane, exchanges inside the wave, no barrier), which leaves four consecutive words in every lane -- the positions whose key words
+// it then reads -- and multiplies.  With a Galois element the wave transforms the row that the map takes its own row from (aligned
+// blocks go to aligned blocks) and exchanges once more.  The digits' row pass as a launch of its own wrote and re-read every digit.
+// The rows from inv_from on go straight into the row pass of the inverse transform, whose order of words is the one they are in.
+// Bound by the vector ALU at two waves a SIMD (up to 240 registers: sums, twiddles, and the next digit requested ahead, which is
+// worth 1 %; three waves spill 26 registers and lose 3 to 10 %, four lose 20 %).  Row passes and inner products in launches of
+// their own -> here: the seven giant steps at level 22 195 + 236 -> 388 us; two launches a key switch fewer: ciphertext product at
+// level 13 151.6 -> 145.6 us, rotary embedding at level 3 82.9 -> 76.9, query times K at level 12 16730 -> 16020, scores times V at
+// level 22 4082 -> 3852, 4096 x 4096 product at level 23 4738 -> 4532.  Eight relinearisations at level 22, whose key draws the
+// shared-key kernel forms once, 218 + 205 + 25 (inverse row pass) -> 447.
+#define RIP_WAVES 4
+typedef u64 u64x2_t __attribute__((ext_vector_type(2)));
+// Sums of products d w and d v, w in multiplier form, v a raw draw.  LAZY: they run over all items of an output (each term is below
+// 2^57 and an accumulator holds 128); the integer limbs' are reduced item by item (eight terms below q 2^64 fit 128 bits).
+struct RipFp {
+    static constexpr bool LAZY = true;
+    Acc50 b, a;
+    __device__ __forceinline__ void mac(u64 d, u64 w, u64 v) {
+        const unsigned d0 = (unsigned)d & LOW25, d1 = (unsigned)(d >> 25);
+        b.mac(d0, d1, w), a.mac(d0, d1, v);
+    }
+    __device__ __forceinline__ void mac_b(u64 d, u64 w) { b.mac((unsigned)d & LOW25, (unsigned)(d >> 25), w); }
+    __device__ __forceinline__ u64 sum_b(const ModC &m) const { return redc(b.total(), m.q, m.qinv); }
+    __device__ __forceinline__ u64 sum_a(const ModC &m) const { return redc_raw(a.total(), m); }
+};
+struct RipInt {
+    static constexpr bool LAZY = false;
+    u128 b = 0, a = 0;
+    __device__ __forceinline__ void mac(u64 d, u64 w, u64 v) { b += (u128)d * w, a += (u128)d * v; }
+    __device__ __forceinline__ void mac_b(u64 d, u64 w) { b += (u128)d * w; }
+    __device__ __forceinline__ u64 sum_b(const ModC &m) const { return redc(b, m.q, m.qinv); }
+    __device__ __forceinline__ u64 sum_a(const ModC &m) const { return redc_raw(a, m); }
+};
+struct RipArgs {
+    int beta, ext, level, alpha, L, nmod, n, logn, kdig, inv_from;
+    const u64 *ubound, *pmont;
+};
+// words k of the wave's row in out, or, from inv_from on, the row pass of the inverse transform of them
+template <class A>
+__device__ __forceinline__ void rip_out(u64 *lds, u64 *out, const u64 (&x)[4], const RipArgs &p, const NttTables &ti, int r, int mi, unsigned R, int sub) {
+    if (!p.inv_from || r < p.inv_from) {
+#pragma unroll
+        for (int k = 0; k < 4; k += 2) {
+            const u64x2_t w = {x[k], x[k + 1]};
+            *reinterpret_cast<u64x2_t *>(word_at(out + 256 * R, 4 * sub + k)) = w;
+        }
+        return;
+    }
+    A ai;
+    ai.init(ti, mi, p.n);
+    typename A::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = ai.from_rest(x[k]);
+    wave_sync();
+    small_inv(lds, v, ai, 256 + R, sub, SmallRow{0}, WaveSync());
+#pragma unroll
+    for (int k = 0; k < 4; k++) ntt_store(0, word_at(out + 256 * R, sub + 64 * k), ai.to_mid(v[k]));
+}
+template <class A, class S>
+__device__ __forceinline__ void rip_body(u64 *lds, const IpBatch &b, const RipArgs &p, const FoldIn &fi, const NttTables &t, const NttTables &ti,
+                                         int r, int mi, unsigned R, int z) {
+    const ModC m = t.modc[mi];
+    const int n = p.n, sub = threadIdx.x & 63, special = p.ext - p.level - 1, out_rows = b.apart ? p.ext + (b.nsum - 1) * special : p.ext;
+    const unsigned pos = 256 * R + 4 * sub;
+    const u64 bound = p.ubound[mi];
+    const SmallRow at{0};
+    const bool apart = b.apart && r > p.level;
+    // addresses: uniform bases and 32-bit offsets; the draws' counters: a lane's part and a uniform one
+    const u64 gv = (u64)(4 * sub) * GOLD;
+    A ar;
+    ar.init(t, mi, n);
+    S acc[4];
+    u64 r0[4], r1[4];                                     // what the sums leave, integer limbs: item by item
+#pragma unroll
+    for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
+    // The words of digit j of item s, half-transformed (or, of the digit that holds limb r itself, as they are), and of its key:
+    // requested one digit ahead.
+    const int jo = r <= p.level ? r / p.alpha : -1;
+    u64 raw[4];
+    u64x2_t w01, w23;
+    auto request = [&](int s, int j) {
+        const IpItem &it = b.it[z * b.nsum + s];
+        const u64 *kb = it.key + ((size_t)j * p.nmod + mi) * n + 256 * R;
+        if (j == jo) {
+            const unsigned gg = it.g ? it.g : it.own_g;
+            unsigned ps = pos;
+            OPAQUE(ps);                                   // what the rarer branches derive from it is not kept over the loop
+#pragma unroll
+            for (int k = 0; k < 4; k++) raw[k] = *word_at(it.own + (size_t)r * n, gg ? perm_src(ps + k, gg, p.logn) : ps + k);
+        } else {
+            const u64 *h = it.dig + ((size_t)j * p.ext + r) * n + (it.g ? perm_src(256 * R, it.g, p.logn) & ~255u : 256 * R);
+#pragma unroll
+            for (int k = 0; k < 4; k++) raw[k] = __builtin_nontemporal_load(word_at(h, 64 * k + sub));
+        }
+        w01 = __builtin_nontemporal_load(reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub)));
+        w23 = __builtin_nontemporal_load(reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub + 2)));
+    };
+    request(0, 0);
+    for (int s = 0; s < b.nsum; s++) {
+        const IpItem &it = b.it[z * b.nsum + s];
+        const unsigned g = it.g, src_row = g ? perm_src(256 * R, g, p.logn) >> 8 : R;
+        const SmallTw<A> tw(ar, 256 + src_row, sub);
+        for (int j = 0; j < p.beta; j++) {
+            const u64 sk = it.key[(size_t)p.kdig * p.nmod * n + (size_t)j * p.nmod + mi];
+            u64 d[4];
+            typename A::T x[4];
+            const u64 wk[4] = {w01.x, w01.y, w23.x, w23.y};
+#pragma unroll
+            for (int k = 0; k < 4; k++) d[k] = raw[k], x[k] = ar.from_mid(raw[k]);
+            if (j + 1 < p.beta) request(s, j + 1);
+            else if (s + 1 < b.nsum) request(s + 1, 0);
+            unsigned ps = pos;
+            OPAQUE(ps);
+            if (j != jo) {
+                wave_sync();
+                small_fwd(lds, x, ar, tw, sub, at, WaveSync());
+#pragma unroll
+                for (int k = 0; k < 4; k++) d[k] = ar.to_rest_fwd(x[k]);
+                if (g) {
+                    wave_sync();
+#pragma unroll
+                    for (int k = 0; k < 4; k++) lds[at(4 * sub, 1, k)] = d[k];
+                    wave_sync();
+#pragma unroll
+                    for (int k = 0; k < 4; k++) d[k] = lds[pad(perm_src(ps + k, g, p.logn) & 255)];
+                }
+            }
+            u64 v[4];
+            bool rej = false;
+#pragma unroll
+            for (int k = 0; k < 4; k++) v[k] = mix64(gv + (sk + ((u64)(256 * R + k) + 1) * GOLD)), rej |= v[k] >= bound;
+            if (rej) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) v[k] = evk_a_draw(sk, ((u64)(ps + k) + 1) * GOLD, ps + k, bound);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k].mac(d[k], wk[k], v[k]);
+        }
+        if (it.c0 && (it.c0_ext || r <= p.level)) {
+            const u64 w = it.c0_ext ? redc((u128)m.r2, m.q, m.qinv) : p.pmont[r];        // 1 or P in multiplier form
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k].mac_b(*word_at(it.c0 + (size_t)r * n, g ? perm_src(pos + k, g, p.logn) : pos + k), w);
+        }
+        if (!S::LAZY || apart || s + 1 == b.nsum) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const u64 x = acc[k].sum_b(m), y = acc[k].sum_a(m);
+                r0[k] = S::LAZY ? x : addmod(r0[k], x, m.q), r1[k] = S::LAZY ? y : addmod(r1[k], y, m.q);
+                acc[k] = S();
+            }
+        }
+        if (apart) {                                      // this item's special limb by itself
+            u64 *out = b.out[z] + (size_t)(r + s * special) * n;
+            rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
+            rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
+#pragma unroll
+            for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
+        }
+    }
+    if (apart) return;
+    if (b.extra[z]) {
+        const u64 *e = b.extra[z] + (size_t)r * n;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            r0[k] = addmod(r0[k], *word_at(e, pos + k), m.q), r1[k] = addmod(r1[k], *word_at(e + (size_t)out_rows * n, pos + k), m.q);
+    }
+    if (fi.per && r == p.level) {
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const size_t row = ((size_t)c * fi.rows + fi.rows - 1) * n;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                u64 x = 0;
+                if (fi.add && c < fi.add_comps) x = fi.add[z * fi.add_stride + row + (fi.g ? perm_src(pos + k, fi.g, p.logn) : pos + k)];
+                if (fi.acc) x = addmod(x, fi.acc[z * fi.acc_stride + row + pos + k], m.q);
+                x = redc((u128)x * fi.pm, m.q, m.qinv);
+                if (c) r1[k] = addmod(r1[k], x, m.q);
+                else r0[k] = addmod(r0[k], x, m.q);
+            }
+        }
+    }
+    u64 *out = b.out[z] + (size_t)r * n;
+    rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
+    rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
+}
+// grid: x = 64 workgroups of four rows, y = limb (special primes first), z = output
+__global__ __launch_bounds__(64 * RIP_WAVES, 2) void k_rows_ip(IpBatch b, RipArgs p, FoldIn fi, NttTables t, NttTables ti) {
+    __shared__ u64 lds[RIP_WAVES * (256 + 16)];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = p.ext - 1 - (int)blockIdx.y;
+    const int mi = r <= p.level ? r : p.L + 1 + (r - p.level - 1);
+    u64 *l = lds + wave * (256 + 16);
+    const unsigned R = blockIdx.x * RIP_WAVES + wave;
+    if (t.fpq[mi].q != 0.0) rip_body<FpArith, RipFp>(l, b, p, fi, t, ti, r, mi, R, blockIdx.z);
+    else rip_body<IntArith, RipInt>(l, b, p, fi, t, ti, r, mi, R, blockIdx.z);
 }
 
 // ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
@@ -1016,8 +1225,6 @@ struct ConvArgs {
     unsigned own_g;
     int tg, groups;               // targets per workgroup, workgroups that convert per (tile, item) (n = 65536)
 };
-// an empty statement that the compiler must take as a new value of x: values derived from x are not loop-invariant
-#define OPAQUE(x) asm volatile("" : "+v"(x))
 // The y_m of NV words.  Source moduli below 2^50 (the digits of a raise): exact integers in doubles; a product with a
 // weight under an FP64 target modulus is then the butterflies' product (6 instructions and an addition per term, no
 // carries), under a 60-bit one a split product (Acc50).  Larger sources (the special primes of a ModDown): 30 + 30 bit
@@ -1395,6 +1602,16 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
         hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g, fi);
     }
 }
+// the second pass of an inverse transform whose row pass is done (launch_rows_ip)
+void launch_cols_inv(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs, hipStream_t st) {
+    if (limbs <= 0) return;
+    Prof prof_(ctx, CM_K_NTT_INV, limbs, st);
+    const int n = ctx->n;
+    const NttTables t = tables_of(ctx, true, limbs);
+    if (limbs <= SMALL_COLS)
+        hipLaunchKernelGGL(small_cols_inv, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, d_rows, d_mod_idx, t, n);
+    else hipLaunchKernelGGL(ntt_cols_inv, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, d_rows, d_mod_idx, t, n, n >> 8);
+}
 void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const FinishBatch &fb, hipStream_t st, const u64 *src,
                            const int *d_src_rows) {
     const int limbs = fb.items * fb.ncomp * (fb.level + 1), n = ctx->n;
@@ -1436,7 +1653,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     a.tg = CCF_TG;
     while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
     a.groups = (b.max_nt + a.tg - 1) / a.tg;
-    const dim3 grid(256 / CCF_W, a.groups + (b.own_src ? 1 : 0), b.batch);
+    const dim3 grid(256 / CCF_W, a.groups + (b.own_src && !b.half ? 1 : 0), b.batch);
     // Eight sources spill twelve registers (128 for two workgroups per compute unit), seven do not: with seven special
     // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
     // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
@@ -1453,8 +1670,23 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     else if (ns <= 7) CCF_LAUNCH(7);
     else CCF_LAUNCH(8);
 #undef CCF_LAUNCH
+    if (b.half) return;
     if (fb) launch_rows_fwd<true>(out, d_rows, d_mods, t, n, limbs, *fb, st);
     else launch_rows_fwd<false>(out, d_rows, d_mods, t, n, limbs, FinishBatch(), st);
+}
+// a digit or a first component is a term of the sums (RipFp: 128 of them); an item of an integer limb holds eight
+#define RIP_MAX_TERMS 120
+bool rows_ip_fits(const cm_ctx *ctx, int beta, int nsum) {
+    return ctx->n == 65536 && !ctx->evk_stored_a && beta <= 7 && nsum * (beta + 1) <= RIP_MAX_TERMS;
+}
+void launch_rows_ip(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st, int inv_from, const FoldIn &fi) {
+    const int ext = level + 1 + ctx->K;
+    Prof prof_(ctx, CM_K_INNER_PRODUCT, b.nz * b.nsum, st);
+    RipArgs p;
+    p.beta = beta, p.ext = ext, p.level = level, p.alpha = ctx->alpha, p.L = ctx->L, p.nmod = ctx->nmod, p.n = ctx->n, p.logn = ctx->logn;
+    p.kdig = (ctx->L + ctx->alpha) / ctx->alpha, p.inv_from = inv_from, p.ubound = ctx->d_ubound, p.pmont = ctx->d_pmont;
+    hipLaunchKernelGGL(k_rows_ip, dim3(ctx->n / (256 * RIP_WAVES), ext, b.nz), dim3(64 * RIP_WAVES), 0, st, b, p, fi,
+                       tables_of(ctx, false, 0), tables_of(ctx, true, 0));
 }
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs,
                      bool inverse, hipStream_t st) {

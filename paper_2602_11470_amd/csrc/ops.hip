@@ -286,7 +286,7 @@ static bool ct_ok(const cm_ctx *ctx, const cm_ct *c) {
 static bool same_scale(double a, double b) { return fabs(a / b - 1.0) < 1e-9; }
 
 // ---- hybrid key switching -------------------------------------------------------------------------
-cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_t st, u64 g) {
+cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_t st, u64 g, bool half) {
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
     const size_t n = ctx->n;
@@ -295,7 +295,7 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     ConvBatch cb;
     cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
-    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g;
+    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half;
     launch_conv_ntt(ctx, cb, digits, A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
 }
@@ -310,12 +310,13 @@ static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, 
     launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
 }
 cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int addend_comps, u64 g, u64 *out,
-                       const u64 *accum, hipStream_t st) {
+                       const u64 *accum, hipStream_t st, bool rows_done) {
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
     const size_t n = ctx->n;
     if (!addend) addend_comps = 0, g = 0;
-    launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
+    if (rows_done) launch_cols_inv(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, st);
+    else launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = addend_comps;
     fb.u[0] = u, fb.out[0] = out, fb.accum[0] = accum, fb.g[0] = (unsigned)g;
@@ -324,12 +325,20 @@ cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int ad
     return CM_OK;
 }
 
-cm_status ks_apply(cm_ctx *ctx, const u64 *digits, const u64 *evk, int level, u64 g, const u64 *addend,
-                   int addend_comps, u64 *out, hipStream_t st, const u64 *accum) {
+cm_status ks_one(cm_ctx *ctx, const u64 *d, const u64 *key, int level, u64 g, const u64 *addend, int addend_comps, u64 *out, hipStream_t st,
+                 const u64 *accum, const u64 *extra) {
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
-    launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, digits, evk, k.beta, level, g, st);
-    return moddown_into(ctx, A.u, level, addend, addend_comps, g, out, accum, st);
+    const bool half = rows_ip_fits(ctx, k.beta, 1);
+    CMCHK(ks_raise(ctx, d, level, A.digits, st, g, half));
+    if (half) {
+        IpBatch b;
+        b.nz = 1, b.it[0].dig = A.digits, b.it[0].key = key, b.it[0].own = d, b.it[0].own_g = (unsigned)g, b.out[0] = A.u, b.extra[0] = extra;
+        launch_rows_ip(ctx, b, k.beta, level, st, level + 1);
+    } else {
+        launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
+    }
+    return moddown_into(ctx, A.u, level, addend, addend_comps, g, out, accum, st, half);
 }
 // A ModDown with a rescale behind it transforms every limb that stays twice, and the two are linear modulo each of those limbs:
 // with x = ModDown's limb under q_level, in coefficients, both are (u - NTT(conv + P x)) (P q_level)^-1, and x comes out of
@@ -349,23 +358,28 @@ bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m) {
     if (pmax < (1ULL << 50)) return ctx->mod[level] < (1ULL << 50);
     return (pmax < (1ULL << 60) && qmax < (1ULL << 50)) || ns + 1 <= 7;
 }
+FoldIn ks_drop_fold(cm_ctx *ctx, int level, int sets, const u64 *add, size_t add_stride, int add_comps, u64 g, const u64 *acc, size_t acc_stride) {
+    FoldIn fi;
+    if (!add && !acc) return fi;
+    const ModC &mc = ctx->modc[level];
+    u64 P = 1;
+    for (int i = 0; i < ctx->K; i++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + i] % mc.q, mc.q);
+    fi.per = sets * ctx->K + 1, fi.rows = level + 1, fi.add_comps = add_comps, fi.g = (unsigned)g;
+    fi.add = add, fi.acc = acc, fi.add_stride = add_stride, fi.acc_stride = acc_stride;
+    fi.pm = h_mulmod(P, (u64)(((u128)1 << 64) % mc.q), mc.q), fi.q = mc.q, fi.qinv = mc.qinv;
+    return fi;
+}
 cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *add, size_t add_stride, int add_comps, u64 g,
-                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st) {
+                  const u64 *acc, size_t acc_stride, u64 *out, hipStream_t st, bool rows_done) {
     if (!ks_drop_fits(ctx, level, sets, m)) return CM_E_INVAL;
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
     const size_t n = ctx->n;
     const int ns = sets * ctx->K, ext = level + 1 + ns;
-    FoldIn fi;
-    if (add || acc) {
-        const ModC &mc = ctx->modc[level];
-        u64 P = 1;
-        for (int i = 0; i < ctx->K; i++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + i] % mc.q, mc.q);
-        fi.per = ns + 1, fi.rows = level + 1, fi.add_comps = add_comps, fi.g = (unsigned)g;
-        fi.add = add, fi.acc = acc, fi.add_stride = add_stride, fi.acc_stride = acc_stride;
-        fi.pm = h_mulmod(P, (u64)(((u128)1 << 64) % mc.q), mc.q), fi.q = mc.q, fi.qinv = mc.qinv;
-    }
-    launch_ntt_src(ctx, us, k.d_drop_rows[sets - 1], nullptr, nullptr, k.d_drop_mods[sets - 1], 2 * m * (ns + 1), true, st, 0, fi);
+    if (rows_done) launch_cols_inv(ctx, us, k.d_drop_rows[sets - 1], k.d_drop_mods[sets - 1], 2 * m * (ns + 1), st);
+    else
+        launch_ntt_src(ctx, us, k.d_drop_rows[sets - 1], nullptr, nullptr, k.d_drop_mods[sets - 1], 2 * m * (ns + 1), true, st, 0,
+                       ks_drop_fold(ctx, level, sets, add, add_stride, add_comps, g, acc, acc_stride));
     FinishBatch fb;
     fb.items = m, fb.level = level - 1, fb.ext = ext, fb.addend_comps = add ? add_comps : 0, fb.in_rows = level + 1;
     for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
@@ -429,11 +443,12 @@ u64 *arena_batch_sums(const cm_ctx *ctx) { return arena_of(ctx).bu; }
 // ModDown of m <= CM_KS_BATCH stacked sums bu[r][2][ext][n] in one batch of launches:
 // outs[r] = ModDown(bu[r]) (+ perm_{gs[r]}(addends[r]) on the first addend_comps components) (+ accums[r])
 static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, const u64 *const *addends, int addend_comps,
-                          const u64 *gs, const u64 *const *accums, u64 *const *outs, hipStream_t st) {
+                          const u64 *gs, const u64 *const *accums, u64 *const *outs, hipStream_t st, bool rows_done = false) {
     Arena A = arena_of(ctx);
     const int level = k.level;
     const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n;
-    launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
+    if (rows_done) launch_cols_inv(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, st);
+    else launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
     auto add_of = [&](int r) { return addends ? addends[r] : nullptr; };
     auto acc_of = [&](int r) { return accums ? accums[r] : nullptr; };
     FinishBatch fb;
@@ -447,11 +462,11 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
     moddown_conv(ctx, k, k.d_moddown, 2 * m, A.bconv, bu, (size_t)k.ext * n, fb, st);
 }
 cm_status moddown_batch_into(cm_ctx *ctx, u64 *us, int level, int m, const u64 *const *addends, int addend_comps, u64 g,
-                             const u64 *const *accums, u64 *const *outs, hipStream_t st) {
+                             const u64 *const *accums, u64 *const *outs, hipStream_t st, bool rows_done) {
     if (m < 1 || m > CM_KS_BATCH) return CM_E_INVAL;
     u64 gs[CM_KS_BATCH];
     for (int r = 0; r < m; r++) gs[r] = g;
-    moddown_batch(ctx, ks_level_full(ctx, level), us, m, addends, addend_comps, gs, accums, outs, st);
+    moddown_batch(ctx, ks_level_full(ctx, level), us, m, addends, addend_comps, gs, accums, outs, st, rows_done);
     return CM_OK;
 }
 cm_status moddown_many(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *const *outs, hipStream_t st) {
@@ -538,7 +553,7 @@ void ks_many_tables_destroy(KsManyTables *t) {
     *t = KsManyTables();
 }
 cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 *ksin, u64 *digits, hipStream_t st, int m,
-                        u64 g) {
+                        u64 g, bool half) {
     if (m < 0) m = t.cnt;
     if (m == 0) return CM_OK;
     if (m > t.cnt) return CM_E_INVAL;
@@ -550,7 +565,7 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     cb.tabs = k.d_modup, cb.batch = m * k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt;
     cb.tab_period = k.beta, cb.in_group = k.beta;
     cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
-    cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln;
+    cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln, cb.half = half;
     launch_conv_ntt(ctx, cb, digits, ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
     return CM_OK;
 }
@@ -602,8 +617,7 @@ extern "C" cm_status cm_keyswitch(cm_ctx *ctx, const cm_evk *evk, int32_t step, 
     const u64 *key = find_key(evk, relin ? 0 : galois_of_step(ctx, step));
     if (!key) return CM_E_NOKEY;
     Arena A = arena_of(ctx);
-    CMCHK(ks_raise(ctx, (const u64 *)d, level, A.digits, st));
-    CMCHK(ks_apply(ctx, A.digits, key, level, 0, nullptr, 0, A.tmp[0], st));
+    CMCHK(ks_one(ctx, (const u64 *)d, key, level, 0, nullptr, 0, A.tmp[0], st));
     size_t bytes = (size_t)(level + 1) * ctx->n * 8;
     HIPCHK(hipMemcpyAsync(ks0, A.tmp[0], bytes, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(ks1, A.tmp[0] + (size_t)(level + 1) * ctx->n, bytes, hipMemcpyDeviceToDevice, st));
@@ -938,10 +952,8 @@ extern "C" cm_status cm_relinearize(cm_ctx *ctx, const cm_evk *evk, const cm_ct 
     if (!key) return CM_E_NOKEY;
     CM_TRY
     hipStream_t st = (hipStream_t)stream;
-    Arena A = arena_of(ctx);
     const size_t ln = (size_t)(a->level + 1) * ctx->n;
-    CMCHK(ks_raise(ctx, a->dev + 2 * ln, a->level, A.digits, st));
-    CMCHK(ks_apply(ctx, A.digits, key, a->level, 0, a->dev, 2, out->dev, st));
+    CMCHK(ks_one(ctx, a->dev + 2 * ln, key, a->level, 0, a->dev, 2, out->dev, st));
     out->level = a->level, out->ncomp = 2, out->scale = a->scale;
     return CM_OK;
     CM_CATCH
@@ -1140,11 +1152,7 @@ cm_status rotate_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64
     // c1, the copy of the digits' own limbs, and the c0 added at the end), never as a pass of its own.
     // The inner product sees already mapped digits, so it runs without permutation; the ModDown
     // tail gathers c0 through the permutation.
-    Arena A = arena_of(ctx);
-    CMCHK(ks_raise(ctx, in + (size_t)(level + 1) * ctx->n, level, A.digits, st, g));
-    const KsLevelFull &k = ks_level_full(ctx, level);
-    launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
-    return moddown_into(ctx, A.u, level, in, 1, g, out, accum, st);
+    return ks_one(ctx, in + (size_t)(level + 1) * ctx->n, key, level, g, in, 1, out, st, accum, extra);
 }
 cm_status rotate_rescale_into(cm_ctx *ctx, const u64 *key, const u64 *in, int level, u64 g, u64 *tmp, u64 *out, hipStream_t st,
                               const u64 *accum, const u64 *extra) {
@@ -1152,11 +1160,19 @@ cm_status rotate_rescale_into(cm_ctx *ctx, const u64 *key, const u64 *in, int le
         CMCHK(rotate_into(ctx, key, in, level, g, tmp, st, accum, extra));
         return rescale_into(ctx, tmp, 2, level, out, st);
     }
-    Arena A = arena_of(ctx);
-    CMCHK(ks_raise(ctx, in + (size_t)(level + 1) * ctx->n, level, A.digits, st, g));
     const KsLevelFull &k = ks_level_full(ctx, level);
-    launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
-    return ks_drop(ctx, A.u, level, 1, 1, in, 0, 1, g, accum, 0, out, st);
+    Arena A = arena_of(ctx);
+    const u64 *d = in + (size_t)(level + 1) * ctx->n;
+    const bool half = rows_ip_fits(ctx, k.beta, 1);
+    CMCHK(ks_raise(ctx, d, level, A.digits, st, g, half));
+    if (half) {
+        IpBatch b;
+        b.nz = 1, b.it[0].dig = A.digits, b.it[0].key = key, b.it[0].own = d, b.it[0].own_g = (unsigned)g, b.out[0] = A.u, b.extra[0] = extra;
+        launch_rows_ip(ctx, b, k.beta, level, st, level, ks_drop_fold(ctx, level, 1, in, 0, 1, g, accum, 0));
+    } else {
+        launch_inner_product(ctx, A.u, A.u + (size_t)k.ext * ctx->n, A.digits, key, k.beta, level, 0, st, nullptr, extra);
+    }
+    return ks_drop(ctx, A.u, level, 1, 1, in, 0, 1, g, accum, 0, out, st, half);
 }
 extern "C" cm_status cm_rotate(cm_ctx *ctx, const cm_evk *evk, const cm_ct *in, int32_t step, cm_ct *out, void *stream) {
     (void)hipGetLastError();          // stale errors of earlier calls are not this call's

@@ -189,13 +189,16 @@ extern "C" cm_status cm_rope_apply(cm_ctx *ctx, const cm_evk *evk, const cm_rope
         u64 *digits = arena_digits(ctx);
         hipLaunchKernelGGL(k_mul_pt3_rot, dim3(n / 256, 2 * limbs), dim3(256), 0, st, a, b, x->dev, r->d_pts, ctx->d_modc, limbs, (int)n,
                            ctx->logn, (unsigned)g_up, (unsigned)g_dn);
-        CMCHK(ks_raise_many(ctx, r->tabs, b, c, digits, st));
+        const bool half = rows_ip_fits(ctx, kl.beta, 2);
+        CMCHK(ks_raise_many(ctx, r->tabs, b, c, digits, st, -1, 0, half));
         IpBatch ip;
         ip.nz = 1, ip.nsum = 2, ip.apart = true;
         ip.it[0].dig = digits, ip.it[0].key = k_up, ip.it[1].dig = digits + dblk, ip.it[1].key = k_dn;
         ip.out[0] = arena_batch_sums(ctx);
-        launch_inner_product_batch(ctx, ip, kl.beta, level, st);
-        CMCHK(ks_drop(ctx, ip.out[0], level, 2, 1, nullptr, 0, 0, 0, a, 0, y->dev, st));
+        ip.it[0].own = b, ip.it[1].own = b + (size_t)limbs * n;
+        if (half) launch_rows_ip(ctx, ip, kl.beta, level, st, level, ks_drop_fold(ctx, level, 2, nullptr, 0, 0, 0, a, 0));
+        else launch_inner_product_batch(ctx, ip, kl.beta, level, st);
+        CMCHK(ks_drop(ctx, ip.out[0], level, 2, 1, nullptr, 0, 0, 0, a, 0, y->dev, st, half));
         y->level = level - 1, y->ncomp = 2;
         y->scale = x->scale;                                      // plaintext scale = the prime just removed
         RETURN_LAUNCH_STATUS();

@@ -408,18 +408,23 @@ static cm_status vmm_raised_finish(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_
         std::vector<u64 *> outs;
         for (int k = 0; k < cnt; k++) outs.push_back(cts + (size_t)k * ctw);
         CMCHK(moddown_many_second(ctx, inner + rw, level, cnt, outs.data(), st));
-        CMCHK(ks_raise_many(ctx, p->many, cts, ksin, digs, st));
-        for (int k0 = 1; k0 < r_o; k0 += IP_MAX_ITEMS) {          // all rotations summed onto inner_0 by one launch
+        int most = cnt < IP_MAX_ITEMS ? cnt : IP_MAX_ITEMS;         // rotations summed onto inner_0 by one launch
+        const bool half = rows_ip_fits(ctx, kl.beta, 1);
+        while (half && most > 1 && !rows_ip_fits(ctx, kl.beta, most)) most--;
+        CMCHK(ks_raise_many(ctx, p->many, cts, ksin, digs, st, -1, 0, half));
+        for (int k0 = 1; k0 < r_o; k0 += most) {
             IpBatch b;
-            b.nz = 1, b.nsum = r_o - k0 < IP_MAX_ITEMS ? r_o - k0 : IP_MAX_ITEMS;
+            b.nz = 1, b.nsum = r_o - k0 < most ? r_o - k0 : most;
             for (int s = 0; s < b.nsum; s++) {
                 const int k = k0 + s;
                 b.it[s].dig = digs + (size_t)(k - 1) * kl.beta * kl.ext * n, b.it[s].key = key_of(k * p->giant_step);
                 b.it[s].c0 = inner + (size_t)k * rw, b.it[s].c0_ext = 1;
                 b.it[s].g = (unsigned)galois_of_step(ctx, k * p->giant_step);
+                b.it[s].own = cts + (size_t)(k - 1) * ctw + (size_t)limbs * n;
             }
             b.out[0] = inner, b.extra[0] = inner;
-            launch_inner_product_batch(ctx, b, kl.beta, level, st);
+            if (half) launch_rows_ip(ctx, b, kl.beta, level, st);
+            else launch_inner_product_batch(ctx, b, kl.beta, level, st);
         }
         u64 *total = inner;
         if (p->unrolled) {

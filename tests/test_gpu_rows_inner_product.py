@@ -1,0 +1,51 @@
+"""Row pass and inner product in one launch at n = 65536 against the oracle, limb for limb: one digit up to seven (and nine, which
+take separate launches), integer and FP64 ciphertext limbs, a rotation (digits through the Galois map before they are raised),
+a relinearisation and a product whose giant steps are summed (digits through the map afterwards)."""
+import numpy as np
+import pytest
+
+from oracle import params
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_q,n_p,alpha,bits,levels", [
+    (9, 1, 1, (50, 49, 60), (8, 6, 0)),
+    (4, 2, 2, (61, 61, 61), (3,)),
+    (4, 2, 2, (50, 49, 60), (3, 1)),
+])
+def test_key_switches_match_the_oracle(n_q, n_p, alpha, bits, levels):
+    from oracle import ckks, packing, vmm
+    from paper_2602_11470_amd import binding as B
+    n = 65536
+    gctx = B.Context(n, n_q, n_p, alpha, *bits, 2.0 ** 40, hamming=64)
+    try:
+        mods = [int(x) for x in gctx.moduli()]
+        octx = ckks.Context(params.Params(n=n, q=mods[:n_q], p=mods[n_q:], alpha=alpha, scale=2.0 ** 40, hamming=64))
+        osk, gsk = octx.keygen_secret(3), gctx.keygen_secret(3)
+        plan = packing.make_plan(octx.S, 512, 512, 2)
+        steps = sorted(set(vmm.unrolled_steps(plan) + [1, -3])) if n_q == 4 and bits[0] == 50 else [1, -3]
+        okeys, gkeys = octx.keygen_rotations(osk, steps, 4, with_relin=True), gctx.keygen_rotations(gsk, steps, 4, with_relin=True)
+        rng = np.random.default_rng(n_q)
+        xc = octx.encode_coeffs(rng.uniform(-1, 1, octx.S), 2.0 ** 40)
+
+        def same(o, g):
+            assert np.array_equal(gctx.ct_export(g), octx.canonical(o))
+
+        for level in levels:
+            o = octx.encrypt(osk, octx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+            g = gctx.encrypt(gsk, gctx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+            for st in (1, -3):
+                same(octx.rotate(o, st, okeys), gctx.rotate(gkeys, g, st))
+            if level:
+                same(octx.relinearize(octx.mul_ct(o, o), okeys), gctx.relinearize(gkeys, gctx.mul_ct(g, g)))
+        if len(steps) > 2:
+            cs = rng.integers(-(1 << 40), 1 << 40, (plan.r_i * plan.r_o, n))
+            level = levels[0]
+            o = octx.encrypt(osk, octx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+            g = gctx.encrypt(gsk, gctx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+            od = [[octx.pt_from_coeffs_ext(cs[j * plan.r_o + k], level, 2.0 ** 40) for k in range(plan.r_o)] for j in range(plan.r_i)]
+            gplan = gctx.vmm_plan(512, 512, level=level, r_i=plan.r_i, coeffs=cs, unrolled_ladders=True)
+            same(vmm.vmm_pt_unrolled(octx, okeys, plan, o, od), gctx.vmm_pt(gkeys, gplan, g))
+    finally:
+        gctx.close()
