@@ -734,8 +734,10 @@ def main():
     conv, ntt = fam["base_conv"], fam["ntt_fwd"]
     ntt_per_launch_limbs = conv["units"] / conv["launches"]
     ntt_launch_s = conv["ms"] / conv["launches"] * 1e-3
-    # algorithmic bytes = read + write each limb once (1 MiB per 2^16-point limb)
-    ntt_gbs = ntt_per_launch_limbs * 2 * limb_bytes / ntt_launch_s / 1e9
+    # algorithmic bytes = read + write each limb once (1 MiB per 2^16-point limb); of the digits of the unrolled giant steps the
+    # family holds the first pass only (one write): their row pass is part of the inner products
+    half_limbs = (g["plan"].r_o - 1) * (beta * (limbs + K) - limbs) if not a.stored_a and not nested else 0
+    ntt_gbs = (2 * conv["units"] - half_limbs) * limb_bytes / (conv["ms"] * 1e-3) / 1e9
     # inner products: a launch of the batched kernel carries several (63 hoisted rotations, 7 giant
     # steps), so the figure is per inner product: family time / inner products
     ip = fam["inner_product"]
@@ -762,7 +764,7 @@ def main():
     mac = fam["vmm_mac"]
     # weight plaintexts under the 50-bit primes are stored in 50 of 64 bits
     mac_limbs = ext if not a.plain_sums else limbs
-    mac_bytes = limb_bytes * ((limbs * 50 / 64 + mac_limbs - limbs) * plan.r_i * plan.r_o + mac_limbs * 2 * (plan.r_i + plan.r_o))
+    mac_bytes = limb_bytes * ((limbs * 50 + (mac_limbs - limbs) * 60) / 64 * plan.r_i * plan.r_o + mac_limbs * 2 * (plan.r_i + plan.r_o))
     mac_s = mac["ms"] / mac["launches"] * 1e-3
     mac_gbs = mac_bytes / mac_s / 1e9
     tr = measured_traffic()
@@ -770,25 +772,25 @@ def main():
     roofs = {
         "ntt_fwd": {"bound": "hbm", "achieved": ntt_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": ntt_gbs / HBM_PEAK_GBS, "traffic": ntt_traffic,
-                    "kernel": "conv_cols_fwd+ntt_rows256_fwd (one launch of the pair: base conversion and columns, rows)",
+                    "kernel": "conv_cols_fwd (+ ntt_rows256_fwd, except for the digits of the giant steps)",
                     "limbs_per_launch": ntt_per_launch_limbs, "us_per_launch": ntt_launch_s * 1e6},
         "inner_product": {"bound": "hbm", "achieved": ip_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": ip_gbs / HBM_PEAK_GBS,
                           "traffic": (tr["inner_product_family_per_step"] / ip["units"]
                                       if default_form and "inner_product_family_per_step" in tr else None),
                           "kernel": "k_inner_product_fanout (the hoisted baby steps, digits read once per 8 keys) + "
-                                    "k_inner_product_batch (giant steps, ladder runs): per inner product, averaged over "
+                                    "k_rows_ip (giant steps, with the row pass of their digits) + k_inner_product_batch (ladder runs): per inner product, averaged over "
                                     "the inner products of a step",
                           "algorithmic_bytes_per_inner_product": ip_bytes,
                           "inner_products_per_step": ip["units"], "launches_per_step": ip["launches"],
                           "us_per_launch": ip_launch_s * 1e6},
         "inner_product_single": {"bound": "hbm", "achieved": ((1 + kh) * beta * W_ + 2 * W_) / t_ip_single / 1e9, "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": ((1 + kh) * beta * W_ + 2 * W_) / t_ip_single / 1e9 / HBM_PEAK_GBS,
-                                 "traffic": tr.get("k_inner_product"),
-                                 "kernel": "k_inner_product (the inner product of one un-hoisted key switch)",
+                                 "traffic": tr.get("k_rows_ip"),
+                                 "kernel": "k_rows_ip (row pass of the digits and inner product of one un-hoisted key switch)",
                                  "us_per_launch": t_ip_single * 1e6},
         "vmm_mac": {"bound": "hbm", "achieved": mac_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": mac_gbs / HBM_PEAK_GBS,
-                    "traffic": tr.get("k_vmm_mac<2>", tr.get("k_vmm_mac")), "kernel": "k_vmm_mac (one launch per step)",
+                    "traffic": tr.get("k_vmm_mac"), "kernel": "k_vmm_mac (one launch per step)",
                     "algorithmic_bytes_per_launch": mac_bytes, "us_per_launch": mac_s * 1e6},
     }
     # What plain streaming kernels of the same read/write mix reach on this device (cm_hbm_probe), and each family's rate
@@ -829,7 +831,7 @@ def main():
         "key_switches_per_s": 1.0 / t_rot, "key_switch_us": t_rot * 1e6,
         "key_switch_algorithmic_gbs": ks_bytes / t_rot / 1e9,
         "key_switch_frac_of_hbm_peak": ks_bytes / t_rot / 1e9 / HBM_PEAK_GBS,
-        "limb_ntts_per_s": (conv["units"] + ntt["units"]) / ((conv["ms"] + ntt["ms"]) * 1e-3),      # conversions in front included
+        "limb_ntts_per_s": (conv["units"] - half_limbs / 2 + ntt["units"]) / ((conv["ms"] + ntt["ms"]) * 1e-3),   # conversions in front included
         "limb_ntts_per_s_by_batch": {k: round(v) for k, v in rates.items()},
         "kernel_ms_per_step": {k: round(v["ms"], 4) for k, v in fam.items()},
         "dominant_kernel_family": dom,

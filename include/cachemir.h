@@ -437,8 +437,10 @@ cm_status cm_keyswitch(cm_ctx *ctx, const cm_evk *evk, int32_t step, int32_t rel
  * base conversion and element-wise kernels, 1 otherwise) and milliseconds of one family; the passes of one transform
  * count as one launch.  A base conversion is one kernel with the start (n = 4096: the whole) of the forward transform of its
  * results: CM_K_BASE_CONV holds the conversions with those transforms from the first pass to the last, CM_K_NTT_FWD the other
- * forward transforms, so that milliseconds over units is the time of a limb in either.  The ModDown tail runs inside
- * a transform: CM_K_MODDOWN_FINISH stays empty. */
+ * forward transforms, so that milliseconds over units is the time of a limb in either.  Two exceptions at n = 65536: the row pass
+ * of digits that meet one key each is part of CM_K_INNER_PRODUCT, and so is the first pass of the inverse transform of the special
+ * limbs of such a sum (CM_K_NTT_INV holds its second).  The ModDown tail runs inside a transform: CM_K_MODDOWN_FINISH stays
+ * empty. */
 enum {
     CM_K_NTT_FWD = 0, CM_K_NTT_INV = 1, CM_K_BASE_CONV = 2, CM_K_INNER_PRODUCT = 3,
     CM_K_MODDOWN_FINISH = 4, CM_K_VMM_MAC = 5, CM_K_ELEMENTWISE = 6, CM_K_RESCALE = 7,

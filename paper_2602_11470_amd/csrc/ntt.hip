@@ -873,9 +873,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict_
 // worth 1 %; three waves spill 26 registers and lose 3 to 10 %, four lose 20 %).  Row passes and inner products in launches of
 // their own -> here: the seven giant steps at level 22 195 + 236 -> 388 us; two launches a key switch fewer: ciphertext product at
 // level 13 151.6 -> 145.6 us, rotary embedding at level 3 82.9 -> 76.9, query times K at level 12 16730 -> 16020, scores times V at
-// level 22 4082 -> 3852, 4096 x 4096 product at level 23 4738 -> 4532.  Eight relinearisations at level 22, whose key draws the
-// shared-key kernel forms once, 218 + 205 + 25 (inverse row pass) -> 447.
+// level 22 4082 -> 3852, 4096 x 4096 product at level 23 4738 -> 4532.  Eight relinearisations with one key at level 22, inverse row
+// pass included: 218 + 205 + 25 in launches of their own, 459 with the draws of every output formed anew, 382 with them kept in LDS
+// (at level 9 132, 159 and 145, one launch instead of three; at level 3 56, 78 and 64; the calls as a whole are faster at all levels).
 #define RIP_WAVES 4
+#define RIP_ROW (256 + 16)
 typedef u64 u64x2_t __attribute__((ext_vector_type(2)));
 // Sums of products d w and d v, w in multiplier form, v a raw draw.  LAZY: they run over all items of an output (each term is below
 // 2^57 and an accumulator holds 128); the integer limbs' are reduced item by item (eight terms below q 2^64 fit 128 bits).
@@ -923,9 +925,11 @@ __device__ __forceinline__ void rip_out(u64 *lds, u64 *out, const u64 (&x)[4], c
 #pragma unroll
     for (int k = 0; k < 4; k++) ntt_store(0, word_at(out + 256 * R, sub + 64 * k), ai.to_mid(v[k]));
 }
-template <class A, class S>
+// SHARED: one key for all outputs (one item each, no Galois element): the wave runs over outputs z0 .. z1-1, draws the uniform half
+// of its key words once into LDS and keeps the twiddles.
+template <class A, class S, bool SHARED>
 __device__ __forceinline__ void rip_body(u64 *lds, const IpBatch &b, const RipArgs &p, const FoldIn &fi, const NttTables &t, const NttTables &ti,
-                                         int r, int mi, unsigned R, int z) {
+                                         int r, int mi, unsigned R, int z0, int z1) {
     const ModC m = t.modc[mi];
     const int n = p.n, sub = threadIdx.x & 63, special = p.ext - p.level - 1, out_rows = b.apart ? p.ext + (b.nsum - 1) * special : p.ext;
     const unsigned pos = 256 * R + 4 * sub;
@@ -938,14 +942,12 @@ __device__ __forceinline__ void rip_body(u64 *lds, const IpBatch &b, const RipAr
     ar.init(t, mi, n);
     S acc[4];
     u64 r0[4], r1[4];                                     // what the sums leave, integer limbs: item by item
-#pragma unroll
-    for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
     // The words of digit j of item s, half-transformed (or, of the digit that holds limb r itself, as they are), and of its key:
     // requested one digit ahead.
     const int jo = r <= p.level ? r / p.alpha : -1;
     u64 raw[4];
     u64x2_t w01, w23;
-    auto request = [&](int s, int j) {
+    auto request = [&](int z, int s, int j) {
         const IpItem &it = b.it[z * b.nsum + s];
         const u64 *kb = it.key + ((size_t)j * p.nmod + mi) * n + 256 * R;
         if (j == jo) {
@@ -959,106 +961,133 @@ __device__ __forceinline__ void rip_body(u64 *lds, const IpBatch &b, const RipAr
 #pragma unroll
             for (int k = 0; k < 4; k++) raw[k] = __builtin_nontemporal_load(word_at(h, 64 * k + sub));
         }
-        w01 = __builtin_nontemporal_load(reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub)));
-        w23 = __builtin_nontemporal_load(reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub + 2)));
+        const u64x2_t *k01 = reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub)), *k23 = reinterpret_cast<const u64x2_t *>(word_at(kb, 4 * sub + 2));
+        if (SHARED) w01 = *k01, w23 = *k23;               // read again for the next output
+        else w01 = __builtin_nontemporal_load(k01), w23 = __builtin_nontemporal_load(k23);
     };
-    request(0, 0);
-    for (int s = 0; s < b.nsum; s++) {
-        const IpItem &it = b.it[z * b.nsum + s];
-        const unsigned g = it.g, src_row = g ? perm_src(256 * R, g, p.logn) >> 8 : R;
-        const SmallTw<A> tw(ar, 256 + src_row, sub);
-        for (int j = 0; j < p.beta; j++) {
-            const u64 sk = it.key[(size_t)p.kdig * p.nmod * n + (size_t)j * p.nmod + mi];
-            u64 d[4];
-            typename A::T x[4];
-            const u64 wk[4] = {w01.x, w01.y, w23.x, w23.y};
+    auto stream_key = [&](const IpItem &it, int j) { return it.key[(size_t)p.kdig * p.nmod * n + (size_t)j * p.nmod + mi]; };
+    auto draws = [&](u64 sk, u64 (&v)[4]) {
+        bool rej = false;
 #pragma unroll
-            for (int k = 0; k < 4; k++) d[k] = raw[k], x[k] = ar.from_mid(raw[k]);
-            if (j + 1 < p.beta) request(s, j + 1);
-            else if (s + 1 < b.nsum) request(s + 1, 0);
+        for (int k = 0; k < 4; k++) v[k] = mix64(gv + (sk + ((u64)(256 * R + k) + 1) * GOLD)), rej |= v[k] >= bound;
+        if (rej) {
             unsigned ps = pos;
             OPAQUE(ps);
-            if (j != jo) {
-                wave_sync();
-                small_fwd(lds, x, ar, tw, sub, at, WaveSync());
 #pragma unroll
-                for (int k = 0; k < 4; k++) d[k] = ar.to_rest_fwd(x[k]);
-                if (g) {
+            for (int k = 0; k < 4; k++) v[k] = evk_a_draw(sk, ((u64)(ps + k) + 1) * GOLD, ps + k, bound);
+        }
+    };
+    u64x2_t *drawn = reinterpret_cast<u64x2_t *>(lds + RIP_ROW) + 2 * sub;           // a lane's own words
+    if (SHARED) {
+        for (int j = 0; j < p.beta; j++) {
+            u64 v[4];
+            draws(stream_key(b.it[z0], j), v);
+            drawn[128 * j] = u64x2_t{v[0], v[1]}, drawn[128 * j + 1] = u64x2_t{v[2], v[3]};
+        }
+    }
+    request(z0, 0, 0);
+    for (int z = z0; z < (SHARED ? z1 : z0 + 1); z++) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
+        for (int s = 0; s < b.nsum; s++) {
+            const IpItem &it = b.it[z * b.nsum + s];
+            const unsigned g = it.g, src_row = g ? perm_src(256 * R, g, p.logn) >> 8 : R;
+            const SmallTw<A> tw(ar, 256 + src_row, sub);
+            for (int j = 0; j < p.beta; j++) {
+                const u64 sk = SHARED ? 0 : stream_key(it, j);
+                u64 d[4];
+                typename A::T x[4];
+                const u64 wk[4] = {w01.x, w01.y, w23.x, w23.y};
+#pragma unroll
+                for (int k = 0; k < 4; k++) d[k] = raw[k], x[k] = ar.from_mid(raw[k]);
+                if (j + 1 < p.beta) request(z, s, j + 1);
+                else if (s + 1 < b.nsum) request(z, s + 1, 0);
+                else if (SHARED && z + 1 < z1) request(z + 1, 0, 0);
+                unsigned ps = pos;
+                OPAQUE(ps);
+                if (j != jo) {
                     wave_sync();
+                    small_fwd(lds, x, ar, tw, sub, at, WaveSync());
 #pragma unroll
-                    for (int k = 0; k < 4; k++) lds[at(4 * sub, 1, k)] = d[k];
-                    wave_sync();
+                    for (int k = 0; k < 4; k++) d[k] = ar.to_rest_fwd(x[k]);
+                    if (g) {
+                        wave_sync();
 #pragma unroll
-                    for (int k = 0; k < 4; k++) d[k] = lds[pad(perm_src(ps + k, g, p.logn) & 255)];
+                        for (int k = 0; k < 4; k++) lds[at(4 * sub, 1, k)] = d[k];
+                        wave_sync();
+#pragma unroll
+                        for (int k = 0; k < 4; k++) d[k] = lds[pad(perm_src(ps + k, g, p.logn) & 255)];
+                    }
+                }
+                u64 v[4];
+                if (SHARED) {
+                    const u64x2_t v01 = drawn[128 * j], v23 = drawn[128 * j + 1];
+                    v[0] = v01.x, v[1] = v01.y, v[2] = v23.x, v[3] = v23.y;
+                } else {
+                    draws(sk, v);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) acc[k].mac(d[k], wk[k], v[k]);
+            }
+            if (it.c0 && (it.c0_ext || r <= p.level)) {
+                const u64 w = it.c0_ext ? redc((u128)m.r2, m.q, m.qinv) : p.pmont[r];        // 1 or P in multiplier form
+#pragma unroll
+                for (int k = 0; k < 4; k++) acc[k].mac_b(*word_at(it.c0 + (size_t)r * n, g ? perm_src(pos + k, g, p.logn) : pos + k), w);
+            }
+            if (!S::LAZY || apart || s + 1 == b.nsum) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const u64 x = acc[k].sum_b(m), y = acc[k].sum_a(m);
+                    r0[k] = S::LAZY ? x : addmod(r0[k], x, m.q), r1[k] = S::LAZY ? y : addmod(r1[k], y, m.q);
+                    acc[k] = S();
                 }
             }
-            u64 v[4];
-            bool rej = false;
+            if (apart) {                                      // this item's special limb by itself
+                u64 *out = b.out[z] + (size_t)(r + s * special) * n;
+                rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
+                rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
 #pragma unroll
-            for (int k = 0; k < 4; k++) v[k] = mix64(gv + (sk + ((u64)(256 * R + k) + 1) * GOLD)), rej |= v[k] >= bound;
-            if (rej) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) v[k] = evk_a_draw(sk, ((u64)(ps + k) + 1) * GOLD, ps + k, bound);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; k++) acc[k].mac(d[k], wk[k], v[k]);
-        }
-        if (it.c0 && (it.c0_ext || r <= p.level)) {
-            const u64 w = it.c0_ext ? redc((u128)m.r2, m.q, m.qinv) : p.pmont[r];        // 1 or P in multiplier form
-#pragma unroll
-            for (int k = 0; k < 4; k++) acc[k].mac_b(*word_at(it.c0 + (size_t)r * n, g ? perm_src(pos + k, g, p.logn) : pos + k), w);
-        }
-        if (!S::LAZY || apart || s + 1 == b.nsum) {
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const u64 x = acc[k].sum_b(m), y = acc[k].sum_a(m);
-                r0[k] = S::LAZY ? x : addmod(r0[k], x, m.q), r1[k] = S::LAZY ? y : addmod(r1[k], y, m.q);
-                acc[k] = S();
+                for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
             }
         }
-        if (apart) {                                      // this item's special limb by itself
-            u64 *out = b.out[z] + (size_t)(r + s * special) * n;
-            rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
-            rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
+        if (apart) continue;
+        if (b.extra[z]) {
+            const u64 *e = b.extra[z] + (size_t)r * n;
 #pragma unroll
-            for (int k = 0; k < 4; k++) r0[k] = r1[k] = 0;
+            for (int k = 0; k < 4; k++)
+                r0[k] = addmod(r0[k], *word_at(e, pos + k), m.q), r1[k] = addmod(r1[k], *word_at(e + (size_t)out_rows * n, pos + k), m.q);
         }
-    }
-    if (apart) return;
-    if (b.extra[z]) {
-        const u64 *e = b.extra[z] + (size_t)r * n;
+        if (fi.per && r == p.level) {
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-            r0[k] = addmod(r0[k], *word_at(e, pos + k), m.q), r1[k] = addmod(r1[k], *word_at(e + (size_t)out_rows * n, pos + k), m.q);
-    }
-    if (fi.per && r == p.level) {
+            for (int c = 0; c < 2; c++) {
+                const size_t row = ((size_t)c * fi.rows + fi.rows - 1) * n;
 #pragma unroll
-        for (int c = 0; c < 2; c++) {
-            const size_t row = ((size_t)c * fi.rows + fi.rows - 1) * n;
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                u64 x = 0;
-                if (fi.add && c < fi.add_comps) x = fi.add[z * fi.add_stride + row + (fi.g ? perm_src(pos + k, fi.g, p.logn) : pos + k)];
-                if (fi.acc) x = addmod(x, fi.acc[z * fi.acc_stride + row + pos + k], m.q);
-                x = redc((u128)x * fi.pm, m.q, m.qinv);
-                if (c) r1[k] = addmod(r1[k], x, m.q);
-                else r0[k] = addmod(r0[k], x, m.q);
+                for (int k = 0; k < 4; k++) {
+                    u64 x = 0;
+                    if (fi.add && c < fi.add_comps) x = fi.add[z * fi.add_stride + row + (fi.g ? perm_src(pos + k, fi.g, p.logn) : pos + k)];
+                    if (fi.acc) x = addmod(x, fi.acc[z * fi.acc_stride + row + pos + k], m.q);
+                    x = redc((u128)x * fi.pm, m.q, m.qinv);
+                    if (c) r1[k] = addmod(r1[k], x, m.q);
+                    else r0[k] = addmod(r0[k], x, m.q);
+                }
             }
         }
+        u64 *out = b.out[z] + (size_t)r * n;
+        rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
+        rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
     }
-    u64 *out = b.out[z] + (size_t)r * n;
-    rip_out<A>(lds, out, r0, p, ti, r, mi, R, sub);
-    rip_out<A>(lds, out + (size_t)out_rows * n, r1, p, ti, r, mi, R, sub);
 }
-// grid: x = 64 workgroups of four rows, y = limb (special primes first), z = output
-__global__ __launch_bounds__(64 * RIP_WAVES, 2) void k_rows_ip(IpBatch b, RipArgs p, FoldIn fi, NttTables t, NttTables ti) {
-    __shared__ u64 lds[RIP_WAVES * (256 + 16)];
+// grid: x = 64 workgroups of four rows, y = limb (special primes first), z = output, or a run of `per` outputs with one key
+template <bool SHARED>
+__global__ __launch_bounds__(64 * RIP_WAVES, 2) void k_rows_ip(IpBatch b, RipArgs p, FoldIn fi, NttTables t, NttTables ti, int per) {
+    extern __shared__ u64 lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = p.ext - 1 - (int)blockIdx.y;
     const int mi = r <= p.level ? r : p.L + 1 + (r - p.level - 1);
-    u64 *l = lds + wave * (256 + 16);
+    u64 *l = lds + wave * (RIP_ROW + (SHARED ? 256 * p.beta : 0));
     const unsigned R = blockIdx.x * RIP_WAVES + wave;
-    if (t.fpq[mi].q != 0.0) rip_body<FpArith, RipFp>(l, b, p, fi, t, ti, r, mi, R, blockIdx.z);
-    else rip_body<IntArith, RipInt>(l, b, p, fi, t, ti, r, mi, R, blockIdx.z);
+    const int z0 = blockIdx.z * per, z1 = min(z0 + per, b.nz);
+    if (t.fpq[mi].q != 0.0) rip_body<FpArith, RipFp, SHARED>(l, b, p, fi, t, ti, r, mi, R, z0, z1);
+    else rip_body<IntArith, RipInt, SHARED>(l, b, p, fi, t, ti, r, mi, R, z0, z1);
 }
 
 // ---- the whole transform of a limb of 4096 words (n = 4096) in one workgroup ---------------------------------
@@ -1676,6 +1705,8 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 }
 // a digit or a first component is a term of the sums (RipFp: 128 of them); an item of an integer limb holds eight
 #define RIP_MAX_TERMS 120
+#define RIP_SHARED_BETA 6          // draws of a wave: 2 KiB a digit, 64 KiB a workgroup
+#define RIP_FILL 4096              // twice the waves that the chip holds at two a SIMD (8192 measured the same)
 bool rows_ip_fits(const cm_ctx *ctx, int beta, int nsum) {
     return ctx->n == 65536 && !ctx->evk_stored_a && beta <= 7 && nsum * (beta + 1) <= RIP_MAX_TERMS;
 }
@@ -1685,8 +1716,19 @@ void launch_rows_ip(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStrea
     RipArgs p;
     p.beta = beta, p.ext = ext, p.level = level, p.alpha = ctx->alpha, p.L = ctx->L, p.nmod = ctx->nmod, p.n = ctx->n, p.logn = ctx->logn;
     p.kdig = (ctx->L + ctx->alpha) / ctx->alpha, p.inv_from = inv_from, p.ubound = ctx->d_ubound, p.pmont = ctx->d_pmont;
-    hipLaunchKernelGGL(k_rows_ip, dim3(ctx->n / (256 * RIP_WAVES), ext, b.nz), dim3(64 * RIP_WAVES), 0, st, b, p, fi,
-                       tables_of(ctx, false, 0), tables_of(ctx, true, 0));
+    const NttTables t = tables_of(ctx, false, 0), ti = tables_of(ctx, true, 0);
+    bool shared = b.nz > 1 && b.nsum == 1 && beta <= RIP_SHARED_BETA;
+    for (int z = 0; z < b.nz; z++) shared = shared && b.it[z].key == b.it[0].key && !b.it[z].g;
+    if (shared) {
+        // runs as long as they leave RIP_FILL waves
+        int per = b.nz;
+        while (per > 1 && ctx->n / 256 * ext * ((b.nz + per - 1) / per) < RIP_FILL) per = (per + 1) / 2;
+        hipLaunchKernelGGL(k_rows_ip<true>, dim3(ctx->n / (256 * RIP_WAVES), ext, (b.nz + per - 1) / per), dim3(64 * RIP_WAVES),
+                           RIP_WAVES * (RIP_ROW + 256 * beta) * 8, st, b, p, fi, t, ti, per);
+        return;
+    }
+    hipLaunchKernelGGL(k_rows_ip<false>, dim3(ctx->n / (256 * RIP_WAVES), ext, b.nz), dim3(64 * RIP_WAVES), RIP_WAVES * RIP_ROW * 8, st, b, p, fi, t,
+                       ti, 1);
 }
 void launch_ntt_rows(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod_idx, int limbs,
                      bool inverse, hipStream_t st) {
