@@ -39,6 +39,8 @@ struct MulPtBatch {
 void launch_mul_pt_rot_batch(cm_ctx *ctx, u64 *out, const MulPtBatch &b, int cnt, const u64 *pt_mont, int limbs, hipStream_t st);
 // the same products on the last of the `limbs` limbs only: out[z][2][n]
 void launch_mul_pt_rot_last(cm_ctx *ctx, u64 *out, const MulPtBatch &b, int cnt, const u64 *pt_mont, int limbs, hipStream_t st);
+// and their inverse transform (modulus indices d_mods: the last limb's, 2 cnt times)
+void launch_mul_pt_rot_last_inv(cm_ctx *ctx, u64 *out, const MulPtBatch &b, int cnt, const u64 *pt_mont, int limbs, const int *d_mods, hipStream_t st);
 // acc[2][limbs][n] (+)= sum_{z<cnt} src[z] * (pt rotated by b.g[z]), src[z] = src + z*2*limbs*n (b.src unused)
 void launch_mac_pt_rot_batch(cm_ctx *ctx, u64 *acc, const u64 *src, const MulPtBatch &b, int cnt, const u64 *pt_mont,
                              int limbs, int accumulate, hipStream_t st);

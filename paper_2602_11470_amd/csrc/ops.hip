@@ -1024,8 +1024,7 @@ bool rescale_masked_into(cm_ctx *ctx, const MulPtBatch &mb, int cnt, const u64 *
     const KsLevelFull &k = ks_level_full(ctx, level);
     if (!k.last_fits || cnt < 1 || cnt > CM_MASK_BATCH || !last || !red) return false;
     if (ctx->two_step_masks) return false;                  // CM_OPT_TWO_STEP_MASKS: multiply, store, then rescale
-    launch_mul_pt_rot_last(ctx, last, mb, cnt, pt, level + 1, st);
-    launch_ntt(ctx, last, k.d_last_mods, 2 * cnt, true, st);
+    launch_mul_pt_rot_last_inv(ctx, last, mb, cnt, pt, level + 1, k.d_last_mods, st);
     FinishBatch fb;
     fb.items = cnt, fb.level = level - 1, fb.ext = level + 1, fb.addend_comps = 0, fb.ncomp = 2, fb.comp0 = 0;
     for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
