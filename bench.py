@@ -794,16 +794,16 @@ def main():
                     "algorithmic_bytes_per_launch": mac_bytes, "us_per_launch": mac_s * 1e6},
     }
     # What plain streaming kernels of the same read/write mix reach on this device (cm_hbm_probe), and each family's rate
-    # as a fraction of it.  A converted limb is written by the conversion, read and written by the row pass; with the sources and
-    # the copied limbs the pair's traffic is what the counter summary holds per limb (1.5 MiB of it for the limb itself).
+    # as a fraction of it.  A converted limb is written by the conversion, read and written by the row pass (1.5 MiB), except where the row pass
+    # is part of the inner product (0.5 MiB).
     B = g["B"]
     probe = {"read": B.hbm_probe(B.CM_PROBE_READ), "read1_write1": B.hbm_probe(B.CM_PROBE_COPY),
              "read3_write1": B.hbm_probe(B.CM_PROBE_READ3_WRITE1), "unit": "GB/s",
              "what": "best of 5 passes of a plain streaming kernel over 4 GiB (16-byte non-temporal accesses): reads only; one "
                      "read and one write stream; three read streams and one write stream"}
-    ntt_moved = ntt_traffic if ntt_traffic else 3 * limb_bytes * ntt_per_launch_limbs
+    ntt_moved = ntt_traffic if ntt_traffic else (3 * conv["units"] - 2 * half_limbs) * limb_bytes / conv["launches"]
     roofs["ntt_fwd"]["frac_of_probe"] = ntt_moved / ntt_launch_s / 1e9 / probe["read1_write1"]
-    roofs["ntt_fwd"]["probe"] = "read1_write1, against the pair's traffic"
+    roofs["ntt_fwd"]["probe"] = "read1_write1, against the limbs' own reads and writes"
     roofs["inner_product"]["frac_of_probe"] = ip_gbs / probe["read3_write1"]
     roofs["inner_product"]["probe"] = "read3_write1"
     roofs["inner_product_single"]["frac_of_probe"] = roofs["inner_product_single"]["achieved"] / probe["read"]
