@@ -88,8 +88,8 @@ struct IpItem {
 };
 struct IpBatch {
     int nz = 0, nsum = 1;
-    // the special limbs of the nsum items are not summed but stored one item after the other: out[z] and extra[z] are
-    // [2][level + 1 + nsum K][n]
+    // the special limbs of the nsum items are not summed but stored one item after the other: out[z] is
+    // [2][level + 1 + nsum K][n], and extra[z] is null
     bool apart = false;
     IpItem it[IP_MAX_ITEMS];
     u64 *out[IP_MAX_ITEMS] = {};

@@ -58,3 +58,27 @@ def test_embedding_and_product_match_the_oracle(n, n_q, n_p, alpha, q0_bits, qi_
                 assert np.array_equal(gctx.ct_export(gctx.vmm_pt(gkeys, gplan, gx)), octx.canonical(oy)), (level, form)
     finally:
         gctx.close()
+
+
+@pytest.mark.parametrize("n,n_q,n_p,alpha", [(4096, 4, 2, 2), (65536, 5, 4, 4)])
+def test_embedding_with_stored_key_halves_matches_the_oracle(n, n_q, n_p, alpha):
+    from oracle import ckks, packing, vmm
+    from paper_2602_11470_amd import binding as B
+    gctx = B.Context(n, n_q, n_p, alpha, 50, 49, 60, 2.0 ** 40, hamming=64)
+    try:
+        gctx.set_option(B.CM_OPT_EVK_STORED_A, 1)
+        mods = [int(x) for x in gctx.moduli()]
+        octx = ckks.Context(params.Params(n=n, q=mods[:n_q], p=mods[n_q:], alpha=alpha, scale=2.0 ** 40, hamming=64))
+        osk, gsk = octx.keygen_secret(3), gctx.keygen_secret(3)
+        rng = np.random.default_rng(n)
+        level, lay = n_q - 1, packing.KvLayout(octx.S, 16, 16)
+        steps = [lay.rope_step, -lay.rope_step]
+        okeys, gkeys = octx.keygen_rotations(osk, steps, 4), gctx.keygen_rotations(gsk, steps, 4)
+        xc, coeffs = octx.encode_coeffs(rng.uniform(-1, 1, octx.S), 2.0 ** 40), rng.integers(-(1 << 40), 1 << 40, (3, n))
+        ox = octx.encrypt(osk, octx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+        gx = gctx.encrypt(gsk, gctx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+        want = vmm.rope(vmm.CkksOps(octx, okeys), lay, ox, [octx.pt_from_coeffs(c, level, float(mods[level])) for c in coeffs])
+        got = gctx.rope_apply(gkeys, gctx.rope(16, 16, level, 1, 0, coeffs=coeffs), gx)
+        assert np.array_equal(gctx.ct_export(got), octx.canonical(want))
+    finally:
+        gctx.close()
