@@ -98,8 +98,10 @@ struct IpBatch {
 void launch_inner_product_batch(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st);
 // The same sums from half-transformed digits (ConvBatch::half): the row pass of every digit, the inner products and, for the rows
 // from inv_from on (0: none), the row pass of the inverse transform in one launch (n = 65536, keys without stored halves:
-// rows_ip_fits).  What fi describes (one output a component pair, row `level`) joins before that.
-bool rows_ip_fits(const cm_ctx *ctx, int beta, int nsum);
+// rows_ip_fits: possible, and the better one, for nz outputs of nsum <= rows_ip_items items each).  What fi describes (one output a
+// component pair, row `level`) joins before that.
+int rows_ip_items(int beta);
+bool rows_ip_fits(const cm_ctx *ctx, int beta, int level, int nz, int nsum);
 void launch_rows_ip(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st, int inv_from = 0, const FoldIn &fi = FoldIn());
 // na = 2 or 3 keys (Galois elements g[a] != 0) applied to the nz digit arrays b.it[z].dig and summed into out[z] together with
 // extra[z] and, per key, the first component b.it[z].c0 (extended basis) through that key's Galois map.  Returns false

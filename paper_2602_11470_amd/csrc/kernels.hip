@@ -1199,9 +1199,9 @@ __global__ __launch_bounds__(TPB) void k_vmm_mac(u64 *__restrict__ out, const u6
 }
 // Fewer than eight baby steps (RI = 1, 2 or 4): a lane keeps its baby words and runs over MAC_FEW_K giant steps, the words of the
 // next one requested ahead.  Bound by HBM, mostly by the sums it writes (2 words for RI read), so these are stored at agent scope.
-// 512 products at level 4, RI = 1, 2, 4 (0.5 to 2.7 GB written, 1.3 GB read): 737, 477 and 353 us; with 8-byte loads at stride two
+// 512 products at level 4, RI = 1, 2, 4 (2.7, 1.3 and 0.7 GB written, 1.3 GB read): 737, 477 and 353 us; with 8-byte loads at stride two
 // and plain stores 752, 692 and 564; in the kernel for eight baby steps and more (with 128-bit sums) 1141, 554 and 371.  32 x 4 at n = 4096:
-// 14 us, 24, 20.  Four or sixteen giant steps a lane: 2 % slower to 4 % faster, and 30 % slower at n = 4096.
+// 14 us, 24, 20.  Four giant steps a lane: 4 % slower to 4 % faster; sixteen: 2 % faster, and 30 % slower at n = 4096.
 #define MAC_FEW_K 8
 template <int RI>
 __global__ __launch_bounds__(TPB) void k_vmm_mac_few(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,

@@ -481,7 +481,7 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         u64 *outs[CM_KS_BATCH];
         // tensor products, relinearised together
         launch_tensor_batch(ctx, TB, cq, kv->d_k + (size_t)c0 * ctw, m, limbs, st);
-        const bool half = rows_ip_fits(ctx, kl.beta, 1), drop = ks_drop_fits(ctx, lv, 1, m);
+        const bool half = rows_ip_fits(ctx, kl.beta, lv, m, 1), drop = ks_drop_fits(ctx, lv, 1, m);
         CMCHK(ks_raise_many(ctx, kv->relin_tabs, TB, ksin, digits, st, m, 0, half));
         const size_t ublk = 2 * (size_t)kl.ext * n, dblk = (size_t)kl.beta * kl.ext * n;
         IpBatch ip;
@@ -577,7 +577,7 @@ static cm_status kv_qk(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         launch_raise_by_P(ctx, cur, kv->d_A, lv - 1, st, 1);
         for (int k0 = 1; k0 < kv->shared; k0 += CM_KS_BATCH) {
             const int m = kv->shared - k0 < CM_KS_BATCH ? kv->shared - k0 : CM_KS_BATCH;
-            const bool half = rows_ip_fits(ctx, kl1.beta, m);
+            const bool half = rows_ip_fits(ctx, kl1.beta, lv - 1, 1, m);
             CMCHK(ks_raise_many(ctx, kv->rot_tabs, kv->d_A + (size_t)k0 * ctw1, ksin, digits, st, m, 0, half));
             IpBatch b;
             b.nz = 1, b.nsum = m;
@@ -657,7 +657,7 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         const int m = kv->r_o - g0 < CM_KS_BATCH ? kv->r_o - g0 : CM_KS_BATCH;
         if (array == kv->d_x) launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * ctw, kv->r_i, m, limbs, st, 1, kv->r_o);
         else launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * kv->r_i * ctw, kv->r_i, m, limbs, st);
-        const bool half = rows_ip_fits(ctx, kl.beta, 1);
+        const bool half = rows_ip_fits(ctx, kl.beta, lv, m, 1);
         CMCHK(ks_raise_many(ctx, kv->relin_tabs, T, ksin, bdigits, st, m, 0, half));
         u64 *bu = arena_batch_sums(ctx);
         IpBatch ip;
@@ -681,7 +681,7 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         launch_raise_by_P(ctx, cur, inner, lv, st);
         for (int g0 = 1; g0 < kv->r_o; g0 += CM_KS_BATCH) {
             const int m = kv->r_o - g0 < CM_KS_BATCH ? kv->r_o - g0 : CM_KS_BATCH;
-            const bool half = rows_ip_fits(ctx, kl.beta, m);
+            const bool half = rows_ip_fits(ctx, kl.beta, lv, 1, m);
             CMCHK(ks_raise_many(ctx, kv->giant_tabs, inner + (size_t)g0 * ctw, ksin, bdigits, st, m, 0, half));
             IpBatch b;
             b.nz = 1, b.nsum = m;

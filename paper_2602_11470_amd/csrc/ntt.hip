@@ -1750,8 +1750,20 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 #define RIP_MAX_TERMS 120
 #define RIP_SHARED_BETA 6          // draws of a wave: 2 KiB a digit, 64 KiB a workgroup
 #define RIP_FILL 4096              // twice the waves that the chip holds at two a SIMD (8192 measured the same)
-bool rows_ip_fits(const cm_ctx *ctx, int beta, int nsum) {
-    return ctx->n == 65536 && !ctx->evk_stored_a && beta <= 7 && nsum * (beta + 1) <= RIP_MAX_TERMS;
+int rows_ip_items(int beta) { return RIP_MAX_TERMS / (beta + 1); }
+// Integer ciphertext limbs (from 2^50 on): every wave of a sum of several items takes about the same long time, 256 of them a limb
+// and output, and the chip holds RIP_WAVES_HELD at two a SIMD, so a launch takes whole rounds.  Where the last one is filled to less
+// than 7/8, the row pass in a launch of its own is faster.  query times K (12 heads x 64, 17 key ciphertexts) with 58-bit primes and
+// two special ones at level 7, 9 limbs, 1.1 rounds: 3320 us joined, 2940 apart; with 61-bit ones at level 2, 0.5 rounds: 1020 and 963;
+// with six special primes at level 11, 2.1 rounds: 3920 and 3680; filled to 7/8 and more: level 13, 15 limbs, 6880 and 7120, embedding
+// at level 4, 7 limbs, 98 and 103, with one special prime at level 6, 8 limbs, 143 and 157.  Single items and FP64 limbs (half the
+// time a wave, more waves' worth of waiting to hide) are as fast or faster joined at every size measured.
+#define RIP_WAVES_HELD 2048
+bool rows_ip_fits(const cm_ctx *ctx, int beta, int level, int nz, int nsum) {
+    if (ctx->n != 65536 || ctx->evk_stored_a || beta > 7 || nsum > rows_ip_items(beta)) return false;
+    if (nsum == 1 || ctx->mod[level] < (1ULL << 50)) return true;
+    const int waves = ctx->n / 256 * (level + 1 + ctx->K) * nz, rounds = (waves + RIP_WAVES_HELD - 1) / RIP_WAVES_HELD;
+    return 8 * waves >= 7 * rounds * RIP_WAVES_HELD;
 }
 void launch_rows_ip(cm_ctx *ctx, const IpBatch &b, int beta, int level, hipStream_t st, int inv_from, const FoldIn &fi) {
     const int ext = level + 1 + ctx->K;

@@ -329,7 +329,7 @@ cm_status ks_one(cm_ctx *ctx, const u64 *d, const u64 *key, int level, u64 g, co
                  const u64 *accum, const u64 *extra) {
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
-    const bool half = rows_ip_fits(ctx, k.beta, 1);
+    const bool half = rows_ip_fits(ctx, k.beta, level, 1, 1);
     CMCHK(ks_raise(ctx, d, level, A.digits, st, g, half));
     if (half) {
         IpBatch b;
@@ -1162,7 +1162,7 @@ cm_status rotate_rescale_into(cm_ctx *ctx, const u64 *key, const u64 *in, int le
     const KsLevelFull &k = ks_level_full(ctx, level);
     Arena A = arena_of(ctx);
     const u64 *d = in + (size_t)(level + 1) * ctx->n;
-    const bool half = rows_ip_fits(ctx, k.beta, 1);
+    const bool half = rows_ip_fits(ctx, k.beta, level, 1, 1);
     CMCHK(ks_raise(ctx, d, level, A.digits, st, g, half));
     if (half) {
         IpBatch b;

@@ -189,7 +189,7 @@ extern "C" cm_status cm_rope_apply(cm_ctx *ctx, const cm_evk *evk, const cm_rope
         u64 *digits = arena_digits(ctx);
         hipLaunchKernelGGL(k_mul_pt3_rot, dim3(n / 256, 2 * limbs), dim3(256), 0, st, a, b, x->dev, r->d_pts, ctx->d_modc, limbs, (int)n,
                            ctx->logn, (unsigned)g_up, (unsigned)g_dn);
-        const bool half = rows_ip_fits(ctx, kl.beta, 2);
+        const bool half = rows_ip_fits(ctx, kl.beta, level, 1, 2);
         CMCHK(ks_raise_many(ctx, r->tabs, b, c, digits, st, -1, 0, half));
         IpBatch ip;
         ip.nz = 1, ip.nsum = 2, ip.apart = true;

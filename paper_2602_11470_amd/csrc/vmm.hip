@@ -409,8 +409,9 @@ static cm_status vmm_raised_finish(cm_ctx *ctx, const cm_evk *evk, const cm_vmm_
         for (int k = 0; k < cnt; k++) outs.push_back(cts + (size_t)k * ctw);
         CMCHK(moddown_many_second(ctx, inner + rw, level, cnt, outs.data(), st));
         int most = cnt < IP_MAX_ITEMS ? cnt : IP_MAX_ITEMS;         // rotations summed onto inner_0 by one launch
-        const bool half = rows_ip_fits(ctx, kl.beta, 1);
-        while (half && most > 1 && !rows_ip_fits(ctx, kl.beta, most)) most--;
+        const int joined = most < rows_ip_items(kl.beta) ? most : rows_ip_items(kl.beta);
+        const bool half = rows_ip_fits(ctx, kl.beta, level, 1, joined);
+        if (half) most = joined;
         CMCHK(ks_raise_many(ctx, p->many, cts, ksin, digs, st, -1, 0, half));
         for (int k0 = 1; k0 < r_o; k0 += most) {
             IpBatch b;

@@ -49,3 +49,28 @@ def test_key_switches_match_the_oracle(n_q, n_p, alpha, bits, levels):
             same(vmm.vmm_pt_unrolled(octx, okeys, plan, o, od), gctx.vmm_pt(gkeys, gplan, g))
     finally:
         gctx.close()
+
+
+@pytest.mark.parametrize("level", [6, 3])
+def test_sums_of_integer_limbs_match_the_oracle(level):
+    """Three giant steps under 61-bit primes: eight limbs fill the chip and are joined, five are not."""
+    from oracle import ckks, packing, vmm
+    from paper_2602_11470_amd import binding as B
+    gctx = B.Context(65536, 7, 1, 1, 61, 61, 61, 2.0 ** 40, hamming=64)
+    try:
+        mods = [int(x) for x in gctx.moduli()]
+        octx = ckks.Context(params.Params(n=65536, q=mods[:7], p=mods[7:], alpha=1, scale=2.0 ** 40, hamming=64))
+        plan = packing.make_plan(octx.S, 512, 512, 2)
+        osk, gsk = octx.keygen_secret(3), gctx.keygen_secret(3)
+        steps = sorted(set(vmm.unrolled_steps(plan)))
+        okeys, gkeys = octx.keygen_rotations(osk, steps, 4), gctx.keygen_rotations(gsk, steps, 4)
+        rng = np.random.default_rng(level)
+        xc = octx.encode_coeffs(rng.uniform(-1, 1, octx.S), 2.0 ** 40)
+        cs = rng.integers(-(1 << 40), 1 << 40, (plan.r_i * plan.r_o, 65536))
+        ox = octx.encrypt(osk, octx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+        gx = gctx.encrypt(gsk, gctx.pt_from_coeffs(xc, level, 2.0 ** 40), 5)
+        od = [[octx.pt_from_coeffs_ext(cs[j * plan.r_o + k], level, 2.0 ** 40) for k in range(plan.r_o)] for j in range(plan.r_i)]
+        got = gctx.vmm_pt(gkeys, gctx.vmm_plan(512, 512, level=level, r_i=plan.r_i, coeffs=cs, unrolled_ladders=True), gx)
+        assert np.array_equal(gctx.ct_export(got), octx.canonical(vmm.vmm_pt_unrolled(octx, okeys, plan, ox, od)))
+    finally:
+        gctx.close()
