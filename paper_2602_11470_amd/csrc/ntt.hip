@@ -1740,7 +1740,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     else if (ns <= 2) CCF_LAUNCH(2);
     else if (ns <= 4) CCF_LAUNCH(4);
     else if (ns <= 6) CCF_LAUNCH(6);
-    else if (ns <= 7) CCF_LAUNCH(7);
+    else if (ns <= 7) hipLaunchKernelGGL((conv_cols_fwd<7, false>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);   // never folded (ks_drop_fits)
     else CCF_LAUNCH(8);
 #undef CCF_LAUNCH
     if (b.half) return;
