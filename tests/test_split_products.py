@@ -1,8 +1,17 @@
-"""The carry-free split products of the inner-product and base-conversion kernels (moduli below 2^50), replayed with
-Python integers: a product d * w with d held as two 25-bit halves and w as two 32-bit halves goes into four 64-bit
-accumulators that are combined once.  Pins the recombination weights (2^0, 2^32, 2^25, 2^57) and that no accumulator
-can pass 2^64 for as many terms as the kernels add (16 digits at most, 8 conversion sources) even at the largest
-operands, including the digit words just below 2^51 that a lazy reduction could hand over."""
+"""The carry-free split products of the kernels, replayed with Python integers at their largest operands: that no accumulator can
+pass its 64 (or 128) bits for as many terms as the kernels add, that the recombination weights are right, and that the reductions
+behind the sums give the canonical residue.
+
+  Acc50 (inner products, conversions of sources below 2^50): d in two 25-bit halves, w in two 32-bit ones, four accumulators with
+    the weights 2^0, 2^32, 2^25, 2^57.  Sums of one item (16 digits at most) also stand the digits just below 2^51 of a lazy
+    reduction; the row-pass form of the inner products (RipFp) keeps one sum over all items of an output, RIP_MAX_TERMS terms,
+    and relies on canonical digits.
+  MacAcc (packed products): both factors in two halves of B bits, three accumulators, the two middle products in one.
+  Conversions: up to eight sources, and one term more where a folded last limb joins them."""
+import re
+from fractions import Fraction
+from pathlib import Path
+
 import numpy as np
 import pytest
 
@@ -39,3 +48,112 @@ def test_largest_operands_do_not_overflow(dmax):
     for terms in (8, 16):
         ds, ws = [dmax] * terms, [M64] * terms
         assert split_sum(ds, ws) == terms * dmax * M64
+
+
+CSRC = Path(__file__).resolve().parents[1] / "paper_2602_11470_amd" / "csrc"
+
+
+def _define(source, name):
+    return int(re.search(rf"#define {name} (\d+)", (CSRC / source).read_text()).group(1))
+
+
+def _redc(T, q):
+    """redc of common.h on 64-bit words: T 2^-64 mod q, in [0, q) where T < q 2^64."""
+    assert 0 <= T < 1 << 128
+    lo, hi = T & M64, T >> 64
+    t = (((lo * pow(q, -1, 1 << 64)) & M64) * q) >> 64
+    r = hi - t if hi >= t else hi - t + q
+    assert 0 <= r <= M64
+    return r
+
+
+def _redc_raw(T, q):
+    """redc_raw of kernels.h: T mod q, also where T is beyond q 2^64, as long as the second product is not."""
+    second = _redc(T, q) * ((1 << 128) % q)
+    assert second < q << 64
+    return _redc(second, q)
+
+
+def _prime_below(bound):
+    for q in range(bound - 1, bound - 4096, -2):
+        if all(pow(a, q - 1, q) == 1 for a in (2, 3, 5, 7, 11, 13)):
+            return q
+
+
+Q50, Q60, Q61 = _prime_below(1 << 50), _prime_below(1 << 60), _prime_below(1 << 61)
+
+
+def test_row_pass_inner_product_sums():
+    terms = _define("ntt.hip", "RIP_MAX_TERMS")
+    q, inv64 = Q50, pow(1 << 64, -1, Q50)
+    d = [q - 1] * terms
+    b, a = split_sum(d, [q - 1] * terms), split_sum(d, [M64] * terms)      # key words below q, raw draws
+    assert b < q << 64 and _redc(b, q) == b * inv64 % q
+    assert _redc_raw(a, q) == a % q
+    # digits of a lazy reduction would not do
+    with pytest.raises(AssertionError):
+        split_sum([2 * q - 1] * terms, [M64] * terms)
+    # integer limbs: reduced item by item, up to seven digits and a first component (key half), seven raw draws
+    for q in (Q60, Q61):
+        b, a = 8 * (q - 1) ** 2, 7 * (q - 1) * M64
+        assert b < q << 64 and _redc(b, q) == b * pow(1 << 64, -1, q) % q
+        assert a < 1 << 128 and _redc_raw(a, q) == a % q
+
+
+def _mac_limits():
+    text = (CSRC / "kernels.hip").read_text()
+    out = {}
+    for name in ("MacPacked50", "MacPacked60", "MacWords"):
+        m = re.search(rf"struct {name} {{[^}}]*?B = (\d+), TERMS = ([^;]+);", text)
+        out[name] = int(m.group(1)), eval(m.group(2))
+    return out
+
+
+@pytest.mark.parametrize("name,q", [("MacPacked50", Q50), ("MacPacked60", Q60), ("MacWords", Q61)])
+def test_packed_product_sums(name, q):
+    B, terms = _mac_limits()[name]
+    mask = (1 << B) - 1
+    for w in (q - 1, mask, (q - 1) & ~mask):                   # the largest word, the largest lower and upper half
+        for b in (q - 1, mask, (q - 1) & ~mask):
+            t0 = terms * (b & mask) * (w & mask)
+            t1 = terms * ((b & mask) * (w >> B) + (b >> B) * (w & mask))
+            t2 = terms * (b >> B) * (w >> B)
+            assert max(t0, t1, t2) <= M64, "a 64-bit accumulator would wrap"
+            T = t0 + (t1 << B) + (t2 << (2 * B))
+            assert T == terms * b * w and T < q << 64
+            assert _redc(T, q) == T * pow(1 << 64, -1, q) % q
+
+
+@pytest.mark.parametrize("sources", [1, 2, 4, 6, 8])
+def test_conversion_sums_with_a_folded_limb(sources):
+    terms = sources + 1
+    # sources below 2^50: Acc50, whatever the weight
+    for q in (Q50, Q61):
+        T = split_sum([Q50 - 1] * terms, [q - 1] * terms)
+        assert T < q << 64 and _redc(T, q) == T * pow(1 << 64, -1, q) % q
+    # sources below 2^60, targets below 2^50: halves of 30 and of 25 bits
+    y, w = Q60 - 1, Q50 - 1
+    y0, y1, w0, w1 = y & ((1 << 30) - 1), y >> 30, w & LOW25, w >> 25
+    parts = [terms * v for v in (y0 * w0, y0 * w1, y1 * w0, y1 * w1)]
+    assert max(parts) <= M64
+    T = parts[0] + (parts[1] << 25) + (parts[2] << 30) + (parts[3] << 55)
+    assert T == terms * y * w < Q50 << 64
+    # 128-bit sums of 61-bit sources: seven terms with the folded limb among them, eight sources without
+    for q in (Q60, Q61):
+        T = min(terms, 7) * (Q61 - 1) * (q - 1)
+        assert T < q << 64 and 8 * (Q61 - 1) * (q - 1) < q << 64
+
+
+def test_conversion_sums_in_doubles_stay_exact():
+    """|y w - c q| <= 0.88 q a term (c = rint of y w / q, off by three roundings of a value below 2^50), nine terms below 2^53."""
+    q = Q50
+    qinv = 1.0 / q
+    rng = np.random.default_rng(5)
+    worst = Fraction(0)
+    pairs = [(q - 1, q - 1), (q - 1, q // 2), (q // 2, q - 1), (q - 1, q // 2 + 1), (q - 2, 3)]
+    pairs += [(int(a), int(b)) for a, b in zip(rng.integers(q - (1 << 20), q, 4000), rng.integers(0, q, 4000))]
+    for y, w in pairs:
+        c = np.rint(float(y) * (float(w) * qinv))
+        worst = max(worst, abs(Fraction(y * w) - int(c) * q) / q)
+    assert worst <= Fraction(88, 100)
+    assert 9 * Fraction(88, 100) * q < 1 << 53
