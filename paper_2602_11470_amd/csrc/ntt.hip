@@ -1283,6 +1283,7 @@ struct ConvArgs {
     size_t in_stride, out_stride, own_stride;
     const u64 *own_src;
     unsigned own_g;
+    int nt;                       // stores of the column pass: non-temporal (NttTables::large says how the passes of a transform store)
     int tg, groups;               // targets per workgroup, workgroups that convert per (tile, item) (n = 65536)
 };
 // The y_m of NV words.  Source moduli below 2^50 (the digits of a raise): exact integers in doubles; a product with a
@@ -1439,6 +1440,12 @@ struct ConvY {
 // 144 limbs 28 + 37 -> 60 us, the 8 limbs of a ModDown at level 3 5.0 + 6.8 -> 8.6 us and a launch less.
 // tg: 8 targets a workgroup, so that the y_m (as much work as one target) are formed once for eight; halved while the
 // launch has fewer than CCF_FILL = 512 workgroups (two for each compute unit); 4 and 12 measured equal and 2 % slower.
+// nt: non-temporal stores from CCF_NT converted limbs on, agent scope below (ntt_store): the passes of a plain transform gain from agent
+// scope up to 255 limbs, this kernel, whose waves wait at barriers between their stores, does not.  With CCF_NT = 256, 192, 128, 64 and
+// 1: 63 hoisted rotations at level 13 (224 limbs a batch) 2563, 2508, 2515, 2517 and 2509 us, at level 11 2184, 2135, 2119, 2127 and 2134;
+// a rotation at level 23 (144 limbs) 182, 183, 175, 176 and 175; three hoisted ones at level 13 197, 195, 196, 194 and 204; scores times V at
+// level 13 2335, 2327, 2308, 2309 and 2338.
+#define CCF_NT 128
 #define CCF_W 8
 #define CCF_THREADS (64 * CCF_W)
 #define CCF_TG 8
@@ -1504,7 +1511,7 @@ __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols
 #pragma unroll
             for (int k = 0; k < 4; k++) w[k] = src[row + (a.own_g ? perm_src(i0 + CCF_THREADS * k, a.own_g, logn) : i0 + CCF_THREADS * k)];
 #pragma unroll
-            for (int k = 0; k < 4; k++) ntt_store(t.large, out + row + i0 + CCF_THREADS * k, w[k]);
+            for (int k = 0; k < 4; k++) ntt_store(a.nt, out + row + i0 + CCF_THREADS * k, w[k]);
         }
         return;
     }
@@ -1541,13 +1548,13 @@ __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols
             ar.init(t, o.mod, n);
             double v[4];
             y.target_any(split, o, ar, v);
-            ccf_body<FpArith>(lds, buf, t.large, p, v, tid, ar, n2);
+            ccf_body<FpArith>(lds, buf, a.nt, p, v, tid, ar, n2);
         } else {
             IntArith ar;
             ar.init(t, o.mod, n);
             u64 x[4];
             y.target(split, o, x);
-            ccf_body<IntArith>(lds, buf, t.large, p, x, tid, ar, n2);
+            ccf_body<IntArith>(lds, buf, a.nt, p, x, tid, ar, n2);
         }
     }
 }
@@ -1706,7 +1713,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     ConvArgs a;
     a.tabs = b.tabs, a.tab_step = b.tab_step, a.tab_period = b.tab_period ? b.tab_period : b.batch, a.in_group = b.in_group;
     a.in_stride = b.in_stride, a.out_stride = b.out_stride, a.own_stride = b.own_stride;
-    a.own_src = b.own_src, a.own_g = b.own_g;
+    a.own_src = b.own_src, a.own_g = b.own_g, a.nt = limbs >= CCF_NT;
     Prof prof_(ctx, CM_K_BASE_CONV, limbs, st);
     if (n == 4096) {
         const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
