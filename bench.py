@@ -48,8 +48,8 @@ D = 4096
 
 def measured_traffic():
     """HBM bytes per unit from the committed rocprofv3 --pmc summary (FETCH_SIZE / WRITE_SIZE scaled
-    by the copy-kernel calibration stated there); keys: 'k_inner_product' (per launch) and
-    'ntt_fwd_per_limb'.  Empty if the summary is missing."""
+    by the copy-kernel calibration stated there); keys: 'inner_product_family_per_step', 'k_vmm_mac' and 'k_rows_ip'
+    (per launch).  Empty if the summary is missing."""
     out = {}
     path = os.path.join(ROOT, "profiles", "pmc_hbm_traffic_bench_config2.txt")
     if os.path.exists(path):
@@ -115,8 +115,9 @@ def kernel_profile(g, steps):
 
 
 def time_rotations(g, reps=20):
-    """Seconds per un-hoisted rotation, and seconds per launch of its inner-product kernel (k_inner_product, which moves
-    the stored key half, the digits and the result of one key switch and shares nothing)."""
+    """Seconds per un-hoisted rotation, and seconds per launch of its inner-product kernel (k_rows_ip, which moves the stored
+    key half, the digits and the result of one key switch, shares nothing and does the row pass of the digits; k_inner_product
+    with stored key halves)."""
     torch, ctx = g["torch"], g["ctx"]
     r = ctx.rotate(g["keys"], g["ct"], 7)
     torch.cuda.synchronize()
@@ -786,8 +787,9 @@ def main():
                           "us_per_launch": ip_launch_s * 1e6},
         "inner_product_single": {"bound": "hbm", "achieved": ((1 + kh) * beta * W_ + 2 * W_) / t_ip_single / 1e9, "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": ((1 + kh) * beta * W_ + 2 * W_) / t_ip_single / 1e9 / HBM_PEAK_GBS,
-                                 "traffic": tr.get("k_rows_ip"),
-                                 "kernel": "k_rows_ip (row pass of the digits and inner product of one un-hoisted key switch)",
+                                 "traffic": None if a.stored_a else tr.get("k_rows_ip"),
+                                 "kernel": "k_inner_product (one un-hoisted key switch)" if a.stored_a else
+                                           "k_rows_ip (row pass of the digits and inner product of one un-hoisted key switch)",
                                  "us_per_launch": t_ip_single * 1e6},
         "vmm_mac": {"bound": "hbm", "achieved": mac_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": mac_gbs / HBM_PEAK_GBS,
                     "traffic": tr.get("k_vmm_mac"), "kernel": "k_vmm_mac (one launch per step)",

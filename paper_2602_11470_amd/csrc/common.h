@@ -118,7 +118,7 @@ struct ConvTarget {
     double w[CONV_MAX_SRC];       // hat_m mod q (exact for moduli below 2^50)
     u64 q, qinv;                  // modulus, q^{-1} mod 2^64
     u64 wm[CONV_MAX_SRC];         // hat_m mod q in multiplier form
-    double wl;                    // the same of the weight of a folded last limb (ConvFold): P mod q
+    double wl;                    // the same of the weight of a folded last limb (ConvDev::fold): P mod q
     u64 wlm;
 };
 struct ConvDev {

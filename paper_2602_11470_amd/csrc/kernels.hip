@@ -1110,7 +1110,8 @@ struct MacWords {                              // 64-bit words, pairs interleave
     }
 };
 // A workgroup owns 64 coefficients of one limb; its four waves take KW giant steps each.  The baby words are staged in LDS as
-// two halves, sixteen baby steps a pass (16 KiB, so that registers set the occupancy: four waves a SIMD; thirty-two measured
+// two halves, sixteen baby steps a pass (16 KiB, so that registers set the occupancy: four waves a SIMD with KW = 1 and 2, 103 and 118
+// registers, three with KW = 4, 151, which the 50-bit groups need; thirty-two measured
 // the same), the first group of a pass requested before them.  The sums stay in registers over the passes and are written once.
 #define MAC_JC 16
 template <int KW, class G>
@@ -1188,7 +1189,7 @@ template <int KW>
 __global__ __launch_bounds__(TPB) void k_vmm_mac(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
                                                    const ModC *__restrict__ modc, MacLayout lay, int limbs, size_t ct_stride, int level, int L) {
     __shared__ uint2 sb[MAC_JC * 2 * MAC_CO];
-    // the limbs of the special primes (64-bit words, the slowest workgroups) are dispatched first, not last
+    // the limbs of the special primes (60 or 64 bits a word, the slowest workgroups) are dispatched first, not last
     const int nsp = limbs - (level + 1), y = blockIdx.y;
     const int l = y < nsp ? level + 1 + y : y - nsp, mi = l <= level ? l : L + 1 + (l - level - 1);
     const ModC m = modc[mi];

@@ -37,9 +37,10 @@ struct NttTables {
     // once.  Small launches find theirs in the caches and read plainly (a single key switch is 3 % slower otherwise).
     // A limb is read again only by a later kernel.  Large launches write with non-temporal stores (after hundreds of MiB of
     // other limbs have gone by; 1 % off the transforms of a step against plain stores), small ones at agent scope, through to
-    // memory at once instead of when the L2 evicts or a kernel ends.  Against non-temporal stores: ciphertext product at level
-    // 13 158.5 -> 154.2 us, rotary embedding at level 3 138.0 -> 134.9, 4096 x 4096 product at level 4 1154 -> 1140; for large
-    // launches agent scope is 2 to 5 % slower (attention, product at level 23), plain stores 1 to 4 %.
+    // memory at once instead of when the L2 evicts or a kernel ends: plain transforms of 24 to 255 limbs take 5 to 40 % less.  Against
+    // non-temporal stores: ciphertext product at level 13 158.5 -> 154.2 us, rotary embedding at level 3 138.0 -> 134.9, 4096 x 4096
+    // product at level 4 1154 -> 1140; for large launches agent scope is 2 to 5 % slower (attention, product at level 23), plain stores
+    // 1 to 4 %.  The column pass of a conversion draws the line at CCF_NT limbs.
     int large;
 };
 
@@ -870,13 +871,19 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict_
 // it then reads -- and multiplies.  With a Galois element the wave transforms the row that the map takes its own row from (aligned
 // blocks go to aligned blocks) and exchanges once more.  The digits' row pass as a launch of its own wrote and re-read every digit.
 // The rows from inv_from on go straight into the row pass of the inverse transform, whose order of words is the one they are in.
-// Bound by the vector ALU at two waves a SIMD (up to 240 registers: sums, twiddles, and the next digit requested ahead, which is
-// worth 1 %; three waves spill 26 registers and lose 3 to 10 %, four lose 20 %).  Row passes and inner products in launches of
+// Bound by the latency that two waves a SIMD leave open: counters of the seven giant steps and of the shared rotations of q K^T show
+// the vector ALU 0.57 to 0.61 busy, 0.35 to 0.40 of the waves' time waiting, and two conflict cycles to an LDS cycle.  240 vector
+// registers (245 in the shared-key form; sums, twiddles, and the next digit requested ahead, which is worth 1 %), 108 (88) scalar ones
+// spilled into lanes and 36 bytes of scratch: the two arithmetics in one kernel.  Three waves spill 26 vector registers and lose 3 to
+// 10 %, four lose 20 %.  Row passes and inner products in launches of
 // their own -> here: the seven giant steps at level 22 195 + 236 -> 388 us; two launches a key switch fewer: ciphertext product at
 // level 13 151.6 -> 145.6 us, rotary embedding at level 3 82.9 -> 76.9, query times K at level 12 16730 -> 16020, scores times V at
 // level 22 4082 -> 3852, 4096 x 4096 product at level 23 4738 -> 4532.  Eight relinearisations with one key at level 22, inverse row
-// pass included: 218 + 205 + 25 in launches of their own, 459 with the draws of every output formed anew, 382 with them kept in LDS
-// (at level 9 132, 159 and 145, one launch instead of three; at level 3 56, 78 and 64; the calls as a whole are faster at all levels).
+// pass included: 218 + 205 + 25 in launches of their own, 459 with the draws of every output formed anew, 382 with them kept in LDS.
+// At the lower levels the launch by itself is no shorter than the three (at level 9 132, 159 and 145, at level 3 56, 78 and 64), the
+// calls are: with their relinearisations in three launches and joined, scores times V at levels 13, 9, 6 and 3 2340 -> 2306, 1689 -> 1677,
+// 1186 -> 1179 and 737 -> 736 us, query times K over 32 key ciphertexts at levels 9, 5 and 3 7142 -> 7075, 4313 -> 4235 and 2402 -> 2409,
+// with no shared rotations at level 3 3566 -> 3589.
 #define RIP_WAVES 4
 #define RIP_ROW (256 + 16)
 typedef u64 u64x2_t __attribute__((ext_vector_type(2)));
@@ -1721,7 +1728,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     if (b.fold) hipLaunchKernelGGL((conv_full_fwd<NS_, true, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
     else if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
     else hipLaunchKernelGGL((conv_full_fwd<NS_, false, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
-        // the instantiation for eight spills 31 of 256 registers and still takes less than conversion and transform in two launches
+        // the instantiation for eight spills 31 of 256 registers (124 with a folded limb: ks_drop_fits) and still takes less than conversion and transform in two launches
         // (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us; five sources 66 -> 56
         if (ns <= 1) { FULL_LAUNCH(1); }
         else if (ns <= 2) { FULL_LAUNCH(2); }
