@@ -341,6 +341,9 @@ __device__ __forceinline__ void radix16_inv_last(u64 (&v)[16], const IntArith &a
     radix16_inv_tw(v, ar, TableTw<IntArith>(ar, base0));
 }
 
+// LARGE: the same as NttTables::large, at compile time for the stores (with both kinds behind a branch the passes of 256 limbs and more
+// took 1 to 3 % longer: 512 limbs under 58-bit primes 249 us inverse, 241 so; 1008 under 50-bit ones 438 and 431).  Not for the loads:
+// without the branch 1008 limbs take 7 % less and 256 to 512 up to 7 % more.
 __device__ __forceinline__ void ntt_store(int large, u64 *p, u64 v) {
     if (large) __builtin_nontemporal_store(v, p);
     else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -354,7 +357,7 @@ __device__ __forceinline__ int pad(int e) { return e + (e >> 4); }
 #define LDS_WORDS (4096 + 256)
 
 // ---- column passes: stages 0..7; tile = rows 0..255 of 16 adjacent columns ---------------------------
-template <class A>
+template <class A, bool LARGE>
 __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, const NttTables &t, int mi, int n, int n2) {
     A ar;
     ar.init(t, mi, n);
@@ -382,9 +385,9 @@ __device__ __forceinline__ void cols_fwd_body(u64 *lds, u64 *p, const u64 *ps, c
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((16 * sub + k) * 16 + c)]);
     radix16_fwd_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) ntt_store(t.large, p + (unsigned)((16 * sub + k) * n2 + c), ar.to_mid(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(LARGE, p + (unsigned)((16 * sub + k) * n2 + c), ar.to_mid(v[k]));
 }
-template <class A>
+template <class A, bool LARGE>
 __device__ __forceinline__ void cols_inv_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int n2) {
     A ar;
     ar.init(t, mi, n);
@@ -412,10 +415,11 @@ __device__ __forceinline__ void cols_inv_body(u64 *lds, u64 *p, const NttTables 
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad((sub + 16 * k) * 16 + c)]);
     radix16_inv_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) ntt_store(t.large, p + (unsigned)((sub + 16 * k) * n2 + c), ar.to_rest_inv(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(LARGE, p + (unsigned)((sub + 16 * k) * n2 + c), ar.to_rest_inv(v[k]));
 }
 
 // grid.x = limbs * (n2/16)
+template <bool LARGE>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_fwd(u64 *__restrict__ data, const u64 *__restrict__ src,
                                                            const int *__restrict__ src_rows,
                                                            const int *__restrict__ rows,
@@ -428,10 +432,11 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_fwd(u64 *__restrict__ da
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
     const u64 *ps = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n + c0 : p;
     if (t.fpq[mi].q != 0.0)
-        cols_fwd_body<FpArith>(lds, p, ps, t, mi, n, n2);
+        cols_fwd_body<FpArith, LARGE>(lds, p, ps, t, mi, n, n2);
     else
-        cols_fwd_body<IntArith>(lds, p, ps, t, mi, n, n2);
+        cols_fwd_body<IntArith, LARGE>(lds, p, ps, t, mi, n, n2);
 }
+template <bool LARGE>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_inv(u64 *__restrict__ data, const int *__restrict__ rows,
                                                            const int *__restrict__ mod_idx, NttTables t, int n,
                                                            int n2) {
@@ -441,9 +446,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_cols_inv(u64 *__restrict__ da
     const int mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + c0;
     if (t.fpq[mi].q != 0.0)
-        cols_inv_body<FpArith>(lds, p, t, mi, n, n2);
+        cols_inv_body<FpArith, LARGE>(lds, p, t, mi, n, n2);
     else
-        cols_inv_body<IntArith>(lds, p, t, mi, n, n2);
+        cols_inv_body<IntArith, LARGE>(lds, p, t, mi, n, n2);
 }
 
 // The exchange between the two radix-16 groups of a row pass stays among the sixteen lanes that share a block of 256 words,
@@ -548,7 +553,7 @@ __device__ __forceinline__ void fold_in(const FoldIn &fi, int limb, int n, int l
 }
 
 // ---- row passes on contiguous blocks of 256 words (n = 65536): a workgroup owns 16 blocks ---------------
-template <class A, bool TAIL>
+template <class A, bool TAIL, bool LARGE>
 __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTables &t, int mi, int n, int chunk,
                                                  int limb, const FinishBatch &fb) {
     A ar;
@@ -583,12 +588,12 @@ __device__ __forceinline__ void rows256_fwd_body(u64 *lds, u64 *p, const NttTabl
     __syncthreads();
     if (!TAIL) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) ntt_store(t.large, p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
+        for (int k = 0; k < 16; k++) ntt_store(LARGE, p + threadIdx.x + 256 * k, lds[pad(threadIdx.x + 256 * k)]);
         return;
     }
     finish_tail<NTT_THREADS>(pad, ar, lds, t, n, chunk, limb, fb);
 }
-template <class A>
+template <class A, bool LARGE>
 __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps, const u64 *psrow, unsigned g,
                                                  const NttTables &t, int mi, int n, int chunk, int limb, const FoldIn &fi) {
     A ar;
@@ -612,7 +617,7 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
 #pragma unroll
             for (int k = 0; k < 16; k++) w[k] = ps[threadIdx.x + 256 * k];
         }
-        fold_in(fi, limb, n, logn, w, [&](int k) { return pos0 + 256 * k; });
+        if (!LARGE) fold_in(fi, limb, n, logn, w, [&](int k) { return pos0 + 256 * k; });
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[pad(threadIdx.x + 256 * k)] = w[k];
         __syncthreads();
@@ -628,11 +633,11 @@ __device__ __forceinline__ void rows256_inv_body(u64 *lds, u64 *p, const u64 *ps
     for (int k = 0; k < 16; k++) v[k] = ar.from_mid(lds[pad(blk * 256 + sub + 16 * k)]);
     radix16_inv_tw(v, ar, tw2);
 #pragma unroll
-    for (int k = 0; k < 16; k++) ntt_store(t.large, p + blk * 256 + sub + 16 * k, ar.to_mid(v[k]));
+    for (int k = 0; k < 16; k++) ntt_store(LARGE, p + blk * 256 + sub + 16 * k, ar.to_mid(v[k]));
 }
 // grid.x = limbs * n/4096; TAIL: the fused ModDown / rescale tail (a kernel of its own, so that the registers its
 // operands take do not lower the occupancy of the plain transform)
-template <bool TAIL>
+template <bool TAIL, bool LARGE>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_fwd(u64 *__restrict__ data, const int *__restrict__ rows,
                                                               const int *__restrict__ mod_idx, NttTables t, int n,
                                                               FinishBatch fb) {
@@ -642,10 +647,11 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_fwd(u64 *__restrict__
     const int mi = mod_idx[limb];
     u64 *p = data + (size_t)(rows ? rows[limb] : limb) * n + (size_t)chunk * 4096;
     if (t.fpq[mi].q != 0.0)
-        rows256_fwd_body<FpArith, TAIL>(lds, p, t, mi, n, chunk, limb, fb);
+        rows256_fwd_body<FpArith, TAIL, LARGE>(lds, p, t, mi, n, chunk, limb, fb);
     else
-        rows256_fwd_body<IntArith, TAIL>(lds, p, t, mi, n, chunk, limb, fb);
+        rows256_fwd_body<IntArith, TAIL, LARGE>(lds, p, t, mi, n, chunk, limb, fb);
 }
+template <bool LARGE>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__ data, const u64 *__restrict__ src,
                                                               const int *__restrict__ src_rows,
                                                               const int *__restrict__ rows,
@@ -659,9 +665,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_rows256_inv(u64 *__restrict__
     const u64 *psrow = src ? src + (size_t)(src_rows ? src_rows[limb] : limb) * n : p - (size_t)chunk * 4096;
     const u64 *ps = psrow + (size_t)chunk * 4096;
     if (t.fpq[mi].q != 0.0)
-        rows256_inv_body<FpArith>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
+        rows256_inv_body<FpArith, LARGE>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
     else
-        rows256_inv_body<IntArith>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
+        rows256_inv_body<IntArith, LARGE>(lds, p, ps, psrow, g, t, mi, n, chunk, limb, fi);
 }
 
 // ---- passes of a few limbs (n = 65536): four words a lane --------------------------------------------------------------
@@ -1636,7 +1642,8 @@ static void launch_cols_fwd(u64 *data, const u64 *src, const int *d_src_rows, co
     if (limbs <= SMALL_COLS)
         hipLaunchKernelGGL(small_cols_fwd, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, src, d_src_rows, d_rows, d_mods, t, n);
     else
-        hipLaunchKernelGGL(ntt_cols_fwd, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, src, d_src_rows, d_rows, d_mods, t, n, n >> 8);
+        hipLaunchKernelGGL(t.large ? ntt_cols_fwd<true> : ntt_cols_fwd<false>, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, src, d_src_rows,
+                           d_rows, d_mods, t, n, n >> 8);
 }
 template <bool TAIL>
 static void launch_rows_fwd(u64 *data, const int *d_rows, const int *d_mods, const NttTables &t, int n, int limbs, const FinishBatch &fb,
@@ -1644,7 +1651,8 @@ static void launch_rows_fwd(u64 *data, const int *d_rows, const int *d_mods, con
     if (limbs <= (TAIL ? SMALL_ROWS : SMALL_PLAIN))
         hipLaunchKernelGGL(small_rows_fwd<TAIL>, dim3(limbs * (n / SMALL_CHUNK)), dim3(SMALL_THREADS), 0, st, data, d_rows, d_mods, t, n, fb);
     else
-        hipLaunchKernelGGL(ntt_rows256_fwd<TAIL>, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, d_rows, d_mods, t, n, fb);
+        hipLaunchKernelGGL((t.large ? ntt_rows256_fwd<TAIL, true> : ntt_rows256_fwd<TAIL, false>), dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data,
+                           d_rows, d_mods, t, n, fb);
 }
 // data rows d_rows[i] (or i) are transformed in place; with src != nullptr the first pass reads row
 // src_rows[i] (or i) of src instead, so the transform is out of place and src is left untouched.
@@ -1668,10 +1676,12 @@ void launch_ntt_src(cm_ctx *ctx, u64 *data, const int *d_rows, const u64 *src, c
         if (limbs <= SMALL_ROWS)
             hipLaunchKernelGGL(small_rows_inv, dim3(limbs * (n / SMALL_CHUNK)), dim3(SMALL_THREADS), 0, st, data, src, d_src_rows, d_rows,
                                d_mod_idx, t, n, (unsigned)g, fi);
-        else hipLaunchKernelGGL(ntt_rows256_inv, grid, block, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g, fi);
+        else
+            hipLaunchKernelGGL(t.large && !fi.per ? ntt_rows256_inv<true> : ntt_rows256_inv<false>, grid, block, 0, st, data, src, d_src_rows, d_rows,
+                               d_mod_idx, t, n, (unsigned)g, fi);
         if (limbs <= SMALL_COLS)
             hipLaunchKernelGGL(small_cols_inv, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, d_rows, d_mod_idx, t, n);
-        else hipLaunchKernelGGL(ntt_cols_inv, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
+        else hipLaunchKernelGGL(t.large ? ntt_cols_inv<true> : ntt_cols_inv<false>, grid, block, 0, st, data, d_rows, d_mod_idx, t, n, n2);
     } else {
         hipLaunchKernelGGL(ntt_full_inv, grid, full, 0, st, data, src, d_src_rows, d_rows, d_mod_idx, t, n, (unsigned)g, fi);
     }
@@ -1684,7 +1694,9 @@ void launch_cols_inv(cm_ctx *ctx, u64 *data, const int *d_rows, const int *d_mod
     const NttTables t = tables_of(ctx, true, limbs);
     if (limbs <= SMALL_COLS)
         hipLaunchKernelGGL(small_cols_inv, dim3(limbs * (256 / SMALL_CW)), dim3(64 * SMALL_CW), 0, st, data, d_rows, d_mod_idx, t, n);
-    else hipLaunchKernelGGL(ntt_cols_inv, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, d_rows, d_mod_idx, t, n, n >> 8);
+    else
+        hipLaunchKernelGGL(t.large ? ntt_cols_inv<true> : ntt_cols_inv<false>, dim3(limbs * (n >> 12)), dim3(NTT_THREADS), 0, st, data, d_rows, d_mod_idx, t, n,
+                           n >> 8);
 }
 void launch_mul_pt_rot_last_inv(cm_ctx *ctx, u64 *out, const MulPtBatch &b, int cnt, const u64 *pt_mont, int limbs, const int *d_mods, hipStream_t st) {
     if (ctx->n != 65536) {
