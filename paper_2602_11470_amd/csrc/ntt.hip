@@ -878,7 +878,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict_
 // blocks go to aligned blocks) and exchanges once more.  The digits' row pass as a launch of its own wrote and re-read every digit.
 // The rows from inv_from on go straight into the row pass of the inverse transform, whose order of words is the one they are in.
 // Bound by the latency that two waves a SIMD leave open: counters of the seven giant steps and of the shared rotations of q K^T show
-// the vector ALU 0.57 to 0.61 busy, 0.35 to 0.40 of the waves' time waiting, and two conflict cycles to an LDS cycle.  240 vector
+// the vector ALU 0.56 to 0.61 busy, 0.35 to 0.40 of the waves' time waiting, and two conflict cycles to an LDS cycle.  240 vector
 // registers (245 in the shared-key form; sums, twiddles, and the next digit requested ahead, which is worth 1 %), 108 (88) scalar ones
 // spilled into lanes and 36 bytes of scratch: the two arithmetics in one kernel.  Three waves spill 26 vector registers and lose 3 to
 // 10 %, four lose 20 %.  Row passes and inner products in launches of
