@@ -81,6 +81,13 @@ __device__ __forceinline__ unsigned perm_src(unsigned i, unsigned g, int logn) {
     return __brev((s - 1u) >> 1) >> (32 - logn);
 }
 
+// A multiplier w of the integer butterflies under a modulus q = 2^b - c from 2^50 on, cut up so that its product with a = a0 + 2^32 a1
+// is two sums of two 32 x 32-bit products: w = w0 + 2^30 (w1 2^(b-61)) and w 2^32 mod q = v0 + 2^30 (v1 2^(b-61)).  The upper parts
+// are scaled by 2^(61-b), whatever b, so that the weight 2^(b+1) of the upper sum's upper word is 2 c (IntArith::mul).
+struct IntTw {
+    unsigned w0, w1, v0, v1;
+};
+
 // modulus as doubles for the FP64 butterflies (moduli below 2^50 only; q = 0 otherwise)
 struct FpQ {
     double q, qinv;       // modulus and 1/q as doubles; q = 0 where the modulus is too large for the FP64 paths
@@ -154,10 +161,9 @@ struct cm_ctx {
     ModC *d_modc = nullptr;               // [nmod]
     u64 *d_pmont = nullptr;               // [L+1] P = p_0 .. p_{K-1} mod q_i, multiplier (Montgomery) form
     u64 *d_ubound = nullptr;              // [nmod] q * floor(2^64 / q): uniform draws at or above it are rejected
-    u64 *d_tw = nullptr, *d_twp = nullptr;      // forward twiddles psi^brev(i) and companions [nmod][n]
-    u64 *d_itw = nullptr, *d_itwp = nullptr;    // inverse
-    u64 *d_ninv = nullptr, *d_ninvp = nullptr;  // n^{-1} [nmod]
-    // the same tables as doubles (w and w/q) for the limbs whose modulus is below 2^50
+    // twiddles psi^brev(i) of the moduli from 2^50 on [nmod][n], forward and inverse, and n^{-1} [nmod]
+    IntTw *d_tw = nullptr, *d_itw = nullptr, *d_ninv = nullptr;
+    // the same as doubles (w and w/q) for the limbs whose modulus is below 2^50
     FpQ *d_fpq = nullptr;                       // [nmod] (q, 1/q), q = 0 for larger moduli
     double *d_twd = nullptr, *d_twqd = nullptr, *d_itwd = nullptr, *d_itwqd = nullptr;
     double *d_ninvd = nullptr, *d_ninvqd = nullptr;
@@ -254,6 +260,7 @@ u64 h_mulmod(u64 a, u64 b, u64 q);
 u64 h_powmod(u64 b, u64 e, u64 q);
 u64 h_invmod(u64 a, u64 q);
 u64 h_shoup(u64 w, u64 q);
+IntTw h_int_tw(u64 w, u64 q);
 u64 galois_of_step(const cm_ctx *ctx, int step);
 const std::vector<ConvTable> &get_modup(cm_ctx *ctx, int level);
 const ConvTable &get_moddown(cm_ctx *ctx, int level);

@@ -87,6 +87,11 @@ u64 h_powmod(u64 b, u64 e, u64 q) {
 }
 u64 h_invmod(u64 a, u64 q) { return h_powmod(a % q, q - 2, q); }   // q prime
 u64 h_shoup(u64 w, u64 q) { return (u64)((((u128)w) << 64) / q); }
+IntTw h_int_tw(u64 w, u64 q) {
+    const int b = 64 - __builtin_clzll(q);
+    const u64 v = h_mulmod(w, (1ULL << 32) % q, q), low = (1ULL << 30) - 1;
+    return IntTw{(unsigned)(w & low), (unsigned)((w >> 30) << (61 - b)), (unsigned)(v & low), (unsigned)((v >> 30) << (61 - b))};
+}
 
 static bool h_is_prime(u64 m) {
     static const u64 bases[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
@@ -295,8 +300,8 @@ extern "C" cm_status cm_ctx_create(const cm_params *p, cm_ctx **out) {
     if (ctx->lazy_terms < 2) { delete ctx; return CM_E_INVAL; }
 
     // Montgomery constants and NTT tables
-    std::vector<u64> tw((size_t)ctx->nmod * n), twp(tw.size()), itw(tw.size()), itwp(tw.size());
-    std::vector<u64> ninv(ctx->nmod), ninvp(ctx->nmod);
+    std::vector<u64> tw((size_t)ctx->nmod * n), itw(tw.size()), ninv(ctx->nmod);
+    std::vector<IntTw> itt(tw.size(), IntTw{0, 0, 0, 0}), iitt(itt), init(ctx->nmod, IntTw{0, 0, 0, 0});
     ctx->modc.resize(ctx->nmod);
     ctx->psi.resize(ctx->nmod);
     for (int m = 0; m < ctx->nmod; m++) {
@@ -317,12 +322,11 @@ extern "C" cm_status cm_ctx_create(const cm_params *p, cm_ctx **out) {
             u64 e = brev((u64)i, ctx->logn);
             size_t o = (size_t)m * n + i;
             tw[o] = pw[e];
-            twp[o] = h_shoup(pw[e], q);
             itw[o] = ipw[e];
-            itwp[o] = h_shoup(ipw[e], q);
+            if (q >= (1ULL << 50)) itt[o] = h_int_tw(tw[o], q), iitt[o] = h_int_tw(itw[o], q);
         }
         ninv[m] = h_invmod((u64)n, q);
-        ninvp[m] = h_shoup(ninv[m], q);
+        if (q >= (1ULL << 50)) init[m] = h_int_tw(ninv[m], q);
     }
     ctx->d_modc = upload(ctx->modc);
     {
@@ -337,12 +341,9 @@ extern "C" cm_status cm_ctx_create(const cm_params *p, cm_ctx **out) {
         for (int i = 0; i < ctx->nmod; i++) ub.push_back(ctx->mod[i] * (0xFFFFFFFFFFFFFFFFULL / ctx->mod[i]));
         ctx->d_ubound = upload(ub);
     }
-    ctx->d_tw = upload(tw);
-    ctx->d_twp = upload(twp);
-    ctx->d_itw = upload(itw);
-    ctx->d_itwp = upload(itwp);
-    ctx->d_ninv = upload(ninv);
-    ctx->d_ninvp = upload(ninvp);
+    ctx->d_tw = upload(itt);
+    ctx->d_itw = upload(iitt);
+    ctx->d_ninv = upload(init);
     {
         // double-precision copies for the FP64 butterflies: w and the correctly rounded w/q
         std::vector<double> twd(tw.size(), 0.0), twqd(tw.size(), 0.0), itwd(tw.size(), 0.0), itwqd(tw.size(), 0.0);
@@ -387,8 +388,8 @@ extern "C" cm_status cm_ctx_create(const cm_params *p, cm_ctx **out) {
                    (size_t)CM_KS_BATCH * 2 * (2 * ext + ctx->L + 1);  // batched ModDown of hoisted rotations
     ctx->arena_words = limbs * n;
     if (hipMalloc((void **)&ctx->arena, ctx->arena_words * sizeof(u64)) != hipSuccess) ctx->arena = nullptr;
-    if (!ctx->d_modc || !ctx->d_pmont || !ctx->d_ubound || !ctx->d_tw || !ctx->d_twp || !ctx->d_itw || !ctx->d_itwp || !ctx->d_ninv ||
-        !ctx->d_ninvp || !ctx->d_idx || !ctx->d_cdt || !ctx->arena) {
+    if (!ctx->d_modc || !ctx->d_pmont || !ctx->d_ubound || !ctx->d_tw || !ctx->d_itw || !ctx->d_ninv ||
+        !ctx->d_idx || !ctx->d_cdt || !ctx->arena) {
         cm_ctx_destroy(ctx);
         return CM_E_NOMEM;
     }
@@ -423,11 +424,8 @@ extern "C" void cm_ctx_destroy(cm_ctx *ctx) {
     hipFree(ctx->d_pmont);
     hipFree(ctx->d_ubound);
     hipFree(ctx->d_tw);
-    hipFree(ctx->d_twp);
     hipFree(ctx->d_itw);
-    hipFree(ctx->d_itwp);
     hipFree(ctx->d_ninv);
-    hipFree(ctx->d_ninvp);
     hipFree(ctx->d_fpq), hipFree(ctx->d_twd), hipFree(ctx->d_twqd), hipFree(ctx->d_itwd), hipFree(ctx->d_itwqd);
     hipFree(ctx->d_ninvd), hipFree(ctx->d_ninvqd);
     hipFree(ctx->d_idx);

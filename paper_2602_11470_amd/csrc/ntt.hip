@@ -11,8 +11,8 @@
 // so a limb makes two round trips to HBM for n = 65536.  For n = 4096 the limb is one tile and both parts run in one kernel.
 //
 // Two butterfly arithmetics, chosen per limb (uniform per workgroup):
-//   IntArith : lazy butterflies with Shoup twiddles on u64 (any modulus below 2^61); about 21 VALU instructions per
-//              butterfly on this machine with its share of the folds.
+//   IntArith : lazy butterflies on u64 (moduli 2^b - c, 50 < b <= 61); about 18 VALU instructions per butterfly with its share
+//              of the folds.
 //   FpArith  : for moduli below 2^50, residues held as exact integers in doubles.  FP64 FMA
 //              issues at full rate here, and a modular product is 6 instructions:
 //                  h = y*w; l = fma(y, w, -h)            (exact product h + l)
@@ -28,9 +28,9 @@
 
 struct NttTables {
     const ModC *modc;
-    const u64 *tw, *twp;          // [nmod][n] integer twiddles and Shoup companions
+    const IntTw *tw;              // [nmod][n] integer twiddles
     const double *twd, *twqd;     // [nmod][n] the same twiddles as doubles, and w/q
-    const u64 *ninv, *ninvp;      // [nmod] n^{-1} (inverse only)
+    const IntTw *ninv;            // [nmod] n^{-1} (inverse only)
     const double *ninvd, *ninvqd;
     const FpQ *fpq;               // [nmod] q and 1/q as doubles; q = 0 where the limb must use IntArith
     // Large launches (256 limbs and more) read with non-temporal loads: their input was written long before and is read
@@ -55,62 +55,67 @@ __device__ __forceinline__ const T *word_at(const T *base, unsigned idx) {
 }
 
 // ---- integer arithmetic --------------------------------------------------------------------------
-// Residues stay lazy: a value is only kept below 2^64, i.e. below 16 q (8 q for 61-bit moduli, `tight`).  A product by a
-// Shoup twiddle drops the low partial products of its quotient (at most two units too small), so it lies in [0, 4q)
-// for every 64-bit operand, and costs 13 instructions instead of the 17 of the exact quotient; additions are not reduced.
-// Every second stage all values (forward) or the sums (inverse) are folded: with 2^(b-1) < q = 2^b - c < 2^b,
-// v = (v mod 2^b) + (v >> b) c < q + 17 c < 2q, three instructions.  (The primes of a context are the first ones below
-// 2^b in steps of 2n, so c is below 2^32 by far.)  Bounds, in units of q:
-//   forward  2 (input: 4) -> 6 (8) -> 10 (12) -> fold < 2 (two stages), 61-bit: 2 (4) -> 6 (8) -> fold
-//   inverse  4 -> 8 (sum), 4 (product) -> 16 (sum, folded), 4; 61-bit: 4 -> 8 (sum, folded), 4
-// Measured against exact quotients with a conditional subtraction per butterfly (32 instructions) and twiddles read
-// where they are used: 8 limbs under 60-bit primes 11.1 + 10.6 -> 9.3 + 9.8 us (inverse rows + columns), 64 limbs
-// 29.5 + 28.3 -> 26.9 + 24.6 us.
+// Moduli q = 2^b - c, 51 <= b <= 61; the primes of a context are the first ones below 2^b in steps of 2n, at most 64 of them, so c
+// is below 2^28.  Residues stay lazy: a value is only kept below 2^64, i.e. below 16 q (8 q for 61-bit moduli, `tight`).
+// A product with a twiddle uses what q looks like instead of a quotient.  With the twiddle cut up as IntTw says and any a =
+// a0 + 2^32 a1 below 2^64,
+//   l = a0 w0 + a1 v0 < 2^63,  h = a0 w1 + a1 v1 < 2^64,  a w = l + 2^(b-31) h  (mod q)  =  l + 2^(b-31) (h mod 2^32) + 2^(b+1) (h >> 32)
+// and 2^(b+1) = 2 c: six multiply-adds without a carry, their sum below 2^63 + 2^(b+1) + 2^33 c < 2^64.  A fold, v = (v mod 2^b) +
+// (v >> b) c, three instructions, leaves less than 2^b + 2^13 c < q + q / 512.  Nine instructions; a product with a Shoup twiddle
+// (quotient from three of its four partial products, below 4 q) took thirteen and moves to zero-extend its halves, a butterfly of
+// it 30 with its share of the folds, now 18.  The passes over a few limbs and the conversions wait more than they multiply, so the calls
+// gain less: 64 x 64 product at n = 4096 449 -> 422 us, rotary embedding at level 3 76.1 -> 72.2, ciphertext product at level 13 153 -> 148,
+// query times K at level 12 16570 -> 16170, decode-step attention at level 3 3490 -> 3410.
+// Additions are not reduced; forward, all values are folded after every fourth stage (tight: second), inverse, the sums after every
+// second (tight: each).  Bounds in units of q (+ 1/512 a product):
+//   forward  4 (input) or 1 -> + 2 a stage -> at most 12, folded to 1; tight: 4 -> 8, folded
+//   inverse  2 -> 4 -> 8 (sums), folded to 1; products 1; tight: 2 -> 4, folded
 struct IntArith {
     typedef u64 T;
-    u64 q, ni, nip;
-    unsigned c, bs, mask;         // 2^b - q, b - 32, low bits of the upper word
-    bool tight;                   // 8 q is the most a word holds: fold after every stage
-    const u64 *w, *wp;
+    u64 q;
+    unsigned c, bs, mask, up;     // 2^b - q, b - 32, low bits of the upper word, 2^(b-31)
+    bool tight;                   // 8 q is the most a word holds
+    const IntTw *w;
+    IntTw ni;
     __device__ __forceinline__ void init(const NttTables &t, int mi, int n) {
         q = t.modc[mi].q;
         bs = 32 - __clz((unsigned)(q >> 32));
-        c = (unsigned)((1ULL << (bs + 32)) - q), mask = (1u << bs) - 1u, tight = bs > 28;
-        w = t.tw + (size_t)mi * n, wp = t.twp + (size_t)mi * n;
-        ni = nip = 0;
-        if (t.ninv) ni = t.ninv[mi], nip = t.ninvp[mi];
+        c = (unsigned)((1ULL << (bs + 32)) - q), mask = (1u << bs) - 1u, up = 2u << bs, tight = bs > 28;
+        w = t.tw + (size_t)mi * n;
+        ni = IntTw{0, 0, 0, 0};
+        if (t.ninv) ni = t.ninv[mi];
     }
     __device__ __forceinline__ T from_rest(u64 raw) const { return raw; }     // inverse: below 2q
     __device__ __forceinline__ T from_lazy(u64 raw) const { return raw; }     // forward: below 4q
     __device__ __forceinline__ T from_mid(u64 raw) const { return raw; }
     __device__ __forceinline__ u64 to_mid(T v) const { return v; }
-    typedef u64 W;
-    struct Word { u64 w, wp; };
-    __device__ __forceinline__ Word word(unsigned idx) const { return Word{*word_at(w, idx), *word_at(wp, idx)}; }
-    __device__ __forceinline__ void pair(const Word &x, W &a, W &b) const { a = x.w, b = x.wp; }
-    __device__ __forceinline__ u64 mul_lazy(u64 a, u64 x, u64 xp) const {     // a x mod q in [0, 4q)
-        const unsigned a0 = (unsigned)a, a1 = (unsigned)(a >> 32), p0 = (unsigned)xp, p1 = (unsigned)(xp >> 32);
-        const u64 h = (u64)a1 * p1 + ((u64)__umulhi(a1, p0) + __umulhi(a0, p1));
-        return a * x - h * q;
+    typedef IntTw W;
+    typedef uint4 Word;                                                       // one 16-byte load
+    __device__ __forceinline__ Word word(unsigned idx) const { return *word_at(reinterpret_cast<const uint4 *>(w), idx); }
+    __device__ __forceinline__ void pair(const Word &x, W &a, W &) const { a = IntTw{x.x, x.y, x.z, x.w}; }
+    __device__ __forceinline__ u64 mul(u64 a, const IntTw &x) const {         // a x mod q, below q + q / 512
+        const unsigned a0 = (unsigned)a, a1 = (unsigned)(a >> 32);
+        const u64 l = (u64)a0 * x.w0 + (u64)a1 * x.v0, h = (u64)a0 * x.w1 + (u64)a1 * x.v1;
+        return fold(l + (u64)(unsigned)h * up + (u64)(unsigned)(h >> 32) * (2 * c));
     }
     __device__ __forceinline__ u64 fold(u64 v) const {
         const unsigned hi = (unsigned)(v >> 32);
         return (u64)(hi >> bs) * c + (((u64)(hi & mask) << 32) | (unsigned)v);
     }
-    __device__ __forceinline__ void ct(T &X, T &Y, W a, W b) const {
-        const u64 t = mul_lazy(Y, a, b), x = X;
+    __device__ __forceinline__ void ct(T &X, T &Y, const W &a, const W &) const {
+        const u64 t = mul(Y, a), x = X;
         X = x + t;
-        Y = (x + 4 * q) - t;
+        Y = (x + 2 * q) - t;
     }
-    __device__ __forceinline__ void gs(T &X, T &Y, W a, W b) const {
-        const u64 d = (X + (tight ? 4 * q : 8 * q)) - Y;
+    __device__ __forceinline__ void gs(T &X, T &Y, const W &a, const W &) const {
+        const u64 d = (X + 4 * q) - Y;
         X = X + Y;
-        Y = mul_lazy(d, a, b);
+        Y = mul(d, a);
     }
     // stage s of the transform is done on all the lane's values
     template <int NV>
     __device__ __forceinline__ void after_fwd(int s, T (&v)[NV]) const {
-        if ((s & 1) || tight) {
+        if ((s & 3) == 3 || ((s & 1) && tight)) {
 #pragma unroll
             for (int k = 0; k < NV; k++) v[k] = fold(v[k]);
         }
@@ -144,7 +149,7 @@ struct IntArith {
             return plain(ar, redc((u128)u * pt, ar.q, qinv), conv, false, 0, has_c, c);
         }
     };
-    __device__ __forceinline__ u64 to_rest_inv(T v) const { return mul_shoup(v, ni, nip, q); }
+    __device__ __forceinline__ u64 to_rest_inv(T v) const { return to_rest_fwd(mul(v, ni)); }
 };
 
 // ---- FP64 arithmetic for moduli below 2^50 -----------------------------------------------------------
@@ -1629,11 +1634,11 @@ static NttTables tables_of(const cm_ctx *ctx, bool inverse, int limbs) {
     t.modc = ctx->d_modc, t.fpq = ctx->d_fpq;
     t.large = limbs >= 256;
     if (!inverse) {
-        t.tw = ctx->d_tw, t.twp = ctx->d_twp, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
-        t.ninv = t.ninvp = nullptr, t.ninvd = t.ninvqd = nullptr;
+        t.tw = ctx->d_tw, t.twd = ctx->d_twd, t.twqd = ctx->d_twqd;
+        t.ninv = nullptr, t.ninvd = t.ninvqd = nullptr;
     } else {
-        t.tw = ctx->d_itw, t.twp = ctx->d_itwp, t.twd = ctx->d_itwd, t.twqd = ctx->d_itwqd;
-        t.ninv = ctx->d_ninv, t.ninvp = ctx->d_ninvp, t.ninvd = ctx->d_ninvd, t.ninvqd = ctx->d_ninvqd;
+        t.tw = ctx->d_itw, t.twd = ctx->d_itwd, t.twqd = ctx->d_itwqd;
+        t.ninv = ctx->d_ninv, t.ninvd = ctx->d_ninvd, t.ninvqd = ctx->d_ninvqd;
     }
     return t;
 }

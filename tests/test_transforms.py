@@ -156,3 +156,27 @@ def test_unreduced_words_that_add_up(limbs):
         assert np.array_equal(*outs)
     finally:
         gctx.close()
+
+
+@pytest.mark.parametrize("n,bits", [(n, bits) for n in (4096, 65536) for bits in (51, 54, 60, 61)])
+def test_product_with_a_cut_up_twiddle(n, bits):
+    """IntArith::mul(): under the first and the 64th prime below 2^bits, any 64-bit word times a twiddle in the form of h_int_tw:
+    no sum passes 2^64, and the result is the product, below q + q / 512."""
+    primes = _moduli(bits, n, 64)
+    assert max((1 << bits) - q for q in primes) < 1 << 28
+    rng = np.random.default_rng(bits)
+    m30, m32 = (1 << 30) - 1, (1 << 32) - 1
+    for q in (primes[0], primes[-1]):
+        b, c = bits, (1 << bits) - q
+        for i in range(2000):
+            a = int(rng.integers(0, 1 << 63)) * 2 + 1 if i % 3 else (1 << 64) - 1 - int(rng.integers(0, 1 << 20))
+            w = int(rng.integers(0, q)) if i % 5 else q - 1
+            v = (w << 32) % q
+            w0, w1, v0, v1 = w & m30, (w >> 30) << (61 - b), v & m30, (v >> 30) << (61 - b)
+            a0, a1 = a & m32, a >> 32
+            lo, hi = a0 * w0 + a1 * v0, a0 * w1 + a1 * v1
+            assert max(w1, v1) <= m32 and hi <= (1 << 64) - 1
+            t = lo + (hi & m32) * (1 << (b - 31)) + (hi >> 32) * 2 * c
+            assert t < 1 << 64
+            r = (t >> b) * c + (t & ((1 << b) - 1))
+            assert r < q + q // 512 and r % q == a * w % q
