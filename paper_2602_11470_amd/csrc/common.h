@@ -118,6 +118,14 @@ struct ConvTable {            // fast base conversion src -> dst (all indices in
 // and target moduli below 2^50; otherwise plain 128-bit sums).  Rows past ns are zero (a zero inverse, zero weights, input
 // row 0), so that a kernel may run over a fixed number of sources.
 enum { CONV_SPLIT_25 = 0, CONV_SPLIT_30 = 1, CONV_SPLIT_NONE = 2 };
+// A weight w of the conversion to q = 2^b - c and v = w 2^s mod q, s = 25 or 30 the bits of the lower part of a y_m = y0 + 2^s y1 (by
+// `split`), each as x0 + 2^t x1.  Below 2^50 t = ceil(b / 2), from there 30; the upper parts are scaled up by 2^z so that the upper word
+// of h = sum y0 w1 + y1 v1 has the weight 2^(b+3) = 8 c (z = 29 - (b - t)) or 2^(b+1) = 2 c (z = 61 - b):
+//   sum y_m w_m = l + mlo (h mod 2^32) + mhi (h >> 32)  (mod q),   l = sum y0 w0 + y1 v0,  mlo = 2^(t-z),  mhi = 8 c or 2 c.
+// With up to nine terms below 2^60 (target below 2^50) or nine below 2^50 or four below 2^60 (others) nothing passes 2^64.
+struct ConvCut {
+    unsigned w0, w1, v0, v1;
+};
 // one target modulus: everything the conversion to it reads, in one record
 struct ConvTarget {
     int mod, row;                 // modulus index, output row
@@ -127,9 +135,13 @@ struct ConvTarget {
     u64 wm[CONV_MAX_SRC];         // hat_m mod q in multiplier form
     double wl;                    // the same of the weight of a folded last limb (ConvDev::fold): P mod q
     u64 wlm;
+    // the same weights cut up (ConvDev::near); q = 2^b - c, cb = b - 32, twice: b < 49 (a second fold)
+    unsigned c, cb, mlo, mhi, twice;
+    ConvCut cut[CONV_MAX_SRC], cutl;
 };
 struct ConvDev {
     int ns, nt, split;
+    int near;                     // all targets are close below a power of two and the sums of the cut weights fit
     int in_rows[CONV_MAX_SRC];
     u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC], src_q[CONV_MAX_SRC];
     double src_qd[CONV_MAX_SRC], inv_hat_d[CONV_MAX_SRC], inv_hat_dq[CONV_MAX_SRC];   // q_m, inv_hat_m, inv_hat_m / q_m as doubles

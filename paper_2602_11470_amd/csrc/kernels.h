@@ -188,6 +188,7 @@ struct ConvBatch {
     size_t in_stride = 0, out_stride = 0, own_stride = 0;
     const u64 *own_src = nullptr;
     unsigned own_g = 0;
+    bool near = false;                // all its tables are (ConvDev::near)
     bool fold = false;                // the tables' folded limb is a source (ConvDev)
     bool half = false;                // n = 65536: column pass only, own rows not copied (launch_rows_ip does the rest)
 };

@@ -1448,6 +1448,106 @@ struct ConvY {
         }
     }
 };
+// The same from cut weights (ConvDev::near): the y_m are kept as their two halves, a sum over the sources is four multiply-adds a
+// term into two accumulators without carries, and what q looks like takes their combination to below q + q / 16: two more
+// multiply-adds and a fold.  With four sources 30 vector instructions a word; the forms above take 31 to FP64 targets and 67 to the
+// 60-bit ones (half of a raise's work at the middle levels) or, from 60-bit sources, 63.  ModDown of 8 ciphertexts at level 22 (368
+// limbs) 131 -> 109 us, with the rescale at level 12 (192 limbs) 89.5 -> 75, raise of 8 at level 12 (440 limbs) 130 -> 122; calls: query
+// times K at level 12 15170 -> 14720 us, grouped-query attention 13340 -> 12970, ciphertext product at level 13 141 -> 138, 64 x 64 at
+// n = 4096 427 -> 407.  Three workgroups a compute unit (80 registers) instead of two: the largest launches 3 % less, those of a single
+// key switch 3 to 9 % more, calls 0 to 2 % more.
+template <int NS, int NV, bool FOLD>
+struct ConvNear {
+    unsigned lo[NV][NS], hi[NV][NS], flo[NV], fhi[NV];
+    __device__ __forceinline__ void set(const ConvDev &t, const u64 (&x)[NV][NS]) {
+        if (t.split == CONV_SPLIT_25) {
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                const double q = t.src_qd[m], w = t.inv_hat_d[m], wq = t.inv_hat_dq[m];
+#pragma unroll
+                for (int k = 0; k < NV; k++) {
+                    const double v = __longlong_as_double((long long)(x[k][m] | 0x4330000000000000ULL)) - TWO52;
+                    const double h = v * w, l = __builtin_fma(v, w, -h), c = __builtin_rint(v * wq);
+                    double y = __builtin_fma(-c, q, h) + l;                  // |y| < q
+                    y += y < 0.0 ? q : 0.0;
+                    const u64 i = (u64)__double_as_longlong(y + TWO52) & 0x000FFFFFFFFFFFFFULL;
+                    lo[k][m] = (unsigned)i & LOW25, hi[k][m] = (unsigned)(i >> 25);
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                const u64 y = mul_shoup(x[k][m], t.inv_hat[m], t.inv_hat_sh[m], t.src_q[m]);
+                lo[k][m] = (unsigned)y & LOW30, hi[k][m] = (unsigned)(y >> 30);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ void fold(const ConvDev &t, const u64 (&x)[NV]) {
+        u64 c[NV];
+        const u64 q = t.fold.t.q;
+#pragma unroll
+        for (int k = 0; k < NV; k++) flo[k] = fhi[k] = 0;
+        opaque();
+        sum<false>(t.fold.t, c);
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const u64 y = mul_shoup((x[k] + 2 * q) - c[k], t.fold.pinv, t.fold.pinv_sh, q);
+            const bool s25 = t.split == CONV_SPLIT_25;
+            flo[k] = (unsigned)y & (s25 ? LOW25 : LOW30), fhi[k] = (unsigned)(s25 ? y >> 25 : y >> 30);
+        }
+    }
+    // 32-bit values to the compiler: extended to 64 bits outside the loop over the targets they lose what is known of their upper halves
+    __device__ __forceinline__ void opaque() {
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                OPAQUE(lo[k][m]);
+                OPAQUE(hi[k][m]);
+            }
+        if (FOLD) {
+#pragma unroll
+            for (int k = 0; k < NV; k++) {
+                OPAQUE(flo[k]);
+                OPAQUE(fhi[k]);
+            }
+        }
+    }
+    template <bool WITH = FOLD>
+    __device__ __forceinline__ void sum(const ConvTarget &o, u64 (&out)[NV]) const {
+        const unsigned mlo = o.mlo, mhi = o.mhi, c = o.c, cb = o.cb, mask = (1u << cb) - 1u;
+        auto fold_word = [&](u64 v) { return (u64)((unsigned)(v >> 32) >> cb) * c + (((u64)((unsigned)(v >> 32) & mask) << 32) | (unsigned)v); };
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            u64 l = 0, h = 0;
+#pragma unroll
+            for (int m = 0; m < NS; m++) {
+                l += (u64)lo[k][m] * o.cut[m].w0, l += (u64)hi[k][m] * o.cut[m].v0;
+                h += (u64)lo[k][m] * o.cut[m].w1, h += (u64)hi[k][m] * o.cut[m].v1;
+            }
+            if (WITH) {
+                l += (u64)flo[k] * o.cutl.w0, l += (u64)fhi[k] * o.cutl.v0;
+                h += (u64)flo[k] * o.cutl.w1, h += (u64)fhi[k] * o.cutl.v1;
+            }
+            out[k] = fold_word(l + (u64)(unsigned)h * mlo + (u64)(unsigned)(h >> 32) * mhi);
+        }
+        if (o.twice) {
+#pragma unroll
+            for (int k = 0; k < NV; k++) out[k] = fold_word(out[k]);
+        }
+    }
+    __device__ __forceinline__ void target_any(int, const ConvTarget &o, const FpArith &ar, double (&v)[NV]) const {
+        u64 x[NV];
+        sum(o, x);
+#pragma unroll
+        for (int k = 0; k < NV; k++) v[k] = ar.from_rest(x[k]);
+    }
+    __device__ __forceinline__ void target(int, const ConvTarget &o, u64 (&out)[NV]) const { sum(o, out); }
+};
 // n = 65536.  A workgroup of 512 lanes owns a column tile (256 rows x 8 columns) of one item: every lane loads four words
 // of each source, keeps the y_m in registers and runs over up to tg targets: conversion, then stages 0..7 as radix
 // 4 x 4 x 4 x 4, the exchanges through two LDS buffers in turn (one barrier each).  The converted limbs are never stored: a
@@ -1512,8 +1612,16 @@ __device__ __forceinline__ void ccf_body(u64 *lds, int buf, int large, u64 *p, t
 #pragma unroll
     for (int k = 0; k < 4; k++) ntt_store(large, word_at(p, (4 * sub + k) * n2 + c), ar.to_mid(v[k]));
 }
+template <int NS, int NV, bool FOLD, bool NEAR>
+struct ConvForm {
+    typedef ConvY<NS, NV, FOLD> T;
+};
+template <int NS, int NV, bool FOLD>
+struct ConvForm<NS, NV, FOLD, true> {
+    typedef ConvNear<NS, NV, FOLD> T;
+};
 // grid: x = column tile, y = target group (the last targets, those under the 60-bit primes, first), then the copies
-template <int NS, bool FOLD>
+template <int NS, bool FOLD, bool NEAR>
 __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a,
                                                                NttTables t, int n, int logn) {
     __shared__ u64 lds[2 * 256 * CCF_W];
@@ -1537,7 +1645,7 @@ __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols
     if (r0 >= nt) return;
     const int c = threadIdx.x % CCF_W, sub = threadIdx.x / CCF_W;
     in += (blockIdx.z / a.in_group) * a.in_stride + tile * CCF_W;
-    ConvY<NS, 4, FOLD> y;
+    typename ConvForm<NS, 4, FOLD, NEAR>::T y;
     {
         u64 x[4][NS], xf[4];
 #pragma unroll
@@ -1577,7 +1685,7 @@ __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols
     }
 }
 // n = 4096: one workgroup per target limb, conversion and the whole transform.  grid: x = target, then the own rows; y = item
-template <int NS, bool TAIL, bool FOLD>
+template <int NS, bool TAIL, bool FOLD, bool NEAR>
 __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a, NttTables t,
                                                              int n, int logn, FinishBatch fb) {
     __shared__ u64 lds[FULL_LDS];
@@ -1597,7 +1705,7 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
         return;
     }
     in += (z / a.in_group) * a.in_stride;
-    ConvY<NS, 8, FOLD> y;
+    typename ConvForm<NS, 8, FOLD, NEAR>::T y;
     {
         u64 x[8][NS], xf[8];
 #pragma unroll
@@ -1611,6 +1719,7 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
         y.set(tab, x);
         if (FOLD) y.fold(tab, xf);
     }
+    y.opaque();
     const ConvTarget &o = tab.t[r];
     const int limb = z * nt + r;                          // of the tail: item, component, limb
     u64 *p = out + (size_t)o.row * n;
@@ -1741,17 +1850,23 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     Prof prof_(ctx, CM_K_BASE_CONV, limbs, st);
     if (n == 4096) {
         const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
+#define FULL_FORM(NS_, NEAR_)                                                                                                    \
+    do {                                                                                                                         \
+        if (b.fold) hipLaunchKernelGGL((conv_full_fwd<NS_, true, true, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
+        else if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true, false, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
+        else hipLaunchKernelGGL((conv_full_fwd<NS_, false, false, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch()); \
+    } while (0)
 #define FULL_LAUNCH(NS_)                                                                                                         \
-    if (b.fold) hipLaunchKernelGGL((conv_full_fwd<NS_, true, true>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
-    else if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
-    else hipLaunchKernelGGL((conv_full_fwd<NS_, false, false>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch())
+    if (b.near) FULL_FORM(NS_, true);                                                                                            \
+    else FULL_FORM(NS_, false)
         // the instantiation for eight spills 31 of 256 registers (124 with a folded limb: ks_drop_fits) and still takes less than conversion and transform in two launches
         // (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us; five sources 66 -> 56
         if (ns <= 1) { FULL_LAUNCH(1); }
         else if (ns <= 2) { FULL_LAUNCH(2); }
         else if (ns <= 4) { FULL_LAUNCH(4); }
-        else { FULL_LAUNCH(8); }
+        else { FULL_FORM(8, false); }              // cut weights spill 40 to 70
 #undef FULL_LAUNCH
+#undef FULL_FORM
         return;
     }
     a.tg = CCF_TG;
@@ -1762,18 +1877,24 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
     // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
     // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
+#define CCF_FORM(NS_, FOLD_)                                                                                                     \
+    do {                                                                                                                         \
+        if (b.near) hipLaunchKernelGGL((conv_cols_fwd<NS_, FOLD_, true>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn); \
+        else hipLaunchKernelGGL((conv_cols_fwd<NS_, FOLD_, false>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);  \
+    } while (0)
 #define CCF_LAUNCH(NS_)                                                                                                          \
     do {                                                                                                                         \
-        if (b.fold) hipLaunchKernelGGL((conv_cols_fwd<NS_, true>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);   \
-        else hipLaunchKernelGGL((conv_cols_fwd<NS_, false>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);         \
+        if (b.fold) CCF_FORM(NS_, true);                                                                                         \
+        else CCF_FORM(NS_, false);                                                                                               \
     } while (0)
     if (ns <= 1) CCF_LAUNCH(1);
     else if (ns <= 2) CCF_LAUNCH(2);
     else if (ns <= 4) CCF_LAUNCH(4);
     else if (ns <= 6) CCF_LAUNCH(6);
-    else if (ns <= 7) hipLaunchKernelGGL((conv_cols_fwd<7, false>), grid, dim3(CCF_THREADS), 0, st, out, in, a, t, n, ctx->logn);   // never folded (ks_drop_fits)
+    else if (ns <= 7) CCF_FORM(7, false);   // never folded (ks_drop_fits)
     else CCF_LAUNCH(8);
 #undef CCF_LAUNCH
+#undef CCF_FORM
     if (b.half) return;
     if (fb) launch_rows_fwd<true>(out, d_rows, d_mods, t, n, limbs, *fb, st);
     else launch_rows_fwd<false>(out, d_rows, d_mods, t, n, limbs, FinishBatch(), st);

@@ -76,10 +76,43 @@ struct KsLevelFull : KsLevel {
     ConvDev *d_modup = nullptr; // one table per digit
     ConvDev *d_moddown = nullptr;
     int modup_max_nt = 0;
+    bool near_up = false, near_down = false, near_drop[2] = {false, false};        // the tables' ConvDev::near
 };
 
 #define RESCALE_MAX_COMPS (2 * CM_KS_BATCH)
 #define IDX_CHUNK_U64 128
+static u64 p_mod(const cm_ctx *ctx, u64 q) {                     // P mod q
+    u64 P = 1;
+    for (int k = 0; k < ctx->K; k++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + k] % q, q);
+    return P;
+}
+// What a near table asks of a target modulus 2^b - c: a word below 2^63 folds to below q + q / 16, once (b >= 49) or twice.
+static bool conv_near_target(u64 q) {
+    const int b = 64 - __builtin_clzll(q);
+    const u64 c = (1ULL << b) - q;
+    if (b < 40 || c >= (1ULL << 28)) return false;
+    if (b > 50) return true;
+    const u64 once = (c << (63 - b)) + (b < 49 ? 1ULL << b : 0);
+    return (b < 49 ? (once >> b) * c : once) < q / 16;
+}
+static void conv_cut(ConvTarget &o, ConvCut &cut, u64 w, int s) {
+    const int b = 64 - __builtin_clzll(o.q), t = b <= 50 ? (b + 1) / 2 : 30, z = b <= 50 ? 29 - (b - t) : 61 - b;
+    const u64 v = h_mulmod(w, (1ULL << s) % o.q, o.q), low = (1ULL << t) - 1;
+    o.c = (unsigned)((1ULL << b) - o.q), o.cb = b - 32, o.mlo = 1u << (t - z), o.mhi = o.c << (b <= 50 ? 3 : 1), o.twice = b < 49;
+    cut = ConvCut{(unsigned)(w & low), (unsigned)((w >> t) << z), (unsigned)(v & low), (unsigned)((v >> t) << z)};
+}
+// The weights of a table cut up, where that form covers it (terms: sources, a folded limb among them, smax the largest of their moduli)
+static void conv_near(const cm_ctx *ctx, ConvDev &d, const ConvTable &t, int terms, u64 smax, bool fold) {
+    const int s = d.split == CONV_SPLIT_25 ? 25 : 30;
+    d.near = smax < (1ULL << 60);
+    for (int r = 0; r < t.nt && d.near; r++) {
+        ConvTarget &o = d.t[r];
+        d.near = conv_near_target(o.q) && (s == 25 || o.q < (1ULL << 50) || terms <= 4);
+        if (!d.near) return;
+        for (int m = 0; m < t.ns; m++) conv_cut(o, o.cut[m], t.hat[(size_t)m * t.nt + r], s);
+        if (fold) conv_cut(o, o.cutl, p_mod(ctx, o.q), s);
+    }
+}
 static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector<int> &in_rows,
                         const std::vector<int> &out_rows) {
     ConvDev d;
@@ -101,6 +134,7 @@ static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector
         tmax = std::max(tmax, mc.q);
     }
     d.split = smax < (1ULL << 50) ? CONV_SPLIT_25 : smax < (1ULL << 60) && tmax < (1ULL << 50) ? CONV_SPLIT_30 : CONV_SPLIT_NONE;
+    conv_near(ctx, d, t, t.ns, smax, false);
     return d;
 }
 // the conversion of a ks_drop: `sets` times the special limbs (rows level + 1 ..), the folded limb in row `level`, targets q_0 .. q_{level-1}
@@ -117,13 +151,15 @@ static ConvDev drop_dev(cm_ctx *ctx, int level, int sets) {
     }
     for (int r = 0; r <= level; r++) out_rows.push_back(r);
     ConvDev d = conv_dev(ctx, w, in_rows, out_rows);
+    u64 smax = *std::max_element(d.src_q, d.src_q + w.ns);
     for (int r = 0; r <= level; r++) {
         const u64 q = ctx->mod[r];
-        u64 P = 1;
-        for (int k = 0; k < ctx->K; k++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + k] % q, q);
+        const u64 P = p_mod(ctx, q);
         d.t[r].wl = (double)P, d.t[r].wlm = h_mulmod(P, (u64)(((u128)1 << 64) % q), q);
+        smax = std::max(smax, r == level ? q : 0);
         if (r == level) d.fold.pinv = h_invmod(P, q), d.fold.pinv_sh = h_shoup(d.fold.pinv, q);
     }
+    conv_near(ctx, d, w, w.ns + 1, smax, true);
     d.fold.row = level, d.fold.t = d.t[level], d.nt = level;
     return d;
 }
@@ -171,6 +207,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
         mu.push_back(conv_dev(ctx, tabs[j], digs[j], out_rows));
         k.modup_max_nt = std::max(k.modup_max_nt, tabs[j].nt);
     }
+    k.near_up = std::all_of(mu.begin(), mu.end(), [](const ConvDev &d) { return d.near; });
     k.d_modup = up(mu);
     {
         // Transform the converted limbs modulus by modulus rather than digit by digit: the limbs that
@@ -239,6 +276,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
         std::vector<int> sp_in;
         for (int s = 0; s < ctx->K; s++) sp_in.push_back(level + 1 + s);
         std::vector<ConvDev> md(1, conv_dev(ctx, get_moddown(ctx, level), sp_in, q_rows));
+        k.near_down = md[0].near;
         k.d_moddown = up(md);
         std::vector<int> sp0, sp1;
         for (int s = 0; s < ctx->K; s++) sp0.push_back(s), sp1.push_back(k.ext + level + 1 + s);
@@ -249,6 +287,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
     for (int sets = 1; sets <= 2; sets++) {
         if (!ks_drop_fits(ctx, level, sets, 1)) continue;
         std::vector<ConvDev> dd(1, drop_dev(ctx, level, sets));
+        k.near_drop[sets - 1] = dd[0].near;
         std::vector<int> rows, mods;
         for (int c = 0; c < (sets == 1 ? 2 * CM_KS_BATCH : 2); c++)
             for (int j = 0; j <= sets * ctx->K; j++) {
@@ -295,7 +334,7 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     ConvBatch cb;
     cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
-    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half;
+    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half, cb.near = k.near_up;
     launch_conv_ntt(ctx, cb, digits, A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
 }
@@ -305,7 +344,7 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
 static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, int batch, u64 *conv, const u64 *in, size_t in_stride,
                          const FinishBatch &fb, hipStream_t st) {
     ConvBatch cb;
-    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1;
+    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1, cb.near = k.near_down;
     cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
     launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
 }
@@ -367,8 +406,7 @@ FoldIn ks_drop_fold(cm_ctx *ctx, int level, int sets, const u64 *add, size_t add
     FoldIn fi;
     if (!add && !acc) return fi;
     const ModC &mc = ctx->modc[level];
-    u64 P = 1;
-    for (int i = 0; i < ctx->K; i++) P = h_mulmod(P, ctx->mod[ctx->L + 1 + i] % mc.q, mc.q);
+    const u64 P = p_mod(ctx, mc.q);
     fi.per = sets * ctx->K + 1, fi.rows = level + 1, fi.add_comps = add_comps, fi.g = (unsigned)g;
     fi.add = add, fi.acc = acc, fi.add_stride = add_stride, fi.acc_stride = acc_stride;
     fi.pm = h_mulmod(P, (u64)(((u128)1 << 64) % mc.q), mc.q), fi.q = mc.q, fi.qinv = mc.qinv;
@@ -394,7 +432,7 @@ cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *a
     }
     fb.pinv = k.d_pqinv, fb.ainv = get_qlinv(ctx, level);
     ConvBatch cb;
-    cb.tabs = k.d_drop[sets - 1], cb.batch = 2 * m, cb.ns = ns, cb.max_nt = level, cb.fold = true;
+    cb.tabs = k.d_drop[sets - 1], cb.batch = 2 * m, cb.ns = ns, cb.max_nt = level, cb.fold = true, cb.near = k.near_drop[sets - 1];
     cb.in_stride = (size_t)ext * n, cb.out_stride = (size_t)level * n;
     launch_conv_ntt(ctx, cb, A.bconv, us, st, nullptr, k.d_red_mods, 2 * m * level, &fb);
     return CM_OK;
@@ -571,6 +609,7 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     cb.tab_period = k.beta, cb.in_group = k.beta;
     cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
     cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln, cb.half = half;
+    cb.near = k.near_up;
     launch_conv_ntt(ctx, cb, digits, ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
     return CM_OK;
 }

@@ -157,3 +157,45 @@ def test_conversion_sums_in_doubles_stay_exact():
         worst = max(worst, abs(Fraction(y * w) - int(c) * q) / q)
     assert worst <= Fraction(88, 100)
     assert 9 * Fraction(88, 100) * q < 1 << 53
+
+
+@pytest.mark.parametrize("n", [4096, 65536])
+@pytest.mark.parametrize("b", [40, 45, 48, 49, 50, 51, 54, 60, 61])
+def test_conversion_sums_from_cut_weights(n, b):
+    """ConvNear::sum: the largest y and w, for as many terms as ops.hip lets a near table have; nothing passes 64 bits (the products'
+    factors 32), and what is left is the sum, below q + q / 16."""
+    from oracle import params
+    q = params.scan_primes(b, n, 8)[-1]
+    c = (1 << b) - q
+    t, z = ((b + 1) // 2, 29 - (b - (b + 1) // 2)) if b <= 50 else (30, 61 - b)
+    up, mlo, mhi = (3 if b <= 50 else 1), 1 << (t - z), c << (3 if b <= 50 else 1)
+    m32, mb = (1 << 32) - 1, (1 << b) - 1
+    assert mhi <= m32
+
+    def cut(w, s):
+        v = (w << s) % q
+        return w & ((1 << t) - 1), (w >> t) << z, v & ((1 << t) - 1), (v >> t) << z
+
+    rng = np.random.default_rng(b)
+    for s, terms in ((25, 9), (30, 9 if b < 51 else 4)):
+        ymax = (1 << 50) - 1 if s == 25 else (1 << 60) - 1
+        for i in range(300):
+            ys = [ymax if i < 2 else int(rng.integers(0, ymax)) for _ in range(terms)]
+            ws = [q - 1 if i % 2 else int(rng.integers(0, q)) for _ in range(terms)]
+            lo = hi = 0
+            for y, w in zip(ys, ws):
+                w0, w1, v0, v1 = cut(w, s)
+                y0, y1 = y & ((1 << s) - 1), y >> s
+                assert max(y0, y1, w0, w1, v0, v1) <= m32
+                lo, hi = lo + y0 * w0 + y1 * v0, hi + y0 * w1 + y1 * v1
+            assert max(lo, hi) <= M64
+            T = lo + (hi & m32) * mlo + (hi >> 32) * mhi
+            assert T <= M64 and (b > 50 or T < 1 << 63)
+            for _ in range(2 if b < 49 else 1):
+                T = (T >> b) * c + (T & mb)
+            assert T < q + q // 16 and T % q == sum(y * w for y, w in zip(ys, ws)) % q
+    # the growth of four FP64 stages that start there, and of the integer stages (at most 4 q asked for)
+    bound = 1 + 1 / 16
+    for _ in range(4):
+        bound += 0.5 + 0.375 * bound
+    assert bound < 8
