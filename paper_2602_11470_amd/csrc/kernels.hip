@@ -1109,94 +1109,121 @@ struct MacWords {                              // 64-bit words, pairs interleave
         w0 = (unsigned)v & LOW30, w1 = (unsigned)(v >> 30);
     }
 };
-// A workgroup owns 64 coefficients of one limb; its four waves take KW giant steps each.  The baby words are staged in LDS as
-// two halves, sixteen baby steps a pass (16 KiB, so that registers set the occupancy: four waves a SIMD with KW = 1 and 2, 103 and 118
-// registers, three with KW = 4, 151, which the 50-bit groups need; thirty-two measured
-// the same), the first group of a pass requested before them.  The sums stay in registers over the passes and are written once.
+// An item is 64 coefficients of one limb and W * KW giant steps, KW to each of a workgroup's W waves.  The baby words are staged in LDS
+// as two halves, sixteen baby steps a pass (16 KiB), the first group of a pass requested before them.  The sums stay in registers over
+// the passes and then wait in LDS, where a lane reads back what it wrote.
 #define MAC_JC 16
-template <int KW, class G>
-__device__ __forceinline__ void mac_body(uint2 *sb, u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
-                                         const ModC &m, const MacLayout &lay, int l, int ch, size_t cs, size_t ct_stride) {
+template <int W, int KW, class G>
+__device__ __forceinline__ void mac_body(uint2 *sb, u64 *res, const u64 *__restrict__ babies, const u64 *__restrict__ pts, const ModC &m,
+                                         const MacLayout &lay, int l, int ch, int kb, bool first, size_t cs, size_t ct_stride) {
     const int co = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t o = (size_t)l * lay.n + ch * MAC_CO;          // uniform: lanes differ by co alone
-    for (int k0 = 0; k0 < lay.r_o; k0 += 4 * KW) {
-        const int kb = k0 + wave * KW;
-        const bool active = kb < lay.r_o;                     // uniform in a wave
-        u64 s[KW][2];
+    const bool active = kb < lay.r_o;                         // uniform in a wave
+    u64 s[KW][2];
 #pragma unroll
-        for (int k = 0; k < KW; k++) s[k][0] = s[k][1] = 0;
-        for (int j0 = 0; j0 < lay.r_i; j0 += MAC_JC) {
-            const int groups = min(MAC_JC, lay.r_i - j0) / MAC_G, rows = 2 * MAC_G * groups;
-            const u64 *p = pts + lay.group(l, ch, j0 / MAC_G, kb);
-            G q;
-            if (active) q.load(p, co);                        // in flight across the staging
-            {
-                // a lane stages word `co` of rows wave, wave + 4, ...: all its loads are issued before the first is used
-                constexpr int ROWS = MAC_JC * 2 / 4;
-                u64 x[ROWS];
+    for (int k = 0; k < KW; k++) s[k][0] = s[k][1] = 0;
+    for (int j0 = 0; j0 < lay.r_i; j0 += MAC_JC) {
+        const int groups = min(MAC_JC, lay.r_i - j0) / MAC_G, rows = 2 * MAC_G * groups;
+        const u64 *p = pts + lay.group(l, ch, j0 / MAC_G, kb);
+        G q;
+        if (active) q.load(p, co);                            // in flight across the staging
+        {
+            // a lane stages word `co` of rows wave, wave + W, ...: all its loads are issued before the first is used
+            constexpr int ROWS = MAC_JC * 2 / W;
+            u64 x[ROWS];
 #pragma unroll
-                for (int it = 0; it < ROWS; it++) {
-                    const int r = min(wave + 4 * it, rows - 1);             // past the last row: one more time, never used
-                    x[it] = __builtin_nontemporal_load(babies + (size_t)(j0 + (r >> 1)) * ct_stride + (r & 1) * cs + o + co);
-                }
-                if (j0 || k0) __syncthreads();
-#pragma unroll
-                for (int it = 0; it < ROWS; it++)
-                    sb[(wave + 4 * it) * MAC_CO + co] = make_uint2((unsigned)x[it] & ((1u << G::B) - 1), (unsigned)(x[it] >> G::B));
-                __syncthreads();
+            for (int it = 0; it < ROWS; it++) {
+                const int r = min(wave + W * it, rows - 1);                 // past the last row: one more time, never used
+                x[it] = __builtin_nontemporal_load(babies + (size_t)(j0 + (r >> 1)) * ct_stride + (r & 1) * cs + o + co);
             }
-            if (!active) continue;
+            if (j0 || !first) __syncthreads();
 #pragma unroll
-            for (int k = 0; k < KW; k++) {
-                MacAcc t[2];
-#pragma unroll 1
-                for (int g = 0; g < groups; g++) {
-                    G nx = q;
-                    // the next group is in flight while this one is multiplied
-                    if (g + 1 < groups) nx.load(p + ((size_t)(g + 1) * lay.r_o + k) * G::GROUP_WORDS, co);
-                    else if (k + 1 < KW) nx.load(p + (size_t)(k + 1) * G::GROUP_WORDS, co);
-#pragma unroll
-                    for (int j = 0; j < MAC_G; j++) {
-                        unsigned w0, w1;
-                        q.word(j, w0, w1);
-#pragma unroll
-                        for (int c = 0; c < 2; c++) {
-                            const uint2 b = sb[((g * MAC_G + j) * 2 + c) * MAC_CO + co];
-                            t[c].mac(b.x, b.y, w0, w1);
-                        }
-                        if (G::TERMS <= MAC_G && (j + 1) % G::TERMS == 0) {
-#pragma unroll
-                            for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q), t[c] = MacAcc();
-                        }
-                    }
-                    q = nx;
-                }
-                if (G::TERMS > MAC_G) {
-#pragma unroll
-                    for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q);
-                }
-            }
+            for (int it = 0; it < ROWS; it++)
+                sb[(wave + W * it) * MAC_CO + co] = make_uint2((unsigned)x[it] & ((1u << G::B) - 1), (unsigned)(x[it] >> G::B));
+            __syncthreads();
         }
         if (!active) continue;
 #pragma unroll
+        for (int k = 0; k < KW; k++) {
+            MacAcc t[2];
+#pragma unroll 1
+            for (int g = 0; g < groups; g++) {
+                G nx = q;
+                // the next group is in flight while this one is multiplied
+                if (g + 1 < groups) nx.load(p + ((size_t)(g + 1) * lay.r_o + k) * G::GROUP_WORDS, co);
+                else if (k + 1 < KW) nx.load(p + (size_t)(k + 1) * G::GROUP_WORDS, co);
+#pragma unroll
+                for (int j = 0; j < MAC_G; j++) {
+                    unsigned w0, w1;
+                    q.word(j, w0, w1);
+#pragma unroll
+                    for (int c = 0; c < 2; c++) {
+                        const uint2 b = sb[((g * MAC_G + j) * 2 + c) * MAC_CO + co];
+                        t[c].mac(b.x, b.y, w0, w1);
+                    }
+                    if (G::TERMS <= MAC_G && (j + 1) % G::TERMS == 0) {
+#pragma unroll
+                        for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q), t[c] = MacAcc();
+                    }
+                }
+                q = nx;
+            }
+            if (G::TERMS > MAC_G) {
+#pragma unroll
+                for (int c = 0; c < 2; c++) s[k][c] = addmod(s[k][c], t[c].template reduce<G::B>(m), m.q);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KW; k++) res[2 * k * MAC_CO] = s[k][0], res[(2 * k + 1) * MAC_CO] = s[k][1];
+}
+// Bound by HBM, whose reads the writes disturb: 3 % of the bytes written while others read cost 20 % of a launch, the same bytes written
+// when nobody reads cost little (a plain kernel that reads 5 GB and writes 5 %: 789 us without its writes, 1012 with them spread over
+// the launch, 844 and 857 as four and eight launches that write last).  So a launch is what the chip holds at once (16 waves a compute
+// unit: 108 and 124 registers), `wgs` workgroups of `rounds` <= P items each, P by the LDS (40 KiB and 64 KiB a workgroup), and all
+// of them write at its end.  Against one launch whose workgroups write as they end: 512 products at levels 23 and 4 1413 -> 1300 and 470 ->
+// 431 us, 2048 at level 3 1359 -> 1305, 1024 at level 9 1267 -> 1155, three times 128 at level 13 292 -> 268 each; one launch that writes
+// after every third item 1439, 448, 1344, 1208 and 282.  P = 8 with eight waves for eight giant steps, P = 4 for sixteen: within 2 %.
+// Item `round` of a workgroup: chunk and limb by unit, then the block of W * KW giant steps.
+struct MacArgs {
+    int wgs, round, rounds, blocks;
+};
+template <int W, int KW, int P>
+__global__ __launch_bounds__(64 * W, 4) void k_vmm_mac(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
+                                                       const ModC *__restrict__ modc, MacLayout lay, MacArgs a, int limbs, size_t ct_stride,
+                                                       int level, int L) {
+    __shared__ uint2 sb[MAC_JC * 2 * MAC_CO];
+    __shared__ u64 res[P * W * KW * 2 * MAC_CO];
+    const int chunks = lay.n / MAC_CO, nsp = limbs - (level + 1);
+    const int co = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t cs = (size_t)limbs * lay.n;
+    // the limbs of the special primes (60 or 64 bits a word) come first
+    auto item = [&](int i, int &l, int &ch, int &kb) {
+        const int r = a.round + i, u = (int)blockIdx.x + a.wgs * (r / a.blocks), y = u / chunks;
+        l = y < nsp ? level + 1 + y : y - nsp, ch = u % chunks, kb = ((r % a.blocks) * W + wave) * KW;
+        return y < limbs;
+    };
+    for (int i = 0; i < a.rounds; i++) {
+        int l, ch, kb;
+        if (!item(i, l, ch, kb)) break;
+        const ModC m = modc[l <= level ? l : L + 1 + (l - level - 1)];
+        u64 *r = res + ((i * W + wave) * KW * 2) * MAC_CO + co;
+        if (lay.is50(l)) mac_body<W, KW, MacPacked50>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
+        else if (lay.is60(l)) mac_body<W, KW, MacPacked60>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
+        else mac_body<W, KW, MacWords>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
+    }
+    for (int i = 0; i < a.rounds; i++) {
+        int l, ch, kb;
+        if (!item(i, l, ch, kb)) break;
+        if (kb >= lay.r_o) continue;
+        const u64 *r = res + ((i * W + wave) * KW * 2) * MAC_CO + co;
+        const size_t o = (size_t)l * lay.n + ch * MAC_CO + co;
+#pragma unroll
         for (int k = 0; k < KW; k++)
 #pragma unroll
-            for (int c = 0; c < 2; c++) 
-                __hip_atomic_store(out + (size_t)(kb + k) * ct_stride + c * cs + o + co, s[k][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int c = 0; c < 2; c++)
+                __hip_atomic_store(out + (size_t)(kb + k) * ct_stride + c * cs + o, r[(2 * k + c) * MAC_CO], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-}
-template <int KW>
-__global__ __launch_bounds__(TPB) void k_vmm_mac(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
-                                                   const ModC *__restrict__ modc, MacLayout lay, int limbs, size_t ct_stride, int level, int L) {
-    __shared__ uint2 sb[MAC_JC * 2 * MAC_CO];
-    // the limbs of the special primes (60 or 64 bits a word, the slowest workgroups) are dispatched first, not last
-    const int nsp = limbs - (level + 1), y = blockIdx.y;
-    const int l = y < nsp ? level + 1 + y : y - nsp, mi = l <= level ? l : L + 1 + (l - level - 1);
-    const ModC m = modc[mi];
-    const size_t cs = (size_t)limbs * lay.n;
-    if (lay.is50(l)) mac_body<KW, MacPacked50>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
-    else if (lay.is60(l)) mac_body<KW, MacPacked60>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
-    else mac_body<KW, MacWords>(sb, out, babies, pts, m, lay, l, blockIdx.x, cs, ct_stride);
 }
 // Fewer than eight baby steps (RI = 1, 2 or 4): a lane keeps its baby words and runs over MAC_FEW_K giant steps, the words of the
 // next one requested ahead.  Bound by HBM, mostly by the sums it writes (2 words for RI read), so these are stored at agent scope.
@@ -1250,13 +1277,18 @@ void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, in
 #undef FEW_LAUNCH
         return;
     }
-    const dim3 grid(ctx->n / MAC_CO, limbs), block(TPB);
-#define MAC_LAUNCH(KW_)                                                                                                            \
-    hipLaunchKernelGGL(k_vmm_mac<KW_>, grid, block, 0, st, out, babies, pts, ctx->d_modc, lay, limbs, ct_stride, level, ctx->L)
-    if (r_o <= 4) MAC_LAUNCH(1);
-    else if (r_o <= 8) MAC_LAUNCH(2);
-    else MAC_LAUNCH(4);
-#undef MAC_LAUNCH
+    auto launch = [&](auto kernel, int waves, int per, int hold) {
+        const int units = ctx->n / MAC_CO * limbs, wgs = std::min(units, 256 * 16 / waves), blocks = (r_o + per - 1) / per;
+        const int rounds = (units + wgs - 1) / wgs * blocks, launches = (rounds + hold - 1) / hold;
+        for (int i = 0; i < launches; i++) {
+            const int r0 = (int)((long long)rounds * i / launches), r1 = (int)((long long)rounds * (i + 1) / launches);
+            hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64 * waves), 0, st, out, babies, pts, ctx->d_modc, lay, MacArgs{wgs, r0, r1 - r0, blocks},
+                               limbs, ct_stride, level, ctx->L);
+        }
+    };
+    if (r_o <= 4) launch(k_vmm_mac<4, 1, 6>, 4, 4, 6);
+    else if (r_o <= 8) launch(k_vmm_mac<4, 2, 3>, 4, 8, 3);
+    else launch(k_vmm_mac<8, 2, 3>, 8, 16, 3);
 }
 // ---- masks before the shared rotations of query-times-K --------------------------------------------------
 // A[k] = sum_{c < nk} T[c] * M[(c + k) mod E] for k < shared: T the nk key-ciphertext sums [2][limbs][n] (stacked),
