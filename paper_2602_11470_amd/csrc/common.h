@@ -143,6 +143,11 @@ struct ConvDev {
     int ns, nt, split;
     int near;                     // all targets are close below a power of two and the sums of the cut weights fit
     int in_rows[CONV_MAX_SRC];
+    // a single source whose inverse transform is part of the conversion (ConvBatch::inv): its modulus index, and n^-1 inv_hat, the last
+    // factor of that transform with its own (below 2^50 as a double, above cut up)
+    int src_mod;
+    double inv_hat_nd;
+    IntTw inv_hat_n;
     u64 inv_hat[CONV_MAX_SRC], inv_hat_sh[CONV_MAX_SRC], src_q[CONV_MAX_SRC];
     double src_qd[CONV_MAX_SRC], inv_hat_d[CONV_MAX_SRC], inv_hat_dq[CONV_MAX_SRC];   // q_m, inv_hat_m, inv_hat_m / q_m as doubles
     ConvTarget t[CONV_MAX_DST];

@@ -190,8 +190,11 @@ struct ConvBatch {
     unsigned own_g = 0;
     bool near = false;                // all its tables are (ConvDev::near)
     bool fold = false;                // the tables' folded limb is a source (ConvDev)
+    // the input is in the evaluation domain (conv_joins_inv): read through the Galois map own_g if there are own rows
+    bool inv = false;
     bool half = false;                // n = 65536: column pass only, own rows not copied (launch_rows_ip does the rest)
 };
+bool conv_joins_inv(const cm_ctx *ctx, bool near, int ns, int targets);
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb = nullptr);
 

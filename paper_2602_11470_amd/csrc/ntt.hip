@@ -1197,13 +1197,10 @@ __device__ __forceinline__ void full_fwd_body(u64 *lds, u64 *p, typename A::T (&
 #pragma unroll
     for (int k = 0; k < 8; k++) p[tid + 512 * k] = lds[pad8(tid + 512 * k)];
 }
+// up to the last factor: v[k] = word tid + 512 k, whose place in lds no other lane touches any more
 template <class A>
-__device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n, int limb,
-                                              const FoldIn &fi) {
-    A ar;
-    ar.init(t, mi, n);
+__device__ __forceinline__ void full_inv_regs(u64 *lds, typename A::T (&v)[8], const A &ar, const u64 *ps, unsigned g, int n, int limb, const FoldIn &fi) {
     const int tid = threadIdx.x, h2 = tid >> 6, l2 = tid & 63, h3 = tid >> 3, l3 = tid & 7;
-    typename A::T v[8];
     {
         const int logn = 31 - __clz(n);
         u64 w[8];
@@ -1245,8 +1242,16 @@ __device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, u
         for (int k = 0; k < 8; k++) v[k] = ar.from_mid(lds[pad8(k * 512 + tid)]);
         radix_inv<3, 0>(v, ar, tw);
     }
+}
+template <class A>
+__device__ __forceinline__ void full_inv_body(u64 *lds, u64 *p, const u64 *ps, unsigned g, const NttTables &t, int mi, int n, int limb,
+                                              const FoldIn &fi) {
+    A ar;
+    ar.init(t, mi, n);
+    typename A::T v[8];
+    full_inv_regs(lds, v, ar, ps, g, n, limb, fi);
 #pragma unroll
-    for (int k = 0; k < 8; k++) p[k * 512 + tid] = ar.to_rest_inv(v[k]);
+    for (int k = 0; k < 8; k++) p[k * 512 + threadIdx.x] = ar.to_rest_inv(v[k]);
 }
 // grid.x = limbs.  The transform may run in place: every word is read before the first is written.
 template <class A, bool TAIL>
@@ -1486,6 +1491,22 @@ struct ConvNear {
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    // one source, from what its inverse transform leaves before the last factor
+    __device__ __forceinline__ void set_inv(const ConvDev &t, const FpArith &ar, const double (&v)[NV]) {
+        const double w = t.inv_hat_nd, wq = w * ar.qinv;
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const u64 y = ar.canon(ar.mulmod(v[k], w, wq));
+            lo[k][0] = (unsigned)y & LOW25, hi[k][0] = (unsigned)(y >> 25);
+        }
+    }
+    __device__ __forceinline__ void set_inv(const ConvDev &t, const IntArith &ar, const u64 (&v)[NV]) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const u64 y = ar.to_rest_fwd(ar.mul(v[k], t.inv_hat_n));
+            lo[k][0] = (unsigned)y & LOW30, hi[k][0] = (unsigned)(y >> 30);
+        }
+    }
     __device__ __forceinline__ void fold(const ConvDev &t, const u64 (&x)[NV]) {
         u64 c[NV];
         const u64 q = t.fold.t.q;
@@ -1685,8 +1706,13 @@ __global__ __launch_bounds__(CCF_THREADS, FOLD && NS > 6 ? 2 : 4) void conv_cols
     }
 }
 // n = 4096: one workgroup per target limb, conversion and the whole transform.  grid: x = target, then the own rows; y = item
-template <int NS, bool TAIL, bool FOLD, bool NEAR>
-__global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a, NttTables t,
+// INV: the workgroup does the inverse transform of its single source first (ConvBatch::inv), which leaves the source's words where the
+// conversion wants them; its last factor is the conversion's first.  Every target of a digit repeats that transform, on compute units
+// that have nothing else to do, and a key switch takes three launches instead of five: 6.7 + 8.8 us -> 12.1 (raise), 6.7 + 10.3 -> 14.9
+// (ModDown), a gap between launches less each; 64 x 64 product at n = 4096 409 -> 357 us, 512 x 512 in the unrolled form 210 -> 190.
+// All twiddles of a transform requested at its start: 13.4 and 15.6.
+template <int NS, bool TAIL, bool FOLD, bool NEAR, bool INV = false>
+__global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ out, const u64 *__restrict__ in, ConvArgs a, NttTables t, NttTables ti,
                                                              int n, int logn, FinishBatch fb) {
     __shared__ u64 lds[FULL_LDS];
     const int z = blockIdx.y, tid = threadIdx.x;
@@ -1706,7 +1732,22 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
     }
     in += (z / a.in_group) * a.in_stride;
     typename ConvForm<NS, 8, FOLD, NEAR>::T y;
-    {
+    if constexpr (INV) {
+        const u64 *src = in + (size_t)tab.in_rows[0] * n;
+        if (tab.split == CONV_SPLIT_25) {
+            FpArith ar;
+            ar.init(ti, tab.src_mod, n);
+            double v[8];
+            full_inv_regs(lds, v, ar, src, a.own_g, n, 0, FoldIn());
+            y.set_inv(tab, ar, v);
+        } else {
+            IntArith ar;
+            ar.init(ti, tab.src_mod, n);
+            u64 v[8];
+            full_inv_regs(lds, v, ar, src, a.own_g, n, 0, FoldIn());
+            y.set_inv(tab, ar, v);
+        }
+    } else {
         u64 x[8][NS], xf[8];
 #pragma unroll
         for (int m = 0; m < NS; m++)
@@ -1839,6 +1880,11 @@ void launch_ntt_fwd_finish(cm_ctx *ctx, u64 *conv, const int *d_mods, const Fini
     launch_cols_fwd(conv, src, d_src_rows, none, d_mods, t, n, limbs, st);
     launch_rows_fwd<true>(conv, none, d_mods, t, n, limbs, fb, st);
 }
+// Up to two workgroups a compute unit the repeated transforms are free; scores times V, eight relinearisations at a time, with 392, 800 and
+// 1352 targets 302, 362 and 436 us joined, 322, 358 and 424 with the launch of its own.  More sources would be transformed one after the
+// other.
+#define JOIN_TARGETS 512
+bool conv_joins_inv(const cm_ctx *ctx, bool near, int ns, int targets) { return ctx->n == 4096 && near && ns == 1 && targets <= JOIN_TARGETS; }
 void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, hipStream_t st, const int *d_rows, const int *d_mods,
                      int limbs, const FinishBatch *fb) {
     const int n = ctx->n, ns = b.ns;              // rounded up to an instantiated bound below
@@ -1850,11 +1896,18 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     Prof prof_(ctx, CM_K_BASE_CONV, limbs, st);
     if (n == 4096) {
         const dim3 grid(b.max_nt + (b.own_src ? ns : 0), b.batch);
+        const NttTables ti = tables_of(ctx, true, 0);
+#define FULL_KERNEL(FB_, ...) hipLaunchKernelGGL((conv_full_fwd<__VA_ARGS__>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, ti, n, ctx->logn, FB_)
+        if (b.inv) {
+            if (fb) FULL_KERNEL(*fb, 1, true, false, true, true);
+            else FULL_KERNEL(FinishBatch(), 1, false, false, true, true);
+            return;
+        }
 #define FULL_FORM(NS_, NEAR_)                                                                                                    \
     do {                                                                                                                         \
-        if (b.fold) hipLaunchKernelGGL((conv_full_fwd<NS_, true, true, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
-        else if (fb) hipLaunchKernelGGL((conv_full_fwd<NS_, true, false, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, *fb); \
-        else hipLaunchKernelGGL((conv_full_fwd<NS_, false, false, NEAR_>), grid, dim3(FULL_THREADS), 0, st, out, in, a, t, n, ctx->logn, FinishBatch()); \
+        if (b.fold) FULL_KERNEL(*fb, NS_, true, true, NEAR_);                                                                    \
+        else if (fb) FULL_KERNEL(*fb, NS_, true, false, NEAR_);                                                                  \
+        else FULL_KERNEL(FinishBatch(), NS_, false, false, NEAR_);                                                               \
     } while (0)
 #define FULL_LAUNCH(NS_)                                                                                                         \
     if (b.near) FULL_FORM(NS_, true);                                                                                            \
@@ -1867,6 +1920,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
         else { FULL_FORM(8, false); }              // cut weights spill 40 to 70
 #undef FULL_LAUNCH
 #undef FULL_FORM
+#undef FULL_KERNEL
         return;
     }
     a.tg = CCF_TG;

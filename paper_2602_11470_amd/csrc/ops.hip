@@ -122,6 +122,11 @@ static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector
     for (int m = 0; m < t.ns; m++) {
         d.in_rows[m] = in_rows[m];
         d.inv_hat[m] = t.inv_hat[m], d.inv_hat_sh[m] = t.inv_hat_sh[m], d.src_q[m] = ctx->mod[t.src[m]];
+        if (t.ns == 1) {
+            const u64 hn = h_mulmod(t.inv_hat[m], h_invmod((u64)ctx->n, d.src_q[m]), d.src_q[m]);
+            d.src_mod = t.src[m], d.inv_hat_nd = (double)hn;
+            if (d.src_q[m] >= (1ULL << 50)) d.inv_hat_n = h_int_tw(hn, d.src_q[m]);
+        }
         d.src_qd[m] = (double)d.src_q[m], d.inv_hat_d[m] = (double)t.inv_hat[m], d.inv_hat_dq[m] = d.inv_hat_d[m] / d.src_qd[m];
         smax = std::max(smax, d.src_q[m]);
     }
@@ -331,20 +336,22 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     const size_t n = ctx->n;
     // coefficient-domain copy of d (out of place), then all digits in one conversion launch; a
     // digit's own limbs are copied from d itself, which is already in the evaluation domain
-    launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     ConvBatch cb;
+    cb.inv = conv_joins_inv(ctx, k.near_up, ctx->alpha, k.beta * k.modup_max_nt);
+    if (!cb.inv) launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
     cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half, cb.near = k.near_up;
-    launch_conv_ntt(ctx, cb, digits, A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
+    launch_conv_ntt(ctx, cb, digits, cb.inv ? d : A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
 }
 
-// second half of a ModDown of `batch` polynomials: their K special limbs (coefficient domain, at in + z*in_stride) converted
+static bool moddown_joins(const cm_ctx *ctx, const KsLevelFull &k, int batch) { return conv_joins_inv(ctx, k.near_down, ctx->K, batch * (k.level + 1)); }
+// second half of a ModDown of `batch` polynomials: their K special limbs (coefficient domain, if moddown_joins not, at in + z*in_stride) converted
 // to q_0 .. q_level and transformed in `conv`, with the tail fb
 static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, int batch, u64 *conv, const u64 *in, size_t in_stride,
                          const FinishBatch &fb, hipStream_t st) {
     ConvBatch cb;
-    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1, cb.near = k.near_down;
+    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1, cb.near = k.near_down, cb.inv = moddown_joins(ctx, k, batch);
     cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
     launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
 }
@@ -355,7 +362,7 @@ cm_status moddown_into(cm_ctx *ctx, u64 *u, int level, const u64 *addend, int ad
     const size_t n = ctx->n;
     if (!addend) addend_comps = 0, g = 0;
     if (rows_done) launch_cols_inv(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, st);
-    else launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
+    else if (!moddown_joins(ctx, k, 2)) launch_ntt_rows(ctx, u, k.d_sp_rows, k.d_sp_mods, 2 * ctx->K, true, st);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = addend_comps;
     fb.u[0] = u, fb.out[0] = out, fb.accum[0] = accum, fb.g[0] = (unsigned)g;
@@ -491,7 +498,7 @@ static void moddown_batch(cm_ctx *ctx, const KsLevelFull &k, u64 *bu, int m, con
     const int level = k.level;
     const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n;
     if (rows_done) launch_cols_inv(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, st);
-    else launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
+    else if (!moddown_joins(ctx, k, 2 * m)) launch_ntt_rows(ctx, bu, k.d_bsp_rows, k.d_bsp_mods, m * 2 * ctx->K, true, st);
     auto add_of = [&](int r) { return addends ? addends[r] : nullptr; };
     auto acc_of = [&](int r) { return accums ? accums[r] : nullptr; };
     FinishBatch fb;
@@ -531,7 +538,7 @@ cm_status moddown_many_second(cm_ctx *ctx, u64 *us, int level, int cnt, u64 *con
         u64 *bu = us + base * ublk;
         // special limbs of the second components to the coefficient domain, converted to q_0..q_level, transformed,
         // and the tail (u - conv) P^{-1} fused into the last pass of that transform
-        launch_ntt_rows(ctx, bu, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st);
+        if (!moddown_joins(ctx, k, m)) launch_ntt_rows(ctx, bu, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st);
         FinishBatch fb;
         fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
         for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
@@ -547,12 +554,14 @@ cm_status moddown_second_keep(cm_ctx *ctx, const u64 *R, int level, u64 *out, hi
     Arena A = arena_of(ctx);
     const size_t n = ctx->n;
     // the K special limbs of the second component, to the coefficient domain in a buffer of their own
-    launch_ntt_src(ctx, A.tmp[0], nullptr, R, k.d_sp1_rows, k.d_sp_mods, ctx->K, true, st, 0);
+    const bool joined = moddown_joins(ctx, k, 1);
+    if (!joined) launch_ntt_src(ctx, A.tmp[0], nullptr, R, k.d_sp1_rows, k.d_sp_mods, ctx->K, true, st, 0);
     FinishBatch fb;
     fb.items = 1, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     fb.u[0] = R, fb.out[0] = out, fb.pinv = get_pinv(ctx, level);
-    moddown_conv(ctx, k, k.d_moddown0, 1, A.bconv, A.tmp[0], 0, fb, st);
+    if (joined) moddown_conv(ctx, k, k.d_moddown, 1, A.bconv, R + (size_t)k.ext * n, 0, fb, st);
+    else moddown_conv(ctx, k, k.d_moddown0, 1, A.bconv, A.tmp[0], 0, fb, st);
     return CM_OK;
 }
 
@@ -563,13 +572,15 @@ cm_status moddown_second_keep_many(cm_ctx *ctx, const u64 *Rs, int level, int m,
     const size_t n = ctx->n, ublk = 2 * (size_t)k.ext * n;
     // the K special limbs of every second component, to the coefficient domain in a buffer of their own
     // (the three temporaries of the arena are contiguous: 9 (L+1) limbs, room for CM_KS_BATCH * K)
-    launch_ntt_src(ctx, A.tmp[0], nullptr, Rs, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st, 0);
+    const bool joined = moddown_joins(ctx, k, m);
+    if (!joined) launch_ntt_src(ctx, A.tmp[0], nullptr, Rs, k.d_bsp1_rows, k.d_bsp_mods, m * ctx->K, true, st, 0);
     FinishBatch fb;
     fb.items = m, fb.level = level, fb.ext = k.ext, fb.addend_comps = 0, fb.ncomp = 1, fb.comp0 = 1;
     for (int r = 0; r < CM_MASK_BATCH; r++) fb.addend[r] = nullptr, fb.accum[r] = nullptr, fb.u[r] = nullptr, fb.out[r] = nullptr, fb.g[r] = 0;
     for (int r = 0; r < m; r++) fb.u[r] = Rs + r * ublk, fb.out[r] = outs[r];
     fb.pinv = get_pinv(ctx, level);
-    moddown_conv(ctx, k, k.d_moddown0, m, A.bconv, A.tmp[0], (size_t)ctx->K * n, fb, st);
+    if (joined) moddown_conv(ctx, k, k.d_moddown, m, A.bconv, Rs + (size_t)k.ext * n, ublk, fb, st);
+    else moddown_conv(ctx, k, k.d_moddown0, m, A.bconv, A.tmp[0], (size_t)ctx->K * n, fb, st);
     return CM_OK;
 }
 
@@ -603,14 +614,16 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     const KsLevelFull &k = ks_level_full(ctx, t.level);
     const size_t n = ctx->n, ln = (size_t)(t.level + 1) * n;
     // the tables list the items in order, so the first m items are a prefix of every table
-    launch_ntt_src(ctx, ksin, nullptr, cts, t.d_src_rows, t.d_in_mods, m * (t.level + 1), true, st, g);
     ConvBatch cb;
+    cb.inv = conv_joins_inv(ctx, k.near_up, ctx->alpha, m * k.beta * k.modup_max_nt);
+    if (!cb.inv) launch_ntt_src(ctx, ksin, nullptr, cts, t.d_src_rows, t.d_in_mods, m * (t.level + 1), true, st, g);
     cb.tabs = k.d_modup, cb.batch = m * k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt;
     cb.tab_period = k.beta, cb.in_group = k.beta;
     cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
     cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln, cb.half = half;
     cb.near = k.near_up;
-    launch_conv_ntt(ctx, cb, digits, ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
+    if (cb.inv) cb.in_stride = cb.own_stride;
+    launch_conv_ntt(ctx, cb, digits, cb.inv ? cb.own_src : ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
     return CM_OK;
 }
 
