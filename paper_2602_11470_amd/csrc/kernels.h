@@ -49,6 +49,9 @@ void launch_tensor(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int limbs,
 // out[z][3][limbs][n] = a (x) b[z], b[z] = b + z*2*limbs*n, z < cnt
 // out[z][3][limbs][n] = sum_{j < cnt} a[j] (x) b[z*cnt + j] for z < groups (a, b stacked ciphertexts [2][limbs][n])
 // b[z*group_stride + j*term_stride] is term j of group z (0, 0 = groups of cnt consecutive ciphertexts)
+bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int limbs);
+void launch_tensor_sum_passes(cm_ctx *ctx, u64 *out, size_t out_pass, const u64 *a, size_t a_pass, int passes, const u64 *b, int cnt, int groups,
+                              int limbs, hipStream_t st, int gs, int ts);
 void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
                        int group_stride = 0, int term_stride = 0);
 void launch_tensor_batch(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int limbs, hipStream_t st);

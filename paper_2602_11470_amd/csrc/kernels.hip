@@ -316,6 +316,80 @@ __global__ __launch_bounds__(TPB) void k_tensor_sum_stationary(u64 *__restrict__
         oz[o + 2 * cs] = F.canon(d2);
     }
 }
+// The same sums for PASSES sets of ciphertexts a against one b: out[pass] and a[pass] stacked at out_pass and a_pass words.  A wave
+// owns a pass for 64 coefficients; the words of a group are staged in LDS for all of them, the next group's requested ahead.
+// Bound by HBM: with a launch a pass the cache was read once per pass of a grouped query.  Four passes over 128 ciphertexts of ten
+// limbs 4 x 317 -> 582 us, grouped-query attention at level 9 12860 -> 11640, with two passes 6750 -> 6390.  108 registers because the
+// terms are worked on four at a time (sched_barrier); left to itself the compiler spills 187 of 128.
+#define TS_CO 64
+template <int PASSES>
+__global__ __launch_bounds__(64 * PASSES, 4) void k_tensor_sum_passes(u64 *__restrict__ out, const u64 *__restrict__ a, const u64 *__restrict__ b,
+                                                                   const FpQ *__restrict__ fpq, int limbs, int n, int cnt, int groups, int gs, int ts,
+                                                                   size_t out_pass, size_t a_pass) {
+    constexpr int ROWS = 2 * TS_MAX_CNT / PASSES;
+    __shared__ double sb[2][2 * TS_MAX_CNT * TS_CO];
+    const int co = threadIdx.x & 63, pass = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = blockIdx.y;
+    const FpQ fq = fpq[l];
+    const MacFp F{fq.q, fq.qinv};
+    const size_t o = (size_t)l * n + blockIdx.x * TS_CO + co, cs = (size_t)limbs * n;
+    a += pass * a_pass, out += pass * out_pass;
+    u64 r[ROWS];
+    // row = 2 j + component; rows of terms at or past cnt hold the last term's words again, and multiply zeros
+    auto request = [&](int z) {
+#pragma unroll
+        for (int it = 0; it < ROWS; it++) {
+            const int row = pass * ROWS + it, j = min(row >> 1, cnt - 1);
+            r[it] = __builtin_nontemporal_load(b + (((size_t)z * gs + (size_t)j * ts) * 2 + (row & 1)) * cs + o);
+        }
+    };
+    request(0);
+    double a0[TS_MAX_CNT], a1[TS_MAX_CNT];
+#pragma unroll
+    for (int j = 0; j < TS_MAX_CNT; j++) {
+        a0[j] = j < cnt ? MacFp::from_u64(a[(size_t)j * 2 * cs + o]) : 0.0;
+        a1[j] = j < cnt ? MacFp::from_u64(a[(size_t)j * 2 * cs + cs + o]) : 0.0;
+    }
+    for (int z = 0; z < groups; z++) {
+        // two buffers in turn: a wave that writes to one has passed the barrier behind the others' reads of it
+        double *s = sb[z & 1] + co;
+#pragma unroll
+        for (int it = 0; it < ROWS; it++) s[(pass * ROWS + it) * TS_CO] = MacFp::from_u64(r[it]);
+        __syncthreads();
+        if (z + 1 < groups) request(z + 1);
+        double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < TS_MAX_CNT; j++) {
+            const double b0 = s[2 * j * TS_CO], b1 = s[(2 * j + 1) * TS_CO], b0q = b0 * F.qinv, b1q = b1 * F.qinv;
+            d0 += F.mulmod(a0[j], b0, b0q);
+            d1 += F.mulmod(a0[j], b1, b1q) + F.mulmod(a1[j], b0, b0q);
+            d2 += F.mulmod(a1[j], b1, b1q);
+            if (j & 1) d0 = F.norm(d0), d1 = F.norm(d1), d2 = F.norm(d2);
+            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        u64 *oz = out + (size_t)z * 3 * cs;
+        oz[o] = F.canon(d0);
+        oz[o + cs] = F.canon(d1);
+        oz[o + 2 * cs] = F.canon(d2);
+    }
+}
+bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int limbs) {
+    for (int l = 0; l < limbs; l++)
+        if (ctx->mod[l] >= (1ULL << 50)) return false;
+    return cnt <= TS_MAX_CNT;
+}
+void launch_tensor_sum_passes(cm_ctx *ctx, u64 *out, size_t out_pass, const u64 *a, size_t a_pass, int passes, const u64 *b, int cnt, int groups,
+                              int limbs, hipStream_t st, int gs, int ts) {
+    Prof prof_(ctx, CM_K_ELEMENTWISE, 3 * limbs * groups * passes, st);
+    const dim3 grid(ctx->n / TS_CO, limbs);
+    for (int p = 0; p < passes; p += 4) {                  // a power of two
+        u64 *op = out + p * out_pass;
+        const u64 *ap = a + p * a_pass;
+        if (passes - p >= 4)
+            hipLaunchKernelGGL(k_tensor_sum_passes<4>, grid, dim3(256), 0, st, op, ap, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts, out_pass, a_pass);
+        else
+            hipLaunchKernelGGL(k_tensor_sum_passes<2>, grid, dim3(128), 0, st, op, ap, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts, out_pass, a_pass);
+    }
+}
 void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
                        int group_stride, int term_stride) {
     const int gs = group_stride ? group_stride : cnt, ts = term_stride ? term_stride : 1;

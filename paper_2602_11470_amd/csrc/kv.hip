@@ -617,17 +617,11 @@ static cm_status kv_sv_keys(const cm_evk *evk, const cm_kv *kv, bool reduce, boo
     }
     return CM_OK;
 }
-static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm_ct *in, cm_ct *out, hipStream_t st,
-                       bool reduce, const u64 *array, bool replicate) {
-    const int lv = kv->level, limbs = lv + 1;
-    CMCHK(kv_sv_keys(evk, kv, reduce, replicate));
-    const size_t n = ctx->n, ctw = kv_ctw(kv), ln = (size_t)limbs * n;
-    const u64 *relin = find_key(evk, 0);
+// the baby steps of in; tmp: a ciphertext
+static cm_status kv_sv_babies(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm_ct *in, u64 *babies, u64 *tmp, hipStream_t st, bool replicate) {
+    const int lv = kv->level;
+    const size_t ctw = kv_ctw(kv), ln = (size_t)(lv + 1) * ctx->n;
     const long long Ht = (long long)kv->H * kv->t;
-    const KsLevel &kl = ks_level(ctx, lv);
-    const size_t B = CM_KS_BATCH, dblk = (size_t)kl.beta * kl.ext * n, ublk = 2 * (size_t)kl.ext * n;
-    u64 *babies = kv->d_work, *inner = babies + (size_t)kv->r_i * ctw, *T = inner + (size_t)kv->r_o * ctw,
-        *tmp = T + B * 3 * ln, *R = tmp + ctw, *ksin = R + ctw, *bdigits = ksin + B * ln;
     u64 *digits = arena_digits(ctx);
     HIPCHK(hipMemcpyAsync(babies, in->dev, ctw * 8, hipMemcpyDeviceToDevice, st));
     if (replicate) {
@@ -651,12 +645,30 @@ static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm
         }
         CMCHK(ks_apply_many(ctx, digits, lv, kv->r_i - 1, keys.data(), gs.data(), babies, dst.data(), st));
     }
+    return CM_OK;
+}
+// sums: the tensor sums of all r_o <= CM_KS_BATCH groups, where they are formed already (in is then its scale alone)
+static cm_status kv_sv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, const cm_ct *in, cm_ct *out, hipStream_t st,
+                       bool reduce, const u64 *array, bool replicate, const u64 *sums = nullptr) {
+    const int lv = kv->level, limbs = lv + 1;
+    CMCHK(kv_sv_keys(evk, kv, reduce, replicate));
+    const size_t n = ctx->n, ctw = kv_ctw(kv), ln = (size_t)limbs * n;
+    const u64 *relin = find_key(evk, 0);
+    const long long Ht = (long long)kv->H * kv->t;
+    const KsLevel &kl = ks_level(ctx, lv);
+    const size_t B = CM_KS_BATCH, dblk = (size_t)kl.beta * kl.ext * n, ublk = 2 * (size_t)kl.ext * n;
+    u64 *babies = kv->d_work, *inner = babies + (size_t)kv->r_i * ctw, *Tw = inner + (size_t)kv->r_o * ctw,
+        *tmp = Tw + B * 3 * ln, *R = tmp + ctw, *ksin = R + ctw, *bdigits = ksin + B * ln;
+    const u64 *T = sums ? sums : Tw;
+    u64 *digits = arena_digits(ctx);
+    if (!sums) CMCHK(kv_sv_babies(ctx, evk, kv, in, babies, tmp, st, replicate));
     // inner_g = relinearise(sum_j baby_j (x) V_{g r_i + j}): the sums of up to CM_KS_BATCH groups by one launch, their
     // third components raised together, one inner-product launch with the relinearisation key read once, one ModDown
     for (int g0 = 0; g0 < kv->r_o; g0 += CM_KS_BATCH) {
         const int m = kv->r_o - g0 < CM_KS_BATCH ? kv->r_o - g0 : CM_KS_BATCH;
-        if (array == kv->d_x) launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * ctw, kv->r_i, m, limbs, st, 1, kv->r_o);
-        else launch_tensor_sum(ctx, T, babies, array + (size_t)g0 * kv->r_i * ctw, kv->r_i, m, limbs, st);
+        if (sums) {
+        } else if (array == kv->d_x) launch_tensor_sum(ctx, Tw, babies, array + (size_t)g0 * ctw, kv->r_i, m, limbs, st, 1, kv->r_o);
+        else launch_tensor_sum(ctx, Tw, babies, array + (size_t)g0 * kv->r_i * ctw, kv->r_i, m, limbs, st);
         const bool half = rows_ip_fits(ctx, kl.beta, lv, m, 1);
         CMCHK(ks_raise_many(ctx, kv->relin_tabs, T, ksin, bdigits, st, m, 0, half));
         u64 *bu = arena_batch_sums(ctx);
@@ -762,12 +774,25 @@ struct cm_gqa {
     int G = 1, t = 1, t_kv = 1, level = 0;       // level of the cache
     std::vector<cm_rope *> fwd, back;            // inner rotations by delta t at level+1 / level-1, delta = 1 .. G-1
     u64 *d_work = nullptr;                       // six ciphertexts of level+2 limbs
+    // baby steps [G][r_i] and tensor sums [G][r_o][3] of all passes, so that they read the cache together; null (a pass at a time)
+    // where the joint kernel does not apply or the memory is not there
+    u64 *d_passes = nullptr;
+    int r_i = 0, r_o = 0;
 };
+static size_t gqa_sum_words(const cm_kv *kv) { return kv->r_o * (kv_ctw(kv) + kv_ctw(kv) / 2); }      // of a pass
+static bool gqa_joint(const cm_gqa *g, const cm_kv *kv) { return g->d_passes && kv->r_i == g->r_i && kv->r_o == g->r_o; }
+static u64 *gqa_babies(const cm_gqa *g, const cm_kv *kv, int pass) { return g->d_passes + pass * (kv->r_i * kv_ctw(kv)); }
+static u64 *gqa_sums(const cm_gqa *g, const cm_kv *kv, int pass) { return gqa_babies(g, kv, g->G) + pass * gqa_sum_words(kv); }
+static void gqa_tensor_sums(cm_ctx *ctx, const cm_gqa *g, const cm_kv *kv, const u64 *array, hipStream_t st) {
+    const bool index = array == kv->d_x;
+    launch_tensor_sum_passes(ctx, gqa_sums(g, kv, 0), gqa_sum_words(kv), gqa_babies(g, kv, 0), kv->r_i * kv_ctw(kv), g->G, array, kv->r_i, kv->r_o,
+                             kv->level + 1, st, index ? 1 : kv->r_i, index ? kv->r_o : 1);
+}
 extern "C" void cm_gqa_destroy(cm_gqa *g) {
     if (!g) return;
     for (cm_rope *r : g->fwd) cm_rope_destroy(r);
     for (cm_rope *r : g->back) cm_rope_destroy(r);
-    hipFree(g->d_work);
+    hipFree(g->d_work), hipFree(g->d_passes);
     delete g;
 }
 extern "C" cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, const int64_t *coeffs, cm_gqa **out) {
@@ -782,6 +807,12 @@ extern "C" cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, 
         if (hipMalloc((void **)&g->d_work, 6 * 2 * (size_t)(kv->level + 2) * n * 8) != hipSuccess) {
             cm_gqa_destroy(g);
             return CM_E_NOMEM;
+        }
+        g->r_i = kv->r_i, g->r_o = kv->r_o;
+        if (group > 1 && kv->r_o <= CM_KS_BATCH && tensor_sum_passes_fits(ctx, kv->r_i, kv->level + 1) &&
+            hipMalloc((void **)&g->d_passes, group * (kv->r_i * kv_ctw(kv) + gqa_sum_words(kv)) * 8) != hipSuccess) {
+            (void)hipGetLastError();
+            g->d_passes = nullptr;
         }
         for (int dir = 0; dir < 2; dir++)
             for (int delta = 1; delta < group; delta++) {
@@ -848,11 +879,20 @@ extern "C" cm_status cm_gqa_qk(cm_ctx *ctx, const cm_evk *evk, const cm_gqa *g, 
         std::swap(cq, alt);
     }
     cm_ct rep{cq, lq, 2, q->scale}, x{xd, kv->level, 2, q->scale};
+    const bool joint = kv->indexed && gqa_joint(g, kv);
+    std::vector<cm_ct> xs;
     for (int delta = 0; delta < g->G; delta++) {
         if (delta == 0) CMCHK(cm_level_drop(ctx, &rep, kv->level, &x, stream));
         else CMCHK(cm_rope_apply(ctx, evk, g->fwd[delta - 1], &rep, &x, stream));
-        if (kv->indexed) CMCHK(kv_sv(ctx, evk, kv, &x, &scores[delta], st, false, kv->d_x, false));
+        xs.push_back(x);
+        if (joint) CMCHK(kv_sv_babies(ctx, evk, kv, &x, gqa_babies(g, kv, delta), alt, st, false));
+        else if (kv->indexed) CMCHK(kv_sv(ctx, evk, kv, &x, &scores[delta], st, false, kv->d_x, false));
         else CMCHK(kv_qk(ctx, evk, kv, &x, &scores[delta], st, false));
+    }
+    if (joint) {
+        gqa_tensor_sums(ctx, g, kv, kv->d_x, st);
+        for (int delta = 0; delta < g->G; delta++)
+            CMCHK(kv_sv(ctx, evk, kv, &xs[delta], &scores[delta], st, false, kv->d_x, false, gqa_sums(g, kv, delta)));
     }
     RETURN_LAUNCH_STATUS();
     CM_CATCH
@@ -876,8 +916,14 @@ extern "C" cm_status cm_gqa_sv(cm_ctx *ctx, const cm_evk *evk, const cm_gqa *g, 
     const size_t n = ctx->n, slot = 2 * (size_t)(lv + 2) * n;
     u64 *pd = g->d_work, *md = pd + slot, *acc = md + slot, *alt = acc + slot;
     cm_ct part{pd, lv - 1, 2, 0.0}, moved{md, lo, 2, 0.0};
+    const bool joint = gqa_joint(g, kv);
+    if (joint) {
+        for (int delta = 0; delta < g->G; delta++)
+            CMCHK(kv_sv_babies(ctx, evk, kv, &scores[delta], gqa_babies(g, kv, delta), alt, st, false));
+        gqa_tensor_sums(ctx, g, kv, kv->d_v, st);
+    }
     for (int delta = 0; delta < g->G; delta++) {
-        CMCHK(kv_sv(ctx, evk, kv, &scores[delta], &part, st, false, kv->d_v, false));
+        CMCHK(kv_sv(ctx, evk, kv, &scores[delta], &part, st, false, kv->d_v, false, joint ? gqa_sums(g, kv, delta) : nullptr));
         const int back = (g->G - delta) % g->G;
         cm_ct dst{delta == 0 ? acc : md, lo, 2, 0.0};
         if (back == 0) CMCHK(cm_level_drop(ctx, &part, lo, &dst, stream));
