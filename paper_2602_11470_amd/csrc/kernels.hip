@@ -270,11 +270,17 @@ __global__ void k_tensor_sum(u64 *__restrict__ out, const u64 *__restrict__ a, c
 }
 // The same sums with the cnt <= TS_MAX_CNT ciphertexts a[j] held in registers (FP64 limbs only) while the lane runs over
 // all groups: a is read once instead of once per group, which is half of the traffic when a does not fit the caches.
+// Stores in a stream of reads cost more than their bytes (k_vmm_mac): the sums wait in LDS (48 KiB for eight groups: TS_HELD workgroups a
+// compute unit) and a launch is the limbs whose workgroups are there at once, which all write at its end.  Against one launch that
+// writes group by group: 128 ciphertexts at level 22 736 -> 666 us, at level 3 120 -> 112; scores times V at level 22 3650 -> 3590.
 #define TS_MAX_CNT 16
-__global__ __launch_bounds__(TPB) void k_tensor_sum_stationary(u64 *__restrict__ out, const u64 *__restrict__ a,
+#define TS_MAX_GROUPS 8
+#define TS_HELD 3
+__global__ __launch_bounds__(TPB, TS_HELD) void k_tensor_sum_stationary(u64 *__restrict__ out, const u64 *__restrict__ a,
                                                                const u64 *__restrict__ b, const FpQ *__restrict__ fpq,
-                                                               int limbs, int n, int cnt, int groups, int gs, int ts) {
-    const int i = blockIdx.x * TPB + threadIdx.x, l = blockIdx.y;
+                                                               int limbs, int n, int cnt, int groups, int gs, int ts, int l0) {
+    extern __shared__ u64 ts_sums[];
+    const int i = blockIdx.x * TPB + threadIdx.x, l = l0 + blockIdx.y;
     const FpQ fq = fpq[l];
     const MacFp F{fq.q, fq.qinv};
     const size_t o = (size_t)l * n + i, cs = (size_t)limbs * n;
@@ -310,16 +316,17 @@ __global__ __launch_bounds__(TPB) void k_tensor_sum_stationary(u64 *__restrict__
                 }
             }
         }
-        u64 *oz = out + (size_t)z * 3 * cs;
-        oz[o] = F.canon(d0);
-        oz[o + cs] = F.canon(d1);
-        oz[o + 2 * cs] = F.canon(d2);
+        u64 *w = ts_sums + z * (3 * TPB) + threadIdx.x;
+        w[0] = F.canon(d0);
+        w[TPB] = F.canon(d1);
+        w[2 * TPB] = F.canon(d2);
     }
+    for (int r = 0; r < 3 * groups; r++) out[r * cs + o] = ts_sums[r * TPB + threadIdx.x];
 }
 // The same sums for PASSES sets of ciphertexts a against one b: out[pass] and a[pass] stacked at out_pass and a_pass words.  A wave
 // owns a pass for 64 coefficients; the words of a group are staged in LDS for all of them, the next group's requested ahead.
 // Bound by HBM: with a launch a pass the cache was read once per pass of a grouped query.  Four passes over 128 ciphertexts of ten
-// limbs 4 x 317 -> 582 us, grouped-query attention at level 9 12860 -> 11640, with two passes 6750 -> 6390.  108 registers because the
+// limbs 4 x 317 -> 582 us, grouped-query attention at level 9 12860 -> 11640.  108 registers because the
 // terms are worked on four at a time (sched_barrier); left to itself the compiler spills 187 of 128.
 #define TS_CO 64
 template <int PASSES>
@@ -396,9 +403,13 @@ void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cn
     Prof prof_(ctx, CM_K_ELEMENTWISE, 3 * limbs * groups, st);
     bool all_fp = true;
     for (int l = 0; l < limbs; l++) all_fp = all_fp && ctx->mod[l] < (1ULL << 50);
-    if (all_fp && cnt <= TS_MAX_CNT && groups > 1) {
-        hipLaunchKernelGGL(k_tensor_sum_stationary, dim3(ctx->n / TPB, limbs), dim3(TPB), 0, st, out, a, b, ctx->d_fpq, limbs, ctx->n,
-                           cnt, groups, gs, ts);
+    if (all_fp && cnt <= TS_MAX_CNT && groups > 1 && groups <= TS_MAX_GROUPS) {
+        const int per = std::max(1, 256 * TS_HELD * TPB / ctx->n), launches = (limbs + per - 1) / per;
+        for (int i = 0; i < launches; i++) {
+            const int l0 = limbs * i / launches, l1 = limbs * (i + 1) / launches;
+            hipLaunchKernelGGL(k_tensor_sum_stationary, dim3(ctx->n / TPB, l1 - l0), dim3(TPB), groups * 3 * TPB * 8, st, out, a, b, ctx->d_fpq, limbs,
+                               ctx->n, cnt, groups, gs, ts, l0);
+        }
         return;
     }
     hipLaunchKernelGGL(k_tensor_sum, dim3(ctx->n / TPB, limbs, groups), dim3(TPB), 0, st, out, a, b, ctx->d_modc, ctx->d_fpq, limbs, ctx->n,

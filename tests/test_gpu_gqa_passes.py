@@ -22,9 +22,18 @@ def _random(B, ctx, level, seed):
                                                     (4, 32, 32, True)])
 def test_joint_passes_match_single_ones(group, dim, r_i, unrolled):
     from paper_2602_11470_amd import binding as B
-    ctx = B.config1()
+    _check(B, B.config1(), 2, 3, group, dim, r_i, unrolled)
+
+
+@pytest.mark.parametrize("lv,r_i", [(2, 2), (3, 16), (6, 4)])
+def test_joint_passes_match_single_ones_on_the_large_ring(lv, r_i):
+    """Three, four and seven limbs: the single passes' sums are formed in one, two and three launches."""
+    from paper_2602_11470_amd import binding as B
+    _check(B, B.llama_ring(8, 4), 32, lv, 2, 16, r_i, True)
+
+
+def _check(B, ctx, heads, lv, group, dim, r_i, unrolled):
     try:
-        heads, lv = 2, 3
         kv = ctx.kv_create(heads, dim, lv, r_i=r_i, unrolled_ladders=unrolled, key_index=True)
         t = ctx.S // (heads * dim)
         run = t // group
