@@ -792,7 +792,7 @@ def main():
                                            "k_rows_ip (row pass of the digits and inner product of one un-hoisted key switch)",
                                  "us_per_launch": t_ip_single * 1e6},
         "vmm_mac": {"bound": "hbm", "achieved": mac_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": mac_gbs / HBM_PEAK_GBS,
-                    "traffic": tr.get("k_vmm_mac"), "kernel": "k_vmm_mac (one launch per step)",
+                    "traffic": tr.get("k_vmm_mac"), "kernel": "k_vmm_mac (all launches of a step's one call)",
                     "algorithmic_bytes_per_launch": mac_bytes, "us_per_launch": mac_s * 1e6},
     }
     # What plain streaming kernels of the same read/write mix reach on this device (cm_hbm_probe), and each family's rate
