@@ -49,11 +49,14 @@ void launch_tensor(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int limbs,
 // out[z][3][limbs][n] = a (x) b[z], b[z] = b + z*2*limbs*n, z < cnt
 // out[z][3][limbs][n] = sum_{j < cnt} a[j] (x) b[z*cnt + j] for z < groups (a, b stacked ciphertexts [2][limbs][n])
 // b[z*group_stride + j*term_stride] is term j of group z (0, 0 = groups of cnt consecutive ciphertexts)
+void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
+                       int group_stride = 0, int term_stride = 0);
+// The same for `passes` (2 or TS_PASSES) sets of ciphertexts a against one b: the outputs and the a of pass p at p out_pass and p a_pass
+// words, the strides of b as above, both given.  cnt and limbs: tensor_sum_passes_fits.
+enum { TS_PASSES = 4 };
 bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int limbs);
 void launch_tensor_sum_passes(cm_ctx *ctx, u64 *out, size_t out_pass, const u64 *a, size_t a_pass, int passes, const u64 *b, int cnt, int groups,
                               int limbs, hipStream_t st, int gs, int ts);
-void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
-                       int group_stride = 0, int term_stride = 0);
 void launch_tensor_batch(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int limbs, hipStream_t st);
 void launch_automorphism(cm_ctx *ctx, u64 *out, const u64 *in, int rows, u64 g, hipStream_t st);
 // A[k][2][limbs][n] = sum_{c < nk} T[c] * M[(c + k) mod E], k < shared (2 <= shared <= E, powers of two); T, A stacked

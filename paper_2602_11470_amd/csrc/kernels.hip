@@ -388,14 +388,11 @@ void launch_tensor_sum_passes(cm_ctx *ctx, u64 *out, size_t out_pass, const u64 
                               int limbs, hipStream_t st, int gs, int ts) {
     Prof prof_(ctx, CM_K_ELEMENTWISE, 3 * limbs * groups * passes, st);
     const dim3 grid(ctx->n / TS_CO, limbs);
-    for (int p = 0; p < passes; p += 4) {                  // a power of two
-        u64 *op = out + p * out_pass;
-        const u64 *ap = a + p * a_pass;
-        if (passes - p >= 4)
-            hipLaunchKernelGGL(k_tensor_sum_passes<4>, grid, dim3(256), 0, st, op, ap, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts, out_pass, a_pass);
-        else
-            hipLaunchKernelGGL(k_tensor_sum_passes<2>, grid, dim3(128), 0, st, op, ap, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts, out_pass, a_pass);
-    }
+    if (passes == 2)
+        hipLaunchKernelGGL(k_tensor_sum_passes<2>, grid, dim3(128), 0, st, out, a, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts, out_pass, a_pass);
+    else
+        hipLaunchKernelGGL(k_tensor_sum_passes<TS_PASSES>, grid, dim3(64 * TS_PASSES), 0, st, out, a, b, ctx->d_fpq, limbs, ctx->n, cnt, groups, gs, ts,
+                           out_pass, a_pass);
 }
 void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
                        int group_stride, int term_stride) {

@@ -774,18 +774,18 @@ struct cm_gqa {
     int G = 1, t = 1, t_kv = 1, level = 0;       // level of the cache
     std::vector<cm_rope *> fwd, back;            // inner rotations by delta t at level+1 / level-1, delta = 1 .. G-1
     u64 *d_work = nullptr;                       // six ciphertexts of level+2 limbs
-    // baby steps [G][r_i] and tensor sums [G][r_o][3] of all passes, so that they read the cache together; null (a pass at a time)
-    // where the joint kernel does not apply or the memory is not there
+    // baby steps [P][r_i] and tensor sums [P][r_o][3] of the P = min(G, TS_PASSES) passes that read the cache together (the others
+    // follow in turns of as many); null (a pass at a time) where the joint kernel does not apply or the memory is not there
     u64 *d_passes = nullptr;
-    int r_i = 0, r_o = 0;
+    int P = 1, r_i = 0, r_o = 0;
 };
 static size_t gqa_sum_words(const cm_kv *kv) { return kv->r_o * (kv_ctw(kv) + kv_ctw(kv) / 2); }      // of a pass
 static bool gqa_joint(const cm_gqa *g, const cm_kv *kv) { return g->d_passes && kv->r_i == g->r_i && kv->r_o == g->r_o; }
 static u64 *gqa_babies(const cm_gqa *g, const cm_kv *kv, int pass) { return g->d_passes + pass * (kv->r_i * kv_ctw(kv)); }
-static u64 *gqa_sums(const cm_gqa *g, const cm_kv *kv, int pass) { return gqa_babies(g, kv, g->G) + pass * gqa_sum_words(kv); }
+static u64 *gqa_sums(const cm_gqa *g, const cm_kv *kv, int pass) { return gqa_babies(g, kv, g->P) + pass * gqa_sum_words(kv); }
 static void gqa_tensor_sums(cm_ctx *ctx, const cm_gqa *g, const cm_kv *kv, const u64 *array, hipStream_t st) {
     const bool index = array == kv->d_x;
-    launch_tensor_sum_passes(ctx, gqa_sums(g, kv, 0), gqa_sum_words(kv), gqa_babies(g, kv, 0), kv->r_i * kv_ctw(kv), g->G, array, kv->r_i, kv->r_o,
+    launch_tensor_sum_passes(ctx, gqa_sums(g, kv, 0), gqa_sum_words(kv), gqa_babies(g, kv, 0), kv->r_i * kv_ctw(kv), g->P, array, kv->r_i, kv->r_o,
                              kv->level + 1, st, index ? 1 : kv->r_i, index ? kv->r_o : 1);
 }
 extern "C" void cm_gqa_destroy(cm_gqa *g) {
@@ -808,12 +808,6 @@ extern "C" cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, 
             cm_gqa_destroy(g);
             return CM_E_NOMEM;
         }
-        g->r_i = kv->r_i, g->r_o = kv->r_o;
-        if (group > 1 && kv->r_o <= CM_KS_BATCH && tensor_sum_passes_fits(ctx, kv->r_i, kv->level + 1) &&
-            hipMalloc((void **)&g->d_passes, group * (kv->r_i * kv_ctw(kv) + gqa_sum_words(kv)) * 8) != hipSuccess) {
-            (void)hipGetLastError();
-            g->d_passes = nullptr;
-        }
         for (int dir = 0; dir < 2; dir++)
             for (int delta = 1; delta < group; delta++) {
                 cm_rope *r = nullptr;
@@ -825,6 +819,13 @@ extern "C" cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, 
                 }
                 (dir == 0 ? g->fwd : g->back).push_back(r);
             }
+        // last, so that what the object cannot do without has its memory
+        g->P = std::min<int>(group, TS_PASSES), g->r_i = kv->r_i, g->r_o = kv->r_o;
+        if (group > 1 && kv->r_o <= CM_KS_BATCH && tensor_sum_passes_fits(ctx, kv->r_i, kv->level + 1) &&
+            hipMalloc((void **)&g->d_passes, g->P * (kv->r_i * kv_ctw(kv) + gqa_sum_words(kv)) * 8) != hipSuccess) {
+            (void)hipGetLastError();
+            g->d_passes = nullptr;
+        }
     } catch (...) {
         cm_gqa_destroy(g);
         return CM_E_NOMEM;
@@ -880,19 +881,21 @@ extern "C" cm_status cm_gqa_qk(cm_ctx *ctx, const cm_evk *evk, const cm_gqa *g, 
     }
     cm_ct rep{cq, lq, 2, q->scale}, x{xd, kv->level, 2, q->scale};
     const bool joint = kv->indexed && gqa_joint(g, kv);
-    std::vector<cm_ct> xs;
-    for (int delta = 0; delta < g->G; delta++) {
-        if (delta == 0) CMCHK(cm_level_drop(ctx, &rep, kv->level, &x, stream));
-        else CMCHK(cm_rope_apply(ctx, evk, g->fwd[delta - 1], &rep, &x, stream));
-        xs.push_back(x);
-        if (joint) CMCHK(kv_sv_babies(ctx, evk, kv, &x, gqa_babies(g, kv, delta), alt, st, false));
-        else if (kv->indexed) CMCHK(kv_sv(ctx, evk, kv, &x, &scores[delta], st, false, kv->d_x, false));
-        else CMCHK(kv_qk(ctx, evk, kv, &x, &scores[delta], st, false));
-    }
-    if (joint) {
+    cm_ct xs[TS_PASSES];                                           // of a turn, for their scales
+    const int turn = joint ? g->P : 1;
+    for (int d0 = 0; d0 < g->G; d0 += turn) {
+        for (int delta = d0; delta < d0 + turn; delta++) {
+            if (delta == 0) CMCHK(cm_level_drop(ctx, &rep, kv->level, &x, stream));
+            else CMCHK(cm_rope_apply(ctx, evk, g->fwd[delta - 1], &rep, &x, stream));
+            xs[delta - d0] = x;
+            if (joint) CMCHK(kv_sv_babies(ctx, evk, kv, &x, gqa_babies(g, kv, delta - d0), alt, st, false));
+            else if (kv->indexed) CMCHK(kv_sv(ctx, evk, kv, &x, &scores[delta], st, false, kv->d_x, false));
+            else CMCHK(kv_qk(ctx, evk, kv, &x, &scores[delta], st, false));
+        }
+        if (!joint) continue;
         gqa_tensor_sums(ctx, g, kv, kv->d_x, st);
-        for (int delta = 0; delta < g->G; delta++)
-            CMCHK(kv_sv(ctx, evk, kv, &xs[delta], &scores[delta], st, false, kv->d_x, false, gqa_sums(g, kv, delta)));
+        for (int delta = d0; delta < d0 + turn; delta++)
+            CMCHK(kv_sv(ctx, evk, kv, &xs[delta - d0], &scores[delta], st, false, kv->d_x, false, gqa_sums(g, kv, delta - d0)));
     }
     RETURN_LAUNCH_STATUS();
     CM_CATCH
@@ -917,13 +920,12 @@ extern "C" cm_status cm_gqa_sv(cm_ctx *ctx, const cm_evk *evk, const cm_gqa *g, 
     u64 *pd = g->d_work, *md = pd + slot, *acc = md + slot, *alt = acc + slot;
     cm_ct part{pd, lv - 1, 2, 0.0}, moved{md, lo, 2, 0.0};
     const bool joint = gqa_joint(g, kv);
-    if (joint) {
-        for (int delta = 0; delta < g->G; delta++)
-            CMCHK(kv_sv_babies(ctx, evk, kv, &scores[delta], gqa_babies(g, kv, delta), alt, st, false));
-        gqa_tensor_sums(ctx, g, kv, kv->d_v, st);
-    }
     for (int delta = 0; delta < g->G; delta++) {
-        CMCHK(kv_sv(ctx, evk, kv, &scores[delta], &part, st, false, kv->d_v, false, joint ? gqa_sums(g, kv, delta) : nullptr));
+        if (joint && delta % g->P == 0) {
+            for (int p = 0; p < g->P; p++) CMCHK(kv_sv_babies(ctx, evk, kv, &scores[delta + p], gqa_babies(g, kv, p), alt, st, false));
+            gqa_tensor_sums(ctx, g, kv, kv->d_v, st);
+        }
+        CMCHK(kv_sv(ctx, evk, kv, &scores[delta], &part, st, false, kv->d_v, false, joint ? gqa_sums(g, kv, delta % g->P) : nullptr));
         const int back = (g->G - delta) % g->G;
         cm_ct dst{delta == 0 ? acc : md, lo, 2, 0.0};
         if (back == 0) CMCHK(cm_level_drop(ctx, &part, lo, &dst, stream));
