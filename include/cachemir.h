@@ -381,9 +381,9 @@ cm_status cm_vmm_kv(cm_ctx *ctx, const cm_evk *evk, const cm_kv *kv, int32_t whi
  * as cm_inner_rot_create takes them.  cm_gqa_steps lists the rotations needed beyond those of cm_kv_steps that are
  * multiples of t_kv (no other step of the cache is used).  q: (e, h, 0) layout, one level above the cache.
  * Device memory of the object: six ciphertexts, the plaintexts of the inner rotations and, where the passes read the cache
- * together (group > 1, moduli below 2^50, r_i <= 16 and r_o = dim/r_i <= 8), r_i + 1.5 r_o ciphertexts of the cache's level
- * for each of up to four passes (4 x 28 = 112 for r_i = 16, r_o = 8: 1.2 GB at level 9).  That last area is asked for after
- * all others; without it the calls work a pass at a time, with the same results. */
+ * together (group > 1, moduli below 2^50, r_i <= 16 and r_o = dim/r_i <= 8, as far as that is the faster form), r_i + 1.5 r_o
+ * ciphertexts of the cache's level for each of up to four passes (4 x 28 = 112 for r_i = 16, r_o = 8: 1.2 GB at level 9).
+ * That last area is asked for after all others; without it the calls work a pass at a time, with the same results. */
 typedef struct cm_gqa cm_gqa;
 cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, const int64_t *coeffs, cm_gqa **out);
 void cm_gqa_destroy(cm_gqa *gqa);

@@ -52,9 +52,10 @@ void launch_tensor(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int limbs,
 void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
                        int group_stride = 0, int term_stride = 0);
 // The same for `passes` (2 or TS_PASSES) sets of ciphertexts a against one b: the outputs and the a of pass p at p out_pass and p a_pass
-// words, the strides of b as above, both given.  cnt and limbs: tensor_sum_passes_fits.
+// words, the strides of b as above, both given.  Only where tensor_sum_passes_fits.
 enum { TS_PASSES = 4 };
-bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int limbs);
+bool tensor_sum_passes_pays(int n, int limbs, int cnt, int groups, int passes);
+bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int groups, int limbs, int passes);
 void launch_tensor_sum_passes(cm_ctx *ctx, u64 *out, size_t out_pass, const u64 *a, size_t a_pass, int passes, const u64 *b, int cnt, int groups,
                               int limbs, hipStream_t st, int gs, int ts);
 void launch_tensor_batch(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int limbs, hipStream_t st);

@@ -821,7 +821,7 @@ extern "C" cm_status cm_gqa_create(cm_ctx *ctx, const cm_kv *kv, int32_t group, 
             }
         // last, so that what the object cannot do without has its memory
         g->P = std::min<int>(group, TS_PASSES), g->r_i = kv->r_i, g->r_o = kv->r_o;
-        if (group > 1 && kv->r_o <= CM_KS_BATCH && tensor_sum_passes_fits(ctx, kv->r_i, kv->level + 1) &&
+        if (kv->r_o <= CM_KS_BATCH && tensor_sum_passes_fits(ctx, kv->r_i, kv->r_o, kv->level + 1, g->P) &&
             hipMalloc((void **)&g->d_passes, g->P * (kv->r_i * kv_ctw(kv) + gqa_sum_words(kv)) * 8) != hipSuccess) {
             (void)hipGetLastError();
             g->d_passes = nullptr;

@@ -32,6 +32,19 @@ def test_joint_passes_match_single_ones_on_the_large_ring(lv, r_i):
     _check(B, B.llama_ring(8, 4), 32, lv, 2, 16, r_i, True)
 
 
+@pytest.mark.parametrize("heads,group,dim,r_i,lv", [(8, 2, 64, 16, 4), (32, 4, 16, 16, 4), (32, 4, 8, 2, 7), (32, 4, 16, 4, 2)])
+def test_joint_passes_on_the_large_ring(heads, group, dim, r_i, lv):
+    """Where the large ring takes the joint form: two passes over four sums of sixteen terms; four passes, one sum and four sums."""
+    from paper_2602_11470_amd import binding as B
+    _check(B, B.llama_ring(9, 4), heads, lv, group, dim, r_i, True)
+
+
+@pytest.mark.parametrize("group,dim,r_i", [(2, 16, 8), (2, 64, 16), (2, 8, 8), (4, 8, 8), (4, 64, 8)])
+def test_joint_passes_of_a_small_launch(group, dim, r_i):
+    from paper_2602_11470_amd import binding as B
+    _check(B, B.config1(), 2, 3, group, dim, r_i, True)
+
+
 def _check(B, ctx, heads, lv, group, dim, r_i, unrolled):
     try:
         kv = ctx.kv_create(heads, dim, lv, r_i=r_i, unrolled_ladders=unrolled, key_index=True)
