@@ -383,12 +383,13 @@ __global__ __launch_bounds__(64 * PASSES, 4) void k_tensor_sum_passes(u64 *__res
 // terms, and two passes with few groups, a launch a pass takes less.  Ten limbs at n = 65536, (cnt, groups), joint against single: two
 // passes (16, 8) 464 us, 565; (16, 4) 310, 330; (16, 1) 200, 132; (8, 8) 358, 316; (1, 2) 87, 63; four passes (16, 8) 585, 1129;
 // (16, 1) 234, 265; (8, 1) 141, 146 (13 limbs: 180, 179); (4, 1) 78, 70; (1, 2) 104, 127; (2, 4) 208, 235; (2, 8) 398, 407 (21 limbs: 818, 790).
-// A launch that the chip holds at once (n = 4096) is bound by its own latency: 8 limbs, four passes 6 to 36 us joint, 16 to 110 single;
-// two passes 6.5 to 32 against 8.5 to 51, but (4, 8) 28.0 against 27.5 and, with 13 limbs, (2, 4) 17.8 against 17.2.
+// A launch that the chip holds at once (n = 4096) is bound by its own latency, and calls of it are faster joint or equal: 8 limbs, four
+// passes 6 to 36 us joint, 16 to 110 single, two passes 6.5 to 32 against 8.5 to 51; grouped-query attention at level 3 with two passes over
+// (2, 8), (1, 8) and (4, 4) 912, 847 and 810 us against 938, 866 and 825, with 13 limbs within 0.3 % of each other.
 bool tensor_sum_passes_pays(int n, int limbs, int cnt, int groups, int passes) {
-    const bool small = n / TS_CO * limbs <= 1024;
-    if (passes == 2) return (cnt >= 16 && groups >= 4) || (small && (groups <= 2 || cnt >= 2 * groups));
-    return small || (groups == 1 ? cnt >= 16 : cnt >= 4 || groups <= 4);
+    if (n / TS_CO * limbs <= 1024) return true;
+    if (passes == 2) return cnt >= 16 && groups >= 4;
+    return groups == 1 ? cnt >= 16 : cnt >= 4 || groups <= 4;
 }
 bool tensor_sum_passes_fits(const cm_ctx *ctx, int cnt, int groups, int limbs, int passes) {
     if ((passes != 2 && passes != TS_PASSES) || cnt > TS_MAX_CNT) return false;

@@ -15,7 +15,7 @@ def _rule(name):
 @pytest.mark.parametrize("n,limbs,cnt,groups,passes,pays", [
     (65536, 10, 16, 8, 2, True), (65536, 4, 16, 4, 2, True), (65536, 10, 16, 1, 2, False), (65536, 21, 8, 8, 2, False), (65536, 10, 1, 2, 2, False),
     (65536, 10, 16, 8, 4, True), (65536, 10, 16, 1, 4, True), (65536, 10, 4, 1, 4, False), (65536, 21, 8, 1, 4, False), (65536, 21, 2, 8, 4, False),
-    (65536, 10, 1, 2, 4, True), (65536, 21, 4, 8, 4, True), (4096, 5, 1, 1, 2, True), (4096, 5, 1, 8, 2, False), (4096, 13, 16, 8, 2, True),
+    (65536, 10, 1, 2, 4, True), (65536, 21, 4, 8, 4, True), (4096, 5, 1, 1, 2, True), (4096, 5, 1, 8, 2, True), (4096, 13, 16, 8, 2, True),
     (4096, 25, 8, 4, 2, False), (4096, 5, 1, 8, 4, True)])
 def test_joint_passes_where_they_are_faster(n, limbs, cnt, groups, passes, pays):
     assert _rule("_Z22tensor_sum_passes_paysiiiii")(n, limbs, cnt, groups, passes) == pays
