@@ -51,6 +51,7 @@ void launch_tensor(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int limbs,
 // b[z*group_stride + j*term_stride] is term j of group z (0, 0 = groups of cnt consecutive ciphertexts)
 void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cnt, int groups, int limbs, hipStream_t st,
                        int group_stride = 0, int term_stride = 0);
+bool tensor_sum_held(int n, int limbs, int cnt, int groups);
 // The same for `passes` (2 or TS_PASSES) sets of ciphertexts a against one b: the outputs and the a of pass p at p out_pass and p a_pass
 // words, the strides of b as above, both given.  Only where tensor_sum_passes_fits.
 enum { TS_PASSES = 4 };

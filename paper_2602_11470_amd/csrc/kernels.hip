@@ -270,13 +270,15 @@ __global__ void k_tensor_sum(u64 *__restrict__ out, const u64 *__restrict__ a, c
 }
 // The same sums with the cnt <= TS_MAX_CNT ciphertexts a[j] held in registers (FP64 limbs only) while the lane runs over
 // all groups: a is read once instead of once per group, which is half of the traffic when a does not fit the caches.
-// Stores in a stream of reads cost more than their bytes (k_vmm_mac): the sums wait in LDS (48 KiB for eight groups: TS_HELD workgroups a
-// compute unit) and a launch is the limbs whose workgroups are there at once, which all write at its end.  Against one launch that
-// writes group by group: 128 ciphertexts at level 22 736 -> 666 us, at level 3 120 -> 112; scores times V at level 22 3650 -> 3590.
+// HELD: stores in a stream of reads cost more than their bytes (k_vmm_mac); the sums wait in LDS (48 KiB for eight groups: TS_HELD
+// workgroups a compute unit) and a launch is the limbs whose workgroups are there at once, which all write at its end.  Against one
+// launch that writes group by group: 128 ciphertexts at level 22 736 -> 666 us, at level 3 120 -> 112; scores times V at level 22 3650 ->
+// 3590.  Which of the two a sum takes: tensor_sum_held.
 #define TS_MAX_CNT 16
 #define TS_MAX_GROUPS 8
 #define TS_HELD 3
-__global__ __launch_bounds__(TPB, TS_HELD) void k_tensor_sum_stationary(u64 *__restrict__ out, const u64 *__restrict__ a,
+template <bool HELD>
+__global__ __launch_bounds__(TPB, HELD ? TS_HELD : 1) void k_tensor_sum_stationary(u64 *__restrict__ out, const u64 *__restrict__ a,
                                                                const u64 *__restrict__ b, const FpQ *__restrict__ fpq,
                                                                int limbs, int n, int cnt, int groups, int gs, int ts, int l0) {
     extern __shared__ u64 ts_sums[];
@@ -316,12 +318,26 @@ __global__ __launch_bounds__(TPB, TS_HELD) void k_tensor_sum_stationary(u64 *__r
                 }
             }
         }
-        u64 *w = ts_sums + z * (3 * TPB) + threadIdx.x;
+        u64 *w = HELD ? ts_sums + z * (3 * TPB) + threadIdx.x : out + (size_t)z * 3 * cs + o;
+        const size_t ws = HELD ? TPB : cs;
         w[0] = F.canon(d0);
-        w[TPB] = F.canon(d1);
-        w[2 * TPB] = F.canon(d2);
+        w[ws] = F.canon(d1);
+        w[2 * ws] = F.canon(d2);
     }
-    for (int r = 0; r < 3 * groups; r++) out[r * cs + o] = ts_sums[r * TPB + threadIdx.x];
+    if (HELD) {
+        for (int r = 0; r < 3 * groups; r++) out[r * cs + o] = ts_sums[r * TPB + threadIdx.x];
+    }
+}
+static int ts_launch_limbs(int n) { return std::max(1, 256 * TS_HELD * TPB / n); }
+// A launch that ends before the next begins pays for its start and its last wave: short ones (few terms), many of them, and launches
+// that do not fill the chip lose more than the writes cost.  Held against written as they come, (cnt, groups), three limbs to a launch at
+// n = 65536: one launch always gains (3 limbs (1, 2) 10.6 us, 11.7; (16, 8) 77, 90; n = 4096, 8 limbs 6.0, 7.0 and 25.7, 41); two launches
+// that are full (6 limbs) from (2, 4) on: 34.3, 38.1; 4 limbs (16, 2) 40.9, 39.2; (16, 4) 64.8, 65.2; (4, 8) 47.2, 44.5; 10 limbs (8, 8)
+// 150, 160; (8, 4) 86, 89; (8, 2) 56.2, 53.9; (2, 8) 105, 99; 21 limbs (16, 2) 211, 230; (8, 4) 189, 199; (8, 2) 109.5, 106.8; (1, 2) 74, 60.
+bool tensor_sum_held(int n, int limbs, int cnt, int groups) {
+    const int per = ts_launch_limbs(n), launches = (limbs + per - 1) / per, terms = cnt * groups;
+    if (launches == 1 || terms >= 64) return true;
+    return 4 * limbs >= 3 * launches * per && terms >= (launches == 2 ? 8 : 32);
 }
 // The same sums for PASSES sets of ciphertexts a against one b: out[pass] and a[pass] stacked at out_pass and a_pass words.  A wave
 // owns a pass for 64 coefficients; the words of a group are staged in LDS for all of them, the next group's requested ahead.
@@ -414,10 +430,15 @@ void launch_tensor_sum(cm_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int cn
     bool all_fp = true;
     for (int l = 0; l < limbs; l++) all_fp = all_fp && ctx->mod[l] < (1ULL << 50);
     if (all_fp && cnt <= TS_MAX_CNT && groups > 1 && groups <= TS_MAX_GROUPS) {
-        const int per = std::max(1, 256 * TS_HELD * TPB / ctx->n), launches = (limbs + per - 1) / per;
+        if (!tensor_sum_held(ctx->n, limbs, cnt, groups)) {
+            hipLaunchKernelGGL(k_tensor_sum_stationary<false>, dim3(ctx->n / TPB, limbs), dim3(TPB), 0, st, out, a, b, ctx->d_fpq, limbs, ctx->n, cnt,
+                               groups, gs, ts, 0);
+            return;
+        }
+        const int per = ts_launch_limbs(ctx->n), launches = (limbs + per - 1) / per;
         for (int i = 0; i < launches; i++) {
             const int l0 = limbs * i / launches, l1 = limbs * (i + 1) / launches;
-            hipLaunchKernelGGL(k_tensor_sum_stationary, dim3(ctx->n / TPB, l1 - l0), dim3(TPB), groups * 3 * TPB * 8, st, out, a, b, ctx->d_fpq, limbs,
+            hipLaunchKernelGGL(k_tensor_sum_stationary<true>, dim3(ctx->n / TPB, l1 - l0), dim3(TPB), groups * 3 * TPB * 8, st, out, a, b, ctx->d_fpq, limbs,
                                ctx->n, cnt, groups, gs, ts, l0);
         }
         return;

@@ -19,3 +19,11 @@ def _rule(name):
     (4096, 25, 8, 4, 2, False), (4096, 5, 1, 8, 4, True)])
 def test_joint_passes_where_they_are_faster(n, limbs, cnt, groups, passes, pays):
     assert _rule("_Z22tensor_sum_passes_paysiiiii")(n, limbs, cnt, groups, passes) == pays
+
+
+@pytest.mark.parametrize("n,limbs,cnt,groups,held", [
+    (65536, 3, 1, 2, True), (4096, 25, 1, 2, True), (65536, 6, 2, 4, True), (65536, 5, 2, 2, False), (65536, 4, 16, 2, False), (65536, 4, 4, 8, False),
+    (65536, 4, 16, 8, True), (65536, 10, 8, 8, True), (65536, 10, 8, 2, False), (65536, 10, 2, 8, False), (65536, 21, 16, 2, True), (65536, 21, 8, 2, False),
+    (65536, 21, 1, 2, False), (65536, 13, 4, 4, False), (65536, 8, 2, 8, False)])
+def test_tensor_sums_held_where_that_is_faster(n, limbs, cnt, groups, held):
+    assert _rule("_Z15tensor_sum_heldiiii")(n, limbs, cnt, groups) == held
