@@ -152,6 +152,10 @@ void launch_decrypt(cm_ctx *ctx, u64 *out, const u64 *ct, const u64 *s_mont, int
 // pts: all r_i*r_o plaintexts in the blocked layout written by launch_pt_block
 void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
                     size_t ct_stride, hipStream_t st);
+// the same in a given form (r_i from 8 on): sums held until the launch ends, or written as they come
+bool vmm_mac_held(int n, int limbs, int r_i, int r_o);
+void launch_vmm_mac_form(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level, size_t ct_stride,
+                         hipStream_t st, bool held);
 // words of the blocked array
 size_t vmm_pts_words(const cm_ctx *ctx, int r_i, int r_o, int limbs, int level);
 // copies plaintext (j,k) from plain[limbs][n] into the blocked array (to_blocked) or back

@@ -1227,11 +1227,11 @@ struct MacWords {                              // 64-bit words, pairs interleave
 };
 // An item is 64 coefficients of one limb and W * KW giant steps, KW to each of a workgroup's W waves.  The baby words are staged in LDS
 // as two halves, sixteen baby steps a pass (16 KiB), the first group of a pass requested before them.  The sums stay in registers over
-// the passes and then wait in LDS, where a lane reads back what it wrote.
+// the passes and go to put(giant step, component, sum).
 #define MAC_JC 16
-template <int W, int KW, class G>
-__device__ __forceinline__ void mac_body(uint2 *sb, u64 *res, const u64 *__restrict__ babies, const u64 *__restrict__ pts, const ModC &m,
-                                         const MacLayout &lay, int l, int ch, int kb, bool first, size_t cs, size_t ct_stride) {
+template <int W, int KW, class G, class PUT>
+__device__ __forceinline__ void mac_body(uint2 *sb, const u64 *__restrict__ babies, const u64 *__restrict__ pts, const ModC &m,
+                                         const MacLayout &lay, int l, int ch, int kb, bool first, size_t cs, size_t ct_stride, PUT put) {
     const int co = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t o = (size_t)l * lay.n + ch * MAC_CO;          // uniform: lanes differ by co alone
     const bool active = kb < lay.r_o;                         // uniform in a wave
@@ -1290,15 +1290,38 @@ __device__ __forceinline__ void mac_body(uint2 *sb, u64 *res, const u64 *__restr
             }
         }
     }
+    if (!active) return;
 #pragma unroll
-    for (int k = 0; k < KW; k++) res[2 * k * MAC_CO] = s[k][0], res[(2 * k + 1) * MAC_CO] = s[k][1];
+    for (int k = 0; k < KW; k++) put(k, 0, s[k][0]), put(k, 1, s[k][1]);
+}
+__device__ __forceinline__ void mac_store(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// A workgroup for every 64 coefficients of a limb, which runs over the blocks of W * KW giant steps and writes as it goes.
+template <int W, int KW>
+__global__ __launch_bounds__(64 * W) void k_vmm_mac_direct(u64 *__restrict__ out, const u64 *__restrict__ babies, const u64 *__restrict__ pts,
+                                                           const ModC *__restrict__ modc, MacLayout lay, int limbs, size_t ct_stride, int level, int L) {
+    __shared__ uint2 sb[MAC_JC * 2 * MAC_CO];
+    // the limbs of the special primes (60 or 64 bits a word, the slowest workgroups) are dispatched first, not last
+    const int nsp = limbs - (level + 1), y = blockIdx.y, ch = blockIdx.x;
+    const int l = y < nsp ? level + 1 + y : y - nsp;
+    const ModC m = modc[l <= level ? l : L + 1 + (l - level - 1)];
+    const size_t cs = (size_t)limbs * lay.n, o = (size_t)l * lay.n + ch * MAC_CO;          // uniform: lanes differ by their coefficient alone
+    auto run = [&](auto g) {
+        for (int k0 = 0; k0 < lay.r_o; k0 += W * KW) {
+            const int kb = k0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * KW;
+            auto put = [=](int k, int c, u64 v) { mac_store(out + (size_t)(kb + k) * ct_stride + c * cs + o + (threadIdx.x & 63), v); };
+            mac_body<W, KW, decltype(g)>(sb, babies, pts, m, lay, l, ch, kb, k0 == 0, cs, ct_stride, put);
+        }
+    };
+    if (lay.is50(l)) run(MacPacked50());
+    else if (lay.is60(l)) run(MacPacked60());
+    else run(MacWords());
 }
 // Bound by HBM, whose reads the writes disturb: 3 % of the bytes written while others read cost 20 % of a launch, the same bytes written
 // when nobody reads cost little (a plain kernel that reads 5 GB and writes 5 %: 789 us without its writes, 1012 with them spread over
 // the launch, 844 and 857 as four and eight launches that write last).  So a launch is what the chip holds at once (16 waves a compute
 // unit: 108 and 124 registers), `wgs` workgroups of `rounds` <= P items each, P by the LDS (40 KiB and 64 KiB a workgroup), and all
-// of them write at its end.  Against one launch whose workgroups write as they end: 512 products at levels 23 and 4 1413 -> 1300 and 470 ->
-// 431 us, 2048 at level 3 1359 -> 1305, 1024 at level 9 1267 -> 1155, three times 128 at level 13 292 -> 268 each; one launch that writes
+// of them write at its end.  Against k_vmm_mac_direct: 512 products at levels 23 and 4 1413 -> 1300 and 470 -> 431 us, 2048 at level 3
+// 1359 -> 1305, 1024 at level 9 1267 -> 1155, three times 128 at level 13 292 -> 268 each (vmm_mac_held: where not); one launch that writes
 // after every third item 1439, 448, 1344, 1208 and 282.  P = 8 with eight waves for eight giant steps, P = 4 for sixteen: within 2 %.
 // Item `round` of a workgroup: chunk and limb by unit, then the block of W * KW giant steps.
 struct MacArgs {
@@ -1324,9 +1347,10 @@ __global__ __launch_bounds__(64 * W, 4) void k_vmm_mac(u64 *__restrict__ out, co
         if (!item(i, l, ch, kb)) break;
         const ModC m = modc[l <= level ? l : L + 1 + (l - level - 1)];
         u64 *r = res + ((i * W + wave) * KW * 2) * MAC_CO + co;
-        if (lay.is50(l)) mac_body<W, KW, MacPacked50>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
-        else if (lay.is60(l)) mac_body<W, KW, MacPacked60>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
-        else mac_body<W, KW, MacWords>(sb, r, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride);
+        auto put = [&](int k, int c, u64 v) { r[(2 * k + c) * MAC_CO] = v; };             // a lane reads back what it wrote
+        if (lay.is50(l)) mac_body<W, KW, MacPacked50>(sb, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride, put);
+        else if (lay.is60(l)) mac_body<W, KW, MacPacked60>(sb, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride, put);
+        else mac_body<W, KW, MacWords>(sb, babies, pts, m, lay, l, ch, kb, i == 0, cs, ct_stride, put);
     }
     for (int i = 0; i < a.rounds; i++) {
         int l, ch, kb;
@@ -1337,8 +1361,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_vmm_mac(u64 *__restrict__ out, co
 #pragma unroll
         for (int k = 0; k < KW; k++)
 #pragma unroll
-            for (int c = 0; c < 2; c++)
-                __hip_atomic_store(out + (size_t)(kb + k) * ct_stride + c * cs + o, r[(2 * k + c) * MAC_CO], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int c = 0; c < 2; c++) mac_store(out + (size_t)(kb + k) * ct_stride + c * cs + o, r[(2 * k + c) * MAC_CO]);
     }
 }
 // Fewer than eight baby steps (RI = 1, 2 or 4): a lane keeps its baby words and runs over MAC_FEW_K giant steps, the words of the
@@ -1380,8 +1403,26 @@ __global__ __launch_bounds__(TPB) void k_vmm_mac_few(u64 *__restrict__ out, cons
         __hip_atomic_store(out + k * ct_stride + cs + o, redc(s1, m.q, m.qinv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
+// Held sums gain where the plaintexts outweigh what is written, 2 words of sums to r_i of plaintext a giant step, and lose where the chip waits
+// for the last item of every launch.  Held against direct, us, (limbs, r_i, r_o) at n = 65536: (28, 32, 16) 1190, 1365; (9, 32, 16) 397,
+// 420; (9, 64, 2) 183, 192; (3, 32, 2) 32.3, 32.0; one giant step (9, 64, 1) 147, 142; (28, 8, 1) 127, 82; (28, 8, 32) 917, 813; sixteen
+// baby steps (9, 16, 8) 122, 127; (28, 16, 4) 228, 228; (9, 16, 2) 55.7, 52.1; (6, 16, 8) 84.6, 83.7; (6, 16, 64) 640, 691; (14, 16, 16)
+// 326, 321; (18, 16, 16) 441, 468.  Two, four and eight limbs put the ciphertexts of a sum at distances of a power of two, which a
+// resident set that works on one limb feels: (8, 32, 4) 128.8, 126.6; (4, 16, 8) 56.8, 51.6; (8, 64, 8) 382, 395.  At n = 4096 (14, 32, 64) 154,
+// 159; (7, 16, 16) 13.3, 12.5; (4, 64, 8) 21.4, 20.1.
+bool vmm_mac_held(int n, int limbs, int r_i, int r_o) {
+    if (n == 4096) return r_i >= 32 && r_o >= 32 && limbs >= 14;
+    if (r_i < 16 || r_o < 2) return false;
+    const bool pow2 = !(limbs & (limbs - 1)) && limbs <= 8;
+    if (r_i > 16) return !pow2 || r_i * r_o >= 512;
+    return r_o >= 64 ? limbs >= 5 : r_o == 16 ? limbs > 16 : r_o >= 4 && limbs >= 7 && !pow2;
+}
 void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
                     size_t ct_stride, hipStream_t st) {
+    launch_vmm_mac_form(ctx, out, babies, pts, r_i, r_o, limbs, level, ct_stride, st, vmm_mac_held(ctx->n, limbs, r_i, r_o));
+}
+void launch_vmm_mac_form(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, int r_i, int r_o, int limbs, int level,
+                         size_t ct_stride, hipStream_t st, bool held) {
     Prof prof_(ctx, CM_K_VMM_MAC, r_i * r_o, st);
     const MacLayout lay = mac_layout(ctx, r_i, r_o, limbs, level);
     if (r_i % 8) {
@@ -1391,6 +1432,18 @@ void launch_vmm_mac(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pts, in
         else if (r_i == 2) FEW_LAUNCH(2);
         else FEW_LAUNCH(4);
 #undef FEW_LAUNCH
+        return;
+    }
+    if (!held) {
+        const dim3 grid(ctx->n / MAC_CO, limbs);
+#define DIRECT_LAUNCH(W_, KW_) hipLaunchKernelGGL((k_vmm_mac_direct<W_, KW_>), grid, dim3(64 * W_), 0, st, out, babies, pts, ctx->d_modc, lay, limbs, ct_stride, level, ctx->L)
+        // n = 4096 leaves compute units idle, which eight waves of half the giant steps use: (limbs, r_i, r_o) (2, 32, 16) 14.4 -> 10.9 us,
+        // (4, 16, 32) 18.4 -> 15.2, (26, 32, 64) 314 -> 302; not (14, 8, 16) 14.3 -> 15.1, nor n = 65536 (5, 8, 16) 64.8 -> 69.0
+        if (r_o <= 4) DIRECT_LAUNCH(4, 1);
+        else if (r_o <= 8) DIRECT_LAUNCH(4, 2);
+        else if (ctx->n == 4096 && (r_i >= 16 || limbs <= 7)) DIRECT_LAUNCH(8, 2);
+        else DIRECT_LAUNCH(4, 4);
+#undef DIRECT_LAUNCH
         return;
     }
     auto launch = [&](auto kernel, int waves, int per, int hold) {

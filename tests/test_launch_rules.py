@@ -27,3 +27,12 @@ def test_joint_passes_where_they_are_faster(n, limbs, cnt, groups, passes, pays)
     (65536, 21, 1, 2, False), (65536, 13, 4, 4, False), (65536, 8, 2, 8, False)])
 def test_tensor_sums_held_where_that_is_faster(n, limbs, cnt, groups, held):
     assert _rule("_Z15tensor_sum_heldiiii")(n, limbs, cnt, groups) == held
+
+
+@pytest.mark.parametrize("n,limbs,r_i,r_o,held", [
+    (65536, 28, 32, 16, True), (65536, 9, 32, 16, True), (65536, 8, 64, 32, True), (65536, 28, 8, 1, False), (65536, 28, 8, 32, False),
+    (65536, 9, 64, 1, False), (65536, 9, 16, 8, True), (65536, 9, 16, 2, False), (65536, 6, 16, 8, False), (65536, 14, 16, 16, False),
+    (65536, 18, 16, 16, True), (65536, 6, 16, 64, True), (65536, 4, 16, 8, False), (65536, 8, 32, 4, False), (4096, 6, 16, 8, False),
+    (4096, 6, 8, 1, False), (4096, 14, 32, 64, True)])
+def test_packed_products_held_where_that_is_faster(n, limbs, r_i, r_o, held):
+    assert _rule("_Z12vmm_mac_heldiiii")(n, limbs, r_i, r_o) == held
