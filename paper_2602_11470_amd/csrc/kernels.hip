@@ -1438,10 +1438,10 @@ void launch_vmm_mac_form(cm_ctx *ctx, u64 *out, const u64 *babies, const u64 *pt
         const dim3 grid(ctx->n / MAC_CO, limbs);
 #define DIRECT_LAUNCH(W_, KW_) hipLaunchKernelGGL((k_vmm_mac_direct<W_, KW_>), grid, dim3(64 * W_), 0, st, out, babies, pts, ctx->d_modc, lay, limbs, ct_stride, level, ctx->L)
         // n = 4096 leaves compute units idle, which eight waves of half the giant steps use: (limbs, r_i, r_o) (2, 32, 16) 14.4 -> 10.9 us,
-        // (4, 16, 32) 18.4 -> 15.2, (26, 32, 64) 314 -> 302; not (14, 8, 16) 14.3 -> 15.1, nor n = 65536 (5, 8, 16) 64.8 -> 69.0
+        // (4, 16, 32) 18.4 -> 15.2, (26, 32, 64) 314 -> 302; not (5, 8, 16) 7.5 -> 8.0 and (14, 8, 16) 14.3 -> 15.1, nor n = 65536 (5, 8, 16) 64.8 -> 69.0
         if (r_o <= 4) DIRECT_LAUNCH(4, 1);
         else if (r_o <= 8) DIRECT_LAUNCH(4, 2);
-        else if (ctx->n == 4096 && (r_i >= 16 || limbs <= 7)) DIRECT_LAUNCH(8, 2);
+        else if (ctx->n == 4096 && (r_i >= 16 || r_o > 16 || limbs <= 4)) DIRECT_LAUNCH(8, 2);
         else DIRECT_LAUNCH(4, 4);
 #undef DIRECT_LAUNCH
         return;

@@ -77,6 +77,7 @@ struct KsLevelFull : KsLevel {
     ConvDev *d_moddown = nullptr;
     int modup_max_nt = 0;
     bool near_up = false, near_down = false, near_drop[2] = {false, false};        // the tables' ConvDev::near
+    bool pays_up = false, pays_down = false, pays_drop[2] = {false, false};        // table_pays of them
 };
 
 #define RESCALE_MAX_COMPS (2 * CM_KS_BATCH)
@@ -100,6 +101,18 @@ static void conv_cut(ConvTarget &o, ConvCut &cut, u64 w, int s) {
     const u64 v = h_mulmod(w, (1ULL << s) % o.q, o.q), low = (1ULL << t) - 1;
     o.c = (unsigned)((1ULL << b) - o.q), o.cb = b - 32, o.mlo = 1u << (t - z), o.mhi = o.c << (b <= 50 ? 3 : 1), o.twice = b < 49;
     cut = ConvCut{(unsigned)(w & low), (unsigned)((w >> t) << z), (unsigned)(v & low), (unsigned)((v >> t) << z)};
+}
+// Where cut weights are the faster form of a table that they cover.  Between moduli below 2^50 alone FP64 needs as many instructions (31 for
+// four sources against 30): with two to seven sources calls are within 1 % of each other, with one source at n = 65536 a rotation on 8 + 1
+// primes takes 81.4 us by cut weights and 79.7 in FP64, a ciphertext product 110.8 and 108.7, with eight sources 95.6 and 93.1, 125.5 and
+// 123.2.  The conversion that does the inverse transform of its source knows no other form.
+bool conv_near_pays(int split, u64 tmax, int ns, bool joined) {
+    return joined || split != CONV_SPLIT_25 || tmax >= (1ULL << 50) || (ns > 1 && ns < 8);
+}
+static bool table_pays(const ConvDev &d) {
+    u64 tmax = 0;
+    for (int r = 0; r < d.nt; r++) tmax = std::max(tmax, d.t[r].q);
+    return conv_near_pays(d.split, tmax, d.ns, false);
 }
 // The weights of a table cut up, where that form covers it (terms: sources, a folded limb among them, smax the largest of their moduli)
 static void conv_near(const cm_ctx *ctx, ConvDev &d, const ConvTable &t, int terms, u64 smax, bool fold) {
@@ -213,6 +226,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
         k.modup_max_nt = std::max(k.modup_max_nt, tabs[j].nt);
     }
     k.near_up = std::all_of(mu.begin(), mu.end(), [](const ConvDev &d) { return d.near; });
+    k.pays_up = std::any_of(mu.begin(), mu.end(), [](const ConvDev &d) { return table_pays(d); });
     k.d_modup = up(mu);
     {
         // Transform the converted limbs modulus by modulus rather than digit by digit: the limbs that
@@ -281,7 +295,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
         std::vector<int> sp_in;
         for (int s = 0; s < ctx->K; s++) sp_in.push_back(level + 1 + s);
         std::vector<ConvDev> md(1, conv_dev(ctx, get_moddown(ctx, level), sp_in, q_rows));
-        k.near_down = md[0].near;
+        k.near_down = md[0].near, k.pays_down = table_pays(md[0]);
         k.d_moddown = up(md);
         std::vector<int> sp0, sp1;
         for (int s = 0; s < ctx->K; s++) sp0.push_back(s), sp1.push_back(k.ext + level + 1 + s);
@@ -292,7 +306,7 @@ static void build_ks(cm_ctx *ctx, int level, KsLevelFull &k) {
     for (int sets = 1; sets <= 2; sets++) {
         if (!ks_drop_fits(ctx, level, sets, 1)) continue;
         std::vector<ConvDev> dd(1, drop_dev(ctx, level, sets));
-        k.near_drop[sets - 1] = dd[0].near;
+        k.near_drop[sets - 1] = dd[0].near, k.pays_drop[sets - 1] = table_pays(dd[0]);
         std::vector<int> rows, mods;
         for (int c = 0; c < (sets == 1 ? 2 * CM_KS_BATCH : 2); c++)
             for (int j = 0; j <= sets * ctx->K; j++) {
@@ -340,7 +354,7 @@ cm_status ks_raise(cm_ctx *ctx, const u64 *d, int level, u64 *digits, hipStream_
     cb.inv = conv_joins_inv(ctx, k.near_up, ctx->alpha, k.beta * k.modup_max_nt);
     if (!cb.inv) launch_ntt_src(ctx, A.ksin, nullptr, d, nullptr, iota_idx(ctx), level + 1, true, st, g);
     cb.tabs = k.d_modup, cb.batch = k.beta, cb.tab_step = 1, cb.ns = ctx->alpha, cb.max_nt = k.modup_max_nt, cb.in_group = k.beta;
-    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half, cb.near = k.near_up;
+    cb.out_stride = (size_t)k.ext * n, cb.own_src = d, cb.own_g = (unsigned)g, cb.half = half, cb.near = k.near_up && (cb.inv || k.pays_up);
     launch_conv_ntt(ctx, cb, digits, cb.inv ? d : A.ksin, st, k.d_ntt_rows, k.d_ntt_mods, k.n_ntt);
     return CM_OK;
 }
@@ -351,7 +365,8 @@ static bool moddown_joins(const cm_ctx *ctx, const KsLevelFull &k, int batch) { 
 static void moddown_conv(cm_ctx *ctx, const KsLevelFull &k, const ConvDev *tab, int batch, u64 *conv, const u64 *in, size_t in_stride,
                          const FinishBatch &fb, hipStream_t st) {
     ConvBatch cb;
-    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1, cb.near = k.near_down, cb.inv = moddown_joins(ctx, k, batch);
+    cb.tabs = tab, cb.batch = batch, cb.ns = ctx->K, cb.max_nt = k.level + 1, cb.inv = moddown_joins(ctx, k, batch);
+    cb.near = k.near_down && (cb.inv || k.pays_down);
     cb.in_stride = in_stride, cb.out_stride = (size_t)(k.level + 1) * ctx->n;
     launch_conv_ntt(ctx, cb, conv, in, st, nullptr, k.d_bq_mods, batch * (k.level + 1), &fb);
 }
@@ -439,7 +454,7 @@ cm_status ks_drop(cm_ctx *ctx, u64 *us, int level, int sets, int m, const u64 *a
     }
     fb.pinv = k.d_pqinv, fb.ainv = get_qlinv(ctx, level);
     ConvBatch cb;
-    cb.tabs = k.d_drop[sets - 1], cb.batch = 2 * m, cb.ns = ns, cb.max_nt = level, cb.fold = true, cb.near = k.near_drop[sets - 1];
+    cb.tabs = k.d_drop[sets - 1], cb.batch = 2 * m, cb.ns = ns, cb.max_nt = level, cb.fold = true, cb.near = k.near_drop[sets - 1] && k.pays_drop[sets - 1];
     cb.in_stride = (size_t)ext * n, cb.out_stride = (size_t)level * n;
     launch_conv_ntt(ctx, cb, A.bconv, us, st, nullptr, k.d_red_mods, 2 * m * level, &fb);
     return CM_OK;
@@ -621,7 +636,7 @@ cm_status ks_raise_many(cm_ctx *ctx, const KsManyTables &t, const u64 *cts, u64 
     cb.tab_period = k.beta, cb.in_group = k.beta;
     cb.in_stride = ln, cb.out_stride = (size_t)k.ext * n;
     cb.own_src = cts + (size_t)t.comp * ln, cb.own_g = (unsigned)g, cb.own_stride = (size_t)t.ncomp * ln, cb.half = half;
-    cb.near = k.near_up;
+    cb.near = k.near_up && (cb.inv || k.pays_up);
     if (cb.inv) cb.in_stride = cb.own_stride;
     launch_conv_ntt(ctx, cb, digits, cb.inv ? cb.own_src : ksin, st, t.d_ntt_rows, t.d_ntt_mods, m * t.n_ntt);
     return CM_OK;

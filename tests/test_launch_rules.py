@@ -36,3 +36,10 @@ def test_tensor_sums_held_where_that_is_faster(n, limbs, cnt, groups, held):
     (4096, 6, 8, 1, False), (4096, 14, 32, 64, True)])
 def test_packed_products_held_where_that_is_faster(n, limbs, r_i, r_o, held):
     assert _rule("_Z12vmm_mac_heldiiii")(n, limbs, r_i, r_o) == held
+
+
+@pytest.mark.parametrize("split,bits,ns,joined,pays", [(0, 50, 1, False, False), (0, 50, 8, False, False), (0, 50, 4, False, True), (0, 50, 1, True, True),
+                                                       (0, 60, 1, False, True), (0, 60, 8, False, True), (1, 50, 1, False, True), (2, 60, 1, False, True)])
+def test_cut_weights_where_they_are_faster(split, bits, ns, joined, pays):
+    """split: how the sources' words are split (0: all below 2^50); bits: of the largest target modulus."""
+    assert _rule("_Z14conv_near_paysimib")(split, ctypes.c_ulong((1 << bits) - 1), ns, ctypes.c_bool(joined)) == pays
