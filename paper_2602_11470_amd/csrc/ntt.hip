@@ -248,8 +248,8 @@ struct FpArith {
 // Twiddle providers for four stages starting at stage s0 with base0 = 2^s0 + (block index):
 // stage s0 + a, group g uses table entry (base0 << a) + g.
 // Both arithmetics read all fifteen entries up front (one exposure to memory latency instead of one per stage, and the
-// loads overlap the data loads or the LDS exchange in front of them).  Integer limbs read the Shoup companions with
-// them; FP64 limbs take the second factor w/q as w * (1/q), one multiplication instead
+// loads overlap the data loads or the LDS exchange in front of them).  Integer limbs read a multiplier cut up as
+// IntTw, one 16-byte word; FP64 limbs take the second factor w/q as w * (1/q), one multiplication instead
 // of a second table: the quotient estimate may then be off by one more unit, the product stays exact
 // (|r| <= (1/2 + 3/8 B) q for |y| <= B q, see FpArith).
 template <class A, int ST>                      // ST stages
@@ -467,7 +467,7 @@ __device__ __forceinline__ void wave_sync() {
 }
 // The fused ModDown / rescale tail of a forward transform: the canonical words of a chunk of CH sit in LDS.
 // at(e): where word e of the chunk sits.  DROP: the rescale may be part of it (FinishBatch::ainv); at n = 4096 only the folded
-// conversions end so, and the others keep their registers (eight sources: 31 spilled instead of 48, 20.2 us instead of 20.9).
+// conversions end so, and the others keep their registers (eight sources: 20.2 us instead of 20.9).
 template <int LANES, int CH = 4096, bool DROP = true, class AT, class A>
 __device__ __forceinline__ void finish_tail(AT at, const A &ar, const u64 *lds, const NttTables &t, int n, int chunk, int limb, const FinishBatch &fb) {
     constexpr int NW = CH / LANES;
@@ -883,9 +883,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_rows_inv(u64 *__restrict_
 // blocks go to aligned blocks) and exchanges once more.  The digits' row pass as a launch of its own wrote and re-read every digit.
 // The rows from inv_from on go straight into the row pass of the inverse transform, whose order of words is the one they are in.
 // Bound by the latency that two waves a SIMD leave open: counters of the seven giant steps and of the shared rotations of q K^T show
-// the vector ALU 0.56 to 0.61 busy, 0.35 to 0.40 of the waves' time waiting, and two conflict cycles to an LDS cycle.  240 vector
-// registers (245 in the shared-key form; sums, twiddles, and the next digit requested ahead, which is worth 1 %), 108 (88) scalar ones
-// spilled into lanes and 36 bytes of scratch: the two arithmetics in one kernel.  Three waves spill 26 vector registers and lose 3 to
+// the vector ALU 0.56 to 0.61 busy, 0.35 to 0.40 of the waves' time waiting, and two conflict cycles to an LDS cycle.  239 vector
+// registers (244 in the shared-key form; sums, twiddles, and the next digit requested ahead, which is worth 1 %), 95 (71) scalar ones
+// spilled into lanes: the two arithmetics in one kernel.  Three waves spill 26 vector registers and lose 3 to
 // 10 %, four lose 20 %.  Row passes and inner products in launches of
 // their own -> here: the seven giant steps at level 22 195 + 236 -> 388 us; two launches a key switch fewer: ciphertext product at
 // level 13 151.6 -> 145.6 us, rotary embedding at level 3 82.9 -> 76.9, query times K at level 12 16730 -> 16020, scores times V at
@@ -1760,7 +1760,8 @@ __global__ __launch_bounds__(FULL_THREADS) void conv_full_fwd(u64 *__restrict__ 
         y.set(tab, x);
         if (FOLD) y.fold(tab, xf);
     }
-    y.opaque();
+    // the other form keeps its registers without: eight sources spill 60 with it, seven hoisted rotations on 16 + 8 primes 65.4 -> 67.8 us
+    if (NEAR || FOLD) y.opaque();
     const ConvTarget &o = tab.t[r];
     const int limb = z * nt + r;                          // of the tail: item, component, limb
     u64 *p = out + (size_t)o.row * n;
@@ -1912,8 +1913,9 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
 #define FULL_LAUNCH(NS_)                                                                                                         \
     if (b.near) FULL_FORM(NS_, true);                                                                                            \
     else FULL_FORM(NS_, false)
-        // the instantiation for eight spills 31 of 256 registers (124 with a folded limb: ks_drop_fits) and still takes less than conversion and transform in two launches
-        // (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us; five sources 66 -> 56
+        // the instantiation for eight spills 32 of 256 registers (27 with a tail, 59 with a folded limb) and still takes less than conversion
+        // and transform in two launches (36 registers, no spills): a rotation on 16 + 8 primes, digits of eight, level 15, 69 -> 57 us;
+        // five sources 66 -> 56
         if (ns <= 1) { FULL_LAUNCH(1); }
         else if (ns <= 2) { FULL_LAUNCH(2); }
         else if (ns <= 4) { FULL_LAUNCH(4); }
@@ -1927,7 +1929,7 @@ void launch_conv_ntt(cm_ctx *ctx, const ConvBatch &b, u64 *out, const u64 *in, h
     while (a.tg > 1 && 256 / CCF_W * b.batch * ((b.max_nt + a.tg - 1) / a.tg) < CCF_FILL) a.tg >>= 1;
     a.groups = (b.max_nt + a.tg - 1) / a.tg;
     const dim3 grid(256 / CCF_W, a.groups + (b.own_src && !b.half ? 1 : 0), b.batch);
-    // Eight sources spill twelve registers (128 for two workgroups per compute unit), seven do not: with seven special
+    // Eight sources spill twelve registers, 15 with cut weights (128 for two workgroups per compute unit), seven do not: with seven special
     // primes and digits of seven (14 + 7 primes, level 13) a rotation takes 129 us in the instantiation for eight and 116
     // in its own; 124 with conversion and column pass in two launches.  A raise and a ModDown each go by their own
     // count: eight special primes and digits of four, level 11, 128 us by the larger of the two, 116 by their own (123).
