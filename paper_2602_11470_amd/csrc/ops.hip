@@ -409,11 +409,9 @@ cm_status ks_one(cm_ctx *ctx, const u64 *d, const u64 *key, int level, u64 g, co
 // in one (two sets) that takes 83 us at level 3 instead of 134.
 // The product forms of the conversion hold one more term below 2^50 (or below 2^60, split in 30 bits) where the split ones
 // apply, and up to seven below 2^61 as 128-bit sums.  One set of seven or eight special primes stays with two steps: the folded
-// limb's registers come on top of an instantiation that spills.  At n = 4096 the instantiation for more than four sources spills 124
-// registers with the folded limb (31 without): 38 us at level 11 with six special primes, 37 for the two steps' conversion and
-// transforms.  With the sources split in 30 bits the two steps are the faster ones (query times K of 16 heads x 16: 420 us, 424 in
-// one); with the 25-bit split (371 and 362) and the 128-bit sums (475 and 451) they are not, nor is the rotary embedding's two sets
-// (109 and 73).
+// limb's registers come on top of an instantiation that spills.  At n = 4096 the one for more than four sources spills 59 with the
+// folded limb and is still the faster way with five and six special primes of 60 bits: query times K of 8 heads x 16 at levels 5 to 16
+// with shared rotations 426 to 502 us in two steps, 413 to 487 in one, scores times V 332 to 387 and 326 to 381.
 bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m) {
     const int ns = sets * ctx->K;
     if (level < 1 || m < 1 || ns > CONV_MAX_SRC || (sets == 1 ? m > CM_KS_BATCH || ns > 6 : m > 1)) return false;
@@ -421,7 +419,7 @@ bool ks_drop_fits(cm_ctx *ctx, int level, int sets, int m) {
     for (int k = 0; k < ctx->K; k++) pmax = std::max(pmax, ctx->mod[ctx->L + 1 + k]);
     for (int i = 0; i <= level; i++) qmax = std::max(qmax, ctx->mod[i]);
     if (pmax < (1ULL << 50)) return ctx->mod[level] < (1ULL << 50);
-    if (pmax < (1ULL << 60) && qmax < (1ULL << 50)) return ctx->n == 65536 || sets == 2 || ns <= 4;
+    if (pmax < (1ULL << 60) && qmax < (1ULL << 50)) return true;
     return ns + 1 <= 7;
 }
 FoldIn ks_drop_fold(cm_ctx *ctx, int level, int sets, const u64 *add, size_t add_stride, int add_comps, u64 g, const u64 *acc, size_t acc_stride) {

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
     (4096, 4, 2, 2, 58, 54, 60, (3, 1)),                 # 128-bit sums
     (4096, 4, 3, 2, 50, 49, 61, (3,)),                   # seven terms of 128-bit sums; two sets do not fit
     (4096, 4, 4, 2, 50, 49, 50, (3,)),                   # special primes below 2^50, two sets of four
-    (4096, 3, 6, 2, 50, 49, 60, (2,)),                   # two sets do not fit, one set is slower in one
+    (4096, 3, 6, 2, 50, 49, 60, (2,)),                   # two sets do not fit, one set of six in one
     (4096, 3, 5, 2, 50, 49, 50, (2,)),                   # one set of five in one
     (4096, 3, 6, 2, 58, 54, 60, (2,)),                   # one set of six in one, 128-bit sums
     (65536, 3, 1, 1, 50, 50, 60, (2, 1)),
