@@ -278,6 +278,7 @@ u64 h_powmod(u64 b, u64 e, u64 q);
 u64 h_invmod(u64 a, u64 q);
 u64 h_shoup(u64 w, u64 q);
 IntTw h_int_tw(u64 w, u64 q);
+ConvCut conv_cut(u64 q, u64 w, int s);         // of a weight w for a target q
 u64 galois_of_step(const cm_ctx *ctx, int step);
 const std::vector<ConvTable> &get_modup(cm_ctx *ctx, int level);
 const ConvTable &get_moddown(cm_ctx *ctx, int level);

@@ -96,11 +96,16 @@ static bool conv_near_target(u64 q) {
     const u64 once = (c << (63 - b)) + (b < 49 ? 1ULL << b : 0);
     return (b < 49 ? (once >> b) * c : once) < q / 16;
 }
-static void conv_cut(ConvTarget &o, ConvCut &cut, u64 w, int s) {
-    const int b = 64 - __builtin_clzll(o.q), t = b <= 50 ? (b + 1) / 2 : 30, z = b <= 50 ? 29 - (b - t) : 61 - b;
-    const u64 v = h_mulmod(w, (1ULL << s) % o.q, o.q), low = (1ULL << t) - 1;
-    o.c = (unsigned)((1ULL << b) - o.q), o.cb = b - 32, o.mlo = 1u << (t - z), o.mhi = o.c << (b <= 50 ? 3 : 1), o.twice = b < 49;
-    cut = ConvCut{(unsigned)(w & low), (unsigned)((w >> t) << z), (unsigned)(v & low), (unsigned)((v >> t) << z)};
+static int cut_t(int b) { return b <= 50 ? (b + 1) / 2 : 30; }
+static int cut_z(int b) { return b <= 50 ? 29 - (b - cut_t(b)) : 61 - b; }
+ConvCut conv_cut(u64 q, u64 w, int s) {
+    const int b = 64 - __builtin_clzll(q), t = cut_t(b), z = cut_z(b);
+    const u64 v = h_mulmod(w, (1ULL << s) % q, q), low = (1ULL << t) - 1;
+    return ConvCut{(unsigned)(w & low), (unsigned)((w >> t) << z), (unsigned)(v & low), (unsigned)((v >> t) << z)};
+}
+static void conv_cut_target(ConvTarget &o) {
+    const int b = 64 - __builtin_clzll(o.q);
+    o.c = (unsigned)((1ULL << b) - o.q), o.cb = b - 32, o.mlo = 1u << (cut_t(b) - cut_z(b)), o.mhi = o.c << (b <= 50 ? 3 : 1), o.twice = b < 49;
 }
 // Where cut weights are the faster form of a table that they cover.  Between moduli below 2^50 alone FP64 needs as many instructions (31 for
 // four sources against 30): with two to seven sources calls are within 1 % of each other, with one source at n = 65536 a rotation on 8 + 1
@@ -122,8 +127,9 @@ static void conv_near(const cm_ctx *ctx, ConvDev &d, const ConvTable &t, int ter
         ConvTarget &o = d.t[r];
         d.near = conv_near_target(o.q) && (s == 25 || o.q < (1ULL << 50) || terms <= 4);
         if (!d.near) return;
-        for (int m = 0; m < t.ns; m++) conv_cut(o, o.cut[m], t.hat[(size_t)m * t.nt + r], s);
-        if (fold) conv_cut(o, o.cutl, p_mod(ctx, o.q), s);
+        conv_cut_target(o);
+        for (int m = 0; m < t.ns; m++) o.cut[m] = conv_cut(o.q, t.hat[(size_t)m * t.nt + r], s);
+        if (fold) o.cutl = conv_cut(o.q, p_mod(ctx, o.q), s);
     }
 }
 static ConvDev conv_dev(const cm_ctx *ctx, const ConvTable &t, const std::vector<int> &in_rows,

@@ -36,7 +36,8 @@ def _same(e, o, g):
     assert np.array_equal(e["gctx"].ct_export(g), e["octx"].canonical(o))
 
 
-@pytest.mark.parametrize("unrolled,r_i,index", [(False, 4, False), (True, 0, False), (False, 4, True), (True, 4, True)])
+@pytest.mark.parametrize("unrolled,r_i,index", [(False, 4, False), (True, 0, False), (False, 4, True), (True, 4, True),
+                                                  (True, 16, True), (True, 8, True), (True, 2, True)])
 def test_gqa_products_match_oracle_and_float64(env, unrolled, r_i, index):
     """8 query heads on 2 KV heads of 16 dims (G = 4, t_kv = 64, t = 16) on the 2048-slot ring: the four score
     ciphertexts of q K^T and the output of scores V limb for limb against the oracle's composition of the same

@@ -162,32 +162,38 @@ def test_conversion_sums_in_doubles_stay_exact():
 @pytest.mark.parametrize("n", [4096, 65536])
 @pytest.mark.parametrize("b", [40, 45, 48, 49, 50, 51, 54, 60, 61])
 def test_conversion_sums_from_cut_weights(n, b):
-    """ConvNear::sum: the largest y and w, for as many terms as ops.hip lets a near table have; nothing passes 64 bits (the products'
-    factors 32), and what is left is the sum, below q + q / 16."""
+    """ConvNear::sum with the weights as the library cuts them up: the largest y and w, for as many terms as conv_near of ops.hip lets a
+    table have (a folded limb among them); nothing passes 64 bits (the products' factors 32), and what is left is the sum, below
+    q + q / 16."""
+    import ctypes
     from oracle import params
+    from paper_2602_11470_amd import binding as B
+
+    class Cut(ctypes.Structure):
+        _fields_ = [(name, ctypes.c_uint) for name in ("w0", "w1", "v0", "v1")]
+    cut = B.lib._Z8conv_cutmmi
+    cut.argtypes, cut.restype = [ctypes.c_ulong, ctypes.c_ulong, ctypes.c_int], Cut
+    most = _define("common.h", "CONV_MAX_SRC") + 1
+    few = int(re.search(r"o\.q < \(1ULL << 50\) \|\| terms <= (\d+)", (CSRC / "ops.hip").read_text()).group(1))
+    assert int(re.search(r"if \(b < (\d+) \|\| c >=", (CSRC / "ops.hip").read_text()).group(1)) == 40
     q = params.scan_primes(b, n, 8)[-1]
     c = (1 << b) - q
     t, z = ((b + 1) // 2, 29 - (b - (b + 1) // 2)) if b <= 50 else (30, 61 - b)
-    up, mlo, mhi = (3 if b <= 50 else 1), 1 << (t - z), c << (3 if b <= 50 else 1)
+    mlo, mhi = 1 << (t - z), c << (3 if b <= 50 else 1)
     m32, mb = (1 << 32) - 1, (1 << b) - 1
     assert mhi <= m32
-
-    def cut(w, s):
-        v = (w << s) % q
-        return w & ((1 << t) - 1), (w >> t) << z, v & ((1 << t) - 1), (v >> t) << z
-
     rng = np.random.default_rng(b)
-    for s, terms in ((25, 9), (30, 9 if b < 51 else 4)):
+    for s, terms in ((25, most), (30, most if b < 51 else few)):
         ymax = (1 << 50) - 1 if s == 25 else (1 << 60) - 1
         for i in range(300):
             ys = [ymax if i < 2 else int(rng.integers(0, ymax)) for _ in range(terms)]
             ws = [q - 1 if i % 2 else int(rng.integers(0, q)) for _ in range(terms)]
             lo = hi = 0
             for y, w in zip(ys, ws):
-                w0, w1, v0, v1 = cut(w, s)
+                x = cut(q, w, s)
                 y0, y1 = y & ((1 << s) - 1), y >> s
-                assert max(y0, y1, w0, w1, v0, v1) <= m32
-                lo, hi = lo + y0 * w0 + y1 * v0, hi + y0 * w1 + y1 * v1
+                assert max(y0, y1) <= m32
+                lo, hi = lo + y0 * x.w0 + y1 * x.v0, hi + y0 * x.w1 + y1 * x.v1
             assert max(lo, hi) <= M64
             T = lo + (hi & m32) * mlo + (hi >> 32) * mhi
             assert T <= M64 and (b > 50 or T < 1 << 63)
