@@ -48,8 +48,8 @@ D = 4096
 
 def measured_traffic():
     """HBM bytes per unit from the committed rocprofv3 --pmc summary (FETCH_SIZE / WRITE_SIZE scaled
-    by the copy-kernel calibration stated there); keys: 'inner_product_family_per_step', 'k_vmm_mac' and 'k_rows_ip'
-    (per launch).  Empty if the summary is missing."""
+    by the copy-kernel calibration stated there); keys: 'inner_product_family_per_step', 'k_vmm_mac' (all
+    launches of a call) and 'k_rows_ip' (per launch).  Empty if the summary is missing."""
     out = {}
     path = os.path.join(ROOT, "profiles", "pmc_hbm_traffic_bench_config2.txt")
     if os.path.exists(path):

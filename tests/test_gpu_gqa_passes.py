@@ -1,6 +1,6 @@
 """Grouped-query products whose passes read the cache together against the same passes one call after the other, limb for limb: groups
-of two, four and eight (one, one and two launches), one to sixteen terms a sum, one to eight sums, and a cache with more sums or terms
-than the joint form takes."""
+of two, four and eight (one, one and two turns), one to sixteen terms a sum, one to eight sums, calls that the rule leaves a pass at a time,
+and a cache with more sums or terms than the joint form takes."""
 import numpy as np
 import pytest
 import torch
